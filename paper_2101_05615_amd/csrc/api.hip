@@ -1064,7 +1064,9 @@ int qg_conv_dense_u8s8_requant(const uint8_t* in_nhwc, int Nb, int H, int W, int
     c.clamp_hi = (float)(255 - p->c_zp);
     c.has_bzp = Wp->has_bzp;
     if (Nb == 0) return QG_OK;
-    return qg_launch_conv_dense_plain(c, static_cast<hipStream_t>(stream)) == hipSuccess ? QG_OK : QG_ELAUNCH;
+    const hipError_t e = qg_conv_runs_applies(c) ? qg_launch_conv_runs(c, static_cast<hipStream_t>(stream))
+                                                 : qg_launch_conv_dense_plain(c, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? QG_OK : QG_ELAUNCH;
   }
   // 32-bit byte offsets into the image (tap offsets included) and 32-bit pixel counts
   if ((uint64_t)Nb * H * W * Cin >= (1ull << 30) || (uint64_t)Nb * Ho * Wo >= (1ull << 31) / 4) return QG_EUNSUPPORTED;

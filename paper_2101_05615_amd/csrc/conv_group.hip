@@ -514,9 +514,9 @@ __global__ __launch_bounds__(256) void qg_conv_group_any_kernel(const qg_conv_ar
   }
 }
 
-// Dense convolution for the extents no requested staging takes (channel counts that are not a multiple of 16 -- the
-// three channels of a first layer --, an image that is not 16-byte aligned): the im2col tile is GATHERED, byte by
-// byte, into LDS.  Workgroup = 64 output pixels x 64 output channels, four waves of one 32 x 32 block each; per
+// Dense convolution for the extents no other kernel takes (channel counts that are not a multiple of 16 or an image that
+// is not 16-byte aligned, with a 1 x 1 filter or more weights per column block than conv_runs.hip keeps in LDS): the
+// im2col tile is GATHERED, byte by byte, into LDS.  Workgroup = 64 output pixels x 64 output channels, four waves of one 32 x 32 block each; per
 // 64-deep k chunk every thread gathers 16 consecutive k of one pixel row (walking (channel, kw, kh) as it goes; a tap
 // outside the image reads as theta_A, k past K as 0x80, the K padding of every A stage) and copies 16 bytes of the
 // packed weights, then two MFMAs per wave.  One stage, two barriers per chunk: K is short where this kernel is used.
@@ -524,7 +524,7 @@ __global__ __launch_bounds__(256) void qg_conv_group_any_kernel(const qg_conv_ar
 __device__ __forceinline__ int gather_swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); }
 
 // GW = bytes per gathered piece: 4 when the channel count is a multiple of 4 and the image 4-byte aligned (a piece is
-// then four channels of one tap: a first layer with its RGB input padded to four channels), else 1.
+// then four channels of one tap), else 1.
 template <bool HAS_BZP, int GW>
 __global__ __launch_bounds__(256) void qg_conv_dense_gather_kernel(const qg_conv_args p) {
   __shared__ __align__(16) unsigned char a_s[64 * 64];

@@ -299,6 +299,9 @@ hipError_t qg_launch_quantize_a(const float* A, int M, int K, int lda, float inv
                                 int ldq, hipStream_t s);
 hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s);
 hipError_t qg_launch_conv_dense_plain(const qg_conv_args& a, hipStream_t s);
+// the image rows of an output tile in LDS, a filter row of a pixel read as one run of bytes (false: LDS too small for it)
+bool qg_conv_runs_applies(const qg_conv_args& a);
+hipError_t qg_launch_conv_runs(const qg_conv_args& a, hipStream_t s);
 // the kernels with the input patch in LDS ("same" convolutions); form 0 = 64 pixels x 128 channels, 1 = 128 x 64, 2 = 256 x 64, 3 = 256 x 128, 4 = 512 x 128
 bool qg_conv_patch_applies(const qg_gemm_args& a, int form);
 int qg_conv_patch_per_cu(const qg_gemm_args& a, int form);  // workgroups a CU holds side by side; 0 = does not apply
