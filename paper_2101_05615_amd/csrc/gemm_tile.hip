@@ -80,6 +80,15 @@ __device__ __forceinline__ int a_swz(int r) { return ((r >> 1) & 3) ^ ((r >> 3) 
 // swizzled byte offset of 16-byte chunk kc (0..3) of row r in an A stage
 __device__ __forceinline__ int a_lds_off(int r, int kc) { return r * BK + ((kc ^ a_swz(r)) << 4); }
 
+// The hand-scheduled loop of the 256 x 256 tile keeps A in a ring of six half buffers (a half = half of the tile's
+// rows, 128 bytes = two k tiles of each) in front of NSTAGE stages of B: A is requested a whole 128-byte cache line at a
+// time.  Requested 64 bytes per row and k tile, every line came from the L2 twice (6.4 GB at 8192^3, now 4.3).  8192^3 472 -> 449 us.
+constexpr bool pair_a(int path, int tm, int tn, int conv) { return path == PATH_ASM && tm == 4 && tn == 4 && conv == 0; }
+// bytes of LDS the main loop uses
+constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair) {
+  return pair ? 6 * (bm * BK) + NSTAGE * (bn * BK) : (path == PATH_ASM ? asm_stages(blocks) : pipe_stages(blocks)) * (bm + bn) * BK;
+}
+
 // operand list shared by the two generated loop variants (gen_tile_loop.py)
 #define QG_TILE_LOOP_OPERANDS \
                  : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[0][2]), [c3] "+a"(acc[0][3]), \
@@ -87,8 +96,8 @@ __device__ __forceinline__ int a_lds_off(int r, int kc) { return r * BK + ((kc ^
                    [c8] "+a"(acc[2][0]), [c9] "+a"(acc[2][1]), [c10] "+a"(acc[2][2]), [c11] "+a"(acc[2][3]), \
                    [c12] "+a"(acc[3][0]), [c13] "+a"(acc[3][1]), [c14] "+a"(acc[3][2]), [c15] "+a"(acc[3][3]), \
                    [rs01] "=v"(rs01), [rs23] "=v"(rs23) \
-                 : [av01] "v"(av01), [av23] "v"(av23), [bv01] "v"(bv01), [bv23] "v"(bv23), [ard] "v"(ard), \
-                   [brd] "v"(brd), [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
+                 : [av01] "v"(av01), [av23] "v"(av23), [aw01] "v"(aw01), [aw23] "v"(aw23), [afix] "v"(pair_fix), \
+                   [bv01] "v"(bv01), [bv23] "v"(bv23), [ard] "v"(pard), [brd] "v"(pbrd), [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
                    [lds] "s"(lds_base), [bstep] "s"(b_step) \
                  : QG_TILE_LOOP_CLOBBERS
 
@@ -192,6 +201,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
   constexpr int A_DMA = A_STAGE / 1024 / NW;  // 1 KiB wave-loads per wave per tile
   constexpr int B_DMA = B_STAGE / 1024 / NW;
   constexpr int N_DMA = A_DMA + B_DMA;
+  constexpr bool PAIR = pair_a(PATH, TM, TN, CONV);
   static_assert(A_STAGE % (1024 * NW) == 0 && B_STAGE % (1024 * NW) == 0, "tile/wave mismatch");
   constexpr int NS = pipe_stages(TM * TN);  // PATH_PIPE
   static_assert((PATH == PATH_PIPE ? NS - 2 : 2) * N_DMA <= 63, "vmcnt is a 6-bit counter");
@@ -226,14 +236,23 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
   // physical chunk l%4, so it fetches the logical chunk that the swizzle maps there.  B: the tile is
   // BN/16 fragments of 1 KiB, one contiguous run of the packed buffer.  Addresses are a wave-uniform
   // base (advanced per tile on the scalar unit) plus a fixed 32-bit per-lane offset.
+  // PAIR: the loop's requests are 8 rows x 128 B; lane l lands at row l/8, physical chunk l%8 of a half buffer.
   unsigned a_voff[A_DMA], b_voff[B_DMA];
+  unsigned a_half1[A_DMA];  // PAIR: the offsets of half 1 (a_voff: half 0)
   int a_pix[A_DMA];  // CONV: byte offset of the chunk this lane requests, at tap (0, 0) (may be negative)
   int a_h[A_DMA], a_w[A_DMA];  // CONV: image row and column of that tap
 #pragma unroll
   for (int q = 0; q < A_DMA; ++q) {
+    if (PAIR) {
+      const int r = (wave * A_DMA + q) * 8 + (lane >> 3);
+      const unsigned in_row = (((lane & 7) ^ ((r >> 1) & 7)) << 4) + (A_DMA - 1 - q) * 1024;  // (see the bias below)
+      a_voff[q] = (unsigned)min(m0 + r, M - 1) * (unsigned)lda + in_row;  // rows past M re-read the last row; never stored
+      a_half1[q] = (unsigned)min(m0 + BM / 2 + r, M - 1) * (unsigned)lda + in_row;
+      continue;
+    }
     const int r = (wave * A_DMA + q) * 16 + (lane >> 2);
     const int kc = (lane & 3) ^ a_swz(r);
-    const int rg = min(m0 + r, M - 1);  // rows past M re-read the last row; never stored
+    const int rg = min(m0 + r, M - 1);
     if (CONV) {
       const int wo = rg % p.cv_Wo, t = rg / p.cv_Wo;
       const int ho = t % p.cv_Ho, n = t / p.cv_Ho;
@@ -327,7 +346,17 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)smem);
     const unsigned lds_dma = lds_base + wave * (A_DMA * 1024);
     unsigned long long rs01;
+    // PAIR: LDS offsets of the fragments (A: pitch 128, this wave's half, k step 0 / 1 of an even tile; B: in its stage)
+    const int p_row = wave_m * TM * 32 + l32;
+    auto p_rd = [&](int ks) { return (unsigned)(p_row * 128 + (((ks * 2 + lg) ^ ((p_row >> 1) & 7)) << 4)); };
+    const unsigned long long pard = p_rd(0) | ((unsigned long long)p_rd(1) << 32);
+    const unsigned long long pbrd = (unsigned)(b_rd - A_STAGE);
+    // 64 for the lanes whose chunk belongs to the odd tile of a pair in a request of even number, 0 for the others (in a
+    // request of odd number the other way round: its rows are 8 further, which turns bit 2 of the chunk)
+    const unsigned pair_fix = (lane & 4) << 4;
     if constexpr (TM == 4) {
+      const unsigned long long aw01 = a_half1[0] | ((unsigned long long)a_half1[1] << 32);
+      const unsigned long long aw23 = a_half1[2] | ((unsigned long long)a_half1[3] << 32);
       const unsigned long long av23 = a_voff[2] | ((unsigned long long)a_voff[3] << 32);
       const unsigned long long bv23 = b_voff[2] | ((unsigned long long)b_voff[3] << 32);
       unsigned long long rs23;
@@ -716,9 +745,9 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
 template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int KS = 1, int EPI = EPI_CLAMP>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr int BM = NWM * TM * 32, BN = NWN * TN * 32;
-  constexpr int STAGES = (PATH == PATH_ASM ? asm_stages(TM * TN) : pipe_stages(TM * TN)) * KS;
+  constexpr int LOOP = loop_lds(PATH, BM, BN, TM * TN, pair_a(PATH, TM, TN, 0)) * KS;
   // the output pipeline's per-column constants (12 B per column) reuse the stage memory
-  constexpr int SMEM = STAGES * (BM + BN) * BK > 12 * BN ? STAGES * (BM + BN) * BK : 12 * BN;
+  constexpr int SMEM = LOOP > 12 * BN ? LOOP : 12 * BN;
   const int tiles_m = (a.M + BM - 1) / BM;
   const int tiles_n = (a.N + BN - 1) / BN;
   if constexpr (PATH == PATH_ASM && TM == 2 && TN == 2 && KS == 1) {

@@ -28,6 +28,22 @@ two and the row sums and shifts of both A fragments behind the last two.  A thir
 tile: 8 accumulators, three 24 KiB stages so that two workgroups share a CU, fixed registers from v56, one more
 SGPR input bofs = distance from a wave's A request slots to its B request slots), has eight MFMAs per k-step.
 
+PAIR (4 x 4): A is requested 128 bytes of a row at a time -- two k tiles, one whole cache line --, one half of the
+tile's rows per k tile.  Requesting 64 bytes per row and tile fetched every line twice: the other half had left the 32 KB
+L1 by the time it was asked for (6.4 GB from the L2s instead of 4.3 at 8192^3), and this tile is limited by power, not by
+issue.  A's LDS is a ring of six half buffers (rows 128 bytes apart, chunk c of row r at c ^ (r >> 1 & 7)), two of which
+make the pair of tiles 2 P, 2 P + 1; B keeps its four stages behind them.  Tile t requests half t + 5 (rows of half
+t + 5 & 1 of pair t + 5 >> 1) and B tile t + 4, so every wait is the one of the plain loop.  With an even number of tiles
+the last tile that requests asks for half KT, which does not exist: the pointer is not advanced and the last pair comes
+again, into a slot nobody reads.  With an odd number the last pair has 64 valid bytes per row: lanes whose chunk lies past
+them ask for one 64 bytes earlier (afix: 64 or 0 for requests of even number, 64 minus that for odd ones).  The scalar
+work sits in the first k step of a tile, in the slots behind its reads.  (The 2 x 2 tile is not limited by power; there the
+scalar work, with three MFMAs to hide it behind, cost more than the lines: 2048^3 12.0 -> 12.7 us.)  Extra inputs: aw01
+aw23 per-lane offsets of half 1, afix.  Registers: AW offsets of the half not due next (swapped behind every tile); s70
+step of the A base (0 / 128), s96/s79 A and B request slots with ring ends s71/s72 and starts s91/s83, s76/s77 A and B read
+bases of the next tile with ends s75/s74 and starts s92/s75, s73 step of the A read base, s78 temporary, s80/s81 values of
+s90 at which the advance is skipped / the offsets are fixed.
+
 CONV variants (2 x 2 and 2 x 4): the A side of a dense convolution with the im2col folded into the requests.
 Tile kt is 64 channels of one filter tap (Cin % 64 == 0, at most 32 taps); a lane's chunk comes from the image at
 (its pixel's byte offset at tap (0, 0)) + (tap offset, kept on the scalar unit), or, when that tap of its pixel
@@ -47,6 +63,7 @@ import os
 def configure(tm, tn, nstage=4, conv=False):
     """sets the module-level plan for TM x TN blocks of 32 x 32 per wave (2 x 2 waves per workgroup)"""
     global TM, TN, NM, A, B, RS, AV, BV, ARD0, ARD1, BRD, VA, VB, STAGE_BYTES, A_STAGE, A_DMA, N_DMA, NREAD, RSLOTS
+    global AW, PAIR, B_STAGE
     global FIRST_VGPR, LAST_VGPR, NSTAGE, CT, APIX, AMASK, TABLO, TABHI, IMGHI
     assert (tm, tn) in ((4, 4), (2, 2), (2, 4)) and nstage in (3, 4)
     TM, TN, NM, NSTAGE = tm, tn, tm * tn, nstage
@@ -60,6 +77,9 @@ def configure(tm, tn, nstage=4, conv=False):
     BV = AV + 4                                     # ... of the B requests (only the first is used: B is contiguous)
     ARD0, ARD1, BRD = BV + 4, BV + 5, BV + 6        # BRD is moved as a 64-bit pair
     VA, VB = BV + 8, BV + 9
+    PAIR = tm == 4
+    AW = VB + 1                                     # PAIR: the offsets of the half that is not due next
+    B_STAGE = tn * 4096
     FIRST_VGPR, LAST_VGPR = base, 255 if tm == 4 else VB
     CT = VB + 1 + ((VB + 1) & 1)                    # CONV: even-aligned address pairs of the two A requests
     APIX, AMASK, TABLO, TABHI, IMGHI = CT + 4, CT + 6, CT + 8, CT + 10, CT + 11
@@ -96,7 +116,10 @@ def dma(e, q):
     if q == 0:
         e("s_mov_b32 m0, s96")
         e("s_nop 0")
-    if q == A_DMA:
+    if q == A_DMA and PAIR:
+        e("s_mov_b32 m0, s79")
+        e("s_nop 0")
+    elif q == A_DMA:
         # B slots of this wave: A_STAGE further when a wave requests as many KiB of B as of A; otherwise the
         # distance is wave dependent and comes in as an operand (s85)
         e(f"s_add_u32 m0, s96, {A_STAGE}" if TM == TN else "s_add_u32 m0, s96, s85")
@@ -140,6 +163,44 @@ def advance_request_pointers(e):
     e("s_addc_u32 s89, s89, 0")
 
 
+def pair_advance(e, cond):
+    """request pointers: A to the next half, B to the next tile.  cond: None, or (value of s90 to skip the A advance at,
+    value to fix the offsets at)"""
+    for q in range(A_DMA):
+        e(f"v_swap_b32 v{AV + q}, v{AW + q}")
+    if cond is None:
+        e("s_add_u32 s86, s86, s70\\n s_addc_u32 s87, s87, 0")
+    else:
+        skip, fix = cond
+        e(f"s_cmp_eq_u32 s90, {skip}\\n s_cselect_b32 s78, 0, s70\\n s_add_u32 s86, s86, s78\\n s_addc_u32 s87, s87, 0")
+    e("s_xor_b32 s70, s70, 128")
+    if cond is not None:
+        e(f"s_cmp_lg_u32 s90, {fix}\\n s_cbranch_scc1 3f\\n " +
+          "\\n ".join((f"v_add_u32 v{v + q}, %[afix], v{v + q}\\n v_subrev_u32 v{v + q}, 64, v{v + q}" if q & 1 else
+                       f"v_sub_u32 v{v + q}, v{v + q}, %[afix]") for q in range(A_DMA) for v in (AV, AW)) + "\\n 3:")
+
+
+def pair_advance_b(e):
+    e("s_add_u32 s88, s88, s99\\n s_addc_u32 s89, s89, 0")
+
+
+def ring(e, reg, step, end, start):
+    """reg = reg + step, or start where that is end"""
+    e(f"s_add_u32 {reg}, {reg}, {step}\\n s_cmp_eq_u32 {reg}, {end}\\n s_cselect_b32 {reg}, {start}, {reg}")
+
+
+def pair_request_slots(e):
+    ring(e, "s96", A_STAGE, "s71", "s91")
+    ring(e, "s79", B_STAGE, "s72", "s83")
+
+
+def pair_read_bases(e):
+    """read bases of the next tile; the pair moves on when that is an even one"""
+    ring(e, "s77", B_STAGE, "s74", "s75")
+    e(f"s_xor_b32 s73, s73, {2 * A_STAGE}")
+    ring(e, "s76", "s73", "s75", "s92")
+
+
 def mfma(e, i, use):
     mb, nb = i // TN, i % TN
     e(f"v_mfma_i32_32x32x32_i8 %[c{i}], {vr(B[use] + 4 * nb)}, {vr(A[use] + 4 * mb)}, %[c{i}]")
@@ -151,7 +212,7 @@ def reads(e, slot, ld, ks):
         if j >= NREAD:
             continue
         if j < TM:
-            e(f"ds_read_b128 {vr(A[ld] + 4 * j)}, v{VA} offset:{j * 2048}")
+            e(f"ds_read_b128 {vr(A[ld] + 4 * j)}, v{VA} offset:{j * (4096 if PAIR else 2048)}")
         else:
             nb = j - TM
             e(f"ds_read_b128 {vr(B[ld] + 4 * nb)}, v{VB} offset:{nb * 2048 + ks * 512}")
@@ -184,11 +245,15 @@ def prep(e, slot, ld):
             e(f"v_xor_b32 v{base + c}, s84, v{base + c}")
 
 
-def step(e, use, ks_load, request, next_va, load=True):
+def step(e, use, ks_load, request, next_va, load=True, early=(), late=()):
     """TM*TN MFMAs on fragment set `use`; meanwhile fetch the next k-step's fragments into the other set
     (k-step ks_load of the stage VA/VB point at), row-sum and shift its A fragments, and optionally
-    issue the tile requests.  next_va: which A offset (0/1) the NEXT step's reads use."""
+    issue the tile requests.  next_va: which A offset (0/1) the NEXT step's reads use.
+    PAIR: scalar work (groups that stay together) in the slots that hold neither reads nor row sums -- `early`, which the
+    next read addresses need, then `late`, what is left of it behind those."""
     ld = 1 - use
+    early, late = list(early), list(late)
+    move_on = prep_slots()[0] - 1 if early else RSLOTS + 1
     for slot in range(NM):
         mfma(e, slot, use)
         if load and slot < RSLOTS:
@@ -197,11 +262,20 @@ def step(e, use, ks_load, request, next_va, load=True):
             dma(e, slot)
         if load and slot >= prep_slots()[0]:
             prep(e, slot, ld)
-        if slot == RSLOTS + 1 and next_va is not None:
+        if early and slot >= RSLOTS:
+            for _ in range(-(-len(early) // (move_on + 1 - slot))):
+                e(early.pop(0))
+        elif late and slot >= RSLOTS:
+            for _ in range(-(-len(late) // (NM - slot))):
+                e(late.pop(0))
+        if slot == move_on and next_va is not None:
             # all reads of this step are issued: point v240/v241 at the next step's fragments
-            e(f"v_add_u32 v{VA}, s98, v{ARD0 if next_va == 0 else ARD1}")
+            if PAIR and next_va == 0:  # the next tile is the other one of its pair: chunk bit 2
+                e(f"v_xor_b32 v{ARD0}, 64, v{ARD0}")
+                e(f"v_xor_b32 v{ARD1}, 64, v{ARD1}")
+            e(f"v_add_u32 v{VA}, {'s76' if PAIR else 's98'}, v{ARD0 if next_va == 0 else ARD1}")
             if next_va == 0:
-                e(f"v_add_u32 v{VB}, s98, v{BRD}")
+                e(f"v_add_u32 v{VB}, {'s77' if PAIR else 's98'}, v{BRD}")
 
 
 def wrap_stage(e, reg):
@@ -233,6 +307,9 @@ def rotate_stage(e):
 
 
 def tile(e, wait_vm, request, last=False):
+    if PAIR:
+        tile_pair(e, wait_vm, request, last)
+        return
     # k-step 0 of tile t: consume set 0, fetch (t, 1) into set 1 from the current stage
     step(e, use=0, ks_load=1, request=False, next_va=None if last else 0)
     if last:
@@ -250,6 +327,26 @@ def tile(e, wait_vm, request, last=False):
     if request:
         advance_request_pointers(e)
     rotate_stage(e)
+    e("s_waitcnt lgkmcnt(0)")
+
+
+def tile_pair(e, wait_vm, request, last):
+    """tile() of the PAIR loops: the same steps and waits; the pointers are moved on in the first k step, behind its reads"""
+    early, late = Emit(), Emit()
+    if not last:
+        pair_read_bases(early)
+    if request:
+        pair_advance(late, ("s80", "s81"))
+        pair_advance_b(late)
+        pair_request_slots(late)
+    step(e, use=0, ks_load=1, request=False, next_va=None if last else 0, early=early.lines, late=late.lines)
+    if last:
+        e("s_waitcnt lgkmcnt(0)")
+        step(e, use=1, ks_load=0, request=False, next_va=None, load=False)
+        return
+    e(f"s_waitcnt vmcnt({wait_vm}) lgkmcnt(0)")
+    e("s_barrier")
+    step(e, use=1, ks_load=0, request=request, next_va=1)
     e("s_waitcnt lgkmcnt(0)")
 
 
@@ -280,6 +377,10 @@ def generate_loop(rowsum, conv=False):
         e(f"v_mov_b64 v[{AV}:{AV + 1}], %[av01]")
     if TM == 4:
         e(f"v_mov_b64 v[{AV + 2}:{AV + 3}], %[av23]")
+    if PAIR:
+        e(f"v_mov_b64 v[{AW}:{AW + 1}], %[aw01]")
+        if TM == 4:
+            e(f"v_mov_b64 v[{AW + 2}:{AW + 3}], %[aw23]")
     e(f"v_mov_b64 v[{BV}:{BV + 1}], %[bv01]")
     if TM == 4:
         e(f"v_mov_b64 v[{BV + 2}:{BV + 3}], %[bv23]")
@@ -298,19 +399,49 @@ def generate_loop(rowsum, conv=False):
     for f in range(TM):
         e(f"v_mov_b32 v{RS + f}, 0")
     # ---- request tiles 0..NSTAGE-1 into stages 0..NSTAGE-1
-    for st in range(NSTAGE):
-        e(f"s_add_u32 s96, s91, {st * STAGE_BYTES}")
-        for q in range(N_DMA):
-            dma(e, q)
-        advance_request_pointers(e)
-    e("s_mov_b32 s93, 0")
-    e("s_mov_b32 s97, s92")
-    e(f"s_add_u32 s98, s92, {STAGE_BYTES}")
+    if PAIR:
+        e("s_mov_b32 s70, 0")
+        for half in range(NSTAGE + 1):
+            e(f"s_add_u32 s96, s91, {half * A_STAGE}")
+            for q in range(A_DMA):
+                dma(e, q)
+            if half < NSTAGE:  # (behind the last one: in the first tile)
+                pair_advance(e, ("0", "1") if half == NSTAGE - 1 else None)
+            if half > 0:
+                e(f"s_add_u32 s79, s91, {6 * A_STAGE + (half - 1) * B_STAGE}")
+                for q in range(A_DMA, N_DMA):
+                    dma(e, q)
+                if half < NSTAGE:
+                    pair_advance_b(e)
+        # an even number of tiles: skip the advance in the last tile that requests (s90 == 1); an odd one: fix the offsets
+        # in the one before, in front of the requests for the last pair (s90 == 2)
+        e("s_and_b32 s78, s90, 1")
+        e("s_cmp_eq_u32 s78, 0\\n s_cselect_b32 s80, 1, -1\\n s_cselect_b32 s81, -1, 2")
+        e(f"s_add_u32 s71, s91, {6 * A_STAGE}")
+        e("s_mov_b32 s83, s71")
+        e(f"s_add_u32 s72, s83, {4 * B_STAGE}")
+        e(f"s_mov_b32 s73, {2 * A_STAGE}")
+        e(f"s_add_u32 s75, s92, {6 * A_STAGE}")
+        e(f"s_add_u32 s74, s75, {4 * B_STAGE}")
+        e("s_mov_b32 s76, s92")
+        e("s_mov_b32 s77, s75")
+        e("s_mov_b32 s97, s92")
+    else:
+        for st in range(NSTAGE):
+            e(f"s_add_u32 s96, s91, {st * STAGE_BYTES}")
+            for q in range(N_DMA):
+                dma(e, q)
+            advance_request_pointers(e)
+        e(f"s_add_u32 s98, s92, {STAGE_BYTES}")
+        e("s_mov_b32 s93, 0")
+        e("s_mov_b32 s97, s92")
     e(f"s_waitcnt vmcnt({(NSTAGE - 1) * N_DMA})")
     e("s_barrier")
     # ---- fragments (0, 0) into set 0
     e(f"v_add_u32 v{VA}, s97, v{ARD0}")
     e(f"v_add_u32 v{VB}, s97, v{BRD}")
+    if PAIR:
+        e(f"v_add_u32 v{VB}, {6 * A_STAGE}, v{VB}")
     for slot in range(RSLOTS):
         reads(e, slot, 0, 0)
     for f in range(TM):
@@ -350,7 +481,7 @@ def generate():
     out = "// GENERATED by gen_tile_loop.py -- do not edit.\n"
     for tm, tn, nstage, suffix in ((4, 4, 4, ""), (2, 2, 4, "_2X2"), (2, 4, 3, "_2X4")):
         configure(tm, tn, nstage)
-        clob = [f'"v{i}"' for i in range(FIRST_VGPR, LAST_VGPR + 1)] + [f'"s{i}"' for i in range(84, 100)] + \
+        clob = [f'"v{i}"' for i in range(FIRST_VGPR, LAST_VGPR + 1)] + [f'"s{i}"' for i in range(70 if PAIR else 84, 100)] + \
                ['"scc"', '"memory"']
         for name, rowsum in (("QG_TILE_LOOP_ASM", True), ("QG_TILE_LOOP_ASM_NOROWSUM", False)):
             out += (f"#define {name}{suffix} \\\n" +
