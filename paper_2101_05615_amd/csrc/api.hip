@@ -150,17 +150,29 @@ double tile_estimate(const tile_cost& c, int M, int N, int K) {
   return us;
 }
 
-int builtin_select(int M, int N, int K) {
+// The 128 x 64 form of QG_KERNEL_TILE128 (at most one tile per CU): fitted to 128 shapes, M 96 .. 1024 x N, K 1024 .. 8192;
+// where the choice falls on it, it is up to 1.35x faster than the best of the others (256 x 8192 x 8192), at worst 1.01x slower.
+const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.4, 0.145, 0.0, 0.0};
+
+// a_words: rows of A start at multiples of 4 bytes.  From other addresses the tile requests run at a third of their rate
+// whatever the tile (32 bytes per cycle and CU against 75 to 97), which leaves the small form of TILE128 behind the 64 x 64
+// tiles, that more CUs share (999 x 1531 x 2047 13.9 us against 13.6): it is then not considered, and only tiled kernels are
+// compared (a streaming one would want a workspace that nobody was told of).
+int builtin_select(int M, int N, int K, bool a_words = true) {
+  const bool few = qg_tile128_few(M, N, K);
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  for (const stream_cost& c : k_stream_cost) {
-    const long long blocks = ceil_div(M, c.rows);
-    if (blocks > 65535) continue;
-    const double us = stream_estimate(c, M, N, K, true);
-    if (us < best_us) best_us = us, best = c.kernel;
-  }
+  if (a_words || !few || builtin_select(M, N, K) != QG_KERNEL_TILE128)
+    for (const stream_cost& c : k_stream_cost) {
+      const long long blocks = ceil_div(M, c.rows);
+      if (blocks > 65535) continue;
+      const double us = stream_estimate(c, M, N, K, true);
+      if (us < best_us) best_us = us, best = c.kernel;
+    }
   for (const tile_cost& c : k_tile_cost) {
-    const double us = tile_estimate(c, M, N, K);
+    const bool few_form = few && c.kernel == QG_KERNEL_TILE128;
+    if (few_form && !a_words) continue;
+    const double us = tile_estimate(few_form ? k_tile128_few_cost : c, M, N, K);
     if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
@@ -193,12 +205,12 @@ int select_stream_kernel(int M, int N, int K) {
   return best;
 }
 
-int select_kernel(int M, int N, int K) {
+int select_kernel(int M, int N, int K, bool a_words = true) {
   for (int i = 0; i < g_nrules; ++i) {
     const qg_dispatch_rule& r = g_rules[i];
     if (M >= r.m_lo && M <= r.m_hi && N >= r.n_lo && N <= r.n_hi && K >= r.k_lo && K <= r.k_hi) return r.kernel;
   }
-  return builtin_select(M, N, K);
+  return builtin_select(M, N, K, a_words);
 }
 
 hipError_t launch_rows(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
@@ -230,7 +242,7 @@ hipError_t launch_gemm(const qg_gemm_args& a, int mode, int kernel, hipStream_t 
 
 // resolves QG_KERNEL_AUTO for a descriptor and checks an explicit choice against it: QG_OK, or
 // QG_EINVAL (unknown id / too many row blocks), QG_EUNSUPPORTED (tiled kernel on a split descriptor)
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel);
+int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool a_words = true);
 
 // kernel id valid for this M (the streaming kernels put row blocks on the 16-bit grid dimension)
 bool kernel_ok(int kernel, int M) {
@@ -240,7 +252,7 @@ bool kernel_ok(int kernel, int M) {
   return true;
 }
 
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel) {
+int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool a_words) {
   if (!kernel_ok(*kernel, M)) return QG_EINVAL;
   if (Bp->split) {
     if (*kernel == QG_KERNEL_AUTO) *kernel = select_stream_kernel(M, Bp->N, Bp->K);
@@ -248,8 +260,8 @@ int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel) {
     return kernel_ok(*kernel, M) ? QG_OK : QG_EINVAL;
   }
   if (*kernel == QG_KERNEL_AUTO) {
-    *kernel = select_kernel(M, Bp->N, Bp->K);
-    if (!kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K);
+    *kernel = select_kernel(M, Bp->N, Bp->K, a_words);
+    if (!kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K, a_words);
   }
   return QG_OK;
 }
@@ -660,7 +672,7 @@ static int gemm_requant(const uint8_t* A_dev, int M, int lda, const qg_packed_b*
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel);
+  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_requant(p, Bp->N);
@@ -725,7 +737,7 @@ static int gemm_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* B
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel);
+  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
   if (rc != QG_OK) return rc;
   if (!C32_dev && M != 0) return QG_ENULL;
   if (ldc < Bp->N) return QG_EINVAL;
@@ -771,7 +783,7 @@ int qg_gemm_u8s8_dequant_f32(const uint8_t* A_dev, int M, int lda, const qg_pack
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel);
+  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_dequant(p, Bp->N);

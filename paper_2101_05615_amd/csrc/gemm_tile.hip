@@ -26,7 +26,8 @@
 // problem mapped to one of them): 256 x 256, 128 x 256 and 128 x 128 with a hand-scheduled loop (one
 // generator, three register tiles; four LDS stages, three for 128 x 256 so that two workgroups share a CU),
 // and 64 x 64 with a compiler-scheduled three-stage loop, several workgroups per CU, for shapes that would
-// leave most CUs idle at the larger tiles; the compiler-scheduled loop also serves the dense convolution and
+// leave most CUs idle at the larger tiles; the 128 x 128 kernel has a second form for at most one tile per CU, 128 x 64 with
+// four sets of two waves that split K, on the same hand-scheduled loop (DIST below); the compiler-scheduled loop also serves the dense convolution and
 // K below the pipeline depth of the hand-scheduled one.  The 64 x 64 workgroup has two or four sets of four
 // waves that take alternate k tiles and add their accumulators at the end.
 #include "qg_internal.h"
@@ -41,7 +42,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 constexpr int BK = 64;      // k extent of one LDS stage = one packed fragment deep
 constexpr int NSTAGE = 4;   // LDS stages of the hand-scheduled loop: three tiles in flight behind the one being consumed
 // (three stages, two tiles in flight, for the 128 x 256 tile, so that two workgroups fit the LDS of a CU)
-constexpr int asm_stages(int blocks) { return blocks == 8 ? 3 : NSTAGE; }
+// (three stages also for each of the four wave sets of the 128 x 64 tile: 144 KiB)
+constexpr int asm_stages(int blocks, int sets = 1) { return blocks == 8 || sets > 1 ? 3 : NSTAGE; }
 // LDS stages of the compiler-scheduled loop, by 32 x 32 blocks per wave.  Three everywhere: measured with 3 to 8
 // stages, a thin grid's k step (0.28 us at 64 x 64) does not get shorter with more tiles in flight -- it is the
 // barrier / LDS read / MFMA chain of a lone workgroup -- while deeper buffers cost occupancy on full grids.
@@ -85,8 +87,9 @@ __device__ __forceinline__ int a_lds_off(int r, int kc) { return r * BK + ((kc ^
 // time.  Requested 64 bytes per row and k tile, every line came from the L2 twice (6.4 GB at 8192^3, now 4.3).  8192^3 472 -> 449 us.
 constexpr bool pair_a(int path, int tm, int tn, int conv) { return path == PATH_ASM && tm == 4 && tn == 4 && conv == 0; }
 // bytes of LDS the main loop uses
-constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair) {
-  return pair ? 6 * (bm * BK) + NSTAGE * (bn * BK) : (path == PATH_ASM ? asm_stages(blocks) : pipe_stages(blocks)) * (bm + bn) * BK;
+constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair, int sets) {
+  return pair ? 6 * (bm * BK) + NSTAGE * (bn * BK)
+              : (path == PATH_ASM ? asm_stages(blocks, sets) : pipe_stages(blocks)) * sets * (bm + bn) * BK;
 }
 
 // operand list shared by the two generated loop variants (gen_tile_loop.py)
@@ -108,6 +111,16 @@ constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair) {
                    [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
                    [lds] "s"(lds_base), [bstep] "s"(b_step) \
                  : QG_TILE_LOOP_CLOBBERS_2X2
+
+#define QG_TILE_LOOP_OPERANDS_2X2K4 \
+                 : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[1][0]), [c3] "+a"(acc[1][1]), \
+                   [rs01] "=v"(rs01) \
+                 : [av01] "v"(av01), [av23] "v"(av23), [bv01] "v"(bv01), [ard] "v"(pard), [brd] "v"(pbrd), \
+                   [aptr] "s"(A + (wave_all >> 2) * 128 - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0 + (size_t)kg * b_step), \
+                   [kt] "s"(KTF / KS), [ldsdma] "s"(lds_base + wave_all * (A_DMA * 1024)), [lds] "s"(lds_base), \
+                   [bstep] "s"(b_step * KS), \
+                   [bofs] "s"(KS * A_STAGE + (kg * NW + wave) * (B_DMA * 1024) - wave_all * (A_DMA * 1024)) \
+                 : QG_TILE_LOOP_CLOBBERS_2X2K4
 
 #define QG_TILE_LOOP_OPERANDS_2X4 \
                  : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[0][2]), [c3] "+a"(acc[0][3]), \
@@ -185,7 +198,7 @@ constexpr int EPI_CLAMP = 0, EPI_SAT = 1, EPI_SAT0 = 2;
 // problem are fewer than the CUs and each would walk all of K alone.
 template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int CONV = 0, int KS = 1, int EPI = EPI_CLAMP,
           bool SPLIT = false>
-__global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) / KS) void qg_gemm_tile_kernel(
+__global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2 : min_wg_per_cu(PATH, TM * TN) / KS) void qg_gemm_tile_kernel(
     const uint8_t* A0, const int8_t* Bp, const int M, const int N, const int K0, const int nb16_total, const int lda,
     const int tiles_m, const int tiles_n, const qg_gemm_args p) {
   static_assert(!SPLIT || (PATH == PATH_ASM && TM == 2 && TN == 2 && CONV == 0 && KS == 1), "the cross-workgroup K split is built for the 128 x 128 tile");
@@ -193,7 +206,11 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
   const int k_first = SPLIT ? (int)blockIdx.y * p.ks_per : 0;  // in 64-deep tiles
   const uint8_t* const A = A0 + (SPLIT ? k_first * BK : 0);
   const int K = SPLIT ? min(K0 - k_first * BK, p.ks_per * BK) : K0;
-  static_assert(KS == 1 || ((KS == 2 || KS == 4 || KS == 8) && PATH == PATH_PIPE), "K split: wave sets on the pipelined path");
+  // DIST: the hand-scheduled 128 x 64 tile, four sets of two waves; when they add up, every set ends with one of the four
+  // 32 x 32 blocks of its waves' 64 x 64 and runs the output pipeline for that
+  constexpr bool DIST = PATH == PATH_ASM && KS == 4;
+  static_assert(KS == 1 || DIST || ((KS == 2 || KS == 4 || KS == 8) && PATH == PATH_PIPE), "K split: wave sets");
+  static_assert(!DIST || (NWM == 2 && NWN == 1 && TM == 2 && TN == 2 && CONV == 0 && !SPLIT), "generated for this tile");
   constexpr bool CVG = CONV == 2;  // per-chunk taps
   constexpr int NW = NWM * NWN, NT = NW * KS * 64;  // NW: waves of one set; NT: threads of the workgroup
   constexpr int BM = NWM * TM * 32, BN = NWN * TN * 32;
@@ -248,6 +265,11 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
       const unsigned in_row = (((lane & 7) ^ ((r >> 1) & 7)) << 4) + (A_DMA - 1 - q) * 1024;  // (see the bias below)
       a_voff[q] = (unsigned)min(m0 + r, M - 1) * (unsigned)lda + in_row;  // rows past M re-read the last row; never stored
       a_half1[q] = (unsigned)min(m0 + BM / 2 + r, M - 1) * (unsigned)lda + in_row;
+      continue;
+    }
+    if (DIST) {  // 8 rows x 128 B too; waves 0-3 fill the region of sets 0 and 1, waves 4-7 that of sets 2 and 3
+      const int r = ((wave_all & 3) * A_DMA + q) * 8 + (lane >> 3);
+      a_voff[q] = (unsigned)min(m0 + r, M - 1) * (unsigned)lda + (((lane & 7) ^ ((r >> 1) & 7)) << 4) + (A_DMA - 1 - q) * 1024;
       continue;
     }
     const int r = (wave * A_DMA + q) * 16 + (lane >> 2);
@@ -328,6 +350,28 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
   // registers afterwards, once per workgroup
   const int KTF = CVG ? KT : K / BK;  // (CVG: chunks past K are replaced like taps outside the image)
   v4i a0[TM], b0[TN], a1[TM], b1[TN];
+  // Tiles that the loop leaves over: a ragged last one and, DIST, those that do not make a step of all four sets, one per
+  // set.  Their loads are issued in front of the loop (300 x 1000 x 1000: a latency of 1.4 us behind it otherwise).
+  const int KTL = DIST ? KTF / KS * KS : KTF;    // tiles the loop does
+  const int ktl = DIST ? KTL + kg : KTF;         // the left-over tile of this set
+  const bool left = DIST ? ktl < KT : kg == 0;   // (with KTL < KT)
+  const size_t a_end = (size_t)(M - 1) * (size_t)lda + (size_t)K;  // one past the last byte A is known to have
+  auto left_off = [&](int q) {
+    const int r = (wave * A_DMA + q) * 16 + (lane >> 2);
+    return (size_t)min(m0 + r, M - 1) * (size_t)lda + (size_t)((((lane & 3) ^ a_swz(r)) << 4) + ktl * BK);
+  };
+  v4i left_a[DIST ? A_DMA : 1], left_b[DIST ? B_DMA : 1];
+  if constexpr (DIST) {
+    if (left) {
+#pragma unroll
+      for (int q = 0; q < A_DMA; ++q) {
+        const size_t off = left_off(q);
+        left_a[q] = *reinterpret_cast<const qg_v4i_unaligned*>(A + (off + 16 <= a_end ? off : 0));  // (0: loaded again below)
+      }
+#pragma unroll
+      for (int q = 0; q < B_DMA; ++q) left_b[q] = *reinterpret_cast<const v4i*>(b_tile0 + (size_t)ktl * b_step + b_voff[q]);
+    }
+  }
   if constexpr (PATH == PATH_ASM) {
     // Tile kt lives in stage kt % 4.  In iteration kt: the first k-step runs while the fragments of
     // the second are fetched; then every wave waits until ITS requests for tile kt+1 have landed
@@ -336,7 +380,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     // second k-step runs while the first fragments of tile kt+1 are fetched.  The loop is one
     // hand-scheduled asm statement (gen_tile_loop.py): behind every MFMA sit at most seven other
     // instructions, so LDS reads, row sums, shifts and tile requests issue in the MFMA's shadow.
-    static_assert(PATH != PATH_ASM || (NWM == 2 && NWN == 2 && BK == 64 && NSTAGE == 4 &&
+    static_assert(PATH != PATH_ASM || DIST || (NWM == 2 && NWN == 2 && BK == 64 && NSTAGE == 4 &&
                                        ((TM == 4 && TN == 4) || (TM == 2 && TN == 2) || (TM == 2 && TN == 4))),
                   "the scheduled loop is generated for these configurations");
     const unsigned long long av01 = a_voff[0] | ((unsigned long long)a_voff[1] << 32);
@@ -346,11 +390,15 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)smem);
     const unsigned lds_dma = lds_base + wave * (A_DMA * 1024);
     unsigned long long rs01;
-    // PAIR: LDS offsets of the fragments (A: pitch 128, this wave's half, k step 0 / 1 of an even tile; B: in its stage)
+    // PAIR: LDS offsets of the fragments (A: pitch 128, this wave's half, k step 0 / 1 of an even tile; B: in its stage);
+    // DIST: A in the region of its pair of sets, B behind the regions
     const int p_row = wave_m * TM * 32 + l32;
-    auto p_rd = [&](int ks) { return (unsigned)(p_row * 128 + (((ks * 2 + lg) ^ ((p_row >> 1) & 7)) << 4)); };
+    auto p_rd = [&](int ks) {
+      const int chunk = ks * 2 + lg + (DIST ? (kg & 1) * 4 : 0);
+      return (unsigned)((DIST ? (kg >> 1) * (2 * A_STAGE) : 0) + p_row * 128 + ((chunk ^ ((p_row >> 1) & 7)) << 4));
+    };
     const unsigned long long pard = p_rd(0) | ((unsigned long long)p_rd(1) << 32);
-    const unsigned long long pbrd = (unsigned)(b_rd - A_STAGE);
+    const unsigned long long pbrd = (unsigned)(b_rd - A_STAGE + (DIST ? KS * A_STAGE + kg * B_STAGE : 0));
     // 64 for the lanes whose chunk belongs to the odd tile of a pair in a request of even number, 0 for the others (in a
     // request of odd number the other way round: its rows are 8 further, which turns bit 2 of the chunk)
     const unsigned pair_fix = (lane & 4) << 4;
@@ -393,6 +441,12 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
         else
           asm volatile(QG_TILE_LOOP_ASM_CONV_NOROWSUM_2X4 QG_TILE_LOOP_OPERANDS_CONV_2X4);
       }
+    } else if constexpr (DIST) {
+      const unsigned long long av23 = a_voff[2] | ((unsigned long long)a_voff[3] << 32);
+      if (ROWSUM)
+        asm volatile(QG_TILE_LOOP_ASM_2X2K4 QG_TILE_LOOP_OPERANDS_2X2K4);
+      else
+        asm volatile(QG_TILE_LOOP_ASM_NOROWSUM_2X2K4 QG_TILE_LOOP_OPERANDS_2X2K4);
     } else if constexpr (TN == 2) {
       if (ROWSUM)
         asm volatile(QG_TILE_LOOP_ASM_2X2 QG_TILE_LOOP_OPERANDS_2X2);
@@ -508,28 +562,31 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     if (KS > 1 && KT2 > KTall) step(KTall, KTall < KTg);
   }
 
-  // ---- ragged last tile of the pipelined paths: bytes past K are staged as 0x80 (int8 zero after the shift)
-  if (KTF < KT) {
-    const int k0 = KTF * BK;
+  // ---- left-over tiles: bytes past K are staged as 0x80 (int8 zero after the shift)
+  if (KTL < KT) {
+    unsigned char* const st0 = smem + (DIST ? kg * STAGE : 0);
     __syncthreads();  // every wave is done with the stages
-    if (kg == 0) {
-      const size_t a_end = (size_t)(M - 1) * (size_t)lda + (size_t)K;  // one past the last byte A is known to have
+    if (left) {
 #pragma unroll
       for (int q = 0; q < A_DMA; ++q) {
-        const int r = (wave * A_DMA + q) * 16 + (lane >> 2);
-        const int kc = (lane & 3) ^ a_swz(r);
-        const size_t off = (size_t)min(m0 + r, M - 1) * (size_t)lda + (size_t)(kc * 16 + k0);
-        *reinterpret_cast<v4i*>(smem + (wave * A_DMA + q) * 1024 + lane * 16) =
-            qg_load_a_chunk(A + off, K - (k0 + kc * 16), off + 16 <= a_end);
+        const size_t off = left_off(q);
+        const int kvalid = K - ktl * BK - (((lane & 3) ^ a_swz((wave * A_DMA + q) * 16 + (lane >> 2))) << 4);
+        const bool safe = off + 16 <= a_end;
+        v4i v;
+        if (DIST && safe)
+          v = qg_mask_a_chunk(left_a[DIST ? q : 0], kvalid);
+        else
+          v = qg_load_a_chunk(A + off, kvalid, safe);
+        *reinterpret_cast<v4i*>(st0 + (wave * A_DMA + q) * 1024 + lane * 16) = v;
       }
-      const int8_t* b_base = b_tile0 + (size_t)KTF * b_step;
+      const int8_t* b_base = b_tile0 + (size_t)ktl * b_step;
 #pragma unroll
       for (int q = 0; q < B_DMA; ++q)
-        *reinterpret_cast<v4i*>(smem + A_STAGE + (wave * B_DMA + q) * 1024 + lane * 16) =
-            *reinterpret_cast<const v4i*>(b_base + b_voff[q]);
+        *reinterpret_cast<v4i*>(st0 + A_STAGE + (wave * B_DMA + q) * 1024 + lane * 16) =
+            DIST ? left_b[DIST ? q : 0] : *reinterpret_cast<const v4i*>(b_base + b_voff[q]);
     }
     __syncthreads();
-    if (kg == 0) {
+    if (left) {
       // (a convolution has no ragged tile: Cin % 64 == 0, or its last tile went through the loop above)
       fetch(0, 0, a0, b0);
       fetch(0, 1, a1, b1);
@@ -540,8 +597,44 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     }
   }
 
-  // ---- K split: the other wave sets hand their accumulators and byte sums to the first through LDS
-  if constexpr (KS > 1) {
+  // ---- K split: the wave sets add up through LDS.  DIST: every set hands three blocks to the sets they belong to and keeps
+  // one, (kg >> 1, kg & 1): a quarter of the output pipeline each
+  v16i own[1][1];
+  unsigned own_rs = 0;
+  if constexpr (DIST) {
+    constexpr int LANES = NW * 64, REGION = 16 * LANES;  // ints: 16 sums per lane, four at a time
+    constexpr int RED = 1024, RED_RS = RED + KS * (KS - 1) * REGION;  // past the per-column constants staged below; byte sums
+    static_assert((RED_RS + KS * (KS - 1) * LANES) * 4 <= loop_lds(PATH, BM, BN, TM * TN, false, KS), "partials must fit the stage memory");
+    __syncthreads();  // every wave is done with the stages
+    int* const red = reinterpret_cast<int*>(smem) + RED + (wave * 64 + lane) * 4;
+    int* const red_rs = reinterpret_cast<int*>(smem) + RED_RS + wave * 64 + lane;
+#pragma unroll
+    for (int d = 0; d < KS; ++d) {
+      if (d == kg) {
+        own[0][0] = acc[d >> 1][d & 1];
+        own_rs = rs[d >> 1];
+      } else {
+        const int region = d * (KS - 1) + (kg < d ? kg : kg - 1);
+#pragma unroll
+        for (int r = 0; r < 16; r += 4)
+          *reinterpret_cast<v4i*>(red + region * REGION + r * LANES) =
+              (v4i){acc[d >> 1][d & 1][r], acc[d >> 1][d & 1][r + 1], acc[d >> 1][d & 1][r + 2], acc[d >> 1][d & 1][r + 3]};
+        if (ROWSUM) red_rs[region * LANES] = (int)rs[d >> 1];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < KS - 1; ++g) {
+      const int region = kg * (KS - 1) + g;
+#pragma unroll
+      for (int r = 0; r < 16; r += 4) {
+        const v4i v = *reinterpret_cast<const v4i*>(red + region * REGION + r * LANES);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) own[0][0][r + i] += v[i];
+      }
+      if (ROWSUM) own_rs += (unsigned)red_rs[region * LANES];
+    }
+  } else if constexpr (KS > 1) {
     constexpr int PER_LANE = TM * TN * 16 + TM;
     constexpr int SET = PER_LANE * NW * 64;  // ints per handing set
     static_assert(4096 + (KS - 1) * SET * 4 <= NS * KS * STAGE, "partials must fit the stage memory");
@@ -577,9 +670,18 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
 
   // ---- row offsets: lane (m, k-half) holds half of row m's byte sum; every one of the KT*64 bytes
   // summed (padding reads as 0x80) is 128 above its int8 value
-  int rsum_s[TM];
+  constexpr int EM = DIST ? 1 : TM, EN = DIST ? 1 : TN;                            // blocks of this wave's output pipeline
+  const int em0 = wave_m * TM + (DIST ? kg >> 1 : 0), en0 = wave_n * TN + (DIST ? kg & 1 : 0);  // ... the first of them
+  v16i(&ea)[EM][EN] = [&]() -> v16i(&)[EM][EN] {
+    if constexpr (DIST)
+      return own;
+    else
+      return acc;
+  }();
+  if (DIST) rs[0] = own_rs;
+  int rsum_s[EM];
 #pragma unroll
-  for (int mb = 0; mb < TM; ++mb)
+  for (int mb = 0; mb < EM; ++mb)
     rsum_s[mb] = (int)(rs[mb] + (unsigned)__shfl_xor((int)rs[mb], 32)) - 128 * (KT * BK);
 
   // ---- K split across workgroups: hand the partial tile in, the last slice to arrive carries on
@@ -639,7 +741,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     bz_s[t] = -bz;  // negated: x = acc + cj + (-theta_B) * rowsum
   }
   __syncthreads();
-  if (KS > 1 && kg != 0) return;  // the first wave set holds the sums and runs the output pipeline
+  if (KS > 1 && !DIST && kg != 0) return;  // the first wave set holds the sums and runs the output pipeline
 
   // ---- epilogue straight from the accumulators.  Lane (l32, lg) of block (mb, nb) holds row
   // 32*mb + l32 and the 16 consecutive columns 32*nb + 16*lg .. +15; the per-column constants of a
@@ -648,8 +750,8 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     const bool full_cols = p.c_vec && (n0 + BN <= N);  // uniform: every 16-byte store is in range
     const float czp_f = (float)p.c_zp;
 #pragma unroll
-    for (int nb = 0; nb < TN; ++nb) {
-      const int col_l = (wave_n * TN + nb) * 32 + lg * 16;
+    for (int nb = 0; nb < EN; ++nb) {
+      const int col_l = (en0 + nb) * 32 + lg * 16;
       const int col = n0 + col_l;
       int cj[16], nbz[16];
       float sc[16];
@@ -660,8 +762,8 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
         *reinterpret_cast<float4*>(&sc[4 * q]) = *reinterpret_cast<const float4*>(&sc_s[col_l + 4 * q]);
       }
 #pragma unroll
-      for (int mb = 0; mb < TM; ++mb) {
-        const int row = m0 + (wave_m * TM + mb) * 32 + l32;
+      for (int mb = 0; mb < EM; ++mb) {
+        const int row = m0 + (em0 + mb) * 32 + l32;
         const int rsum = rsum_s[mb];
         if (MODE == QG_MODE_REQUANT) {
           unsigned out[4];
@@ -671,7 +773,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               const int i = 4 * q + t;
-              const int x = acc[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
+              const int x = ea[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
               if constexpr (EPI == EPI_SAT0)
                 w = qg_requant_pack0(x, sc[i], t, w);
               else
@@ -698,7 +800,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
           float out[16];
 #pragma unroll
           for (int i = 0; i < 16; ++i) {
-            const int x = acc[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
+            const int x = ea[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
             out[i] = qg_dequant_one(x, sc[i], p.relu_lo);
           }
           if (row < M) {
@@ -724,19 +826,19 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
     }
   } else {
 #pragma unroll
-    for (int mb = 0; mb < TM; ++mb) {
-      const int row = m0 + (wave_m * TM + mb) * 32 + l32;
+    for (int mb = 0; mb < EM; ++mb) {
+      const int row = m0 + (em0 + mb) * 32 + l32;
       if (row >= M) continue;
-      if (p.rowsum_out != nullptr && tn == 0 && wave_n == 0 && lg == 0)
+      if (p.rowsum_out != nullptr && tn == 0 && en0 == 0 && lg == 0)
         p.rowsum_out[row] = rsum_s[mb] + 128 * K0;
 #pragma unroll
-      for (int nb = 0; nb < TN; ++nb) {
-        const int col_l = (wave_n * TN + nb) * 32 + lg * 16;
+      for (int nb = 0; nb < EN; ++nb) {
+        const int col_l = (en0 + nb) * 32 + lg * 16;
         const int col = n0 + col_l;
         int32_t* dst = p.C32 + (size_t)row * p.ldc + col;
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (col + i < N) dst[i] = acc[mb][nb][i] + cj_s[col_l + i];
+          if (col + i < N) dst[i] = ea[mb][nb][i] + cj_s[col_l + i];
       }
     }
   }
@@ -745,7 +847,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, min_wg_per_cu(PATH, TM * TN) /
 template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int KS = 1, int EPI = EPI_CLAMP>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr int BM = NWM * TM * 32, BN = NWN * TN * 32;
-  constexpr int LOOP = loop_lds(PATH, BM, BN, TM * TN, pair_a(PATH, TM, TN, 0)) * KS;
+  constexpr int LOOP = loop_lds(PATH, BM, BN, TM * TN, pair_a(PATH, TM, TN, 0), KS);
   // the output pipeline's per-column constants (12 B per column) reuse the stage memory
   constexpr int SMEM = LOOP > 12 * BN ? LOOP : 12 * BN;
   const int tiles_m = (a.M + BM - 1) / BM;
@@ -859,6 +961,7 @@ hipError_t qg_launch_gemm_tile(const qg_gemm_args& a, int mode, int kernel, hipS
   switch (kernel) {
     case QG_KERNEL_TILE64: return launch_cfg<PATH_PIPE, 2, 2, 1, 1, 2>(a, mode, s);  // two wave sets split K
     case QG_KERNEL_TILE128:
+      if (a.ksplit <= 1 && qg_tile128_few(a.M, a.N, a.K)) return launch_cfg<PATH_ASM, 2, 1, 2, 2, 4>(a, mode, s);
       if (a.K >= NSTAGE * BK) return launch_cfg<PATH_ASM, 2, 2, 2, 2>(a, mode, s);
       return launch_cfg<PATH_PIPE, 2, 2, 2, 2>(a, mode, s);
     case QG_KERNEL_TILE128X256:

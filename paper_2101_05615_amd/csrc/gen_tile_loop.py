@@ -28,6 +28,12 @@ two and the row sums and shifts of both A fragments behind the last two.  A thir
 tile: 8 accumulators, three 24 KiB stages so that two workgroups share a CU, fixed registers from v56, one more
 SGPR input bofs = distance from a wave's A request slots to its B request slots), has eight MFMAs per k-step.
 
+Fourth, the 2 x 2 loop for a set of only two waves (128 x 64 tile, four sets that split K, three 48 KiB stages of four k
+tiles): A is requested by all eight waves together, 128 bytes = two tiles of a row at a time (the L1 looks up one line
+per cycle whether 64 or 128 bytes of it are wanted: 55 against 86 bytes per cycle measured), into 16 KiB regions of 128
+rows x 128 bytes that two sets share; a wave makes four requests of A and two of its set's B per step (inputs av23 and bofs
+as well) and moves on by 256 bytes of A (ASTEP) and four slabs of B (bstep).  Rows are 128 bytes apart (A_BLOCK).
+
 PAIR (4 x 4): A is requested 128 bytes of a row at a time -- two k tiles, one whole cache line --, one half of the
 tile's rows per k tile.  Requesting 64 bytes per row and tile fetched every line twice: the other half had left the 32 KB
 L1 by the time it was asked for (6.4 GB from the L2s instead of 4.3 at 8192^3), and this tile is limited by power, not by
@@ -60,10 +66,11 @@ VGPR), aptr = image, tab = row of theta_A bytes (64-bit SGPR), nc, fs (S), rowju
 """
 import os
 
-def configure(tm, tn, nstage=4, conv=False):
-    """sets the module-level plan for TM x TN blocks of 32 x 32 per wave (2 x 2 waves per workgroup)"""
+def configure(tm, tn, nstage=4, conv=False, nwn=2, sets=1):
+    """sets the module-level plan for TM x TN blocks of 32 x 32 per wave (2 x nwn waves per set, `sets` wave sets that
+    take every sets-th k tile from stages of their own)"""
     global TM, TN, NM, A, B, RS, AV, BV, ARD0, ARD1, BRD, VA, VB, STAGE_BYTES, A_STAGE, A_DMA, N_DMA, NREAD, RSLOTS
-    global AW, PAIR, B_STAGE
+    global AW, PAIR, B_STAGE, B_DMA, ASTEP, A_BLOCK
     global FIRST_VGPR, LAST_VGPR, NSTAGE, CT, APIX, AMASK, TABLO, TABHI, IMGHI
     assert (tm, tn) in ((4, 4), (2, 2), (2, 4)) and nstage in (3, 4)
     TM, TN, NM, NSTAGE = tm, tn, tm * tn, nstage
@@ -79,14 +86,16 @@ def configure(tm, tn, nstage=4, conv=False):
     VA, VB = BV + 8, BV + 9
     PAIR = tm == 4
     AW = VB + 1                                     # PAIR: the offsets of the half that is not due next
-    B_STAGE = tn * 4096
+    B_STAGE = nwn * tn * 2048
+    ASTEP = 64 * sets                               # bytes of a row of A from one tile of a set to its next
     FIRST_VGPR, LAST_VGPR = base, 255 if tm == 4 else VB
     CT = VB + 1 + ((VB + 1) & 1)                    # CONV: even-aligned address pairs of the two A requests
     APIX, AMASK, TABLO, TABHI, IMGHI = CT + 4, CT + 6, CT + 8, CT + 10, CT + 11
     A_STAGE = tm * 4096                             # 64 * TM rows of 64 bytes
-    STAGE_BYTES = (tm + tn) * 4096
-    A_DMA = tm                                      # 1 KiB requests per wave and tile: TM for A, then TN for B
-    N_DMA = tm + tn
+    STAGE_BYTES = (A_STAGE + B_STAGE) * sets
+    A_BLOCK = 4096 if PAIR or sets > 1 else 2048    # LDS bytes of 32 rows of A
+    A_DMA, B_DMA = 2 * tm // nwn, tn                # 1 KiB requests per wave and tile: A, then B
+    N_DMA = A_DMA + B_DMA
     NREAD = tm + tn                                 # LDS reads per k-step
     RSLOTS = (NREAD + 1) // 2                       # slots that carry them, two each
 
@@ -122,7 +131,7 @@ def dma(e, q):
     elif q == A_DMA:
         # B slots of this wave: A_STAGE further when a wave requests as many KiB of B as of A; otherwise the
         # distance is wave dependent and comes in as an operand (s85)
-        e(f"s_add_u32 m0, s96, {A_STAGE}" if TM == TN else "s_add_u32 m0, s96, s85")
+        e(f"s_add_u32 m0, s96, {A_STAGE}" if A_DMA == B_DMA else "s_add_u32 m0, s96, s85")
         e("s_nop 0")
     if q < A_DMA and CONV:
         lo, hi = CT + 2 * q, CT + 2 * q + 1
@@ -157,7 +166,7 @@ def advance_request_pointers(e):
         e("s_cselect_b32 s79, s77, 0")
         e("s_add_u32 s72, s72, s79")
     else:
-        e("s_add_u32 s86, s86, 64")
+        e(f"s_add_u32 s86, s86, {ASTEP}")
         e("s_addc_u32 s87, s87, 0")
     e("s_add_u32 s88, s88, s99")
     e("s_addc_u32 s89, s89, 0")
@@ -212,7 +221,7 @@ def reads(e, slot, ld, ks):
         if j >= NREAD:
             continue
         if j < TM:
-            e(f"ds_read_b128 {vr(A[ld] + 4 * j)}, v{VA} offset:{j * (4096 if PAIR else 2048)}")
+            e(f"ds_read_b128 {vr(A[ld] + 4 * j)}, v{VA} offset:{j * A_BLOCK}")
         else:
             nb = j - TM
             e(f"ds_read_b128 {vr(B[ld] + 4 * nb)}, v{VB} offset:{nb * 2048 + ks * 512}")
@@ -258,8 +267,10 @@ def step(e, use, ks_load, request, next_va, load=True, early=(), late=()):
         mfma(e, slot, use)
         if load and slot < RSLOTS:
             reads(e, slot, ld, ks_load)
-        if request and slot < N_DMA:
-            dma(e, slot)
+        per = -(-N_DMA // NM)
+        for q in range(slot * per, min(slot * per + per, N_DMA)):
+            if request:
+                dma(e, q)
         if load and slot >= prep_slots()[0]:
             prep(e, slot, ld)
         if early and slot >= RSLOTS:
@@ -375,7 +386,7 @@ def generate_loop(rowsum, conv=False):
         e("s_mov_b32 s80, %[tapjump]")
     else:
         e(f"v_mov_b64 v[{AV}:{AV + 1}], %[av01]")
-    if TM == 4:
+    if A_DMA == 4:
         e(f"v_mov_b64 v[{AV + 2}:{AV + 3}], %[av23]")
     if PAIR:
         e(f"v_mov_b64 v[{AW}:{AW + 1}], %[aw01]")
@@ -387,7 +398,7 @@ def generate_loop(rowsum, conv=False):
     e(f"v_mov_b64 v[{ARD0}:{ARD1}], %[ard]")
     e(f"v_mov_b64 v[{BRD}:{BRD + 1}], %[brd]")
     e("s_mov_b32 s84, 0x80808080")
-    if TM != TN:
+    if A_DMA != B_DMA:
         e("s_mov_b32 s85, %[bofs]")
     if not conv:
         e("s_mov_b64 s[86:87], %[aptr]")
@@ -495,6 +506,12 @@ def generate():
                 out += (f"#define {name}{suffix} \\\n" +
                         "".join(f'  "{l}\\n" \\\n' for l in generate_loop(rowsum, conv=True)) + "  \"\"\n")
             out += f"#define QG_TILE_LOOP_CLOBBERS_CONV{suffix} " + ", ".join(clob) + "\n"
+    # the 128 x 64 tile: 64 x 64 per wave, four sets of two waves
+    configure(2, 2, 3, nwn=1, sets=4)
+    clob = [f'"v{i}"' for i in range(FIRST_VGPR, LAST_VGPR + 1)] + [f'"s{i}"' for i in range(84, 100)] + ['"scc"', '"memory"']
+    for name, rowsum in (("QG_TILE_LOOP_ASM_2X2K4", True), ("QG_TILE_LOOP_ASM_NOROWSUM_2X2K4", False)):
+        out += f"#define {name} \\\n" + "".join(f'  "{l}\\n" \\\n' for l in generate_loop(rowsum)) + "  \"\"\n"
+    out += "#define QG_TILE_LOOP_CLOBBERS_2X2K4 " + ", ".join(clob) + "\n"
     configure(4, 4)
     return out
 

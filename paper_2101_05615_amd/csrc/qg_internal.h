@@ -177,6 +177,17 @@ static __device__ const qg_byte_rows_t qg_byte_rows = qg_make_byte_rows();  // o
 typedef int qg_v4i __attribute__((ext_vector_type(4)));
 typedef qg_v4i qg_v4i_unaligned __attribute__((aligned(1)));  // a 16-byte load from any address (one instruction)
 
+// the first `kvalid` bytes of v, 0x80 behind them
+__device__ __forceinline__ qg_v4i qg_mask_a_chunk(qg_v4i v, int kvalid) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int nb = min(max(kvalid - 4 * j, 0), 4);  // valid bytes of this dword
+    const unsigned keep = nb == 4 ? 0xFFFFFFFFu : ((1u << (8 * nb)) - 1u);
+    v[j] = (int)(((unsigned)v[j] & keep) | (0x80808080u & ~keep));
+  }
+  return v;
+}
+
 // 16 bytes of a row of A of which the first `kvalid` belong to the matrix; the rest reads as 0x80 (the int8
 // zero after the uint8 -> int8 shift).  `safe`: all 16 bytes lie inside the caller's buffer, so one vector
 // load and a byte mask do; otherwise byte by byte with bounds checks.  Any address.
@@ -191,14 +202,7 @@ __device__ __forceinline__ qg_v4i qg_load_a_chunk(const uint8_t* p, int kvalid, 
     for (int i = 0; i < 16; ++i) u.b[i] = (i < kvalid) ? p[i] : (uint8_t)0x80;
     return u.v;
   }
-  qg_v4i v = *reinterpret_cast<const qg_v4i_unaligned*>(p);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int nb = min(max(kvalid - 4 * j, 0), 4);  // valid bytes of this dword
-    const unsigned keep = nb == 4 ? 0xFFFFFFFFu : ((1u << (8 * nb)) - 1u);
-    v[j] = (int)(((unsigned)v[j] & keep) | (0x80808080u & ~keep));
-  }
-  return v;
+  return qg_mask_a_chunk(*reinterpret_cast<const qg_v4i_unaligned*>(p), kvalid);
 }
 
 // Requantization of one corrected int32 accumulator, the fixed fp32 sequence of the output pipeline
@@ -256,6 +260,15 @@ __device__ __forceinline__ float qg_dequant_one(int x, float sc, float lo) {
 
 // host side of qg_requant_needs_lo (clamp_lo == 0 means ReLU: lo - theta_C with lo = theta_C)
 static inline bool qg_requant_needs_lo_host(float clamp_lo, int c_zp) { return clamp_lo == 0.0f && c_zp != 0; }
+
+// QG_KERNEL_TILE128 has two forms.  With at most one 128 x 64 tile per CU, 128 x 64 on eight waves: four sets of two waves of
+// 64 x 64 each split K, so that all CUs stream the weights and no workgroup walks K alone; otherwise 128 x 128 on four waves.
+// 12 k tiles fill the pipeline of the four sets.  Cold or far weights, 128 x 128 -> 128 x 64: 256 x 8192 x 8192 29.6 -> 23.7
+// us, 512 x 4096 x 8192 30.2 (64 x 64 tiles) -> 23.3, 256 x 4096 x 4096 16.6 -> 12.0, 1024 x 1024 x 1024 6.5 -> 5.8; with
+// more tiles than CUs the first form wins (2048^3 12.5 against 17.7).
+static inline bool qg_tile128_few(int M, int N, int K) {
+  return (long long)((M + 127) / 128) * ((N + 63) / 64) <= 256 && K >= 12 * QG_FRAG_K;
+}
 
 #ifdef __HIPCC__
 // Raises kernel Fn's dynamic-LDS limit to `bytes` on the current device unless that was already done: the
