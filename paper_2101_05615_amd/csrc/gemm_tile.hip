@@ -100,15 +100,15 @@ constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair, int sets
                    [c12] "+a"(acc[3][0]), [c13] "+a"(acc[3][1]), [c14] "+a"(acc[3][2]), [c15] "+a"(acc[3][3]), \
                    [rs01] "=v"(rs01), [rs23] "=v"(rs23) \
                  : [av01] "v"(av01), [av23] "v"(av23), [aw01] "v"(aw01), [aw23] "v"(aw23), [afix] "v"(pair_fix), \
-                   [bv01] "v"(bv01), [bv23] "v"(bv23), [ard] "v"(pard), [brd] "v"(pbrd), [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
-                   [lds] "s"(lds_base), [bstep] "s"(b_step) \
+                   [bv01] "v"(bv01), [bv23] "v"(bv23), [ard] "v"(pard), [brd] "v"(pbrd), [aptr] "s"(A + 256 - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0 + 3 * (size_t)b_step), [kt] "s"(KTF), \
+                   [ldsdma] "s"(lds_dma), [lds] "s"(lds_base), [bstep] "s"(b_step) \
                  : QG_TILE_LOOP_CLOBBERS
 
 #define QG_TILE_LOOP_OPERANDS_2X2 \
                  : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[1][0]), [c3] "+a"(acc[1][1]), \
                    [rs01] "=v"(rs01) \
                  : [av01] "v"(av01), [bv01] "v"(bv01), [ard] "v"(ard), [brd] "v"(brd), \
-                   [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
+                   [aptr] "s"(A + NST * BK - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0 + NST * (size_t)b_step), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
                    [lds] "s"(lds_base), [bstep] "s"(b_step) \
                  : QG_TILE_LOOP_CLOBBERS_2X2
 
@@ -116,7 +116,8 @@ constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair, int sets
                  : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[1][0]), [c3] "+a"(acc[1][1]), \
                    [rs01] "=v"(rs01) \
                  : [av01] "v"(av01), [av23] "v"(av23), [bv01] "v"(bv01), [ard] "v"(pard), [brd] "v"(pbrd), \
-                   [aptr] "s"(A + (wave_all >> 2) * 128 - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0 + (size_t)kg * b_step), \
+                   [aptr] "s"(A + NST * KS * BK + (wave_all >> 2) * 128 - (A_DMA - 1) * 1024), \
+                   [bptr] "s"(b_tile0 + (size_t)(NST * KS + kg) * b_step), \
                    [kt] "s"(KTF / KS), [ldsdma] "s"(lds_base + wave_all * (A_DMA * 1024)), [lds] "s"(lds_base), \
                    [bstep] "s"(b_step * KS), \
                    [bofs] "s"(KS * A_STAGE + (kg * NW + wave) * (B_DMA * 1024) - wave_all * (A_DMA * 1024)) \
@@ -127,7 +128,7 @@ constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair, int sets
                    [c4] "+a"(acc[1][0]), [c5] "+a"(acc[1][1]), [c6] "+a"(acc[1][2]), [c7] "+a"(acc[1][3]), \
                    [rs01] "=v"(rs01) \
                  : [av01] "v"(av01), [bv01] "v"(bv01), [ard] "v"(ard), [brd] "v"(brd), \
-                   [aptr] "s"(A - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
+                   [aptr] "s"(A + NST * BK - (A_DMA - 1) * 1024), [bptr] "s"(b_tile0 + NST * (size_t)b_step), [kt] "s"(KTF), [ldsdma] "s"(lds_dma), \
                    [lds] "s"(lds_base), [bstep] "s"(b_step), [bofs] "s"(A_STAGE + wave * ((B_DMA - A_DMA) * 1024)) \
                  : QG_TILE_LOOP_CLOBBERS_2X4
 
@@ -240,13 +241,18 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   int lin = blockIdx.x;
   if ((total & 7) == 0) lin = (lin & 7) * (total >> 3) + (lin >> 3);
   constexpr int BAND = 8;
-  const int band_sz = BAND * tiles_n;
-  const int band = lin / band_sz;
+  // (small quotients through the reciprocal: exact below 2^20, where (x + 0.5) / d is further from a whole number than the
+  // rounding errors reach; an integer division is 25 instructions of a wave that has not issued a request yet)
+  const bool small = total < (1 << 20);
+  auto quot = [&](int x, int d) {
+    return small ? __builtin_amdgcn_readfirstlane((int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d))) : x / d;
+  };
+  const int band = tiles_m <= BAND ? 0 : quot(lin, BAND * tiles_n);
   const int first_m = band * BAND;
   const int rows_in_band = min(tiles_m - first_m, BAND);
-  const int in_band = lin - band * band_sz;
-  const int tm = first_m + in_band % rows_in_band;
-  const int tn = in_band / rows_in_band;
+  const int in_band = lin - first_m * tiles_n;
+  const int tn = quot(in_band, rows_in_band);
+  const int tm = first_m + in_band - tn * rows_in_band;
   const int m0 = tm * BM, n0 = tn * BN;
 
   // ---- staging.  A: one wave-load fills 1 KiB of LDS = 16 rows x 64 B; lane l lands at row l/4,
@@ -350,6 +356,22 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   // registers afterwards, once per workgroup
   const int KTF = CVG ? KT : K / BK;  // (CVG: chunks past K are replaced like taps outside the image)
   v4i a0[TM], b0[TN], a1[TM], b1[TN];
+  // The per-column constants of the output pipeline, column tid of the tile: loaded behind the first tile requests (the
+  // pointers come from the argument buffer, a trip that these then hide) and staged in LDS after the loop.  Loaded after
+  // the loop they cost every workgroup 0.5 us and more.
+  static_assert(BN <= NT, "one column per thread");
+  int pre_co = 0, pre_bz = 0, pre_bias = 0;
+  float pre_sc = 1.0f;
+  auto prefetch_columns = [&]() {
+    const int col = n0 + tid;
+    if (tid < BN) {
+      pre_co = p.col_off[col], pre_bz = p.bzp[col];  // (padded to N_pad; bias and scales are not)
+      if (MODE != QG_MODE_ACC32 && col < N) {
+        if (p.bias != nullptr) pre_bias = p.bias[col];
+        pre_sc = p.scales[(size_t)col * p.scale_stride];
+      }
+    }
+  };
   // Tiles that the loop leaves over: a ragged last one and, DIST, those that do not make a step of all four sets, one per
   // set.  Their loads are issued in front of the loop (300 x 1000 x 1000: a latency of 1.4 us behind it otherwise).
   const int KTL = DIST ? KTF / KS * KS : KTF;    // tiles the loop does
@@ -371,6 +393,36 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
 #pragma unroll
       for (int q = 0; q < B_DMA; ++q) left_b[q] = *reinterpret_cast<const v4i*>(b_tile0 + (size_t)ktl * b_step + b_voff[q]);
     }
+  }
+  // ---- hand-scheduled loops: the first requests (the convolution's are part of its loop)
+  constexpr int NST = PATH == PATH_ASM ? asm_stages(TM * TN, KS) : NS;
+  if constexpr (PATH == PATH_ASM && CONV == 0) {
+#pragma unroll
+    for (int st = 0; st <= NST; ++st) {
+      // PAIR: half st of A, tile st - 1 of B; otherwise tile st of both
+      if (!PAIR && st == NST) break;
+      unsigned char* const sa = smem + (PAIR ? st * A_STAGE : st * KS * STAGE);
+      unsigned char* const sb = smem + (PAIR ? 6 * A_STAGE + (st - 1) * B_STAGE : st * KS * STAGE + KS * A_STAGE + kg * B_STAGE);
+      if (PAIR && st == 4 && KTF == 5) {  // 64 valid bytes per row: chunks past them 64 bytes earlier, here and in the loop
+#pragma unroll
+        for (int q = 0; q < A_DMA; ++q) {
+          const unsigned past = ((unsigned)((lane >> 2) ^ q) & 1u) << 6;
+          a_voff[q] -= past, a_half1[q] -= past;
+        }
+      }
+      // (PAIR with four tiles: there is no half 4, half 2 comes again)
+      const int a_k = PAIR ? (st == 4 && KTF == 4 ? 128 : (st >> 1) * 128) : st * KS * BK + (DIST ? (wave_all >> 2) * 128 : 0);
+#pragma unroll
+      for (int q = 0; q < A_DMA; ++q)
+        dma16(A + a_k + ((PAIR && (st & 1) ? a_half1[q] : a_voff[q]) - (A_DMA - 1 - q) * 1024),
+              sa + ((DIST ? wave_all : wave) * A_DMA + q) * 1024);
+      if (!PAIR || st > 0) {
+        const int8_t* const b = b_tile0 + (size_t)(PAIR ? st - 1 : st * KS + kg) * b_step;
+#pragma unroll
+        for (int q = 0; q < B_DMA; ++q) dma16(b + b_voff[q], sb + (wave * B_DMA + q) * 1024);
+      }
+    }
+    prefetch_columns();
   }
   if constexpr (PATH == PATH_ASM) {
     // Tile kt lives in stage kt % 4.  In iteration kt: the first k-step runs while the fragments of
@@ -536,6 +588,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t)
       if (t < KTg) request(t * KS + kg, t);
+    prefetch_columns();
     int stage = 0;
     // one common step: `consume` says whether this wave set has a tile in it (always, except in the last step
     // of the other set when the number of tiles is odd)
@@ -728,17 +781,15 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   int* cj_s = reinterpret_cast<int*>(smem);
   int* bz_s = cj_s + BN;
   float* sc_s = reinterpret_cast<float*>(bz_s + BN);
-  for (int t = tid; t < BN; t += NT) {
-    const int col = n0 + t;  // col_off / bzp are padded to N_pad, bias / scales are not
-    const int co = p.col_off[col], bz = p.bzp[col];
+  if (PATH == PATH_ASM && CONV != 0) prefetch_columns();
+  if (tid < BN) {
     if (MODE != QG_MODE_ACC32) {
-      const int b = (p.bias != nullptr && col < N) ? p.bias[col] : 0;
-      cj_s[t] = b - p.a_zp_m128 * co;
-      sc_s[t] = (col < N) ? p.scales[(size_t)col * p.scale_stride] : 1.0f;
+      cj_s[tid] = pre_bias - p.a_zp_m128 * pre_co;
+      sc_s[tid] = pre_sc;
     } else {
-      cj_s[t] = 128 * (co + K0 * bz);  // acc_u = acc_s + 128 * colsum
+      cj_s[tid] = 128 * (pre_co + K0 * pre_bz);  // acc_u = acc_s + 128 * colsum
     }
-    bz_s[t] = -bz;  // negated: x = acc + cj + (-theta_B) * rowsum
+    bz_s[tid] = -pre_bz;  // negated: x = acc + cj + (-theta_B) * rowsum
   }
   __syncthreads();
   if (KS > 1 && !DIST && kg != 0) return;  // the first wave set holds the sums and runs the output pipeline

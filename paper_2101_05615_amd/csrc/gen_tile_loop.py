@@ -172,21 +172,15 @@ def advance_request_pointers(e):
     e("s_addc_u32 s89, s89, 0")
 
 
-def pair_advance(e, cond):
-    """request pointers: A to the next half, B to the next tile.  cond: None, or (value of s90 to skip the A advance at,
-    value to fix the offsets at)"""
+def pair_advance(e):
+    """A request pointer to the next half; not at s90 == s80; offsets fixed at s90 == s81"""
     for q in range(A_DMA):
         e(f"v_swap_b32 v{AV + q}, v{AW + q}")
-    if cond is None:
-        e("s_add_u32 s86, s86, s70\\n s_addc_u32 s87, s87, 0")
-    else:
-        skip, fix = cond
-        e(f"s_cmp_eq_u32 s90, {skip}\\n s_cselect_b32 s78, 0, s70\\n s_add_u32 s86, s86, s78\\n s_addc_u32 s87, s87, 0")
+    e("s_cmp_eq_u32 s90, s80\\n s_cselect_b32 s78, 0, s70\\n s_add_u32 s86, s86, s78\\n s_addc_u32 s87, s87, 0")
     e("s_xor_b32 s70, s70, 128")
-    if cond is not None:
-        e(f"s_cmp_lg_u32 s90, {fix}\\n s_cbranch_scc1 3f\\n " +
-          "\\n ".join((f"v_add_u32 v{v + q}, %[afix], v{v + q}\\n v_subrev_u32 v{v + q}, 64, v{v + q}" if q & 1 else
-                       f"v_sub_u32 v{v + q}, v{v + q}, %[afix]") for q in range(A_DMA) for v in (AV, AW)) + "\\n 3:")
+    e("s_cmp_lg_u32 s90, s81\\n s_cbranch_scc1 3f\\n " +
+      "\\n ".join((f"v_add_u32 v{v + q}, %[afix], v{v + q}\\n v_subrev_u32 v{v + q}, 64, v{v + q}" if q & 1 else
+                   f"v_sub_u32 v{v + q}, v{v + q}, %[afix]") for q in range(A_DMA) for v in (AV, AW)) + "\\n 3:")
 
 
 def pair_advance_b(e):
@@ -347,7 +341,7 @@ def tile_pair(e, wait_vm, request, last):
     if not last:
         pair_read_bases(early)
     if request:
-        pair_advance(late, ("s80", "s81"))
+        pair_advance(late)
         pair_advance_b(late)
         pair_request_slots(late)
     step(e, use=0, ks_load=1, request=False, next_va=None if last else 0, early=early.lines, late=late.lines)
@@ -409,21 +403,13 @@ def generate_loop(rowsum, conv=False):
     e("s_mov_b32 s99, %[bstep]")
     for f in range(TM):
         e(f"v_mov_b32 v{RS + f}, 0")
-    # ---- request tiles 0..NSTAGE-1 into stages 0..NSTAGE-1
+    # The first NSTAGE tiles (PAIR: five halves of A, four tiles of B) have been requested by the surrounding C++ code, in
+    # the order of the loop; the pointers come in at the next tile (PAIR: at the last requests, advanced in the first tile).
+    # The convolution requests them here.
     if PAIR:
         e("s_mov_b32 s70, 0")
-        for half in range(NSTAGE + 1):
-            e(f"s_add_u32 s96, s91, {half * A_STAGE}")
-            for q in range(A_DMA):
-                dma(e, q)
-            if half < NSTAGE:  # (behind the last one: in the first tile)
-                pair_advance(e, ("0", "1") if half == NSTAGE - 1 else None)
-            if half > 0:
-                e(f"s_add_u32 s79, s91, {6 * A_STAGE + (half - 1) * B_STAGE}")
-                for q in range(A_DMA, N_DMA):
-                    dma(e, q)
-                if half < NSTAGE:
-                    pair_advance_b(e)
+        e(f"s_add_u32 s96, s91, {4 * A_STAGE}")
+        e(f"s_add_u32 s79, s91, {6 * A_STAGE + 3 * B_STAGE}")
         # an even number of tiles: skip the advance in the last tile that requests (s90 == 1); an odd one: fix the offsets
         # in the one before, in front of the requests for the last pair (s90 == 2)
         e("s_and_b32 s78, s90, 1")
@@ -438,7 +424,7 @@ def generate_loop(rowsum, conv=False):
         e("s_mov_b32 s77, s75")
         e("s_mov_b32 s97, s92")
     else:
-        for st in range(NSTAGE):
+        for st in range(NSTAGE if conv else 0):
             e(f"s_add_u32 s96, s91, {st * STAGE_BYTES}")
             for q in range(N_DMA):
                 dma(e, q)
