@@ -26,16 +26,17 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // Byte sums of a lane's four dwords (16 input channels of one pixel) -> per dword, the sum over the whole group the
 // dword belongs to: groups of 4 channels are the dwords themselves, of 8 pairs of dwords, of 16 the lane's four, of 32
 // those of both lanes of the pixel (lanes 32 apart).  lcg = log2(channels per group), uniform.
-__device__ __forceinline__ void group_sums(unsigned (&rs)[4], int lcg) {
+template <typename T>
+__device__ __forceinline__ void group_sums(T (&rs)[4], int lcg) {
   if (lcg <= 2) return;
-  const unsigned a = rs[0] + rs[1], b = rs[2] + rs[3];
+  const T a = rs[0] + rs[1], b = rs[2] + rs[3];
   if (lcg == 3) {
     rs[0] = rs[1] = a;
     rs[2] = rs[3] = b;
     return;
   }
-  unsigned t = a + b;
-  if (lcg == 5) t += (unsigned)__shfl_xor((int)t, 32);
+  T t = a + b;
+  if (lcg == 5) t += (T)__shfl_xor((int)t, 32);
   rs[0] = rs[1] = rs[2] = rs[3] = t;
 }
 
@@ -210,110 +211,158 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned char* lds_base)
                                    (__attribute__((address_space(3))) void*)lds_base, 16, 0, 0);
 }
 
+// Exact unsigned division by a number the host knows: q = (t + ((n - t) >> s1)) >> s2 with t the high word of m * n (Granlund
+// and Montgomery, "Division by invariant integers using multiplication", 1994).  All of it on the scalar unit; an integer
+// division is 25 vector instructions.
+struct udiv {
+  unsigned m, s;  // s: s1 | s2 << 8
+};
+udiv make_udiv(unsigned d) {
+  int l = 0;
+  while ((1ull << l) < d) ++l;
+  const unsigned m = (unsigned)((((1ull << l) - d) << 32) / d) + 1u;
+  return {m, (unsigned)(l < 1 ? l : 1) | (unsigned)(l > 0 ? l - 1 : 0) << 8};
+}
+__device__ __forceinline__ unsigned quot(unsigned n, unsigned m, unsigned s) {
+  const unsigned t = __umulhi(m, n);
+  return (t + ((n - t) >> (s & 1))) >> (s >> 8 & 31);
+}
+
 // "Same" convolution (stride 1, 2*pad == R-1 == S-1): the input pixel of tap (kh, kw) of output pixel q
 // is pixel q + (kh-pad)*W + (kw-pad) of the same linear NHWC pixel sequence.  A workgroup owns 128
 // consecutive output pixels of one group of NCB*32 channels; it requests its whole input patch (the 128
-// pixels plus pad*W+pad on either side) and its weights with global_load_lds in one burst -- one memory
-// latency per workgroup -- and every tap then comes from LDS.  Pixel p's 16-byte channel chunks are
-// stored swizzled so that the 32 consecutive pixels a half-wave reads hit different banks.
-template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA = false>
-__global__ __launch_bounds__(256, HAS_BZP ? 2 : 3) void qg_conv_same_mfma_kernel(
-    const uint8_t* in, const int8_t* Wfrag, const int Nb, const int H, const int W, const int C, const int halo,
-    const int nchunks_pad, const qg_conv_args p) {
+// pixels plus pad*W+pad on either side) and its weights in one burst -- one memory latency per workgroup -- and every
+// tap then comes from LDS.
+// What bounds it is vector-instruction issue (32 x 56 x 56 x 128 in 32 groups of 4: 443 per wave of 32 pixels x 64 channels
+// before, 24 500 cycles of a SIMD's issue per launch against 10 000 for the memory).  So the patch passes through registers,
+// where each byte is shifted to int8 once instead of once per tap; its pixels lie an odd number of 16-byte chunks apart, so
+// that a tap's chunk is at pixel base + a scalar, no swizzle; a tap outside the image reads a row of theta_A instead of
+// being masked, one select per tap; and positions and tile numbers are divided on the scalar unit.  32 x 56 x 56 x 128, groups
+// of 4 10.9 -> 9.3 us, depthwise 11.0 -> 9.1, groups of 16 11.6 -> 10.5; 32 x 28 x 28 x 256, groups of 4 8.0 -> 5.7;
+// 8 x 14 x 14 x 512, groups of 16 3.85 -> 3.24.
+//
+// COMPACT (log2 of the channels per group, -1: no): groups of at most 4 channels.  A lane's 16 bytes of a block-diagonal
+// fragment are then one dword and twelve zero bytes, so LDS holds the dwords alone (from the layouts of the plain kernels; 2.3
+// instead of 18 KiB) and the lane masks its dword into place: seven workgroups share a CU instead of four, and the grid of
+// 1568 is one round (10.5 -> 9.5 us at 32 x 56 x 56 x 128).  Fetching that dword per lane and fragment from memory instead
+// took 14.5 us: a load whose lanes lie 16 bytes apart keeps the L1 busy as long as one of 16 bytes per lane.
+template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT>
+__global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >= 0 ? 7 : 4)) void qg_conv_same_mfma_kernel(
+    const uint8_t* in, const int8_t* Wfrag, const int npix, const int H, const int W, const int C, const int halo,
+    const int ntile, const int nslice, const unsigned mS, const unsigned mW, const unsigned mH, const unsigned shifts_WH,
+    const unsigned shift_S, const qg_conv_args p) {
   static_assert(!RS_MFMA || HAS_BZP, "row sums are only needed with a nonzero theta_B");
-  // the leading scalar arguments repeat the fields of p that the request burst needs: the file is compiled with
+  // the leading scalar arguments hold what the request burst and the set-up need: the file is compiled with
   // kernel-argument preloading, so they arrive in scalar registers with the wave
   constexpr int RS = R * S;
   constexpr int NCH = NCB * 32;
-  constexpr int CP = NCH / 16;       // 16-byte chunks per pixel
+  constexpr int CP = NCH / 16;         // 16-byte chunks per pixel
+  constexpr int PITCH = (CP + 1) * 16; // bytes from one patch pixel to the next: sixteen pixels' chunks in sixteen bank groups
   constexpr int PAD_H = (R - 1) / 2, PAD_W = (S - 1) / 2;
-  // chunk swizzle of patch pixel pp: the 16 consecutive pixels whose chunk of one index is read in one cycle
-  // (8 on parts with 128 B of banks) must fall into different 16-byte bank groups; period 16 pixels
-  auto swz = [](int pp) {
-    return CP == 8 ? ((pp & 7) ^ ((pp >> 3) & 1)) : (CP == 4 ? (((pp >> 1) & 3) ^ ((pp >> 3) & 1)) : ((pp >> 3) & 1));
-  };
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* w_s = smem;                                        // [cb][tap] fragments
-  int* cj_s = reinterpret_cast<int*>(smem + NCB * RS * QG_FRAG_BYTES);
+  // COMPACT: one dword per (output channel, tap); groups of 4: [group][tap][channel], smaller: [channel][tap]
+  constexpr int WBYTES = COMPACT >= 0 ? NCH * RS * 4 : NCB * RS * QG_FRAG_BYTES;
+  unsigned char* w_s = smem;                                        // otherwise [cb][tap] fragments
+  int* cj_s = reinterpret_cast<int*>(smem + WBYTES);
   int* nbz_s = cj_s + NCH;
   float* sc_s = reinterpret_cast<float*>(nbz_s + NCH);
-  unsigned char* patch = smem + NCB * RS * QG_FRAG_BYTES + NCH * 12;
+  unsigned char* patch = smem + WBYTES + NCH * 12;                    // 128 + 2 halo pixels, then a row of theta_A
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Workgroup -> (pixel tile, channel slice).  Workgroup ids go round-robin over the 8 XCDs.  The slices of one
-  // pixel tile touch the two halves of the same 128-byte input and output lines, so they are given ids 8 apart:
-  // same XCD, dispatched back to back, and its L2 fetches each input line once and merges the output halves.
-  // Each XCD walks its own contiguous eighth of the tile sequence, so neighbouring tiles, whose input patches
-  // overlap by the halo rows, also meet in one L2.
-  int tile, slice;
-  {
-    const int nslice = C / NCH, ntile = gridDim.x / nslice, id = blockIdx.x;
-    if ((ntile & 7) == 0) {
-      const int j = id >> 3;
-      slice = j % nslice;
-      tile = (id & 7) * (ntile >> 3) + j / nslice;
-    } else {
-      slice = id % nslice;
-      tile = id / nslice;
-    }
-  }
+  // Workgroup -> (pixel tile, channel slice), slices of a tile side by side, one run of the sequence per XCD: the slices of
+  // one pixel tile touch the two halves of the same 128-byte input and output lines and neighbouring tiles' patches overlap
+  // by the halo rows, and both meet in one L2 (32 x 28 x 28 x 256, 196 tiles of four slices dealt out one by one: 8.0 us
+  // against 5.8).
+  const int lin = qg_xcd_run(blockIdx.x, ntile * nslice);
+  const int tile = (int)quot((unsigned)lin, mS, shift_S), slice = lin - tile * nslice;
   const int ch0 = slice * NCH;
-  const int q0 = tile * 128;  // first output pixel of the workgroup
-  const int npix = Nb * H * W;
+  const int q0 = tile * 128;        // first output pixel of the workgroup
   const int lin0 = q0 - halo;       // linear index of patch pixel 0 (may be negative; clamped per chunk)
+  const int npp = 128 + 2 * halo, nchunks = npp * CP;
 
-  // ---- one burst of requests: weights, then the input patch
-  {
+  // ---- one burst of requests: weights, input patch, column constants
+  if constexpr (COMPACT < 0) {
     const int8_t* wsrc = Wfrag + (size_t)slice * NCB * RS * QG_FRAG_BYTES + lane * 16;
     for (int f = wave; f < NCB * RS; f += 4) dma16(wsrc + (size_t)f * QG_FRAG_BYTES, w_s + f * QG_FRAG_BYTES);
-    if (lin0 >= 0 && lin0 + nchunks_pad / CP <= npix) {
-      // the whole patch lies inside the buffer: one address per lane, then 256 chunks = 256 / CP pixels further
-      // per request (the swizzle has period 16 pixels or less, so it is the same for every request of a lane)
-      const int c = wave * 64 + lane;
-      const int pp = c / CP, phys = c % CP;
-      const uint8_t* src = in + (size_t)(lin0 + pp) * C + ch0 + ((phys ^ swz(pp)) << 4);
-      const int step = 256 / CP * C;
-      for (int c0 = wave * 64; c0 < nchunks_pad; c0 += 256, src += step) dma16(src, patch + c0 * 16);
-    } else {
-      for (int c0 = wave * 64; c0 < nchunks_pad; c0 += 256) {
-        const int c = c0 + lane;
-        const int pp = c / CP, phys = c % CP;
-        const int lin = min(max(lin0 + pp, 0), npix - 1);
-        dma16(in + (size_t)lin * C + ch0 + ((phys ^ swz(pp)) << 4), patch + c0 * 16);
-      }
-    }
-    for (int c = tid; c < NCH; c += 256) {
-      const int oc = ch0 + c;
-      cj_s[c] = (p.bias ? p.bias[oc] : 0) - (p.a_zp - 128) * p.col_off[oc];
-      nbz_s[c] = -p.bzp[oc];
-      sc_s[c] = p.scales[(size_t)oc * p.scale_stride];
-    }
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every request of this wave has landed in LDS ...
-  __syncthreads();                                   // ... before any wave reads the others' slots
+  constexpr int BATCH = 4;
+  const int phys = tid % CP, pp0 = tid / CP;  // chunk tid + 256 j is chunk `phys` of patch pixel pp0 + j * (256 / CP)
+  const uint8_t* const src0 = in + ch0 + phys * 16;
+  auto load = [&](int j) {  // (unconditional: a load under a condition makes the compiler wait for the one before it)
+    const int lin = min(max(lin0 + pp0 + j * (256 / CP), 0), npix - 1);
+    return *reinterpret_cast<const v4i*>(src0 + (size_t)(unsigned)lin * (unsigned)C);
+  };
+  auto store = [&](int j, v4i v) {
+    *reinterpret_cast<v4i*>(patch + (pp0 + j * (256 / CP)) * PITCH + phys * 16) = v ^ (int)0x80808080;
+  };
+  v4i v[BATCH];
+#pragma unroll
+  for (int j = 0; j < BATCH; ++j) v[j] = load(j);
+  constexpr int WCHUNKS = COMPACT >= 0 ? NCH * RS / 4 : 0;  // 16-byte chunks of the compact weights
+  static_assert(WCHUNKS <= 256 && NCH * RS % 4 == 0, "one chunk per thread");
+  v4i wv = (v4i){0, 0, 0, 0};
+  if (WCHUNKS > 0) wv = *reinterpret_cast<const v4i*>(Wfrag + (size_t)slice * WBYTES + min(tid, WCHUNKS - 1) * 16);
+  // (their pointers come from the argument buffer: used behind the patch, whose loads are older)
+  const int oc = ch0 + tid % NCH;
+  const int co = p.col_off[oc], bi = (p.bias ? p.bias : p.col_off)[oc], bz = HAS_BZP ? p.bzp[oc] : 0;
+  const float sc = p.scales[(size_t)oc * p.scale_stride];
+#pragma unroll
+  for (int j = 0; j < BATCH; ++j)
+    if (tid + 256 * j < nchunks) store(j, v[j]);
+  for (int j0 = BATCH; 256 * j0 < nchunks; j0 += BATCH) {  // wide images
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) v[j] = load(j0 + j);
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j)
+      if (tid + 256 * (j0 + j) < nchunks) store(j0 + j, v[j]);
+  }
+  if (WCHUNKS > 0 && tid < WCHUNKS) {
+    if (COMPACT < 2) {  // the channel's bytes to their place in its dword of the fragment
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wv[i] = (int)((unsigned)wv[i] << (8 * ((((tid * 4 + i) / RS) & 3) >> COMPACT << COMPACT)));
+    }
+    *reinterpret_cast<v4i*>(w_s + tid * 16) = wv;
+  }
+  if (tid < NCH) {
+    cj_s[tid] = (p.bias ? bi : 0) - (p.a_zp - 128) * co;
+    if (HAS_BZP) nbz_s[tid] = -bz;
+    sc_s[tid] = sc;
+  }
+  if (tid < CP) {
+    const int z = (int)(((unsigned)p.a_zp * 0x01010101u) ^ 0x80808080u);
+    *reinterpret_cast<v4i*>(patch + npp * PITCH + tid * 16) = (v4i){z, z, z, z};
+  }
 
   const int pl = lane & 31, g = lane >> 5;
   const int px = q0 + wave * 32 + pl;
-  // image position of this lane's pixel: the wave's first pixel is divided on the scalar unit, the lane walks
-  // pl pixels on from there (a lane past the last pixel gets a position that is never used for a store)
-  const int pw0 = q0 + wave * 32;
-  int wo = pw0 % W + pl;
-  int ho = (pw0 / W) % H;
-  for (int i = 31 / W + 1; i > 0; --i) {
-    const bool wrap = wo >= W;
-    wo -= wrap ? W : 0;
-    ho += wrap ? 1 : 0;
-    ho = ho == H ? 0 : ho;
+  // image position of this lane's pixel: the wave's first pixel is divided on the scalar unit, the lane is pl pixels on
+  // from there (a lane past the last pixel gets a position that is never used for a store)
+  const unsigned pw0 = (unsigned)(q0 + wave * 32), row0 = quot(pw0, mW, shifts_WH & 0xFFFF);
+  int wo = (int)(pw0 - row0 * W) + pl;
+  int ho = (int)(row0 - quot(row0, mH, shifts_WH >> 16) * H);
+  {
+    const int rows = (int)(((float)wo + 0.5f) * __builtin_amdgcn_rcpf((float)W));  // (wo < W + 31)
+    wo -= rows * W;
+    ho += rows;
+    ho -= (int)(((float)ho + 0.5f) * __builtin_amdgcn_rcpf((float)H)) * H;
   }
   bool row_ok[R], col_ok[S];
 #pragma unroll
   for (int kh = 0; kh < R; ++kh) row_ok[kh] = (unsigned)(ho + kh - PAD_H) < (unsigned)H;
 #pragma unroll
   for (int kw = 0; kw < S; ++kw) col_ok[kw] = (unsigned)(wo + kw - PAD_W) < (unsigned)W;
-  const unsigned azp_word = (unsigned)p.a_zp * 0x01010101u;
   const float czp_f = (float)p.c_zp;
-  const int pp_c = wave * 32 + pl + halo;  // patch index of this lane's centre pixel
+  const unsigned char* const a_px = patch + (wave * 32 + pl + halo) * PITCH + 16 * g;  // this lane's half of its centre pixel
+  const unsigned char* const a_zero = patch + npp * PITCH + 16 * g;
+  // COMPACT: this lane's output channel, its dword's place among the 16 input channels of the lane's half (outside: none)
+  const int oc_l = qg_slot_to_col(pl), wj = (oc_l >> 4) == g ? (oc_l >> 2) & 3 : 4;
+  const v4i wmask = (v4i){wj == 0 ? -1 : 0, wj == 1 ? -1 : 0, wj == 2 ? -1 : 0, wj == 3 ? -1 : 0};
+  const unsigned char* const w_l = w_s + (COMPACT == 2 ? (oc_l >> 2) * (RS * 16) + (oc_l & 3) * 4 : oc_l * (RS * 4));
+  constexpr int WTAP = COMPACT == 2 ? 16 : 4;
+
+  if (COMPACT < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weight requests of this wave have landed in LDS ...
+  __syncthreads();                                                 // ... before any wave reads the others' slots
 
   // the accumulators start at bias - (theta_A - 128) * column offset, so the output pipeline adds nothing
   v16i acc[NCB];
@@ -321,11 +370,11 @@ __global__ __launch_bounds__(256, HAS_BZP ? 2 : 3) void qg_conv_same_mfma_kernel
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const v4i cj = *reinterpret_cast<const v4i*>(&cj_s[cb * 32 + 16 * g + 4 * q]);
+      const v4i c4 = *reinterpret_cast<const v4i*>(&cj_s[cb * 32 + 16 * g + 4 * q]);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[cb][4 * q + r] = cj[r];
+      for (int r = 0; r < 4; ++r) acc[cb][4 * q + r] = c4[r];
     }
-  unsigned rs[NCB][4];
+  int rs[NCB][4];  // row offsets per dword, int8 domain
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
@@ -343,25 +392,20 @@ __global__ __launch_bounds__(256, HAS_BZP ? 2 : 3) void qg_conv_same_mfma_kernel
   for (int kh = 0; kh < R; ++kh) {
 #pragma unroll
     for (int kw = 0; kw < S; ++kw) {
-      const bool ok = row_ok[kh] && col_ok[kw];
-      const int pp = pp_c + (kh - PAD_H) * W + (kw - PAD_W);
-      const unsigned keep = ok ? 0xFFFFFFFFu : 0u;
-      // in-image: x ^ 0x80 (uint8 -> int8); out of image: theta_A - 128 in every byte
-      const unsigned flip = ok ? 0x80808080u : (azp_word ^ 0x80808080u);
-      const unsigned char* src = patch + pp * NCH;
+      const int off = ((kh - PAD_H) * W + (kw - PAD_W)) * PITCH;
+      const unsigned char* const src = row_ok[kh] && col_ok[kw] ? a_px + off : a_zero;
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        v4i x = *reinterpret_cast<const v4i*>(src + (((cb * 2 + g) ^ swz(pp)) << 4));
+        const v4i x = *reinterpret_cast<const v4i*>(src + cb * 32);
         if (HAS_BZP && !RS_MFMA) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const unsigned y = __builtin_amdgcn_bitop3_b32((unsigned)x[j], keep, azp_word, 0xe2);  // keep ? x : theta_A bytes
-            rs[cb][j] = __builtin_amdgcn_sad_u8(y, 0u, rs[cb][j]);
-          }
+          for (int j = 0; j < 4; ++j) rs[cb][j] = __builtin_amdgcn_sdot4(x[j], 0x01010101, rs[cb][j], false);
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = (int)__builtin_amdgcn_bitop3_b32((unsigned)x[j], keep, flip, 0x6a);  // (x & keep) ^ flip
-        const v4i wf = *reinterpret_cast<const v4i*>(w_s + (cb * RS + kh * S + kw) * QG_FRAG_BYTES + lane * 16);
+        v4i wf;
+        if constexpr (COMPACT >= 0)
+          wf = wmask & *reinterpret_cast<const int*>(w_l + cb * (32 * RS * 4) + (kh * S + kw) * WTAP);
+        else
+          wf = *reinterpret_cast<const v4i*>(w_s + (cb * RS + kh * S + kw) * QG_FRAG_BYTES + lane * 16);
         acc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, x, acc[cb], 0, 0, 0);
         if (RS_MFMA) racc[cb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ones, x, racc[cb], 0, 0, 0);
       }
@@ -374,37 +418,38 @@ __global__ __launch_bounds__(256, HAS_BZP ? 2 : 3) void qg_conv_same_mfma_kernel
     for (int cb = 0; cb < NCB; ++cb) group_sums(rs[cb], p.lcg);
   }
   if (px < npix) {
-    auto pipeline = [&](auto lo_tag) {
-    constexpr bool LO = decltype(lo_tag)::value;
+    auto pipeline = [&](auto form_tag) {
+      constexpr int FORM = decltype(form_tag)::value;  // 0: explicit clamp, 1: saturating convert, 2: theta_C == 0
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) {
-      const int c_l = cb * 32 + 16 * g;
-      unsigned out[4];
+      for (int cb = 0; cb < NCB; ++cb) {
+        const int c_l = cb * 32 + 16 * g;
+        unsigned out[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 sc = *reinterpret_cast<const float4*>(&sc_s[c_l + 4 * q]);
-        int x0 = acc[cb][4 * q + 0], x1 = acc[cb][4 * q + 1], x2 = acc[cb][4 * q + 2], x3 = acc[cb][4 * q + 3];
-        if (HAS_BZP) {
-          const v4i nbz = *reinterpret_cast<const v4i*>(&nbz_s[c_l + 4 * q]);
-          const int rsum = (int)rs[cb][q] - ((128 * RS) << p.lcg);
-          x0 += __mul24(nbz.x, RS_MFMA ? racc[RS_MFMA ? cb : 0][4 * q + 0] : rsum);
-          x1 += __mul24(nbz.y, RS_MFMA ? racc[RS_MFMA ? cb : 0][4 * q + 1] : rsum);
-          x2 += __mul24(nbz.z, RS_MFMA ? racc[RS_MFMA ? cb : 0][4 * q + 2] : rsum);
-          x3 += __mul24(nbz.w, RS_MFMA ? racc[RS_MFMA ? cb : 0][4 * q + 3] : rsum);
+        for (int q = 0; q < 4; ++q) {
+          const float4 s4 = *reinterpret_cast<const float4*>(&sc_s[c_l + 4 * q]);
+          int x[4] = {acc[cb][4 * q + 0], acc[cb][4 * q + 1], acc[cb][4 * q + 2], acc[cb][4 * q + 3]};
+          if (HAS_BZP) {
+            const v4i nb4 = *reinterpret_cast<const v4i*>(&nbz_s[c_l + 4 * q]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] += __mul24(nb4[i], RS_MFMA ? racc[RS_MFMA ? cb : 0][4 * q + i] : rs[cb][q]);
+          }
+          const float sc4[4] = {s4.x, s4.y, s4.z, s4.w};
+          unsigned w = 0;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            w = FORM == 2 ? qg_requant_pack0(x[i], sc4[i], i, w)
+                          : qg_requant_pack<FORM == 0>(x[i], sc4[i], p.clamp_lo, p.clamp_hi, czp_f, i, w);
+          out[q] = w;
         }
-        unsigned w = qg_requant_pack<LO>(x0, sc.x, p.clamp_lo, p.clamp_hi, czp_f, 0, 0);
-        w = qg_requant_pack<LO>(x1, sc.y, p.clamp_lo, p.clamp_hi, czp_f, 1, w);
-        w = qg_requant_pack<LO>(x2, sc.z, p.clamp_lo, p.clamp_hi, czp_f, 2, w);
-        out[q] = qg_requant_pack<LO>(x3, sc.w, p.clamp_lo, p.clamp_hi, czp_f, 3, w);
+        *reinterpret_cast<uint4*>(p.out + (size_t)px * p.Cout + ch0 + c_l) = make_uint4(out[0], out[1], out[2], out[3]);
       }
-      *reinterpret_cast<uint4*>(p.out + (size_t)px * p.Cout + ch0 + c_l) =
-          make_uint4(out[0], out[1], out[2], out[3]);
-    }
     };
     if (qg_requant_needs_lo(p.clamp_lo, czp_f))
-      pipeline(std::true_type{});
+      pipeline(std::integral_constant<int, 0>{});
+    else if (p.c_zp == 0)
+      pipeline(std::integral_constant<int, 2>{});
     else
-      pipeline(std::false_type{});
+      pipeline(std::integral_constant<int, 1>{});
   }
 }
 
@@ -692,24 +737,37 @@ hipError_t launch_mfma(const qg_conv_args& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int R, int S, int NCB>
-hipError_t launch_same(const qg_conv_args& a, int smem, int halo, int nchunks_pad, hipStream_t s) {
-  const int npix = a.Nb * a.H * a.W;
-  const dim3 grid((unsigned)(((npix + 127) / 128) * (a.C / (NCB * 32))));
-  if (a.has_bzp && a.lcg < 2) {  // groups of 1 or 2 channels: row offsets from the matrix cores
-    if (hipError_t e = qg_allow_smem<qg_conv_same_mfma_kernel<R, S, NCB, true, true>>(smem); e != hipSuccess) return e;
-    hipLaunchKernelGGL((qg_conv_same_mfma_kernel<R, S, NCB, true, true>), grid, dim3(256), smem, s, a.in, a.Wfrag, a.Nb, a.H, a.W, a.C,
-                       halo, nchunks_pad, a);
-  } else if (a.has_bzp) {
-    if (hipError_t e = qg_allow_smem<qg_conv_same_mfma_kernel<R, S, NCB, true>>(smem); e != hipSuccess) return e;
-    hipLaunchKernelGGL((qg_conv_same_mfma_kernel<R, S, NCB, true>), grid, dim3(256), smem, s, a.in, a.Wfrag, a.Nb, a.H, a.W, a.C, halo,
-                       nchunks_pad, a);
-  } else {
-    if (hipError_t e = qg_allow_smem<qg_conv_same_mfma_kernel<R, S, NCB, false>>(smem); e != hipSuccess) return e;
-    hipLaunchKernelGGL((qg_conv_same_mfma_kernel<R, S, NCB, false>), grid, dim3(256), smem, s, a.in, a.Wfrag, a.Nb, a.H, a.W, a.C, halo,
-                       nchunks_pad, a);
-  }
+// Compact weights: where the layout of one dword per (output channel, tap) exists -- groups of 4 -> 4 (Wp), of 1 and 2
+// (Wany) -- and the grid is more than the four workgroups per CU that fit with whole fragments (below that the masking
+// buys nothing: 32 x 28 x 28 x 256 in groups of 4 8.2 us with fragments, 8.5 without).
+bool compact_ok(const qg_conv_args& a) {
+  if (a.lcg < 2 ? a.Wany == nullptr : a.lcg != 2 || a.Wany != nullptr) return false;
+  const int ncb = a.C % 64 == 0 ? 2 : 1;
+  return (long long)((a.Nb * a.H * a.W + 127) / 128) * (a.C / (ncb * 32)) > 4 * 256;
+}
+template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT>
+hipError_t launch_same_k(const qg_conv_args& a, int smem, int halo, hipStream_t s) {
+  constexpr auto fn = qg_conv_same_mfma_kernel<R, S, NCB, HAS_BZP, RS_MFMA, COMPACT>;
+  if (hipError_t e = qg_allow_smem<fn>(smem); e != hipSuccess) return e;
+  const int npix = a.Nb * a.H * a.W, ntile = (npix + 127) / 128, nslice = a.C / (NCB * 32);
+  const udiv dS = make_udiv((unsigned)nslice), dW = make_udiv((unsigned)a.W), dH = make_udiv((unsigned)a.H);
+  hipLaunchKernelGGL(fn, dim3((unsigned)(ntile * nslice)), dim3(256), smem, s, a.in,
+                     COMPACT < 0 ? a.Wfrag : COMPACT == 2 ? a.Wp : a.Wany, npix, a.H, a.W, a.C, halo, ntile,
+                     nslice, dS.m, dW.m, dH.m, dW.s | dH.s << 16, dS.s, a);
   return hipGetLastError();
+}
+template <int R, int S, int NCB>
+hipError_t launch_same(const qg_conv_args& a, int smem, int halo, hipStream_t s) {
+  if (compact_ok(a)) {
+    switch (a.lcg) {
+      case 0: return a.has_bzp ? launch_same_k<R, S, NCB, true, true, 0>(a, smem, halo, s) : launch_same_k<R, S, NCB, false, false, 0>(a, smem, halo, s);
+      case 1: return a.has_bzp ? launch_same_k<R, S, NCB, true, true, 1>(a, smem, halo, s) : launch_same_k<R, S, NCB, false, false, 1>(a, smem, halo, s);
+      default: return a.has_bzp ? launch_same_k<R, S, NCB, true, false, 2>(a, smem, halo, s) : launch_same_k<R, S, NCB, false, false, 2>(a, smem, halo, s);
+    }
+  }
+  if (a.has_bzp && a.lcg < 2) return launch_same_k<R, S, NCB, true, true, -1>(a, smem, halo, s);
+  return a.has_bzp ? launch_same_k<R, S, NCB, true, false, -1>(a, smem, halo, s)
+                   : launch_same_k<R, S, NCB, false, false, -1>(a, smem, halo, s);
 }
 
 hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
@@ -719,19 +777,15 @@ hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
   // "same" convolution: whole input patch staged in LDS, if it fits
   const int R = RS == 9 ? 3 : 1;
   if (mfma_ok && a.stride == 1 && 2 * a.pad == R - 1 && a.Ho == a.H && a.Wo == a.W) {
-    // 64 channels per workgroup: about 35 KB of LDS at W = 56, so four workgroups share a CU and one's
-    // request burst overlaps the others' arithmetic (128 channels halve the weight traffic but leave two)
-    const int ncb = a.C % 64 == 0 ? 2 : 1;
+    // 64 channels per workgroup: about 39 KB of LDS at W = 56, so four workgroups share a CU and one's
+    // request burst overlaps the others' arithmetic (128 channels halve the weight traffic but leave two);
+    // 32 where C asks for it or the image is too wide for 64
     const int halo = a.pad * a.W + a.pad;
-    const int cp = ncb * 2;
-    const int nchunks_pad = ((128 + 2 * halo) * cp + 255) / 256 * 256;
-    const int smem = ncb * RS * QG_FRAG_BYTES + ncb * 32 * 12 + nchunks_pad * 16;
-    if (smem <= 160 * 1024) {
-      if (ncb == 2) return RS == 9 ? launch_same<3, 3, 2>(a, smem, halo, nchunks_pad, s)
-                                   : launch_same<1, 1, 2>(a, smem, halo, nchunks_pad, s);
-      return RS == 9 ? launch_same<3, 3, 1>(a, smem, halo, nchunks_pad, s)
-                     : launch_same<1, 1, 1>(a, smem, halo, nchunks_pad, s);
-    }
+    auto smem_of = [&](int ncb) { return (compact_ok(a) ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 + (128 + 2 * halo + 1) * (ncb * 2 + 1) * 16; };
+    if (a.C % 64 == 0 && smem_of(2) <= 160 * 1024)
+      return RS == 9 ? launch_same<3, 3, 2>(a, smem_of(2), halo, s) : launch_same<1, 1, 2>(a, smem_of(2), halo, s);
+    if (smem_of(1) <= 160 * 1024)
+      return RS == 9 ? launch_same<3, 3, 1>(a, smem_of(1), halo, s) : launch_same<1, 1, 1>(a, smem_of(1), halo, s);
   }
   // matrix-core kernel with taps fetched from global memory: needs whole 32-channel blocks and 16-byte aligned pixels
   if (mfma_ok && a.C % 32 == 0 && a.Cout == a.C &&

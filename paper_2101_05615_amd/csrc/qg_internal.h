@@ -188,6 +188,13 @@ __device__ __forceinline__ qg_v4i qg_mask_a_chunk(qg_v4i v, int kvalid) {
   return v;
 }
 
+// Workgroup ids go round-robin over the 8 XCDs, each with an L2 of its own: place of workgroup `id` in a sequence of `total`
+// that gives every XCD one contiguous run (lengths differ by at most one), for neighbours to share what they read.
+__device__ __forceinline__ int qg_xcd_run(int id, int total) {
+  const int x = id & 7;
+  return x * (total >> 3) + min(x, total & 7) + (id >> 3);
+}
+
 // 16 bytes of a row of A of which the first `kvalid` belong to the matrix; the rest reads as 0x80 (the int8
 // zero after the uint8 -> int8 shift).  `safe`: all 16 bytes lie inside the caller's buffer, so one vector
 // load and a byte mask do; otherwise byte by byte with bounds checks.  Any address.
