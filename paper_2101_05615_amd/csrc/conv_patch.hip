@@ -131,20 +131,14 @@ __global__ __launch_bounds__(WM* WN * 64) void qg_conv_patch_kernel(
   // of a tile back to back on the same XCD.
   int tile, slice;
   {
-    const int ntile = (npix + TP - 1) / TP, id = blockIdx.x;
+    const int ntile = (npix + TP - 1) / TP;
     if (N <= TN) {  // one slice: no division
       slice = 0;
-      tile = (ntile & 7) == 0 ? (id & 7) * (ntile >> 3) + (id >> 3) : id;
+      tile = qg_xcd_run(blockIdx.x, ntile);
     } else {
-      const int nslice = (N + TN - 1) / TN;
-      if ((ntile & 7) == 0) {
-        const int j = id >> 3;
-        slice = j % nslice;
-        tile = (id & 7) * (ntile >> 3) + j / nslice;
-      } else {
-        slice = id % nslice;
-        tile = id / nslice;
-      }
+      const int nslice = (N + TN - 1) / TN, lin = qg_xcd_run(blockIdx.x, ntile * nslice);
+      tile = lin / nslice;
+      slice = lin - tile * nslice;
     }
   }
   const int m0 = tile * TP, n0 = slice * TN;

@@ -238,8 +238,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   // the tile sequence, and walk that sequence in bands of 8 tile-rows so that
   // the tiles resident on an XCD at one time share A and B panels in its L2.
   const int total = tiles_m * tiles_n;
-  int lin = blockIdx.x;
-  if ((total & 7) == 0) lin = (lin & 7) * (total >> 3) + (lin >> 3);
+  const int lin = qg_xcd_run(blockIdx.x, total);
   constexpr int BAND = 8;
   // (small quotients through the reciprocal: exact below 2^20, where (x + 0.5) / d is further from a whole number than the
   // rounding errors reach; an integer division is 25 instructions of a wave that has not issued a request yet)
