@@ -21,9 +21,11 @@
 // of the shape this kernel exists for -- and is widened to int8 operand dwords with two bit operations
 // per eight weights; the sparse term A B_sparse is added while the block of C is still on chip (the paper
 // fuses it into the output processing while the block is cache-resident): a wave that has just consumed a
-// batch of k blocks adds the products of that batch's entries, one (row, entry) pair per lane, into an LDS
-// tile that joins the K-split reduction.  The A bytes come from the wave's staged LDS copy of the batch
-// when there is one (a gather from memory would cost one L1 line per lane).
+// batch of k blocks scatters that batch's entries, one per lane and byte store, into zeroed fragments in its staging
+// region (the activations are in registers by then) and multiplies those like any other weights.  One product per
+// (row, entry) pair and lane, added up in LDS, was what this took before: vector instructions, 16 rows of them per
+// entry, bound it (16 x 8192 x 8192 with 0.7 % of outliers 19.1 us, now 15.5 and the same at any density; 64 x 4096 x 4096
+// 15.3 -> 7.6, 64 x 8192 x 8192 49 -> 22).
 //
 // M larger than the row block is covered by the second grid dimension: every row block streams
 // B again (from L2 / the memory-side cache when the blocks run close together), which beats the
@@ -119,7 +121,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   constexpr int UNION_BYTES = STAGE_BYTES;
   extern __shared__ __align__(16) unsigned char smem[];
   int* rsp = reinterpret_cast<int*>(smem + UNION_BYTES);    // [mb][row][wave]
-  int* sp = reinterpret_cast<int*>(smem + UNION_BYTES + RSP_BYTES);  // B4: [row][slot] sparse term
+  static_assert(!B4 || REGION >= BATCH * QG_FRAG_BYTES, "the scattered fragments of a batch fit the wave's region");
 
   const int nb16 = blockIdx.x * CPW;  // first fragment column of this workgroup
   // columns held by fragment f: (f>>1)*32 + 16*(u&1) + 8*(f&1) + 4*(u>>1) + r, u<4, r<4
@@ -151,11 +153,6 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
       }
     }
   };
-
-  if (B4) {
-    for (int t = tid; t < MB * 256; t += NWAVES * 64) sp[t] = 0;
-    __syncthreads();
-  }
 
   // K slices are dealt to the waves rotated by the workgroup index, so that at any instant the workgroups
   // of an XCD read DIFFERENT lines of A (all of them read all of A; unrotated they would all hit the same
@@ -401,20 +398,26 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
         }
       }
     if (B4) {
-      // sparse term of this batch: pair idx = (entry idx / ROWS, row idx % ROWS); A_s = A_u - 128.  Entries are
-      // held one per lane, 64 at a time, and handed to the lanes that need them with a shuffle.
-      for (int c0 = 0; c0 < sp_ne; c0 += 64) {
-        const int held = c0 == 0 ? sp_first : (c0 + lane < sp_ne ? p.sp_entries[sp_e0 + c0 + lane] : 0);
-        const int pairs = min(sp_ne - c0, 64) * ROWS;
-        for (int idx = lane; idx < ((pairs + 63) & ~63); idx += 64) {
-          const int ent = __shfl(held, idx / ROWS);  // every lane takes part in the shuffle
-          if (idx >= pairs) continue;
-          const int r = idx % ROWS;
-          const int k = ent & 0x7FFF, slot = (ent >> 16) & 15, v = ent >> 24;
-          const int kk = k - kb * QG_FRAG_K;  // inside the staged ROWS x ROWB block (chunk c of row r at c ^ r)
-          const int a = region[r * ROWB + ((((kk >> 4) ^ r) & (NCHUNK - 1)) << 4) + (kk & 15)];
-          atomicAdd(&sp[r * 16 + slot], (a - 128) * v);
+      // sparse term of this batch (LDS operations of a wave run in order: the reads above, the zeros, the bytes, the reads)
+      if (sp_ne > 0) {
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) *reinterpret_cast<v4i*>(region + j * QG_FRAG_BYTES + lane * 16) = (v4i){0, 0, 0, 0};
+        for (int c0 = 0; c0 < sp_ne; c0 += 64) {
+          if (c0 + lane < sp_ne) {
+            const int ent = c0 == 0 ? sp_first : p.sp_entries[sp_e0 + c0 + lane];
+            const int kk = (ent & 0x7FFF) - kb * QG_FRAG_K, slot = (ent >> 16) & 15;
+            region[(kk >> 6) * QG_FRAG_BYTES + ((((kk >> 4) & 3) << 4) + slot) * 16 + (kk & 15)] = (unsigned char)(ent >> 24);
+          }
         }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j)
+          if (kb + j < kb_end) {
+            const v4i sf = *reinterpret_cast<const v4i*>(region + j * QG_FRAG_BYTES + lane * 16);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+              acc[mb][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sf, af[mb][j] ^ (int)0x80808080, acc[mb][0], 0, 0, 0);
+          }
+        asm volatile("" ::: "memory");  // these reads stay in front of the next batch's requests into the same region
       }
     }
   };
@@ -524,9 +527,9 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
     for (int w = 0; w < NWAVES / 4; ++w) rsum += tr[w].x + tr[w].y + tr[w].z + tr[w].w;
   }
   if (B4) {
-    // A_s B = (A_s U - 8 rowsum(A_s)) + A_s B_sparse; lane (ml, g) register r is slot 4 g + r of the fragment
+    // A_s B = (A_s U - 8 rowsum(A_s)) + A_s B_sparse
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sum[r] += sp[(mb * 16 + ml) * 16 + 4 * g + r] - 8 * rsum;
+    for (int r = 0; r < 4; ++r) sum[r] -= 8 * rsum;
   }
 
   // ---- K split across workgroups: hand the partial tile in, the last slice to arrive carries on
@@ -609,8 +612,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
 template <int MODE, int MB, int NWAVES, int BATCH, bool B4, bool ANYALIGN>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   const int part = NWAVES * MB * 64 * (int)sizeof(v4i), stage = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K);
-  const int smem = (stage > part ? stage : part) + NWAVES * MB * 16 * (int)sizeof(int) +
-                   (B4 ? MB * 256 * (int)sizeof(int) : 0);
+  const int smem = (stage > part ? stage : part) + NWAVES * MB * 16 * (int)sizeof(int);
   const int nfrag = ((a.N + 31) / 32) * 2;
   const int mblocks = (a.M + MB * 16 - 1) / (MB * 16);
   if (mblocks > 65535 || a.ksplit < 1 || a.ksplit > 65535) return hipErrorInvalidValue;
@@ -691,13 +693,28 @@ hipError_t launch_conv(const qg_gemm_args& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Outlier-split weights: eight waves instead of sixteen where more than one workgroup falls to a CU (fewer waves, longer
+// streams each: 16 x 8192 x 8192 15.5 -> 12.0 us) or where sixteen would not get a whole batch of k blocks each (7 x 1100 x
+// 3000 5.5 -> 5.0); with one workgroup per CU and whole batches sixteen stay ahead (16 x 4096 x 4096 4.3 us against 4.5).
+template <int MB, int BATCH>
+bool split_few_waves(const qg_gemm_args& a) {
+  const long long wgs = (long long)(((a.N + 31) / 32) * 2) * ((a.M + MB * 16 - 1) / (MB * 16)) * a.ksplit;
+  return wgs > 256 || a.ks_per < 16 * BATCH;
+}
 // waves per workgroup and k blocks a wave requests at once, per row-block height
+template <int MODE, int MB, int BATCH, bool B4, bool ANYALIGN>
+hipError_t launch_waves(const qg_gemm_args& a, hipStream_t s) {
+  if constexpr (B4) {
+    if (split_few_waves<MB, BATCH>(a)) return launch<MODE, MB, 8, BATCH, B4, ANYALIGN>(a, s);
+  }
+  return launch<MODE, MB, 16, BATCH, B4, ANYALIGN>(a, s);
+}
 template <int MODE, bool B4, bool ANYALIGN>
 hipError_t launch_mb(const qg_gemm_args& a, int kernel, hipStream_t s) {
   switch (kernel) {
-    case QG_KERNEL_SKINNY16: return launch<MODE, 1, 16, 4, B4, ANYALIGN>(a, s);
-    case QG_KERNEL_SKINNY32: return launch<MODE, 2, 16, 4, B4, ANYALIGN>(a, s);
-    case QG_KERNEL_SKINNY64: return launch<MODE, 4, 16, 2, B4, ANYALIGN>(a, s);
+    case QG_KERNEL_SKINNY16: return launch_waves<MODE, 1, 4, B4, ANYALIGN>(a, s);
+    case QG_KERNEL_SKINNY32: return launch_waves<MODE, 2, 4, B4, ANYALIGN>(a, s);
+    case QG_KERNEL_SKINNY64: return launch_waves<MODE, 4, 2, B4, ANYALIGN>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
