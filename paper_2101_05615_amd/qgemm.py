@@ -349,7 +349,7 @@ class PreparedGemm:
         self._keep = (A, Bp, bias, scales, out, workspace)
         self._p = _params(a_zp, bias, scales, c_zp, relu)
         self._args = (A.data_ptr(), A.shape[0], A.stride(0), Bp.handle, ctypes.byref(self._p), out.data_ptr(),
-                      out.stride(0), workspace.data_ptr() if workspace is not None else None, ctypes.c_void_p(_stream()),
+                      out.stride(0), workspace.data_ptr() if workspace is not None else None, _stream(),
                       kernel_id(kernel))
         self.out = out
 
@@ -360,7 +360,7 @@ class PreparedGemm:
 
     def rebind(self):
         """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
-        self._args = self._args[:8] + (ctypes.c_void_p(_stream()),) + self._args[9:]
+        self._args = self._args[:8] + (_stream(),) + self._args[9:]
         return self
 
 
