@@ -16,6 +16,7 @@
 //  * dot4 kernel (any C = 4 G): thread = (pixel, group), one tap of one group is one dword = one
 //    v_dot4_i32_i8 operand, the 36 x 4 weight block lives in 36 registers.
 #include "qg_internal.h"
+#include "qg_position.h"
 #include <type_traits>
 
 namespace {
@@ -211,23 +212,6 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned char* lds_base)
                                    (__attribute__((address_space(3))) void*)lds_base, 16, 0, 0);
 }
 
-// Exact unsigned division by a number the host knows: q = (t + ((n - t) >> s1)) >> s2 with t the high word of m * n (Granlund
-// and Montgomery, "Division by invariant integers using multiplication", 1994).  All of it on the scalar unit; an integer
-// division is 25 vector instructions.
-struct udiv {
-  unsigned m, s;  // s: s1 | s2 << 8
-};
-udiv make_udiv(unsigned d) {
-  int l = 0;
-  while ((1ull << l) < d) ++l;
-  const unsigned m = (unsigned)((((1ull << l) - d) << 32) / d) + 1u;
-  return {m, (unsigned)(l < 1 ? l : 1) | (unsigned)(l > 0 ? l - 1 : 0) << 8};
-}
-__device__ __forceinline__ unsigned quot(unsigned n, unsigned m, unsigned s) {
-  const unsigned t = __umulhi(m, n);
-  return (t + ((n - t) >> (s & 1))) >> (s >> 8 & 31);
-}
-
 // "Same" convolution (stride 1, 2*pad == R-1 == S-1): the input pixel of tap (kh, kw) of output pixel q
 // is pixel q + (kh-pad)*W + (kw-pad) of the same linear NHWC pixel sequence.  A workgroup owns 128
 // consecutive output pixels of one group of NCB*32 channels; it requests its whole input patch (the 128
@@ -275,7 +259,7 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   // by the halo rows, and both meet in one L2 (32 x 28 x 28 x 256, 196 tiles of four slices dealt out one by one: 8.0 us
   // against 5.8).
   const int lin = qg_xcd_run(blockIdx.x, ntile * nslice);
-  const int tile = (int)quot((unsigned)lin, mS, shift_S), slice = lin - tile * nslice;
+  const int tile = (int)qg_quot((unsigned)lin, mS, shift_S), slice = lin - tile * nslice;
   const int ch0 = slice * NCH;
   const int q0 = tile * 128;        // first output pixel of the workgroup
   const int lin0 = q0 - halo;       // linear index of patch pixel 0 (may be negative; clamped per chunk)
@@ -338,15 +322,8 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   const int px = q0 + wave * 32 + pl;
   // image position of this lane's pixel: the wave's first pixel is divided on the scalar unit, the lane is pl pixels on
   // from there (a lane past the last pixel gets a position that is never used for a store)
-  const unsigned pw0 = (unsigned)(q0 + wave * 32), row0 = quot(pw0, mW, shifts_WH & 0xFFFF);
-  int wo = (int)(pw0 - row0 * W) + pl;
-  int ho = (int)(row0 - quot(row0, mH, shifts_WH >> 16) * H);
-  {
-    const int rows = (int)(((float)wo + 0.5f) * __builtin_amdgcn_rcpf((float)W));  // (wo < W + 31)
-    wo -= rows * W;
-    ho += rows;
-    ho -= (int)(((float)ho + 0.5f) * __builtin_amdgcn_rcpf((float)H)) * H;
-  }
+  int ho, wo;
+  qg_pixel_position((unsigned)(q0 + wave * 32), (unsigned)pl, (unsigned)W, mW, shifts_WH & 0xFFFF, (unsigned)H, mH, shifts_WH >> 16, &ho, &wo);
   bool row_ok[R], col_ok[S];
 #pragma unroll
   for (int kh = 0; kh < R; ++kh) row_ok[kh] = (unsigned)(ho + kh - PAD_H) < (unsigned)H;
@@ -750,7 +727,7 @@ hipError_t launch_same_k(const qg_conv_args& a, int smem, int halo, hipStream_t 
   constexpr auto fn = qg_conv_same_mfma_kernel<R, S, NCB, HAS_BZP, RS_MFMA, COMPACT>;
   if (hipError_t e = qg_allow_smem<fn>(smem); e != hipSuccess) return e;
   const int npix = a.Nb * a.H * a.W, ntile = (npix + 127) / 128, nslice = a.C / (NCB * 32);
-  const udiv dS = make_udiv((unsigned)nslice), dW = make_udiv((unsigned)a.W), dH = make_udiv((unsigned)a.H);
+  const qg_udiv dS = qg_make_udiv((unsigned)nslice), dW = qg_make_udiv((unsigned)a.W), dH = qg_make_udiv((unsigned)a.H);
   hipLaunchKernelGGL(fn, dim3((unsigned)(ntile * nslice)), dim3(256), smem, s, a.in,
                      COMPACT < 0 ? a.Wfrag : COMPACT == 2 ? a.Wp : a.Wany, npix, a.H, a.W, a.C, halo, ntile,
                      nslice, dS.m, dW.m, dH.m, dW.s | dH.s << 16, dS.s, a);

@@ -43,3 +43,32 @@ def test_group_conv_same(cfg, bzp, relu, c_zp):
                                         torch.from_numpy(c.scales).to(dev), c.c_zp, c.relu, c.pad, c.stride)
     torch.cuda.synchronize()
     assert_same(got.cpu().numpy(), want, f"group conv {cfg}")
+
+
+@pytest.mark.parametrize("H,W,R", [(1, 1 << 24, 1), (1 << 24, 1, 1), (1 << 24, 1, 3), (3, (1 << 23) + 5, 1)])
+def test_group_conv_positions_of_long_images(H, W, R):
+    """Rows and columns beyond 2^23 pixels: the last ones must not be taken for pixels outside the image.  A 1 x 1 filter
+    does not know the shape of the image, and of a column of pixels a 3 x 3 filter sees the middle column only: the same
+    pixels as an image of short rows, or the last ones as a shorter column, give the same bytes."""
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    say(f"group conv long image {H}x{W} filter {R}")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    G, C, n = 8, 32, H * W
+    wt = torch.randint(-128, 128, (G, R, R, 4, 4), dtype=torch.int8, device="cuda", generator=g)
+    Wp = q.pack_conv_w(wt, np.zeros(1, np.int32))
+    img = torch.randint(0, 256, (n, C), dtype=torch.uint8, device="cuda", generator=g)
+    scales = torch.full((C,), 2.0 ** -7, device="cuda")
+    bias = torch.zeros(C, dtype=torch.int32, device="cuda")
+    got = q.conv_groupwise_u8s8_requant(img.view(1, H, W, C), Wp, 3, bias, scales, 100, False, R // 2, 1).view(n, C)
+    if R == 1:
+        side = 4096 if n == 1 << 24 else 3
+        want = q.conv_groupwise_u8s8_requant(img.view(1, n // side, side, C), Wp, 3, bias, scales, 100, False, 0, 1).view(n, C)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    else:
+        for a, b in ((0, 5000), (n // 2, n // 2 + 5000), (n - 5000, n)):
+            part = q.conv_groupwise_u8s8_requant(img[a:b].view(1, b - a, 1, C), Wp, 3, bias, scales, 100, False, 1, 1).view(b - a, C)
+            torch.cuda.synchronize()
+            lo, hi = (0 if a == 0 else 1), (b - a if b == n else b - a - 1)  # rows whose neighbours are all in the part
+            assert torch.equal(got[a + lo:a + hi], part[lo:hi]), (a, b)
