@@ -154,25 +154,24 @@ double tile_estimate(const tile_cost& c, int M, int N, int K) {
 // where the choice falls on it, it is up to 1.35x faster than the best of the others (256 x 8192 x 8192), at worst 1.01x slower.
 const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.4, 0.145, 0.0, 0.0};
 
-// a_words: rows of A start at multiples of 4 bytes.  From other addresses the tile requests run at a third of their rate
-// whatever the tile (32 bytes per cycle and CU against 75 to 97), which leaves the small form of TILE128 behind the 64 x 64
-// tiles, that more CUs share (999 x 1531 x 2047 13.9 us against 13.6): it is then not considered, and only tiled kernels are
-// compared (a streaming one would want a workspace that nobody was told of).
-int builtin_select(int M, int N, int K, bool a_words = true) {
-  const bool few = qg_tile128_few(M, N, K);
+// few_ok: the 128 x 64 form may be considered.  Not
+//  - for rows of A that start off multiples of 4 bytes: there the tile requests run at a third of their rate whatever the
+//    tile (32 bytes per cycle and CU against 75 to 97), which leaves the form behind the 64 x 64 tiles, that more CUs share
+//    (999 x 1531 x 2047 13.9 us against 13.6);
+//  - for a call that asks for a K split across workgroups, which the form does not have, and for the queries about one: the
+//    answers and the calls are then the same for every alignment.
+int builtin_select(int M, int N, int K, bool few_ok = true) {
+  const bool few = few_ok && qg_tile128_few(M, N, K);
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  if (a_words || !few || builtin_select(M, N, K) != QG_KERNEL_TILE128)
-    for (const stream_cost& c : k_stream_cost) {
-      const long long blocks = ceil_div(M, c.rows);
-      if (blocks > 65535) continue;
-      const double us = stream_estimate(c, M, N, K, true);
-      if (us < best_us) best_us = us, best = c.kernel;
-    }
+  for (const stream_cost& c : k_stream_cost) {
+    const long long blocks = ceil_div(M, c.rows);
+    if (blocks > 65535) continue;
+    const double us = stream_estimate(c, M, N, K, true);
+    if (us < best_us) best_us = us, best = c.kernel;
+  }
   for (const tile_cost& c : k_tile_cost) {
-    const bool few_form = few && c.kernel == QG_KERNEL_TILE128;
-    if (few_form && !a_words) continue;
-    const double us = tile_estimate(few_form ? k_tile128_few_cost : c, M, N, K);
+    const double us = tile_estimate(few && c.kernel == QG_KERNEL_TILE128 ? k_tile128_few_cost : c, M, N, K);
     if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
@@ -205,12 +204,12 @@ int select_stream_kernel(int M, int N, int K) {
   return best;
 }
 
-int select_kernel(int M, int N, int K, bool a_words = true) {
+int select_kernel(int M, int N, int K, bool few_ok = true) {
   for (int i = 0; i < g_nrules; ++i) {
     const qg_dispatch_rule& r = g_rules[i];
     if (M >= r.m_lo && M <= r.m_hi && N >= r.n_lo && N <= r.n_hi && K >= r.k_lo && K <= r.k_hi) return r.kernel;
   }
-  return builtin_select(M, N, K, a_words);
+  return builtin_select(M, N, K, few_ok);
 }
 
 hipError_t launch_rows(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
@@ -242,7 +241,10 @@ hipError_t launch_gemm(const qg_gemm_args& a, int mode, int kernel, hipStream_t 
 
 // resolves QG_KERNEL_AUTO for a descriptor and checks an explicit choice against it: QG_OK, or
 // QG_EINVAL (unknown id / too many row blocks), QG_EUNSUPPORTED (tiled kernel on a split descriptor)
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool a_words = true);
+int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool few_ok);
+
+// rows of A at multiples of 4 bytes (see builtin_select)
+bool word_rows(const uint8_t* A_dev, int lda) { return aligned(A_dev, 4) && lda % 4 == 0; }
 
 // kernel id valid for this M (the streaming kernels put row blocks on the 16-bit grid dimension)
 bool kernel_ok(int kernel, int M) {
@@ -252,7 +254,7 @@ bool kernel_ok(int kernel, int M) {
   return true;
 }
 
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool a_words) {
+int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool few_ok) {
   if (!kernel_ok(*kernel, M)) return QG_EINVAL;
   if (Bp->split) {
     if (*kernel == QG_KERNEL_AUTO) *kernel = select_stream_kernel(M, Bp->N, Bp->K);
@@ -260,8 +262,8 @@ int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool a_words) {
     return kernel_ok(*kernel, M) ? QG_OK : QG_EINVAL;
   }
   if (*kernel == QG_KERNEL_AUTO) {
-    *kernel = select_kernel(M, Bp->N, Bp->K, a_words);
-    if (!kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K, a_words);
+    *kernel = select_kernel(M, Bp->N, Bp->K, few_ok);
+    if (!kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K, few_ok);
   }
   return QG_OK;
 }
@@ -604,14 +606,14 @@ size_t qg_packed_b_nnz(const qg_packed_b* p) { return (p && p->split) ? (size_t)
 size_t qg_gemm_workspace_bytes(int M, const qg_packed_b* Bp) {
   if (!Bp || M <= 0 || Bp->kind != QG_KIND_GEMM) return 0;
   int kernel = QG_KERNEL_AUTO;
-  if (resolve_kernel(Bp, M, &kernel) != QG_OK) return 0;
+  if (resolve_kernel(Bp, M, &kernel, false) != QG_OK) return 0;
   const int s = auto_ksplit(kernel, M, Bp);
   return s > 1 ? splitk_ws(kernel, M, Bp->N, s).bytes() : 0;
 }
 
 size_t qg_gemm_splitk_workspace_bytes(int M, const qg_packed_b* Bp, int kernel, int ksplit) {
   if (!Bp || M <= 0 || Bp->kind != QG_KIND_GEMM || ksplit < 0 || ksplit > kMaxKsplit) return 0;
-  if (resolve_kernel(Bp, M, &kernel) != QG_OK) return 0;
+  if (resolve_kernel(Bp, M, &kernel, false) != QG_OK) return 0;
   if (kernel == QG_KERNEL_TILE128) {
     const int s = ksplit > 1 ? clamp_ksplit_tile128(Bp, ksplit) : 1;
     return s > 1 ? splitk_ws(kernel, M, Bp->N, s).bytes() : 0;
@@ -624,7 +626,7 @@ size_t qg_gemm_splitk_workspace_bytes(int M, const qg_packed_b* Bp, int kernel, 
 int qg_gemm_splitk_factor(int M, const qg_packed_b* Bp, int kernel, int ksplit) {
   if (!Bp || Bp->kind != QG_KIND_GEMM) return QG_ENULL;
   if (M <= 0 || ksplit < 0 || ksplit > kMaxKsplit) return QG_EINVAL;
-  const int rc = resolve_kernel(Bp, M, &kernel);
+  const int rc = resolve_kernel(Bp, M, &kernel, false);
   if (rc != QG_OK) return rc;
   if (kernel == QG_KERNEL_TILE128) return ksplit > 1 ? clamp_ksplit_tile128(Bp, ksplit) : 1;
   if (kernel > QG_KERNEL_SKINNY64) return 1;
@@ -672,7 +674,7 @@ static int gemm_requant(const uint8_t* A_dev, int M, int lda, const qg_packed_b*
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
+  rc = resolve_kernel(Bp, M, &kernel, ksplit <= 1 && word_rows(A_dev, lda));
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_requant(p, Bp->N);
@@ -737,7 +739,7 @@ static int gemm_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* B
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
+  rc = resolve_kernel(Bp, M, &kernel, ksplit <= 1 && word_rows(A_dev, lda));
   if (rc != QG_OK) return rc;
   if (!C32_dev && M != 0) return QG_ENULL;
   if (ldc < Bp->N) return QG_EINVAL;
@@ -783,7 +785,7 @@ int qg_gemm_u8s8_dequant_f32(const uint8_t* A_dev, int M, int lda, const qg_pack
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, aligned(A_dev, 4) && lda % 4 == 0);
+  rc = resolve_kernel(Bp, M, &kernel, word_rows(A_dev, lda));
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_dequant(p, Bp->N);
@@ -870,7 +872,7 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   int rc = check_requant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel);
+  rc = resolve_kernel(Bp, M, &kernel, true);
   if (rc != QG_OK) return rc;
   {
     qg_gemm_args a = {};
@@ -909,7 +911,7 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   int rc = check_dequant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel);
+  rc = resolve_kernel(Bp, M, &kernel, true);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {

@@ -48,3 +48,25 @@ def test_tile128_forms_meet(M, N, K):
     got = q.gemm_u8s8_acc32(A, Bp, kernel="tile128")
     want = (A.double() @ B.double()).to(torch.int32)
     assert torch.equal(got, want), f"tile128 {M}x{N}x{K}"
+
+
+@pytest.mark.parametrize("a_off,lda_pad", [(0, 0), (1, 0), (0, 3), (2, 2)])
+def test_automatic_choice_with_a_split(a_off, lda_pad):
+    """An automatic kernel with a K split asked for, on a shape whose automatic kernel without one is the 128 x 64 form."""
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    M, N, K = 141, 6144, 4096
+    assert q.kernel_names()[q.kernel_select(M, N, K)] == "tile128"
+    say(f"auto + split {M}x{N}x{K} offset {a_off} lda+{lda_pad}")
+    case = wl.random_gemm(7, M, N, K)
+    A, B, bias, scales, C, c_store = dev_case(case, torch, torch.device("cuda:0"), lda_pad=lda_pad, a_off=a_off)
+    Bp = q.pack_b(B, case.b_zp)
+    want = q.gemm_u8s8_requant(A, case.a_zp, Bp, bias, scales, case.c_zp, case.relu, kernel="tile64")
+    plain = q.gemm_u8s8_requant(A, case.a_zp, Bp, bias, scales, case.c_zp, case.relu, workspace=q.gemm_workspace(M, Bp))
+    assert torch.equal(plain, want)
+    for ksplit in (2, 4):
+        assert q.gemm_splitk_factor(M, Bp, ksplit=ksplit) == ksplit
+        ws = q.gemm_workspace(M, Bp, ksplit=ksplit)
+        got = q.gemm_u8s8_requant_splitk(A, case.a_zp, Bp, bias, scales, case.c_zp, case.relu, ws, ksplit=ksplit)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), ksplit
