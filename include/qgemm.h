@@ -217,8 +217,8 @@ int qg_gemm_u8s8_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* 
 const char* qg_kernel_name(int kernel);
 
 /* The id QG_KERNEL_AUTO resolves to for this shape (never QG_KERNEL_AUTO) when the rows of A start at multiples
- * of 4 bytes and no K split is asked for; where that is the 128 x 64 form of QG_KERNEL_TILE128, other rows and
- * calls with ksplit > 1 run the best of the other kernels.
+ * of 4 bytes and no K split is asked for; where that is the 128 x 64 form of QG_KERNEL_TILE128, other rows,
+ * calls with ksplit > 1 and fp32 activations without a workspace run the best of the other kernels.
  * QG_EINVAL (negative) if a size is not positive. */
 int qg_kernel_select(int M, int N, int K);
 

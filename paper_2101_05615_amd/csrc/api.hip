@@ -159,7 +159,8 @@ const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.4, 0.145, 0.
 //    tile (32 bytes per cycle and CU against 75 to 97), which leaves the form behind the 64 x 64 tiles, that more CUs share
 //    (999 x 1531 x 2047 13.9 us against 13.6);
 //  - for a call that asks for a K split across workgroups, which the form does not have, and for the queries about one: the
-//    answers and the calls are then the same for every alignment.
+//    answers and the calls are then the same for every alignment;
+//  - for fp32 activations without a workspace, which only a streaming kernel takes.
 int builtin_select(int M, int N, int K, bool few_ok = true) {
   const bool few = few_ok && qg_tile128_few(M, N, K);
   int best = QG_KERNEL_TILE64;
@@ -872,7 +873,7 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   int rc = check_requant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel, true);
+  rc = resolve_kernel(Bp, M, &kernel, workspace_dev != nullptr);
   if (rc != QG_OK) return rc;
   {
     qg_gemm_args a = {};
@@ -911,7 +912,7 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   int rc = check_dequant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel, true);
+  rc = resolve_kernel(Bp, M, &kernel, workspace_dev != nullptr);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {

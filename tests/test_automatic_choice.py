@@ -68,3 +68,16 @@ def test_no_split_by_itself_where_the_form_is_the_choice():
                     assert q.lib.qg_gemm_splitk_factor(M, ctypes.byref(d), 0, 0) == 1, (M, N, K)
                     assert q.lib.qg_gemm_workspace_bytes(M, ctypes.byref(d)) == 0, (M, N, K)
     assert seen > 100
+
+
+def test_fp32_activations_without_a_workspace():
+    """The one-launch form on a streaming kernel stays the choice where that is the best kernel but for the form."""
+    p, dq = q.RequantParams(0, None, 4096, 1, 0, 0), q.DequantParams(0, None, 4096, 1, 0)
+    for M, N, K, one_launch in [(129, 6144, 2048, True), (141, 6144, 4096, True), (80, 12288, 12288, True), (65, 12288, 2048, True),
+                                (256, 8192, 8192, False), (999, 1531, 2047, False)]:
+        assert few(M, N, K)
+        d = descriptor(K, N)
+        # A off 4 bytes: the one-launch form refuses it, a tiled kernel refuses the missing workspace
+        want = q.EALIGN if one_launch else q.EWORKSPACE
+        assert q.lib.qg_gemm_f32s8_requant(4097, M, K, 1.0, ctypes.byref(d), ctypes.byref(p), 4096, N, None, None, 0) == want
+        assert q.lib.qg_gemm_f32s8_dequant_f32(4097, M, K, 1.0, ctypes.byref(d), ctypes.byref(dq), 4096, N, None, None, 0) == want

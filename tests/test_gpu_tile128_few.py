@@ -70,3 +70,20 @@ def test_automatic_choice_with_a_split(a_off, lda_pad):
         got = q.gemm_u8s8_requant_splitk(A, case.a_zp, Bp, bias, scales, case.c_zp, case.relu, ws, ksplit=ksplit)
         torch.cuda.synchronize()
         assert torch.equal(got, want), ksplit
+
+
+def test_fp32_activations_without_a_workspace():
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    M, N, K = 129, 6144, 2048
+    assert q.kernel_names()[q.kernel_select(M, N, K)] == "tile128"
+    g = torch.Generator(device="cuda").manual_seed(9)
+    A = torch.randn((M, K), device="cuda", generator=g)
+    Bp = q.pack_b(torch.randint(-128, 128, (K, N), dtype=torch.int8, device="cuda", generator=g), [3])
+    bias = torch.randint(-1000, 1001, (N,), dtype=torch.int32, device="cuda", generator=g)
+    scales = torch.full((1,), 2.0 ** -13, device="cuda")
+    for fn, last in ((q.gemm_f32s8_requant, (100, False)), (q.gemm_f32s8_dequant_f32, (False,))):
+        want = fn(A, 25.0, 120, Bp, bias, scales, *last)
+        got = fn(A, 25.0, 120, Bp, bias, scales, *last, workspace=q.NO_WORKSPACE)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
