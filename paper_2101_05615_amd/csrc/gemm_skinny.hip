@@ -398,10 +398,14 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
         }
       }
     if (B4) {
-      // sparse term of this batch (LDS operations of a wave run in order: the reads above, the zeros, the bytes, the reads)
+      // sparse term of this batch.  The lanes hand each other bytes through the wave's region: its LDS operations run in order
+      // -- the reads above, the zeros, the bytes, the reads --, and the empty statements keep the compiler, which looks at one
+      // lane at a time, from reordering them or from taking a lane's own zeros for what it will read.
       if (sp_ne > 0) {
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) *reinterpret_cast<v4i*>(region + j * QG_FRAG_BYTES + lane * 16) = (v4i){0, 0, 0, 0};
+        asm volatile("" ::: "memory");
         for (int c0 = 0; c0 < sp_ne; c0 += 64) {
           if (c0 + lane < sp_ne) {
             const int ent = c0 == 0 ? sp_first : p.sp_entries[sp_e0 + c0 + lane];
@@ -409,6 +413,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
             region[(kk >> 6) * QG_FRAG_BYTES + ((((kk >> 4) & 3) << 4) + slot) * 16 + (kk & 15)] = (unsigned char)(ent >> 24);
           }
         }
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int j = 0; j < BATCH; ++j)
           if (kb + j < kb_end) {
