@@ -270,11 +270,15 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
     const int8_t* wsrc = Wfrag + (size_t)slice * NCB * RS * QG_FRAG_BYTES + lane * 16;
     for (int f = wave; f < NCB * RS; f += 4) dma16(wsrc + (size_t)f * QG_FRAG_BYTES, w_s + f * QG_FRAG_BYTES);
   }
-  constexpr int BATCH = 4;
+  // a 1 x 1 filter has no halo: its patch takes one or two loads per thread
+  constexpr int BATCH = 4, FIRST = RS == 1 ? CP / 2 : BATCH;
+  static_assert(FIRST >= 1 && FIRST <= BATCH, "v holds the first batch too");
   const int phys = tid % CP, pp0 = tid / CP;  // chunk tid + 256 j is chunk `phys` of patch pixel pp0 + j * (256 / CP)
   const uint8_t* const src0 = in + ch0 + phys * 16;
-  auto load = [&](int j) {  // (unconditional: a load under a condition makes the compiler wait for the one before it)
-    const int lin = min(max(lin0 + pp0 + j * (256 / CP), 0), npix - 1);
+  const int lin_end = min(lin0 + npp, npix) - 1;
+  auto load = [&](int j) {  // (unconditional: a load under a condition makes the compiler wait for the one before it.
+    // Past the patch all lanes ask for its last pixel, which costs an issue slot but no line.)
+    const int lin = min(max(lin0 + pp0 + j * (256 / CP), 0), lin_end);
     return *reinterpret_cast<const v4i*>(src0 + (size_t)(unsigned)lin * (unsigned)C);
   };
   auto store = [&](int j, v4i v) {
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   };
   v4i v[BATCH];
 #pragma unroll
-  for (int j = 0; j < BATCH; ++j) v[j] = load(j);
+  for (int j = 0; j < FIRST; ++j) v[j] = load(j);
   constexpr int WCHUNKS = COMPACT >= 0 ? NCH * RS / 4 : 0;  // 16-byte chunks of the compact weights
   static_assert(WCHUNKS <= 256 && NCH * RS % 4 == 0, "one chunk per thread");
   v4i wv = (v4i){0, 0, 0, 0};
@@ -292,9 +296,9 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   const int co = p.col_off[oc], bi = (p.bias ? p.bias : p.col_off)[oc], bz = HAS_BZP ? p.bzp[oc] : 0;
   const float sc = p.scales[(size_t)oc * p.scale_stride];
 #pragma unroll
-  for (int j = 0; j < BATCH; ++j)
+  for (int j = 0; j < FIRST; ++j)
     if (tid + 256 * j < nchunks) store(j, v[j]);
-  for (int j0 = BATCH; 256 * j0 < nchunks; j0 += BATCH) {  // wide images
+  for (int j0 = FIRST; 256 * j0 < nchunks; j0 += BATCH) {  // wide images
 #pragma unroll
     for (int j = 0; j < BATCH; ++j) v[j] = load(j0 + j);
 #pragma unroll

@@ -24,6 +24,8 @@ pytestmark = pytest.mark.gpu
     dict(Nb=1, H=262, W=259, C=128, G=64),           # ... of 2
     dict(Nb=2, H=20, W=21, C=64, G=2),               # groups of 32
     dict(Nb=2, H=20, W=21, C=64, G=16, R=1, S=1, pad=0),
+    dict(Nb=3, H=19, W=23, C=96, G=24, R=1, S=1, pad=0),        # 1 x 1, 32-channel slices: one chunk per thread
+    dict(Nb=1, H=262, W=259, C=128, G=128, R=1, S=1, pad=0),    # 1 x 1, compact weights
 ])
 @pytest.mark.parametrize("bzp,relu,c_zp", [(True, False, 77), (False, True, 0), (False, True, 9), (True, False, 0)])
 def test_group_conv_same(cfg, bzp, relu, c_zp):
