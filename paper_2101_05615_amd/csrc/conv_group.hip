@@ -17,6 +17,7 @@
 //    v_dot4_i32_i8 operand, the 36 x 4 weight block lives in 36 registers.
 #include "qg_internal.h"
 #include "qg_position.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace {
@@ -224,13 +225,15 @@ __device__ __forceinline__ void dma16(const void* gptr, unsigned char* lds_base)
 // being masked, one select per tap; and positions and tile numbers are divided on the scalar unit.  32 x 56 x 56 x 128, groups
 // of 4 10.9 -> 9.3 us, depthwise 11.0 -> 9.1, groups of 16 11.6 -> 10.5; 32 x 28 x 28 x 256, groups of 4 8.0 -> 5.7;
 // 8 x 14 x 14 x 512, groups of 16 3.85 -> 3.24.
+// RAW: the patch goes straight to LDS instead (all requests in flight at once, no gap between pixels: a fifth less LDS, a third
+// for 32-channel slices), swizzled, and each tap shifts its bytes; for wide images, see the launcher.
 //
 // COMPACT (log2 of the channels per group, -1: no): groups of at most 4 channels.  A lane's 16 bytes of a block-diagonal
 // fragment are then one dword and twelve zero bytes, so LDS holds the dwords alone (from the layouts of the plain kernels; 2.3
 // instead of 18 KiB) and the lane masks its dword into place: seven workgroups share a CU instead of four, and the grid of
 // 1568 is one round (10.5 -> 9.5 us at 32 x 56 x 56 x 128).  Fetching that dword per lane and fragment from memory instead
 // took 14.5 us: a load whose lanes lie 16 bytes apart keeps the L1 busy as long as one of 16 bytes per lane.
-template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT>
+template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT, bool RAW>
 __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >= 0 ? 7 : 4)) void qg_conv_same_mfma_kernel(
     const uint8_t* in, const int8_t* Wfrag, const int npix, const int H, const int W, const int C, const int halo,
     const int ntile, const int nslice, const unsigned mS, const unsigned mW, const unsigned mH, const unsigned shifts_WH,
@@ -241,7 +244,10 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   constexpr int RS = R * S;
   constexpr int NCH = NCB * 32;
   constexpr int CP = NCH / 16;         // 16-byte chunks per pixel
-  constexpr int PITCH = (CP + 1) * 16; // bytes from one patch pixel to the next: sixteen pixels' chunks in sixteen bank groups
+  // bytes from one patch pixel to the next.  Odd number of chunks: sixteen pixels' chunks lie in sixteen bank groups; RAW: the
+  // chunks of a pixel are swizzled instead (period 16 pixels)
+  constexpr int PITCH = (RAW ? CP : CP + 1) * 16;
+  auto swz = [](int pp) { return CP == 4 ? (((pp >> 1) & 3) ^ ((pp >> 3) & 1)) : ((pp >> 3) & 1); };
   constexpr int PAD_H = (R - 1) / 2, PAD_W = (S - 1) / 2;
   extern __shared__ __align__(16) unsigned char smem[];
   // COMPACT: one dword per (output channel, tap); groups of 4: [group][tap][channel], smaller: [channel][tap]
@@ -264,6 +270,7 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   const int q0 = tile * 128;        // first output pixel of the workgroup
   const int lin0 = q0 - halo;       // linear index of patch pixel 0 (may be negative; clamped per chunk)
   const int npp = 128 + 2 * halo, nchunks = npp * CP;
+  unsigned char* const azp_row = patch + (RAW ? (nchunks + 63) / 64 * 1024 : npp * PITCH);
 
   // ---- one burst of requests: weights, input patch, column constants
   if constexpr (COMPACT < 0) {
@@ -285,8 +292,16 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
     *reinterpret_cast<v4i*>(patch + (pp0 + j * (256 / CP)) * PITCH + phys * 16) = v ^ (int)0x80808080;
   };
   v4i v[BATCH];
+  if constexpr (RAW) {
+    for (int c0 = wave * 64; c0 < nchunks; c0 += 256) {
+      const int c = c0 + lane, pp = c / CP;
+      const int at = min(max(lin0 + pp, 0), lin_end);
+      dma16(in + (size_t)(unsigned)at * (unsigned)C + ch0 + ((c % CP ^ swz(pp)) << 4), patch + c0 * 16);
+    }
+  } else {
 #pragma unroll
-  for (int j = 0; j < FIRST; ++j) v[j] = load(j);
+    for (int j = 0; j < FIRST; ++j) v[j] = load(j);
+  }
   constexpr int WCHUNKS = COMPACT >= 0 ? NCH * RS / 4 : 0;  // 16-byte chunks of the compact weights
   static_assert(WCHUNKS <= 256 && NCH * RS % 4 == 0, "one chunk per thread");
   v4i wv = (v4i){0, 0, 0, 0};
@@ -295,15 +310,17 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   const int oc = ch0 + tid % NCH;
   const int co = p.col_off[oc], bi = (p.bias ? p.bias : p.col_off)[oc], bz = HAS_BZP ? p.bzp[oc] : 0;
   const float sc = p.scales[(size_t)oc * p.scale_stride];
+  if constexpr (!RAW) {
 #pragma unroll
-  for (int j = 0; j < FIRST; ++j)
-    if (tid + 256 * j < nchunks) store(j, v[j]);
-  for (int j0 = FIRST; 256 * j0 < nchunks; j0 += BATCH) {  // wide images
+    for (int j = 0; j < FIRST; ++j)
+      if (tid + 256 * j < nchunks) store(j, v[j]);
+    for (int j0 = FIRST; 256 * j0 < nchunks; j0 += BATCH) {  // wide images
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j) v[j] = load(j0 + j);
+      for (int j = 0; j < BATCH; ++j) v[j] = load(j0 + j);
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j)
-      if (tid + 256 * (j0 + j) < nchunks) store(j0 + j, v[j]);
+      for (int j = 0; j < BATCH; ++j)
+        if (tid + 256 * (j0 + j) < nchunks) store(j0 + j, v[j]);
+    }
   }
   if (WCHUNKS > 0 && tid < WCHUNKS) {
     if (COMPACT < 2) {  // the channel's bytes to their place in its dword of the fragment
@@ -318,8 +335,8 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
     sc_s[tid] = sc;
   }
   if (tid < CP) {
-    const int z = (int)(((unsigned)p.a_zp * 0x01010101u) ^ 0x80808080u);
-    *reinterpret_cast<v4i*>(patch + npp * PITCH + tid * 16) = (v4i){z, z, z, z};
+    const int z = (int)(((unsigned)p.a_zp * 0x01010101u) ^ (RAW ? 0u : 0x80808080u));
+    *reinterpret_cast<v4i*>(azp_row + tid * 16) = (v4i){z, z, z, z};
   }
 
   const int pl = lane & 31, g = lane >> 5;
@@ -335,14 +352,14 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   for (int kw = 0; kw < S; ++kw) col_ok[kw] = (unsigned)(wo + kw - PAD_W) < (unsigned)W;
   const float czp_f = (float)p.c_zp;
   const unsigned char* const a_px = patch + (wave * 32 + pl + halo) * PITCH + 16 * g;  // this lane's half of its centre pixel
-  const unsigned char* const a_zero = patch + npp * PITCH + 16 * g;
+  const unsigned char* const a_zero = azp_row + 16 * g;
   // COMPACT: this lane's output channel, its dword's place among the 16 input channels of the lane's half (outside: none)
   const int oc_l = qg_slot_to_col(pl), wj = (oc_l >> 4) == g ? (oc_l >> 2) & 3 : 4;
   const v4i wmask = (v4i){wj == 0 ? -1 : 0, wj == 1 ? -1 : 0, wj == 2 ? -1 : 0, wj == 3 ? -1 : 0};
   const unsigned char* const w_l = w_s + (COMPACT == 2 ? (oc_l >> 2) * (RS * 16) + (oc_l & 3) * 4 : oc_l * (RS * 4));
   constexpr int WTAP = COMPACT == 2 ? 16 : 4;
 
-  if (COMPACT < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the weight requests of this wave have landed in LDS ...
+  if (COMPACT < 0 || RAW) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the requests of this wave have landed in LDS ...
   __syncthreads();                                                 // ... before any wave reads the others' slots
 
   // the accumulators start at bias - (theta_A - 128) * column offset, so the output pipeline adds nothing
@@ -373,11 +390,17 @@ __global__ __launch_bounds__(256, HAS_BZP ? (COMPACT >= 0 ? 4 : 2) : (COMPACT >=
   for (int kh = 0; kh < R; ++kh) {
 #pragma unroll
     for (int kw = 0; kw < S; ++kw) {
-      const int off = ((kh - PAD_H) * W + (kw - PAD_W)) * PITCH;
-      const unsigned char* const src = row_ok[kh] && col_ok[kw] ? a_px + off : a_zero;
+      const int step = (kh - PAD_H) * W + (kw - PAD_W);
+      // RAW: chunk g + 2 cb of the pixel lies at its place xor swz
+      const int pp = wave * 32 + pl + halo + step;
+      const unsigned char* const src = row_ok[kh] && col_ok[kw] ? (RAW ? patch + pp * PITCH + ((g ^ swz(pp)) << 4) : a_px + step * PITCH) : a_zero;
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        const v4i x = *reinterpret_cast<const v4i*>(src + cb * 32);
+        v4i x;
+        if constexpr (RAW)
+          x = *reinterpret_cast<const v4i*>(smem + ((src - smem) ^ (cb * 32))) ^ (int)0x80808080;
+        else
+          x = *reinterpret_cast<const v4i*>(src + cb * 32);
         if (HAS_BZP && !RS_MFMA) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) rs[cb][j] = __builtin_amdgcn_sdot4(x[j], 0x01010101, rs[cb][j], false);
@@ -726,9 +749,9 @@ bool compact_ok(const qg_conv_args& a) {
   const int ncb = a.C % 64 == 0 ? 2 : 1;
   return (long long)((a.Nb * a.H * a.W + 127) / 128) * (a.C / (ncb * 32)) > 4 * 256;
 }
-template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT>
+template <int R, int S, int NCB, bool HAS_BZP, bool RS_MFMA, int COMPACT, bool RAW = false>
 hipError_t launch_same_k(const qg_conv_args& a, int smem, int halo, hipStream_t s) {
-  constexpr auto fn = qg_conv_same_mfma_kernel<R, S, NCB, HAS_BZP, RS_MFMA, COMPACT>;
+  constexpr auto fn = qg_conv_same_mfma_kernel<R, S, NCB, HAS_BZP, RS_MFMA, COMPACT, RAW>;
   if (hipError_t e = qg_allow_smem<fn>(smem); e != hipSuccess) return e;
   const int npix = a.Nb * a.H * a.W, ntile = (npix + 127) / 128, nslice = a.C / (NCB * 32);
   const qg_udiv dS = qg_make_udiv((unsigned)nslice), dW = qg_make_udiv((unsigned)a.W), dH = qg_make_udiv((unsigned)a.H);
@@ -738,7 +761,14 @@ hipError_t launch_same_k(const qg_conv_args& a, int smem, int halo, hipStream_t 
   return hipGetLastError();
 }
 template <int R, int S, int NCB>
-hipError_t launch_same(const qg_conv_args& a, int smem, int halo, hipStream_t s) {
+hipError_t launch_same(const qg_conv_args& a, int smem, int halo, bool raw, hipStream_t s) {
+  if constexpr (R > 1) {
+    if (raw) {
+      if (a.has_bzp && a.lcg < 2) return launch_same_k<R, S, NCB, true, true, -1, true>(a, smem, halo, s);
+      return a.has_bzp ? launch_same_k<R, S, NCB, true, false, -1, true>(a, smem, halo, s)
+                       : launch_same_k<R, S, NCB, false, false, -1, true>(a, smem, halo, s);
+    }
+  }
   if (compact_ok(a)) {
     switch (a.lcg) {
       case 0: return a.has_bzp ? launch_same_k<R, S, NCB, true, true, 0>(a, smem, halo, s) : launch_same_k<R, S, NCB, false, false, 0>(a, smem, halo, s);
@@ -749,6 +779,28 @@ hipError_t launch_same(const qg_conv_args& a, int smem, int halo, hipStream_t s)
   if (a.has_bzp && a.lcg < 2) return launch_same_k<R, S, NCB, true, true, -1>(a, smem, halo, s);
   return a.has_bzp ? launch_same_k<R, S, NCB, true, false, -1>(a, smem, halo, s)
                    : launch_same_k<R, S, NCB, false, false, -1>(a, smem, halo, s);
+}
+
+// Channel slice (ncb blocks of 32), LDS and rounds of the grid of the stride-1 "same" kernel; ncb = 0: the patch does not fit.
+struct same_plan {
+  int ncb = 0, smem = 0;
+  long long rounds = 1LL << 40;
+};
+same_plan plan_same(const qg_conv_args& a, int RS, int halo, bool raw) {
+  same_plan pl;
+  const bool compact = !raw && compact_ok(a);
+  const int npp = 128 + 2 * halo;
+  for (int ncb = 2; ncb >= 1 && pl.ncb == 0; --ncb) {
+    if (a.C % (ncb * 32) != 0) continue;
+    const int smem = (compact ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 +
+                     (raw ? (npp * ncb * 2 + 63) / 64 * 1024 + ncb * 32 : (npp + 1) * (ncb * 2 + 1) * 16);
+    if (smem > 160 * 1024) continue;
+    const long long wgs = (long long)((a.Nb * a.H * a.W + 127) / 128) * (a.C / (ncb * 32));
+    const int per_cu = std::min(160 * 1024 / smem, compact && !a.has_bzp ? 7 : 4);  // (more side by side changed nothing)
+    pl.ncb = ncb, pl.smem = smem;
+    pl.rounds = (wgs + 256LL * per_cu - 1) / (256LL * per_cu);
+  }
+  return pl;
 }
 
 hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
@@ -762,11 +814,18 @@ hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
     // request burst overlaps the others' arithmetic (128 channels halve the weight traffic but leave two);
     // 32 where C asks for it or the image is too wide for 64
     const int halo = a.pad * a.W + a.pad;
-    auto smem_of = [&](int ncb) { return (compact_ok(a) ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 + (128 + 2 * halo + 1) * (ncb * 2 + 1) * 16; };
-    if (a.C % 64 == 0 && smem_of(2) <= 160 * 1024)
-      return RS == 9 ? launch_same<3, 3, 2>(a, smem_of(2), halo, s) : launch_same<1, 1, 2>(a, smem_of(2), halo, s);
-    if (smem_of(1) <= 160 * 1024)
-      return RS == 9 ? launch_same<3, 3, 1>(a, smem_of(1), halo, s) : launch_same<1, 1, 1>(a, smem_of(1), halo, s);
+    const same_plan own = plan_same(a, RS, halo, false), raw = plan_same(a, RS, halo, true);
+    // RAW (3 x 3): where it takes fewer rounds of the grid, the LDS of a wide patch being what bounds the workgroups a CU holds
+    // -- measured over 308 layers, W 40 .. 1024: 32 x 83 x 83 x 64 in groups of 8 9.7 -> 8.1 us, 1 x 150 x 400 x 448 in groups of
+    // 32 54 -> 35 --, and with more than one round from W = 256 on, where the register path waits for its loads four at a time
+    // (117 x 512 x 448 53 -> 47).  Elsewhere the register path is ahead by 4 to 15 % (32 x 56 x 56 x 128 in groups of 4 10.9
+    // against 9.3).  Within 1 % of the better one in the mean, 6 % at worst.
+    if (RS == 9 && raw.ncb > 0 && (raw.rounds < own.rounds || (own.rounds > 1 && a.W >= 256)))
+      return raw.ncb == 2 ? launch_same<3, 3, 2>(a, raw.smem, halo, true, s) : launch_same<3, 3, 1>(a, raw.smem, halo, true, s);
+    if (own.ncb == 2)
+      return RS == 9 ? launch_same<3, 3, 2>(a, own.smem, halo, false, s) : launch_same<1, 1, 2>(a, own.smem, halo, false, s);
+    if (own.ncb == 1)
+      return RS == 9 ? launch_same<3, 3, 1>(a, own.smem, halo, false, s) : launch_same<1, 1, 1>(a, own.smem, halo, false, s);
   }
   // matrix-core kernel with taps fetched from global memory: needs whole 32-channel blocks and 16-byte aligned pixels
   if (mfma_ok && a.C % 32 == 0 && a.Cout == a.C &&

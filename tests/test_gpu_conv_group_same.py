@@ -26,6 +26,13 @@ pytestmark = pytest.mark.gpu
     dict(Nb=2, H=20, W=21, C=64, G=16, R=1, S=1, pad=0),
     dict(Nb=3, H=19, W=23, C=96, G=24, R=1, S=1, pad=0),        # 1 x 1, 32-channel slices: one chunk per thread
     dict(Nb=1, H=262, W=259, C=128, G=128, R=1, S=1, pad=0),    # 1 x 1, compact weights
+    # wide rows and more workgroups than the CUs hold: the patch straight to LDS, in both channel slices
+    dict(Nb=1, H=40, W=900, C=64, G=16),
+    dict(Nb=1, H=40, W=900, C=64, G=64),
+    dict(Nb=3, H=12, W=1021, C=96, G=12),
+    dict(Nb=1, H=36, W=1064, C=64, G=4),                        # the widest that 64 channels fit
+    dict(Nb=1, H=36, W=1065, C=64, G=4),
+    dict(Nb=9, H=83, W=83, C=128, G=16),                        # fewer rounds of the grid without the gaps
 ])
 @pytest.mark.parametrize("bzp,relu,c_zp", [(True, False, 77), (False, True, 0), (False, True, 9), (True, False, 0)])
 def test_group_conv_same(cfg, bzp, relu, c_zp):
