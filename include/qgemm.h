@@ -436,8 +436,9 @@ int qg_conv_groupwise_u8s8_requant(const uint8_t* in_nhwc, int Nb, int H, int W,
  *   in_nhwc  dev uint8 [Nb][H][W][Cin]; 16-byte aligned with Cin % 16 == 0 for the staged
  *            kernels below -- any other image runs, under QG_KERNEL_AUTO only, on a kernel
  *            that keeps image rows in LDS and reads each filter row as one run of bytes (a
- *            3- or 4-channel first layer is its case) or, for 1 x 1 filters and weights too
- *            large for that, on one that gathers the im2col rows into LDS; any extents
+ *            3-channel first layer is its case) or on one that gathers the im2col rows into
+ *            LDS (1 x 1 filters, weights too large for the other, layers where it is
+ *            estimated to be faster); any extents
  *   out_nhwc dev uint8 [Nb][Ho][Wo][Cout], Ho = (H + 2*pad - R)/stride + 1
  *   kernel   QG_KERNEL_AUTO (chosen from the extents by a cost model fitted to 3 x 3 and
  *            5 x 5 layers, the patch kernels below included), or QG_KERNEL_TILE64 / TILE64K4 / TILE64X32K8 / TILE64K1 /

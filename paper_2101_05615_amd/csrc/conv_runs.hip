@@ -16,6 +16,7 @@
 // byte-gathering kernel, which spends about 27 vector instructions per byte of the im2col matrix, took 20.8; one image
 // 5.0 (9.1), 32 images 14.5 (65), 3 x 3 stride 2 -> 32 4.4 (9.2), 16 x 256 x 256 x 4, 7 x 7 stride 1 -> 64 29 (76).
 #include "qg_internal.h"
+#include <cmath>
 #include <type_traits>
 
 namespace {
@@ -394,17 +395,52 @@ hipError_t launch_runs_ks(const qg_conv_args& a, const runs_plan& pl, hipStream_
     case 5: return launch_runs<5, NB, false, 512, false>(a, pl, s);
     case 7: return launch_runs<7, NB, false, 512, false>(a, pl, s);
     case 8: return launch_runs<8, NB, false, 512, false>(a, pl, s);
-    default: return launch_runs<0, NB, false, 512, false>(a, pl, s);
+    default: return launch_runs<0, NB, false, 512, false>(a, pl, s);  // (6 and 9 .. 24: few layers have them)
   }
 }
 
 }  // namespace
 
+// Microseconds of this kernel on a planned layer, and of the byte-gathering kernel on the same one (without the time of the
+// stores, which is the same for both): launch, then the larger of a workgroup's own chain and what the workgroups of a CU share.
+// Constants fitted to 3270 drawn layers, C 1 .. 72, filters 2 x 1 .. 16 x 17, strides 1 .. 16, with and without theta_B.
+namespace {
+double runs_estimate(const qg_conv_args& a, const runs_plan& pl) {
+  const int steps = pl.p.steps, px = pl.TW * pl.TH;
+  const bool held = pl.full && steps <= 3 && !a.has_bzp, any_steps = a.has_bzp || steps > 8 || steps == 6;
+  const int waves = held ? 4 : 8, chunks = pl.pitch / 16 * ((pl.TH - 1) * a.stride + a.R);
+  const double mfma = steps * pl.nb * (a.has_bzp ? 1.92 : 1.0);
+  const double chain = 0.325 * ((chunks + waves * 128 - 1) / (waves * 128)) + (any_steps ? 0.075 : 0.038) * steps +
+                       0.0355 * mfma * (((px + 31) / 32 + waves - 1) / waves);
+  const double share = 0.195 + 0.244 * chunks / 512 + 0.096 * steps + ((px + 31) / 32) / 8.0 * (0.505 + 0.06 * mfma);
+  const int by_lds = 160 * 1024 / pl.smem, by_waves = held ? 5 : 3, per_cu = by_lds < by_waves ? by_lds : by_waves;
+  const double wgs = (double)pl.nx * pl.ny * a.Nb * ((a.Cout + pl.nb * 32 - 1) / (pl.nb * 32)) / 256.0;  // per CU
+  const double rounds = floor(wgs / per_cu), left = fmin(wgs - rounds * per_cu, (double)per_cu);
+  return 3.95 + rounds * fmax(chain, per_cu * share) + (left > 0.0 ? fmax(chain, left * share) : 0.0);
+}
+double gather_estimate(const qg_conv_args& a) {
+  const bool words = a.C % 4 == 0 && ((uintptr_t)a.in & 3) == 0;
+  const double kt = (a.R * a.S * a.C + 63) / 64, wgs = (double)(((long long)a.Nb * a.Ho * a.Wo + 63) / 64) * ((a.Cout + 63) / 64) / 256.0;
+  return words ? 2.7 + fmax(kt * (a.has_bzp ? 0.75 : 0.64), wgs * (kt * 0.29 + 0.38))
+               : 2.9 + fmax(kt * (a.has_bzp ? 2.41 : 2.06), wgs * (kt * 0.79 + 0.39));
+}
+}  // namespace
+
 // Not for 1 x 1 filters (nothing overlaps: 4 x 28 x 28 x 40, stride 2 -> 72 takes 4.0 us here, 3.7 on the gathering
-// kernel), nor where the weights of one column block outgrow the LDS (more than 48 pieces).
+// kernel), nor where the weights of one column block outgrow the LDS (more than 48 pieces); otherwise where the estimate is
+// 5 % ahead.  Gathering stays ahead where it loads whole words over a short K and the set-up here is not shared by many
+// pixels (3 x 219 x 219 x 4, 5 x 5, stride 2 -> 16 4.8 us against 7.5 here), and for strides beyond the filter, whose rows
+// hold much that is not needed (250 x 32 x 72 x 24, 2 x 2, stride 8 -> 192 5.3 against 14.4).  Over the drawn layers 0.72 of the
+// gathering kernel's time in the mean, 1 % behind the better of the two.
+// Columns that end inside a 16-byte store are written byte by byte; where that bounds both kernels, the column blocks of a
+// pixel, side by side here, write into the same lines from different XCDs (32 x 94 x 91 x 12, 2 x 2 -> 72 66.5 us, 101 here).
 bool qg_conv_runs_applies(const qg_conv_args& a) {
   runs_plan pl;
-  return a.R * a.S > 1 && plan_runs(a, &pl);
+  if (a.R * a.S == 1 || !plan_runs(a, &pl)) return false;
+  const double gather_us = gather_estimate(a);
+  const bool byte_stores = a.Cout % 16 != 0 || ((uintptr_t)a.out & 15) != 0;
+  if (byte_stores && a.Cout > 64 && (double)a.Nb * a.Ho * a.Wo * a.Cout * 3.9e-6 > gather_us) return false;
+  return runs_estimate(a, pl) * 1.05 < gather_us;
 }
 
 hipError_t qg_launch_conv_runs(const qg_conv_args& a, hipStream_t s) {

@@ -24,6 +24,22 @@ pytestmark = pytest.mark.gpu
     dict(Nb=3, H=150, W=600, C=1, Cout=33, R=3, S=3, pad=1, stride=1),   # very many pixels: four waves holding the weights
     dict(Nb=2, H=6, W=5, C=7, Cout=24, R=1, S=1, pad=0, stride=1),       # 1 x 1: the gathering kernel
     dict(Nb=1, H=6, W=40, C=100, Cout=64, R=3, S=3, pad=1, stride=1),    # 29 steps: beyond this kernel, the gathering one
+    # every number of steps with code of its own, and some without, in one and two column blocks
+    dict(Nb=3, H=11, W=13, C=3, Cout=40, R=2, S=2, pad=1, stride=1),     # 1
+    dict(Nb=2, H=14, W=11, C=2, Cout=48, R=7, S=7, pad=3, stride=1),     # 4
+    dict(Nb=2, H=13, W=9, C=2, Cout=24, R=7, S=7, pad=3, stride=1),
+    dict(Nb=2, H=9, W=10, C=5, Cout=40, R=5, S=5, pad=2, stride=1),      # 5
+    dict(Nb=2, H=9, W=10, C=5, Cout=24, R=5, S=5, pad=2, stride=1),
+    dict(Nb=2, H=9, W=10, C=11, Cout=72, R=4, S=4, pad=2, stride=1),     # 6; 72 channels: a column block of padding
+    dict(Nb=2, H=13, W=9, C=3, Cout=24, R=7, S=7, pad=3, stride=1),      # 7
+    dict(Nb=2, H=9, W=10, C=22, Cout=24, R=3, S=3, pad=1, stride=1),     # 8
+    dict(Nb=2, H=20, W=130, C=33, Cout=64, R=3, S=3, pad=1, stride=8),   # the tile halved for the LDS
+    dict(Nb=1, H=9, W=900, C=66, Cout=64, R=3, S=3, pad=1, stride=3),    # 77 KB of LDS
+    dict(Nb=1, H=310, W=900, C=1, Cout=16, R=2, S=2, pad=0, stride=1),   # very many pixels, 1 and 3 steps
+    dict(Nb=1, H=310, W=900, C=1, Cout=48, R=2, S=2, pad=0, stride=1),
+    dict(Nb=1, H=310, W=900, C=3, Cout=24, R=5, S=5, pad=2, stride=1),
+    dict(Nb=1, H=310, W=900, C=3, Cout=48, R=5, S=5, pad=2, stride=1),
+    dict(Nb=2, H=60, W=60, C=4, Cout=16, R=5, S=5, pad=2, stride=2),     # words to gather, few pixels: the gathering kernel
 ])
 @pytest.mark.parametrize("per_channel,with_bias,relu,c_zp,bzp", [
     (True, True, False, None, True), (False, False, True, 0, False), (True, True, True, 77, False), (True, False, False, 5, False)])
