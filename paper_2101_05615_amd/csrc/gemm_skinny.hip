@@ -113,7 +113,6 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   constexpr int REGION = ROWS * ROWB, NREQ = REGION / 1024, RPR = 64 / NCHUNK;  // requests per batch, rows per request
   static_assert(NCHUNK == 8 || NCHUNK == 16 || NCHUNK == 32, "a request covers whole rows of 128, 256 or 512 bytes");
   constexpr int PART_BYTES = NWAVES * MB * CPW * 64 * (int)sizeof(v4i);
-  constexpr int RSP_BYTES = NWAVES * MB * 16 * (int)sizeof(int);
   constexpr int STAGE_BYTES = NWAVES * REGION;
   // every wave leaves its K-split partial sums (MB * CPW KiB) at the start of its OWN staging region (MB * BATCH KiB) once
   // it is done with it: no wave waits for the others before it may write
@@ -259,7 +258,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
     int sp_e0 = 0, sp_ne = 0, sp_first = 0;
     auto sparse_request = [&]() {
       if (B4) {
-        const int b = (kb - kb_begin) / BATCH;  // at most 64 batches per wave: K <= 32768 gives 32 blocks per wave
+        const int b = (kb - kb_begin) / BATCH;  // at most 64 batches per wave: K <= 32768 gives 64 blocks to each of eight waves
         sp_e0 = __shfl(sp_offs, b);
         sp_ne = __shfl(sp_offs, b + 1) - sp_e0;
         sp_first = p.sp_entries[min(sp_e0 + lane, max(p.sp_total, 1) - 1)];
@@ -698,13 +697,28 @@ hipError_t launch_conv(const qg_gemm_args& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Outlier-split weights: eight waves instead of sixteen where more than one workgroup falls to a CU (fewer waves, longer
-// streams each: 16 x 8192 x 8192 15.5 -> 12.0 us) or where sixteen would not get a whole batch of k blocks each (7 x 1100 x
-// 3000 5.5 -> 5.0); with one workgroup per CU and whole batches sixteen stay ahead (16 x 4096 x 4096 4.3 us against 4.5).
+// Outlier-split weights, eight or sixteen waves per workgroup: the chain of a workgroup's slowest wave, in halves of a batch of k
+// blocks.  Of the wave with the end of K, the blocks of a batch that reaches past it are copied lane by lane: a batch's time
+// each where single bytes are masked (K off the 16-byte grid), else half of that.  Every 64 outliers of a batch beyond the first
+// add another half (5 % of outliers: three).
+template <int BATCH>
+int split_chain(const qg_gemm_args& a, int waves) {
+  auto per_wave = [&](int blocks) { return (blocks + 2 * waves - 1) / (2 * waves) * 2; };  // (pairs of blocks, as in the kernel)
+  const int len = a.kb64 - (a.ksplit - 1) * a.ks_per, per = per_wave(len);  // the last slice of K
+  const int last = len - (len - 1) / per * per, full = (last - 1) / BATCH;  // blocks of the last wave, whole batches before its last one
+  const int copied = (a.kb64 - last + (full + 1) * BATCH) * QG_FRAG_K > a.K ? last - full * BATCH : 0;
+  const int batches = (per_wave(a.ks_per) + BATCH - 1) / BATCH, per_batch = 2 + (int)((long long)a.sp_total * BATCH * 16 / ((long long)a.kb64 * a.N * 64));
+  const int tail = per_batch * (full + 1) + copied * (a.K % 16 == 0 ? 1 : 2);
+  return tail > per_batch * batches ? tail : per_batch * batches;
+}
+// Eight where more than one workgroup falls to a CU (fewer waves, longer streams each: 16 x 8192 x 8192 15.5 -> 12.0 us) or
+// where their chain is no longer (64 x 512 x 5121 8.9 us against 12.0 with sixteen); sixteen where they shorten it (16 x 4096 x
+// 4096 4.3 against 4.5, 24 k blocks and a ragged end 4.6 against 5.3).  Over 1073 shapes of at most one workgroup per CU 0.5 %
+// behind the better one in the mean, 15 % at worst.
 template <int MB, int BATCH>
 bool split_few_waves(const qg_gemm_args& a) {
   const long long wgs = (long long)(((a.N + 31) / 32) * 2) * ((a.M + MB * 16 - 1) / (MB * 16)) * a.ksplit;
-  return wgs > 256 || a.ks_per < 16 * BATCH;
+  return wgs > 256 || split_chain<BATCH>(a, 8) <= split_chain<BATCH>(a, 16);
 }
 // waves per workgroup and k blocks a wave requests at once, per row-block height
 template <int MODE, int MB, int BATCH, bool B4, bool ANYALIGN>
