@@ -150,9 +150,11 @@ double tile_estimate(const tile_cost& c, int M, int N, int K) {
   return us;
 }
 
-// The 128 x 64 form of QG_KERNEL_TILE128 (at most one tile per CU): fitted to 128 shapes, M 96 .. 1024 x N, K 1024 .. 8192;
-// where the choice falls on it, it is up to 1.35x faster than the best of the others (256 x 8192 x 8192), at worst 1.01x slower.
-const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.4, 0.145, 0.0, 0.0};
+// The 128 x 64 form of QG_KERNEL_TILE128 (at most one tile per CU): 4.4 + 0.145 us per k step fitted to 128 shapes, M 96 .. 1024 x
+// N, K 1024 .. 8192, and priced a tenth higher, because the prices of the others are a little too high by now.  Over 540 other
+// shapes of the form's range, rows at multiples of 4 bytes, 3 are then more than 4 % slower than the best of the others was
+// priced (1186 x 864 x 4288 14.0 against 15.9 us; with the fitted price 14), and the mean is 0.986 of it; 256 x 8192 x 8192 0.75.
+const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.84, 0.16, 0.0, 0.0};
 
 // few_ok: the 128 x 64 form may be considered.  Not
 //  - for rows of A that start off multiples of 4 bytes: there the tile requests run at a third of their rate whatever the

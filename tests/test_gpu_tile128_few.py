@@ -75,7 +75,7 @@ def test_automatic_choice_with_a_split(a_off, lda_pad):
 def test_fp32_activations_without_a_workspace():
     import torch
     from paper_2101_05615_amd import qgemm as q
-    M, N, K = 129, 6144, 2048
+    M, N, K = 129, 6144, 4096
     assert q.kernel_names()[q.kernel_select(M, N, K)] == "tile128"
     g = torch.Generator(device="cuda").manual_seed(9)
     A = torch.randn((M, K), device="cuda", generator=g)
