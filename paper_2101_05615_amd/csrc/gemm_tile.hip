@@ -201,7 +201,7 @@ template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int
           bool SPLIT = false>
 __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2 : min_wg_per_cu(PATH, TM * TN) / KS) void qg_gemm_tile_kernel(
     const uint8_t* A0, const int8_t* Bp, const int M, const int N, const int K0, const int nb16_total, const int lda,
-    const int tiles_m, const int tiles_n, const qg_gemm_args p) {
+    const int tiles_m_rr, const int tiles_n, const qg_gemm_args p) {
   static_assert(!SPLIT || (PATH == PATH_ASM && TM == 2 && TN == 2 && CONV == 0 && KS == 1), "the cross-workgroup K split is built for the 128 x 128 tile");
   // this workgroup's part of K (all of it unless SPLIT; K0 stays the K of the whole product)
   const int k_first = SPLIT ? (int)blockIdx.y * p.ks_per : 0;  // in 64-deep tiles
@@ -237,8 +237,10 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   // (8 of them, each with its own L2), so give every XCD one contiguous chunk of
   // the tile sequence, and walk that sequence in bands of 8 tile-rows so that
   // the tiles resident on an XCD at one time share A and B panels in its L2.
+  // (KS == 8, a negative number of tile rows: the sequence dealt out one by one, see deal_out)
+  const int tiles_m = KS == 8 ? abs(tiles_m_rr) : tiles_m_rr;
   const int total = tiles_m * tiles_n;
-  const int lin = qg_xcd_run(blockIdx.x, total);
+  const int lin = KS == 8 && tiles_m_rr < 0 ? (int)blockIdx.x : qg_xcd_run(blockIdx.x, total);
   constexpr int BAND = 8;
   // (small quotients through the reciprocal: exact below 2^20, where (x + 0.5) / d is further from a whole number than the
   // rounding errors reach; an integer division is 25 instructions of a wave that has not issued a request yet)
@@ -894,6 +896,33 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   }
 }
 
+// The 64 x 32 tile with a long K is bound by what its operands take from the L2s' far side.  Of the two ways to give the
+// tiles to the XCDs -- a run of the sequence each, or one by one -- the one whose XCDs together read fewer rows of A and
+// columns of B is taken: one by one, a full band of eight tile rows leaves every XCD one row of it and all columns, a run
+// sees the rows of its bands and few columns.  158 shapes, against a kernel that deals all of them
+// out: 0.954 of its time, none more than 3 % slower; with runs for all 0.980, up to 1.32 (2240 x 64 x 6576 10.0 -> 13.1 us).
+// Estimates, most within 10 % of the counts; a grid of several rounds, or of a multiple of eight tiles, takes runs like the
+// other kernels.
+bool deal_out(int tm, int tn, int bm, int bn) {
+  const int total = tm * tn;
+  if (total > 512 || (total & 7) == 0) return false;
+  const int full = tm / 8, r = tm % 8, share = (r * tn + 7) / 8;  // tiles an XCD has of the last, partial band
+  const int rows_seen = r == 0 ? 8 : r % 4 == 0 ? r / 4 : r % 2 == 0 ? r / 2 : r;  // distinct rows of it in steps of eight tiles
+  int one_a = 8 * full + (r ? 8 * (rows_seen < share ? rows_seen : share) : 0);
+  int one_b = 8 * (full || tn < share ? tn : share);
+  if (full == 0) one_a = one_a < total ? one_a : total, one_b = one_b < total ? one_b : total;
+  const float n = total / 8.0f, rows = tm < 8 ? tm : 8;
+  float run_a, run_b;
+  if (n >= 8.0f * tn) {  // whole bands and more
+    run_a = 8.0f * (n / tn + (full ? 4.0f : 0.0f));
+    run_b = 8.0f * tn;
+  } else {
+    run_a = 8.0f * fminf(n, rows * (tm > 8 ? 1.0f + n / (rows * tn) : 1.0f));  // one that crosses into the next band sees its rows too
+    run_b = 8.0f * fminf(fminf((float)tn, n / rows + (n > rows ? 0.9f : 0.0f)), n);
+  }
+  return one_a * bm + one_b * bn < run_a * bm + run_b * bn;
+}
+
 template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int KS = 1, int EPI = EPI_CLAMP>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr int BM = NWM * TM * 32, BN = NWN * TN * 32;
@@ -919,8 +948,9 @@ hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr auto fn = qg_gemm_tile_kernel<MODE, PATH, ROWSUM, NWM, NWN, TM, TN, false, KS, EPI>;
   hipError_t e = qg_allow_smem<fn>(SMEM);
   if (e != hipSuccess) return e;
+  const int tiles_m_rr = KS == 8 && deal_out(tiles_m, tiles_n, BM, BN) ? -tiles_m : tiles_m;
   hipLaunchKernelGGL(fn, dim3((unsigned)(tiles_m * tiles_n)), dim3(NWM * NWN * KS * 64), SMEM, s, a.A, a.Bp, a.M, a.N, a.K,
-                     a.nb16, a.lda, tiles_m, tiles_n, a);
+                     a.nb16, a.lda, tiles_m_rr, tiles_n, a);
   return hipGetLastError();
 }
 
