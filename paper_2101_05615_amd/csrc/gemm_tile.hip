@@ -589,7 +589,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t)
       if (t < KTg) request(t * KS + kg, t);
-    prefetch_columns();
+    if (MODE != QG_MODE_ACC32) prefetch_columns();  // (64 x 64 without a K split: the int32 form's loop is 5 % slower behind it)
     int stage = 0;
     // one common step: `consume` says whether this wave set has a tile in it (always, except in the last step
     // of the other set when the number of tiles is odd)
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   int* cj_s = reinterpret_cast<int*>(smem);
   int* bz_s = cj_s + BN;
   float* sc_s = reinterpret_cast<float*>(bz_s + BN);
-  if (PATH == PATH_ASM && CONV != 0) prefetch_columns();
+  if ((PATH == PATH_ASM && CONV != 0) || (PATH == PATH_PIPE && MODE == QG_MODE_ACC32)) prefetch_columns();
   if (tid < BN) {
     if (MODE != QG_MODE_ACC32) {
       cj_s[tid] = pre_bias - p.a_zp_m128 * pre_co;
