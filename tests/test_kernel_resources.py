@@ -50,3 +50,26 @@ def test_gemm_kernels_use_no_scratch_memory_and_spill_nothing():
     for name, r in {**tile, **skinny, **patch}.items():
         assert r.get("ScratchSize [bytes/lane]") == 0, f"{name} uses scratch memory: {r}"
         assert r.get("VGPRs Spill") == 0 and r.get("SGPRs Spill") == 0, f"{name} spills registers: {r}"
+
+
+@pytest.mark.timeout(600)
+def test_convolution_kernels_in_lds():
+    """The few-channel and the group convolution: no scratch memory and no spilled vector registers, and the waves per SIMD
+    that their launchers count on."""
+    with ThreadPoolExecutor(2) as ex:
+        runs, group = ex.map(_resources, ["conv_runs.hip", "conv_group.hip"])
+    same = {n: r for n, r in group.items() if "qg_conv_same_mfma_kernel" in n}
+    assert len(runs) >= 20 and len(same) >= 30, "the resource report was not parsed"
+    for name, r in runs.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0, f"{name}: {r}"
+        assert r["SGPRs Spill"] <= 2, f"{name}: {r}"   # (the form for any number of steps keeps two in a vector register)
+        assert r["Occupancy [waves/SIMD]"] >= 4, f"{name}: {r}"   # two workgroups of eight waves per CU
+    for name, r in same.items():
+        assert r["ScratchSize [bytes/lane]"] == 0 and r["VGPRs Spill"] == 0 and r["SGPRs Spill"] == 0, f"{name}: {r}"
+        m = re.search(r"ILi\d+ELi\d+ELi\d+ELb([01])ELb[01]ELi(n?\d+)ELb[01]E", name)
+        compact, zero_points = not m.group(2).startswith("n"), m.group(1) == "1"
+        assert r["Occupancy [waves/SIMD]"] >= (7 if compact and not zero_points else 4), f"{name}: {r}"
+    # taps from memory: the form of 128 channels without zero points keeps three dwords per lane in scratch memory
+    for name, r in group.items():
+        if name not in same:
+            assert r["ScratchSize [bytes/lane]"] <= (12 if "group_mfma_kernelILi3ELi3ELi4ELb0ELb0E" in name else 0), f"{name}: {r}"
