@@ -180,8 +180,8 @@ int builtin_select(int M, int N, int K, bool few_ok = true) {
   return best;
 }
 
-// cheapest streaming kernel (outlier-split descriptors run on these only, always in the 16-wave form: the constants
-// fitted when every shape ran that form, large column counts included)
+// cheapest streaming kernel (outlier-split descriptors run on these only; the constants were fitted when they always ran on
+// sixteen waves and added their sparse term lane by lane: the times are lower now, most of all with 64 rows)
 const stream_cost k_stream_cost_16wave[] = {
     {QG_KERNEL_SKINNY16, 16, 3.58, 7.3e-5, 7.55, 0.74e-3},
     {QG_KERNEL_SKINNY32, 32, 4.13, 1.99e-4, 10.33, 1.28e-3},
@@ -319,7 +319,7 @@ int auto_ksplit(int kernel, int M, const qg_packed_b* Bp) {
   const int rows = 16 << (kernel - QG_KERNEL_SKINNY16);
   const long long wgs = (long long)ceil_div(M, rows) * (2 * ceil_div(Bp->N, 32));
   if (wgs * 2 > 256) return 1;
-  int s = Bp->K_pad / QG_FRAG_K / (16 * 4);  // 16 waves x 4 blocks
+  int s = Bp->K_pad / QG_FRAG_K / (16 * 4);  // 16 waves x 4 blocks (outlier-split slices on eight waves: twice as many each)
   if (s > 256 / wgs) s = (int)(256 / wgs);
   if (s > 16) s = 16;
   if (s < (rows == 64 ? 2 : 4)) return 1;

@@ -743,7 +743,7 @@ hipError_t launch_mfma(const qg_conv_args& a, hipStream_t s) {
 
 // Compact weights: where the layout of one dword per (output channel, tap) exists -- groups of 4 -> 4 (Wp), of 1 and 2
 // (Wany) -- and the grid is more than the four workgroups per CU that fit with whole fragments (below that the masking
-// buys nothing: 32 x 28 x 28 x 256 in groups of 4 8.2 us with fragments, 8.5 without).
+// buys nothing: 32 x 28 x 28 x 256 in groups of 4 6.1 us with fragments, 6.2 without; 24 x 56 x 56 x 128 8.8 and 7.8).
 bool compact_ok(const qg_conv_args& a) {
   if (a.lcg < 2 ? a.Wany == nullptr : a.lcg != 2 || a.Wany != nullptr) return false;
   const int ncb = a.C % 64 == 0 ? 2 : 1;

@@ -12,9 +12,11 @@
 //
 // What bounds it: at 8 x 224 x 224 x 3, 7 x 7, stride 2 -> 64 channels the bytes take 1.5 us and the MFMAs 0.7; the
 // time is the chain of one workgroup, 448 of which are resident at once (cycles: addresses and requests 2000, their
-// latency and the re-cut 2000, a block of 32 pixels 1400 + its output pipeline).  Measured, graph replay: 7.0 us, where the
-// byte-gathering kernel, which spends about 27 vector instructions per byte of the im2col matrix, took 20.8; one image
-// 5.0 (9.1), 32 images 14.5 (65), 3 x 3 stride 2 -> 32 4.4 (9.2), 16 x 256 x 256 x 4, 7 x 7 stride 1 -> 64 29 (76).
+// latency and the re-cut 2000, a block of 32 pixels 1400 + its output pipeline).  Measured, graph replay, theta_B = 0: 7.0 to
+// 7.6 us, where the byte-gathering kernel, which spends about 27 vector instructions per byte of the im2col matrix, takes 21;
+// one image 5.3 (9.3), 32 images 15 (65), 3 x 3 stride 2 -> 32 4.8 (9.6), 16 x 256 x 256 x 4, 7 x 7 stride 1 -> 64 28 (81).  With
+// theta_B, whose row sums are one more MFMA per step and leave the steps to a loop: 8.6 (22), 32 images 18 (69), 3 x 3 5.4
+// (10.2), the last 36 (86).
 #include "qg_internal.h"
 #include <cmath>
 #include <type_traits>
@@ -321,7 +323,7 @@ bool plan_runs(const qg_conv_args& a, runs_plan* pl) {
   pl->pxstep = a.stride * a.C;
   const long long npix = (long long)a.Nb * a.Ho * a.Wo;
   // output pixels per workgroup, 64 to 512: two workgroups per CU, one where re-cutting the weights is most of the set-up
-  // (8 x 56 x 56 x 24, 3 x 3 -> 24, 8 steps: 5.1 us against 5.6; 8 x 224 x 224 x 4, 7 x 7, stride 2 -> 64, 7 steps: 7.3
+  // (8 x 56 x 56 x 24, 3 x 3 -> 24, 8 steps, run on this kernel: 5.1 us against 5.6; 8 x 224 x 224 x 4, 7 x 7, stride 2 -> 64, 7 steps: 7.3
   // against 6.7)
   const long long ncol = (a.Cout + pl->nb * 32 - 1) / (pl->nb * 32);
   long long target = npix * ncol / (p.steps >= 8 ? 256 : 512);

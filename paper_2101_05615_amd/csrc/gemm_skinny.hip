@@ -24,8 +24,9 @@
 // batch of k blocks scatters that batch's entries, one per lane and byte store, into zeroed fragments in its staging
 // region (the activations are in registers by then) and multiplies those like any other weights.  One product per
 // (row, entry) pair and lane, added up in LDS, was what this took before: vector instructions, 16 rows of them per
-// entry, bound it (16 x 8192 x 8192 with 0.7 % of outliers 19.1 us, now 15.5 and the same at any density; 64 x 4096 x 4096
-// 15.3 -> 7.6, 64 x 8192 x 8192 49 -> 22).
+// entry, bound it (16 x 8192 x 8192, weights in the memory-side cache, with 0.7 % of outliers 17.5 -> 10.9 us; 0.1 % 10.8, 1 %
+// 11.2, 2 %, more than 64 entries in some batches, 13.2, and none at all, where batches skip this, 8.5; with 0.5 % 64 x 4096 x 4096
+// 13.4 -> 7.7, 64 x 8192 x 8192 44 -> 20).
 //
 // M larger than the row block is covered by the second grid dimension: every row block streams
 // B again (from L2 / the memory-side cache when the blocks run close together), which beats the

@@ -18,6 +18,8 @@ Fixed register plan (all clobbered by the asm statement):
   s84 xor mask, s[86:87] A request base, s[88:89] B request base, s90 loop counter, s91 LDS base of
   this wave's request slots, s92 LDS base, s99 bytes per 64-deep slab of packed B, s93 stage index, s96 request stage base, s97/s98 read
   stage bases (current / next), s94/s95 temporaries
+m0 is written in front of every group of requests and is not among the clobbered registers: the compiler reserves it,
+refuses it in a clobber list and sets it anew in front of each of its own uses.
 Operands: 16 accumulators c0..c15 ("+a", acc[mb][nb] = c{4*mb+nb}), packed 64-bit VGPR inputs
 av01 av23 bv01 bv23 ard brd, SGPR inputs aptr bptr kt ldsdma lds bstep, 64-bit VGPR outputs rs01 rs23.
 
