@@ -84,29 +84,38 @@ const tile_cost k_tile_cost[] = {
     {QG_KERNEL_TILE64X32K8, 64, 32, 3.817, 0.05427, 0.0602, 2.585},
 };
 // The dense convolution runs the same tile loops with the im2col addressing folded into the requests; the same
-// formula, constants fitted to 56 layers (3 x 3 and 5 x 5, stride 1 and 2, 1 .. 32 images, Cin % 64 == 0; graph-replay
-// times): the choice is within 5 % of the measured best on 54 of them, worst 1.07x.  The 64 x 64 tile comes without a
-// K split and with two or four wave sets that share K, the 64 x 32 tile with eight.
+// formula, constants fitted to 272 layers (3 x 3 and 5 x 5, stride 1 and 2, 1 .. 32 images, 32 .. 512 channels; graph-replay
+// times), one set for whole 64-channel slices and one for the other channel counts, whose requests keep a tap per
+// lane.  Over 120 other layers the choice among all kernels is 1.009 of the measured best in the geometric mean, 6 by more
+// than 5 %, worst 1.18x; with the constants of before, fitted to older kernels, 1.094, 54 and 1.90x.
 const tile_cost k_conv_cost[] = {
-    {QG_KERNEL_TILE64K1, 64, 64, 2.55, 0.412, 0.136, 0.432},
-    {QG_KERNEL_TILE64, 64, 64, 3.95, 0.167, 0.115, 1.24},
-    {QG_KERNEL_TILE64K4, 64, 64, 5.36, 0.118, 0.112, 3.74},
-    {QG_KERNEL_TILE64X32K8, 64, 32, 6.28, 0.0686, 0.0682, 4.43},
-    {QG_KERNEL_TILE128, 128, 128, 5.68, 0.279, 0.229, 2.36},
-    {QG_KERNEL_TILE128X256, 128, 256, 11.1, 0.261, 0.353, 4.01},
+    {QG_KERNEL_TILE64K1, 64, 64, 3.33, 0.286, 0.11, 0.516},
+    {QG_KERNEL_TILE64, 64, 64, 4.07, 0.16, 0.115, 1.0},
+    {QG_KERNEL_TILE64K4, 64, 64, 5.14, 0.116, 0.115, 3.04},
+    {QG_KERNEL_TILE64X32K8, 64, 32, 5.57, 0.0815, 0.0794, 3.47},
+    {QG_KERNEL_TILE128, 128, 128, 5.33, 0.28, 0.239, 1.86},
+    {QG_KERNEL_TILE128X256, 128, 256, 9.17, 0.297, 0.371, 3.21},
+};
+const tile_cost k_conv_chunk_cost[] = {
+    {QG_KERNEL_TILE64K1, 64, 64, 3.68, 0.361, 0.114, 0.832},
+    {QG_KERNEL_TILE64, 64, 64, 4.33, 0.217, 0.145, 1.22},
+    {QG_KERNEL_TILE64K4, 64, 64, 5.28, 0.158, 0.168, 3.0},
+    {QG_KERNEL_TILE64X32K8, 64, 32, 6.15, 0.145, 0.0682, 4.42},
+    {QG_KERNEL_TILE128, 128, 128, 6.01, 0.546, 0.305, 2.86},
+    {QG_KERNEL_TILE128X256, 128, 256, 9.17, 0.88, 0.353, 4.01},
 };
 // "Same" convolutions (stride 1, output as large as the input) with Cin % 32 == 0 also have the kernels that keep the
-// input patch of a pixel tile in LDS; same formula, fitted to 80 layers (3 x 3 and 5 x 5, 1 .. 32 images, 32 .. 512
-// channels; the 512 x 128 form to the layers of the autotuner's convolution grid).  Over the 100 layers of that grid
-// the automatic choice among all of these kernels is within 5 % of the measured best on 91 (geometric mean 1.009x,
-// worst 1.10x), and the best kernel is one of these on 49 (up to 1.74x faster than the best of the others).
+// input patch of a pixel tile in LDS; same formula, fitted to the layers of that kind among the 272.
 const tile_cost k_conv_patch_cost[] = {
-    {QG_KERNEL_PATCH64X128, 64, 128, 4.86, 0.137, 0.119, 1.4},
-    {QG_KERNEL_PATCH128X64, 128, 64, 4.83, 0.148, 0.135, 1.32},
-    {QG_KERNEL_PATCH256X64, 256, 64, 5.5, 0.196, 0.25, 1.84},
-    {QG_KERNEL_PATCH256, 256, 128, 5.78, 0.381, 0.642, 0.756},
-    {QG_KERNEL_PATCH512, 512, 128, 10.0, 0.603, 0.973, 3.72},
+    {QG_KERNEL_PATCH64X128, 64, 128, 4.33, 0.147, 0.14, 0.86},
+    {QG_KERNEL_PATCH128X64, 128, 64, 4.51, 0.133, 0.114, 1.0},
+    {QG_KERNEL_PATCH256X64, 256, 64, 4.66, 0.174, 0.235, 1.15},
+    {QG_KERNEL_PATCH256, 256, 128, 5.24, 0.288, 0.395, 1.32},
+    {QG_KERNEL_PATCH512, 512, 128, 6.63, 0.581, 0.973, 3.72},
 };
+// ... and the builds of QG_KERNEL_PATCH64X128 for at most one tile per CU, with four and two wave sets
+const tile_cost k_conv_few4_cost = {QG_KERNEL_PATCH64X128, 64, 64, 5.45, 0.0453, 0.0, 0.0};
+const tile_cost k_conv_few2_cost = {QG_KERNEL_PATCH64X128, 64, 128, 5.7, 0.0924, 0.0, 0.0};
 const stream_cost k_stream_cost[] = {
     {QG_KERNEL_SKINNY16, 16, 3.826, 3.664e-06, 5.429, 0.002625},
     {QG_KERNEL_SKINNY32, 32, 3.918, 2.404e-05, 8.639, 0.0005841},
@@ -188,11 +197,11 @@ const stream_cost k_stream_cost_16wave[] = {
     {QG_KERNEL_SKINNY64, 64, 4.96, 3.88e-4, 14.26, 2.23e-3},
 };
 // The same kernels with the convolution's per-lane tap addressing in their requests: the streaming formula with
-// constants of their own, fitted to 72 layers (Cin % 64 == 0; 3 x 3 and 5 x 5, stride 1 and 2, 1 .. 32 images).
+// constants of their own (Cin % 64 == 0; the layers above).
 const stream_cost k_conv_stream_cost[] = {
-    {QG_KERNEL_SKINNY16, 16, 5.24, 2.1e-4, 12.0, 1.4e-3},
-    {QG_KERNEL_SKINNY32, 32, 5.74, 4.39e-4, 18.2, 1.85e-3},
-    {QG_KERNEL_SKINNY64, 64, 7.35, 6.52e-4, 24.4, 4.24e-3},
+    {QG_KERNEL_SKINNY16, 16, 5.17, 4.81e-4, 11.1, 3.33e-3},
+    {QG_KERNEL_SKINNY32, 32, 5.8, 6.87e-4, 21.9, 2.38e-3},
+    {QG_KERNEL_SKINNY64, 64, 6.84, 1.32e-3, 24.4, 4.24e-3},
 };
 
 int select_stream_kernel(int M, int N, int K) {
@@ -991,19 +1000,22 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
   const bool stream_ok = Cin % QG_FRAG_K == 0 && R * S <= 32;
   if (kernel == QG_KERNEL_AUTO) {
     double best_us = 1e300;
-    for (const tile_cost& c : k_conv_cost) {
+    for (const tile_cost& c : Cin % QG_FRAG_K == 0 ? k_conv_cost : k_conv_chunk_cost) {
       const double us = tile_estimate(c, a.M, a.N, a.K);
       if (us < best_us) best_us = us, kernel = c.kernel;
     }
     for (const tile_cost& c : k_conv_patch_cost) {
       const int per_cu = qg_conv_patch_per_cu(a, c.kernel - QG_KERNEL_PATCH64X128);
       if (per_cu == 0) continue;
-      double us = tile_estimate(c, a.M, a.N, a.K);
-      // A wide patch leaves room for few workgroups per CU: what does not run side by side runs one after the
-      // other, each pass at the pace of a workgroup alone.
-      const double wgs = (double)ceil_div(a.M, c.bm) * (double)ceil_div(a.N, c.bn);
-      const double passes = ceil(wgs / (256.0 * per_cu));
-      us = fmax(us, 2.5 + passes * (c.fix + ceil_div(a.K, 64) * c.lat - 2.5));
+      const int sets = c.kernel == QG_KERNEL_PATCH64X128 ? qg_conv_patch_sets(a) : 0;
+      double us = tile_estimate(sets == 4 ? k_conv_few4_cost : sets == 2 ? k_conv_few2_cost : c, a.M, a.N, a.K);
+      if (sets == 0) {
+        // A wide patch leaves room for few workgroups per CU: what does not run side by side runs one after the
+        // other, each pass at the pace of a workgroup alone.
+        const double wgs = (double)ceil_div(a.M, c.bm) * (double)ceil_div(a.N, c.bn);
+        const double passes = ceil(wgs / (256.0 * per_cu));
+        us = fmax(us, 2.5 + passes * (c.fix + ceil_div(a.K, 64) * c.lat - 2.5));
+      }
       if (us < best_us) best_us = us, kernel = c.kernel;
     }
     if (stream_ok)

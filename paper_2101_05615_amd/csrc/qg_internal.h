@@ -325,6 +325,7 @@ hipError_t qg_launch_conv_runs(const qg_conv_args& a, hipStream_t s);
 // the kernels with the input patch in LDS ("same" convolutions); form 0 = 64 pixels x 128 channels, 1 = 128 x 64, 2 = 256 x 64, 3 = 256 x 128, 4 = 512 x 128
 bool qg_conv_patch_applies(const qg_gemm_args& a, int form);
 int qg_conv_patch_per_cu(const qg_gemm_args& a, int form);  // workgroups a CU holds side by side; 0 = does not apply
+int qg_conv_patch_sets(const qg_gemm_args& a);  // wave sets that split K in form 0's build for few tiles; 0: its usual build
 hipError_t qg_launch_conv_patch(const qg_gemm_args& a, int form, hipStream_t s);
 
 #define QG_MODE_REQUANT 0
