@@ -92,6 +92,25 @@ constexpr int loop_lds(int path, int bm, int bn, int blocks, bool pair, int sets
               : (path == PATH_ASM ? asm_stages(blocks, sets) : pipe_stages(blocks)) * sets * (bm + bn) * BK;
 }
 
+// One MFMA of the generated loops.  B fragment first: a lane holds 16 consecutive columns of one row (uint8 output: one 16-byte
+// store).  A fragment first: 16 rows of one column, so that the stores of an fp32 result are whole rows of 32 columns
+// (MODE_DEQUANT; see the output pipeline).
+#define QG_MFMA_ROWS(c, b, a) "v_mfma_i32_32x32x32_i8 " c ", " b ", " a ", " c "\n"
+#define QG_MFMA_COLS(c, b, a) "v_mfma_i32_32x32x32_i8 " c ", " a ", " b ", " c "\n"
+// loop `name` with or without the row sums
+#define QG_RUN_LOOP(name, norowsum, operands) \
+  if constexpr (MODE == QG_MODE_DEQUANT) {    \
+    if (ROWSUM)                               \
+      asm volatile(name(QG_MFMA_COLS) operands);     \
+    else                                      \
+      asm volatile(norowsum(QG_MFMA_COLS) operands); \
+  } else {                                    \
+    if (ROWSUM)                               \
+      asm volatile(name(QG_MFMA_ROWS) operands);     \
+    else                                      \
+      asm volatile(norowsum(QG_MFMA_ROWS) operands); \
+  }
+
 // operand list shared by the two generated loop variants (gen_tile_loop.py)
 #define QG_TILE_LOOP_OPERANDS \
                  : [c0] "+a"(acc[0][0]), [c1] "+a"(acc[0][1]), [c2] "+a"(acc[0][2]), [c3] "+a"(acc[0][3]), \
@@ -350,7 +369,8 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
     for (int mb = 0; mb < TM; ++mb)
 #pragma unroll
       for (int nb = 0; nb < TN; ++nb)
-        acc[mb][nb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[nb], af[mb], acc[mb][nb], 0, 0, 0);
+        acc[mb][nb] = MODE == QG_MODE_DEQUANT ? __builtin_amdgcn_mfma_i32_32x32x32_i8(af[mb], bf[nb], acc[mb][nb], 0, 0, 0)
+                                              : __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[nb], af[mb], acc[mb][nb], 0, 0, 0);
   };
   const int KT = (K + BK - 1) / BK;  // tiles that hold real data
   // the pipelined loops run the KTF whole tiles; a ragged last tile (K % 64 bytes of A) is staged through
@@ -461,10 +481,7 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
       const unsigned long long av23 = a_voff[2] | ((unsigned long long)a_voff[3] << 32);
       const unsigned long long bv23 = b_voff[2] | ((unsigned long long)b_voff[3] << 32);
       unsigned long long rs23;
-      if (ROWSUM)
-        asm volatile(QG_TILE_LOOP_ASM QG_TILE_LOOP_OPERANDS);
-      else
-        asm volatile(QG_TILE_LOOP_ASM_NOROWSUM QG_TILE_LOOP_OPERANDS);
+      QG_RUN_LOOP(QG_TILE_LOOP_ASM, QG_TILE_LOOP_ASM_NOROWSUM, QG_TILE_LOOP_OPERANDS)
       rs[2] = (unsigned)rs23;
       rs[3] = (unsigned)(rs23 >> 32);
     } else if constexpr (CONV != 0) {
@@ -484,32 +501,17 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
       const int cv_nc = p.cv_Cin / BK, cv_fs = p.cv_S, cv_rowjump = (p.cv_W - p.cv_S) * p.cv_pix;
       const int cv_tapjump = p.cv_pix - p.cv_Cin;
       if constexpr (TN == 2) {
-        if (ROWSUM)
-          asm volatile(QG_TILE_LOOP_ASM_CONV_2X2 QG_TILE_LOOP_OPERANDS_CONV_2X2);
-        else
-          asm volatile(QG_TILE_LOOP_ASM_CONV_NOROWSUM_2X2 QG_TILE_LOOP_OPERANDS_CONV_2X2);
+        QG_RUN_LOOP(QG_TILE_LOOP_ASM_CONV_2X2, QG_TILE_LOOP_ASM_CONV_NOROWSUM_2X2, QG_TILE_LOOP_OPERANDS_CONV_2X2)
       } else {
-        if (ROWSUM)
-          asm volatile(QG_TILE_LOOP_ASM_CONV_2X4 QG_TILE_LOOP_OPERANDS_CONV_2X4);
-        else
-          asm volatile(QG_TILE_LOOP_ASM_CONV_NOROWSUM_2X4 QG_TILE_LOOP_OPERANDS_CONV_2X4);
+        QG_RUN_LOOP(QG_TILE_LOOP_ASM_CONV_2X4, QG_TILE_LOOP_ASM_CONV_NOROWSUM_2X4, QG_TILE_LOOP_OPERANDS_CONV_2X4)
       }
     } else if constexpr (DIST) {
       const unsigned long long av23 = a_voff[2] | ((unsigned long long)a_voff[3] << 32);
-      if (ROWSUM)
-        asm volatile(QG_TILE_LOOP_ASM_2X2K4 QG_TILE_LOOP_OPERANDS_2X2K4);
-      else
-        asm volatile(QG_TILE_LOOP_ASM_NOROWSUM_2X2K4 QG_TILE_LOOP_OPERANDS_2X2K4);
+      QG_RUN_LOOP(QG_TILE_LOOP_ASM_2X2K4, QG_TILE_LOOP_ASM_NOROWSUM_2X2K4, QG_TILE_LOOP_OPERANDS_2X2K4)
     } else if constexpr (TN == 2) {
-      if (ROWSUM)
-        asm volatile(QG_TILE_LOOP_ASM_2X2 QG_TILE_LOOP_OPERANDS_2X2);
-      else
-        asm volatile(QG_TILE_LOOP_ASM_NOROWSUM_2X2 QG_TILE_LOOP_OPERANDS_2X2);
+      QG_RUN_LOOP(QG_TILE_LOOP_ASM_2X2, QG_TILE_LOOP_ASM_NOROWSUM_2X2, QG_TILE_LOOP_OPERANDS_2X2)
     } else {
-      if (ROWSUM)
-        asm volatile(QG_TILE_LOOP_ASM_2X4 QG_TILE_LOOP_OPERANDS_2X4);
-      else
-        asm volatile(QG_TILE_LOOP_ASM_NOROWSUM_2X4 QG_TILE_LOOP_OPERANDS_2X4);
+      QG_RUN_LOOP(QG_TILE_LOOP_ASM_2X4, QG_TILE_LOOP_ASM_NOROWSUM_2X4, QG_TILE_LOOP_OPERANDS_2X4)
     }
     rs[0] = (unsigned)rs01;
     rs[1] = (unsigned)(rs01 >> 32);
@@ -782,6 +784,11 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   int* cj_s = reinterpret_cast<int*>(smem);
   int* bz_s = cj_s + BN;
   float* sc_s = reinterpret_cast<float*>(bz_s + BN);
+  int* const rs_s = reinterpret_cast<int*>(sc_s + BN);  // MODE_DEQUANT: the row offsets, which a lane needs of 16 rows
+  if (MODE == QG_MODE_DEQUANT && ROWSUM && lg == 0 && wave_n == 0 && (DIST ? (kg & 1) == 0 : kg == 0)) {
+#pragma unroll
+    for (int mb = 0; mb < EM; ++mb) rs_s[(em0 + mb) * 32 + l32] = rsum_s[mb];
+  }
   if ((PATH == PATH_ASM && CONV != 0) || (PATH == PATH_PIPE && MODE == QG_MODE_ACC32)) prefetch_columns();
   if (tid < BN) {
     if (MODE != QG_MODE_ACC32) {
@@ -795,10 +802,48 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
   __syncthreads();
   if (KS > 1 && !DIST && kg != 0) return;  // the first wave set holds the sums and runs the output pipeline
 
+  // ---- fp32 output.  Lane (l32, lg) of a block holds column qg_slot_to_col(l32) of rows 4 lg + 8 j + t: a store is two rows of
+  // 32 columns, whole 128-byte lines at aligned rows.  With 16 columns of a row per lane and four 16-byte stores it was 64
+  // separate pieces, at 16 bytes per cycle and CU: 2048 x 4096 floats alone 13.2 us, so 6.7, at rows off the alignment 14.3 and 7.9.
+  if constexpr (MODE == QG_MODE_DEQUANT) {
+    const bool all_rows = m0 + BM <= M;  // uniform
+#pragma unroll
+    for (int nb = 0; nb < EN; ++nb) {
+      const int col_l = (en0 + nb) * 32 + qg_slot_to_col(l32), col = n0 + col_l;
+      const int cj = cj_s[col_l], nbz = bz_s[col_l];
+      const float sc = sc_s[col_l];
+#pragma unroll
+      for (int mb = 0; mb < EM; ++mb) {
+        if (m0 + (em0 + mb) * 32 >= M) continue;
+        const int row_l = (em0 + mb) * 32 + 4 * lg;
+        float* const dst = p.Cf + (size_t)(m0 + row_l) * p.ldc + col;
+        auto block = [&](auto check_tag) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            v4i rs4 = (v4i){0, 0, 0, 0};
+            if (ROWSUM) rs4 = *reinterpret_cast<const v4i*>(&rs_s[row_l + 8 * j]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              const int x = ea[mb][nb][4 * j + t] + cj + (ROWSUM ? __mul24(nbz, rs4[t]) : 0);
+              const float out = qg_dequant_one(x, sc, p.relu_lo);
+              if (!decltype(check_tag)::value || m0 + row_l + 8 * j + t < M) dst[(size_t)(8 * j + t) * p.ldc] = out;
+            }
+          }
+        };
+        if (col < N) {
+          if (all_rows)
+            block(std::false_type{});
+          else
+            block(std::true_type{});
+        }
+      }
+    }
+    return;
+  }
   // ---- epilogue straight from the accumulators.  Lane (l32, lg) of block (mb, nb) holds row
   // 32*mb + l32 and the 16 consecutive columns 32*nb + 16*lg .. +15; the per-column constants of a
   // column block are fetched once and reused for the wave's TM row blocks.
-  if (MODE != QG_MODE_ACC32) {
+  if constexpr (MODE == QG_MODE_REQUANT) {
     const bool full_cols = p.c_vec && (n0 + BN <= N);  // uniform: every 16-byte store is in range
     const float czp_f = (float)p.c_zp;
 #pragma unroll
@@ -817,66 +862,38 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
       for (int mb = 0; mb < EM; ++mb) {
         const int row = m0 + (em0 + mb) * 32 + l32;
         const int rsum = rsum_s[mb];
-        if (MODE == QG_MODE_REQUANT) {
-          unsigned out[4];
+        unsigned out[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            unsigned w = 0;
+        for (int q = 0; q < 4; ++q) {
+          unsigned w = 0;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const int i = 4 * q + t;
-              const int x = ea[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
-              if constexpr (EPI == EPI_SAT0)
-                w = qg_requant_pack0(x, sc[i], t, w);
-              else
-                w = qg_requant_pack<EPI == EPI_CLAMP>(x, sc[i], p.clamp_lo, p.clamp_hi, czp_f, t, w);
-            }
-            out[q] = w;
-          }
-          if (row < M) {
-            uint8_t* dst = p.C + (size_t)row * p.ldc + col;
-            if (full_cols) {
-              *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
-            } else if (col + 16 <= N) {
-              // any address: one 16-byte store all the same
-              *reinterpret_cast<qg_v4i_unaligned*>(dst) = (v4i){(int)out[0], (int)out[1], (int)out[2], (int)out[3]};
-            } else {
-              // the lanes whose 16 columns N cuts
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                if (col + i < N) dst[i] = (uint8_t)(out[i >> 2] >> ((i & 3) * 8));
-            }
-          }
-        } else {
-          // fp32 output: 16 consecutive floats per lane, four 16-byte stores
-          float out[16];
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
+          for (int t = 0; t < 4; ++t) {
+            const int i = 4 * q + t;
             const int x = ea[mb][nb][i] + cj[i] + (ROWSUM ? __mul24(nbz[i], rsum) : 0);
-            out[i] = qg_dequant_one(x, sc[i], p.relu_lo);
+            if constexpr (EPI == EPI_SAT0)
+              w = qg_requant_pack0(x, sc[i], t, w);
+            else
+              w = qg_requant_pack<EPI == EPI_CLAMP>(x, sc[i], p.clamp_lo, p.clamp_hi, czp_f, t, w);
           }
-          if (row < M) {
-            float* dst = p.Cf + (size_t)row * p.ldc + col;
-            if (full_cols) {
+          out[q] = w;
+        }
+        if (row < M) {
+          uint8_t* dst = p.C + (size_t)row * p.ldc + col;
+          if (full_cols) {
+            *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
+          } else if (col + 16 <= N) {
+            // any address: one 16-byte store all the same
+            *reinterpret_cast<qg_v4i_unaligned*>(dst) = (v4i){(int)out[0], (int)out[1], (int)out[2], (int)out[3]};
+          } else {
+            // the lanes whose 16 columns N cuts
 #pragma unroll
-              for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4*>(dst + 4 * q) = make_float4(out[4 * q], out[4 * q + 1], out[4 * q + 2], out[4 * q + 3]);
-            } else if (col + 16 <= N) {
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<qg_v4i_unaligned*>(dst + 4 * q) =
-                    (v4i){__float_as_int(out[4 * q]), __float_as_int(out[4 * q + 1]), __float_as_int(out[4 * q + 2]),
-                          __float_as_int(out[4 * q + 3])};
-            } else {
-#pragma unroll
-              for (int i = 0; i < 16; ++i)
-                if (col + i < N) dst[i] = out[i];
-            }
+            for (int i = 0; i < 16; ++i)
+              if (col + i < N) dst[i] = (uint8_t)(out[i >> 2] >> ((i & 3) * 8));
           }
         }
       }
     }
-  } else {
+  } else if constexpr (MODE == QG_MODE_ACC32) {
 #pragma unroll
     for (int mb = 0; mb < EM; ++mb) {
       const int row = m0 + (em0 + mb) * 32 + l32;
@@ -927,8 +944,8 @@ template <int MODE, int PATH, bool ROWSUM, int NWM, int NWN, int TM, int TN, int
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr int BM = NWM * TM * 32, BN = NWN * TN * 32;
   constexpr int LOOP = loop_lds(PATH, BM, BN, TM * TN, pair_a(PATH, TM, TN, 0), KS);
-  // the output pipeline's per-column constants (12 B per column) reuse the stage memory
-  constexpr int SMEM = LOOP > 12 * BN ? LOOP : 12 * BN;
+  // the output pipeline's constants (12 B per column, 4 B per row) reuse the stage memory
+  constexpr int SMEM = LOOP > 12 * BN + 4 * BM ? LOOP : 12 * BN + 4 * BM;
   const int tiles_m = (a.M + BM - 1) / BM;
   const int tiles_n = (a.N + BN - 1) / BN;
   if constexpr (PATH == PATH_ASM && TM == 2 && TN == 2 && KS == 1) {

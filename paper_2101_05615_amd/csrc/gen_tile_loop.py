@@ -208,7 +208,7 @@ def pair_read_bases(e):
 
 def mfma(e, i, use):
     mb, nb = i // TN, i % TN
-    e(f"v_mfma_i32_32x32x32_i8 %[c{i}], {vr(B[use] + 4 * nb)}, {vr(A[use] + 4 * mb)}, %[c{i}]")
+    e(f'MM("%[c{i}]", "{vr(B[use] + 4 * nb)}", "{vr(A[use] + 4 * mb)}")')
 
 
 def reads(e, slot, ld, ks):
@@ -476,6 +476,12 @@ def generate_loop(rowsum, conv=False):
     return e.lines
 
 
+def macro(name, lines):
+    """the loop as a macro of MM, which writes one MFMA (accumulator, B fragment, A fragment): the caller chooses which of the
+    two comes first, and so whether a lane ends up with columns of one row or rows of one column"""
+    return f"#define {name}(MM) \\\n" + "".join(f"  {l} \\\n" if l.startswith("MM(") else f'  "{l}\\n" \\\n' for l in lines) + "  \"\"\n"
+
+
 def generate():
     out = "// GENERATED by gen_tile_loop.py -- do not edit.\n"
     for tm, tn, nstage, suffix in ((4, 4, 4, ""), (2, 2, 4, "_2X2"), (2, 4, 3, "_2X4")):
@@ -483,22 +489,20 @@ def generate():
         clob = [f'"v{i}"' for i in range(FIRST_VGPR, LAST_VGPR + 1)] + [f'"s{i}"' for i in range(70 if PAIR else 84, 100)] + \
                ['"scc"', '"memory"']
         for name, rowsum in (("QG_TILE_LOOP_ASM", True), ("QG_TILE_LOOP_ASM_NOROWSUM", False)):
-            out += (f"#define {name}{suffix} \\\n" +
-                    "".join(f'  "{l}\\n" \\\n' for l in generate_loop(rowsum)) + "  \"\"\n")
+            out += macro(name + suffix, generate_loop(rowsum))
         out += f"#define QG_TILE_LOOP_CLOBBERS{suffix} " + ", ".join(clob) + "\n"
         if tm == 2:
             configure(tm, tn, nstage, conv=True)
             clob = [f'"v{i}"' for i in range(FIRST_VGPR, IMGHI + 1)] + [f'"s{i}"' for i in range(72, 82)] + \
                    [f'"s{i}"' for i in range(84, 100)] + ['"vcc"', '"scc"', '"memory"']
             for name, rowsum in (("QG_TILE_LOOP_ASM_CONV", True), ("QG_TILE_LOOP_ASM_CONV_NOROWSUM", False)):
-                out += (f"#define {name}{suffix} \\\n" +
-                        "".join(f'  "{l}\\n" \\\n' for l in generate_loop(rowsum, conv=True)) + "  \"\"\n")
+                out += macro(name + suffix, generate_loop(rowsum, conv=True))
             out += f"#define QG_TILE_LOOP_CLOBBERS_CONV{suffix} " + ", ".join(clob) + "\n"
     # the 128 x 64 tile: 64 x 64 per wave, four sets of two waves
     configure(2, 2, 3, nwn=1, sets=4)
     clob = [f'"v{i}"' for i in range(FIRST_VGPR, LAST_VGPR + 1)] + [f'"s{i}"' for i in range(84, 100)] + ['"scc"', '"memory"']
     for name, rowsum in (("QG_TILE_LOOP_ASM_2X2K4", True), ("QG_TILE_LOOP_ASM_NOROWSUM_2X2K4", False)):
-        out += f"#define {name} \\\n" + "".join(f'  "{l}\\n" \\\n' for l in generate_loop(rowsum)) + "  \"\"\n"
+        out += macro(name, generate_loop(rowsum))
     out += "#define QG_TILE_LOOP_CLOBBERS_2X2K4 " + ", ".join(clob) + "\n"
     configure(4, 4)
     return out
