@@ -7,6 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqgemm.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["api.hip", "pack.hip", "quantize_a.hip", "gemm_tile.hip", "gemm_skinny.hip", "conv_group.hip", "conv_patch.hip", "conv_runs.hip"]
 PROBES_SRC = os.path.join(ROOT, "bench_probes.hip")   # bench.py's measurement probes, a library of their own
 PROBES_LIB = os.path.join(ROOT, "libbench_probes.so")
@@ -56,6 +57,23 @@ def build_lib(verbose=False, extra=(), incremental=False):
     return LIB
 
 
+def build_binding(verbose=False):
+    """The CPython module through which qgemm.py makes its hot calls (host code; links libqgemm.so beside it)."""
+    import sysconfig
+    import torch
+    import torch.utils.cpp_extension as ext
+    includes = ["-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"]]
+    for d in ext.include_paths():
+        includes += ["-isystem", d]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + includes + \
+          [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + HERE, "-l:libqgemm.so", "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return BINDING
+
+
 def build_probes(verbose=False):
     cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Xclang", "-target-feature",
            "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", PROBES_SRC, "-o", PROBES_LIB]
@@ -68,5 +86,6 @@ def build_probes(verbose=False):
 if __name__ == "__main__":
     inc = "--incremental" in sys.argv[1:]
     build_lib(verbose=True, extra=[a for a in sys.argv[1:] if a != "--incremental"], incremental=inc)
+    build_binding(verbose=True)
     build_probes(verbose=True)
     print("built", LIB)

@@ -1,10 +1,12 @@
-"""Thin ctypes binding of libqgemm.so (the C ABI in include/qgemm.h).
+"""Thin binding of libqgemm.so (the C ABI in include/qgemm.h).
 
-Argument marshalling only: every step of the path runs in the HIP kernels.
+Argument marshalling only: every step of the path runs in the HIP kernels.  All of the ABI is reached through ctypes; the calls
+that a program repeats first go through a small extension module (csrc/binding.cpp).
 PyTorch supplies device memory (`tensor.data_ptr()`) and the stream.  There is
 no CPU fallback: if the library is not built, importing this module raises.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch  # noqa: F401  (imported first so that libqgemm binds to the HIP runtime torch loaded)
@@ -119,6 +121,22 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+def _load_binding():
+    path = os.path.join(_HERE, "_binding.so")
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is not built; run `python -c 'import __graft_entry__ as g; g.build()'`")
+    spec = importlib.util.spec_from_file_location("_binding", path)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
+    if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        m.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, QGemmError)
+    return m
+
+
+_binding = _load_binding()
+_CALL_GEMM, _CALL_CONV, _CALL_CONV_DENSE = 0, 1, 2
+
+
 def _host_i32(z):
     import numpy as np
     a = np.ascontiguousarray(np.atleast_1d(np.asarray(z)).astype(np.int32))
@@ -131,6 +149,7 @@ class PackedB:
     def __init__(self, handle, packed, aux, n):
         self.handle, self.packed, self.aux, self._n = handle, packed, aux, n
         self._kn = lib.qg_packed_b_k(handle), lib.qg_packed_b_n(handle)   # (fixed for the descriptor's life)
+        self._fast = (handle.value,) + self._kn
 
     @property
     def col_offsets(self):
@@ -146,6 +165,7 @@ class PackedB:
 
     def close(self):
         if self.handle:
+            self._fast = None
             lib.qg_packed_b_destroy(self.handle)
             self.handle = None
 
@@ -325,6 +345,11 @@ def gemm_u8s8_acc32_splitk(A, Bp, workspace, kernel=KERNEL_AUTO, ksplit=0, want_
 
 def gemm_u8s8_requant(A, a_zp, Bp, bias, scales, c_zp, relu, out=None, workspace=None, kernel=KERNEL_AUTO):
     """C_u8 = requant(A_u8 . B_s8): A uint8 cuda [M, K]; returns / fills uint8 [M, N]."""
+    done = _binding.gemm_u8s8_requant(A, a_zp, Bp, bias, scales, c_zp, relu, out, workspace,
+                                      kernel if type(kernel) is int else kernel_id(kernel))
+    if done is not None:
+        return done
+    # a check failed, an argument is of another type, or the call was refused: say which
     assert A.is_cuda and A.dtype == torch.uint8 and A.dim() == 2 and A.stride(1) == 1
     M, K = A.shape
     assert K == Bp.K
@@ -339,77 +364,57 @@ def gemm_u8s8_requant(A, a_zp, Bp, bias, scales, c_zp, relu, out=None, workspace
     return out
 
 
-class PreparedGemm:
-    """All arguments of one qg_gemm_u8s8_requant call marshalled once; `launch()` is a single ctypes call on
-    the stream that was current when the object was made.  For loops that repeat the same call."""
+class _Prepared:
+    """A call whose arguments are marshalled once, for loops that repeat it; `launch()` issues it on the stream that was
+    current when the object was made (or last rebound)."""
+
+    def _prepare(self, kind, keep, inp, weights, out, workspace, p, ints):
+        self._keep, self.out = keep, out
+        self._call_args = (kind, keep, inp.data_ptr(), weights.handle.value if weights.handle else None, out.data_ptr(),
+                           workspace.data_ptr() if workspace is not None else None)
+        self._call_rest = (p.a_zp, p.bias, p.scales, p.n_scales, p.c_zp, p.relu) + tuple(ints)
+        self.rebind()
+
+    def launch(self):
+        self._call.launch()
+
+    def rebind(self):
+        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
+        self._call = _binding.prepare(*self._call_args, _stream(), *self._call_rest)
+        self.launch = self._call.launch   # (straight into the module; it keeps the tensors alive by itself)
+        return self
+
+
+class PreparedGemm(_Prepared):
+    """qg_gemm_u8s8_requant, marshalled once."""
 
     def __init__(self, A, a_zp, Bp, bias, scales, c_zp, relu, out, kernel=KERNEL_AUTO, workspace=None):
         assert A.is_cuda and A.dtype == torch.uint8 and A.dim() == 2 and A.stride(1) == 1 and A.shape[1] == Bp.K
         assert out.is_cuda and out.dtype == torch.uint8 and out.stride(1) == 1 and out.shape == (A.shape[0], Bp.N)
-        self._keep = (A, Bp, bias, scales, out, workspace)
-        self._p = _params(a_zp, bias, scales, c_zp, relu)
-        self._args = (A.data_ptr(), A.shape[0], A.stride(0), Bp.handle, ctypes.byref(self._p), out.data_ptr(),
-                      out.stride(0), workspace.data_ptr() if workspace is not None else None, _stream(),
-                      kernel_id(kernel))
-        self.out = out
-
-    def launch(self):
-        rc = lib.qg_gemm_u8s8_requant_kernel(*self._args)
-        if rc != OK:
-            raise QGemmError(rc, "qg_gemm_u8s8_requant")
-
-    def rebind(self):
-        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
-        self._args = self._args[:8] + (_stream(),) + self._args[9:]
-        return self
+        self._prepare(_CALL_GEMM, (A, Bp, bias, scales, out, workspace), A, Bp, out, workspace,
+                      _params(a_zp, bias, scales, c_zp, relu), (A.shape[0], A.stride(0), out.stride(0), kernel_id(kernel)))
 
 
-class PreparedConv:
+class PreparedConv(_Prepared):
     """Same for qg_conv_groupwise_u8s8_requant."""
 
     def __init__(self, inp, Wp, a_zp, bias, scales, c_zp, relu, pad, stride, out):
         assert inp.is_cuda and inp.dtype == torch.uint8 and inp.dim() == 4 and inp.is_contiguous()
         assert out.is_cuda and out.dtype == torch.uint8 and out.is_contiguous()
         Nb, H, W, C = inp.shape
-        self._keep = (inp, Wp, bias, scales, out)
-        self._p = _params(a_zp, bias, scales, c_zp, relu)
-        self._args = (inp.data_ptr(), Nb, H, W, C, pad, stride, Wp.handle, ctypes.byref(self._p), out.data_ptr(),
-                      _stream())
-        self.out = out
-
-    def launch(self):
-        rc = lib.qg_conv_groupwise_u8s8_requant(*self._args)
-        if rc != OK:
-            raise QGemmError(rc, "qg_conv_groupwise_u8s8_requant")
-
-    def rebind(self):
-        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
-        self._args = self._args[:-1] + (_stream(),)
-        return self
+        self._prepare(_CALL_CONV, (inp, Wp, bias, scales, out), inp, Wp, out, None, _params(a_zp, bias, scales, c_zp, relu),
+                      (Nb, H, W, C, pad, stride))
 
 
-class PreparedConvDense:
+class PreparedConvDense(_Prepared):
     """Same for qg_conv_dense_u8s8_requant (Wp from pack_conv_dense_w)."""
 
     def __init__(self, inp, Wp, a_zp, bias, scales, c_zp, relu, pad, stride, out, kernel=KERNEL_AUTO):
         assert inp.is_cuda and inp.dtype == torch.uint8 and inp.dim() == 4 and inp.is_contiguous()
         assert out.is_cuda and out.dtype == torch.uint8 and out.is_contiguous()
         Nb, H, W, C = inp.shape
-        self._keep = (inp, Wp, bias, scales, out)
-        self._p = _params(a_zp, bias, scales, c_zp, relu)
-        self._args = (inp.data_ptr(), Nb, H, W, C, Wp.R, Wp.S, pad, stride, Wp.handle, ctypes.byref(self._p), out.data_ptr(),
-                      _stream(), kernel_id(kernel))
-        self.out = out
-
-    def launch(self):
-        rc = lib.qg_conv_dense_u8s8_requant(*self._args)
-        if rc != OK:
-            raise QGemmError(rc, "qg_conv_dense_u8s8_requant")
-
-    def rebind(self):
-        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
-        self._args = self._args[:12] + (_stream(),) + self._args[13:]
-        return self
+        self._prepare(_CALL_CONV_DENSE, (inp, Wp, bias, scales, out), inp, Wp, out, None, _params(a_zp, bias, scales, c_zp, relu),
+                      (Nb, H, W, C, Wp.R, Wp.S, pad, stride, kernel_id(kernel)))
 
 
 def gemm_u8s8_acc32(A, Bp, want_rowsum=False, kernel=KERNEL_AUTO):
@@ -486,6 +491,11 @@ def _f32_ws(A, Bp, workspace):
 def gemm_f32s8_requant(A, a_inv_scale, a_zp, Bp, bias, scales, c_zp, relu, out=None, workspace=None,
                        kernel=KERNEL_AUTO):
     """fp32 activations, quantized by the library, uint8 out."""
+    if c_zp is not None:
+        done = _binding.gemm_f32s8(A, a_inv_scale, a_zp, Bp, bias, scales, c_zp, relu, out, workspace,
+                                   kernel if type(kernel) is int else kernel_id(kernel))
+        if done is not None:
+            return done
     ws = _f32_ws(A, Bp, workspace)
     M = A.shape[0]
     if out is None:
@@ -501,6 +511,10 @@ def gemm_f32s8_requant(A, a_inv_scale, a_zp, Bp, bias, scales, c_zp, relu, out=N
 def gemm_f32s8_dequant_f32(A, a_inv_scale, a_zp, Bp, bias, scales, relu, out=None, workspace=None,
                            kernel=KERNEL_AUTO):
     """fp32 activations in, fp32 result out."""
+    done = _binding.gemm_f32s8(A, a_inv_scale, a_zp, Bp, bias, scales, None, relu, out, workspace,
+                               kernel if type(kernel) is int else kernel_id(kernel))
+    if done is not None:
+        return done
     ws = _f32_ws(A, Bp, workspace)
     M = A.shape[0]
     out = _f32_out(out, M, Bp.N, A.device)
