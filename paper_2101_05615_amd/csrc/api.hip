@@ -159,21 +159,9 @@ double tile_estimate(const tile_cost& c, int M, int N, int K) {
   return us;
 }
 
-// The 128 x 64 form of QG_KERNEL_TILE128 (at most one tile per CU): 4.4 + 0.145 us per k step fitted to 128 shapes, M 96 .. 1024 x
-// N, K 1024 .. 8192, and priced a tenth higher, because the prices of the others are a little too high by now.  Over 540 other
-// shapes of the form's range, rows at multiples of 4 bytes, 3 are then more than 4 % slower than the best of the others was
-// priced (1186 x 864 x 4288 14.0 against 15.9 us; with the fitted price 14), and the mean is 0.986 of it; 256 x 8192 x 8192 0.75.
-const tile_cost k_tile128_few_cost = {QG_KERNEL_TILE128, 128, 64, 4.84, 0.16, 0.0, 0.0};
-
-// few_ok: the 128 x 64 form may be considered.  Not
-//  - for rows of A that start off multiples of 4 bytes: there the tile requests run at a third of their rate whatever the
-//    tile (32 bytes per cycle and CU against 75 to 97), which leaves the form behind the 64 x 64 tiles, that more CUs share
-//    (999 x 1531 x 2047 13.9 us against 13.6);
-//  - for a call that asks for a K split across workgroups, which the form does not have, and for the queries about one: the
-//    answers and the calls are then the same for every alignment;
-//  - for fp32 activations without a workspace, which only a streaming kernel takes.
-int builtin_select(int M, int N, int K, bool few_ok = true) {
-  const bool few = few_ok && qg_tile128_few(M, N, K);
+// What the queries about K splits and workspaces, calls that ask for a split, calls that bring a workspace for one and fp32
+// activations without a workspace go by: one answer for a shape, whatever the alignment of the operands.
+int builtin_select(int M, int N, int K) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
   for (const stream_cost& c : k_stream_cost) {
@@ -183,7 +171,136 @@ int builtin_select(int M, int N, int K, bool few_ok = true) {
     if (us < best_us) best_us = us, best = c.kernel;
   }
   for (const tile_cost& c : k_tile_cost) {
-    const double us = tile_estimate(few && c.kernel == QG_KERNEL_TILE128 ? k_tile128_few_cost : c, M, N, K);
+    const double us = tile_estimate(c, M, N, K);
+    if (us < best_us) best_us = us, best = c.kernel;
+  }
+  return best;
+}
+
+// All other calls: the same idea with the terms that decide close races -- how full the chip is while at most one workgroup
+// runs on a CU, rows of A and C off 16 bytes, 4-byte outputs, the 128 x 64 form of the 128-row kernel, the streaming kernels'
+// wide form -- in two sets of prices, since rows of A that are not 16-byte aligned slow every kernel down,
+// but by very different factors (the streaming kernels by up to 1.8, 64 x 64 tiles by 1.1).
+//   tile, at most 256 workgroups   us = fix + kt * (lat + crowd * wgs / 256)             kt = ceil(K / 64)
+//   beyond                         the larger of that and 2.5 + rounds * epi + kt * thr * (rounds - fill * (rounds - wgs / 256)),
+//                                  rounds = ceil(wgs / 256): a round that does not fill the chip runs faster
+//   streaming                      us = fix + K / 1024 * lat + n * batch; more than 256 workgroups: the larger of that times
+//                                  (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
+// Fitted to graph-replay times of all kernels on 7724 shapes (M 1 .. 65536, N 8 .. 8192, K 16 .. 8192, a quarter of them with
+// K a multiple of 2048).  Against the measured best kernel of other shapes the choice is 1.010 of it in the geometric mean
+// with rows at 16 bytes (1316 shapes, worst 1.52) and 1.006 with others (995, worst 1.24); the prices above, with one price of
+// the 128 x 64 form added, 1.032 (worst 2.18) and 1.049 (1.79).  Largest gains: long K over many columns
+// with few rows (9 x 7996 x 5824 16.4 -> 11.4 us) and tall shapes (20447 x 576 x 752 26.3 -> 21.5).
+struct tile_price {
+  int kernel, bm, bn;
+  double fix, lat, crowd, thr, fill, epi, out;  // out: megabytes of output per microsecond
+  double rag_fix, rag_epi;                // u8 output, rows of C off 16 bytes
+  double wide_fix, wide_epi;              // 4-byte output
+  double byte_lat, byte_thr;              // rows of A off 4 bytes: factors on lat, on thr
+  double tall;                            // M >= N: so much more; half of it from M >= 3/4 N (fewer workgroups share a row of A)
+};
+struct stream_price {
+  int kernel, rows;
+  double fix, lat, batch, second, wg, wg_k;  // lat: per 1024 of K; batch: per batch of requests a wave makes after its first
+  double a_rate, a_far;                   // megabytes of A per us: one workgroup row's; all, in tens, once A is beyond the L2s
+  double wide_fix, wide_wg, byte_lat, byte_wg_k;
+};
+struct price_set {
+  tile_price tile[8];      // the second of QG_KERNEL_TILE128 is the 128 x 64 form (rows at 16 bytes: 2 % below its fit, for near ties)
+  stream_price stream[6];  // rows at 16 bytes: each kernel, and its wide form after it
+  int nstream;
+};
+const price_set k_price_16 = {
+    {
+        {QG_KERNEL_TILE64K1, 64, 64, 3.685, 0.1962, 0.07176, 0.1228, 0.1758, 0.3658, 2.121, 0.07015, 0.1381, 0.1352, 0.2825, 1, 1, 0},
+        {QG_KERNEL_TILE64, 64, 64, 3.951, 0.1109, 0.03765, 0.1061, 0.1983, 0.8019, 1.744, 0.1285, 0.1375, 0.1813, 0.3518, 1, 1, 0},
+        {QG_KERNEL_TILE64K4, 64, 64, 4.44, 0.08052, 0.04065, 0.1095, 0.2493, 2.288, 5.487, 0.1631, 0.2359, 0.2057, 0.3153, 1, 1, 0},
+        {QG_KERNEL_TILE64X32K8, 64, 32, 4.492, 0.0497, 0.02743, 0.06995, 0.2437, 2.313, 1.046, 0.276, 0.2533, 0.3191, 0.3403, 1, 1, 0},
+        {QG_KERNEL_TILE128, 128, 128, 5.443, 0.1437, 0.147, 0.2762, 0.4156, 1.703, 10.51, 0, 0.4648, 1.467, 1.053, 1, 1, 0},
+        {QG_KERNEL_TILE128, 128, 64, 5.136, 0.09021, 0.06707, 0.1449, 0.2737, 0.007244, 0.9298, 0.4242, 0.1952, 0.4441, 0.04453, 1, 1, 0.17},
+        {QG_KERNEL_TILE128X256, 128, 256, 7.448, 0.2583, 0.2161, 0.4479, 0.4333, 3.381, 2.385, 0, 0.6444, 2.352, 0.7592, 1, 1, 0},
+        {QG_KERNEL_TILE256, 256, 256, 14.88, 0.3512, 0.4636, 0.8095, 0.4857, 10.36, 2.432, 0.6005, 1.198, 3.492, 0.4228, 1, 1, 0},
+    },
+    {
+        {QG_KERNEL_SKINNY16, 16, 3.998, 0.2013, 1.204, 0.5315, 6.898, 0.002001, 0.7701, 7.914, 0.1569, 0, 1, 1},
+        {QG_KERNEL_SKINNY16, 16, 3.09, 0.861, 0.2585, 0.3154, 0.7925, 0.003124, 0.3034, 1.351, 0, 0, 1, 1},
+        {QG_KERNEL_SKINNY32, 32, 4.373, 0.4228, 0.8754, 0.6385, 9.142, 0.002984, 0.5606, 4.705, 0.2843, 0.2869, 1, 1},
+        {QG_KERNEL_SKINNY32, 32, 3.453, 1.147, 0.09724, 0.4894, 4.349, 0.005273, 0.2899, 1.582, 0.1091, 0, 1, 1},
+        {QG_KERNEL_SKINNY64, 64, 4.742, 0.2631, 1.478, 0.7853, 10.34, 0.004393, 0.3371, 2.045, 0.3073, 1.718, 1, 1},
+        {QG_KERNEL_SKINNY64, 64, 4.392, 1.397, 0.02116, 0.7001, 10.07, 0.005733, 0.4112, 2.827, 0.1708, 0.5981, 1, 1},
+    },
+    6};
+const price_set k_price_off = {
+    {
+        {QG_KERNEL_TILE64K1, 64, 64, 3.997, 0.2076, 0.06951, 0.1385, 0.01215, 0.3748, 1.545, 0.05743, 0.191, 0.1352, 0.2825, 1.069, 1.09, 0},
+        {QG_KERNEL_TILE64, 64, 64, 4.407, 0.1238, 0.02299, 0.1155, 0, 0.831, 3.026, 0.09853, 0.1816, 0.1813, 0.3518, 1.173, 1.189, 0},
+        {QG_KERNEL_TILE64K4, 64, 64, 4.913, 0.09614, 0.02658, 0.1131, 0.1812, 2.709, 1.687, 0.1347, 0.1713, 0.2057, 0.3153, 1.345, 1.249, 0},
+        {QG_KERNEL_TILE64X32K8, 64, 32, 5.361, 0.05698, 0.03245, 0.08362, 0.1719, 2.893, 0.1426, 0.1281, 0.1673, 0.3191, 0.3403, 1.769, 1.451, 0},
+        {QG_KERNEL_TILE128, 128, 128, 5.638, 0.2323, 0.1034, 0.3049, 0.1808, 1.819, 17.04, 0.4865, 0.57, 1.467, 1.053, 1.167, 1.071, 0},
+        {QG_KERNEL_TILE128, 128, 64, 6.457, 0.1257, 0.05136, 0.002241, 0.2397, 0.4095, 1.567, 0.5513, 0.1302, 0.4441, 0.04453, 1.615, 0.5655, 0.03},
+        {QG_KERNEL_TILE128X256, 128, 256, 8.088, 0.3241, 0.17, 0.4741, 0.3709, 3.606, 9.42, 0.2809, 0.7998, 2.352, 0.7592, 1.183, 1.056, 0},
+        {QG_KERNEL_TILE256, 256, 256, 15.87, 0.4316, 0.37, 0.8081, 0.4086, 11.87, 1.916, 1.057, 0.6666, 3.492, 0.4228, 1.347, 1.202, 0},
+    },
+    {
+        {QG_KERNEL_SKINNY16, 16, 4.072, 0.4924, 0, 0.7103, 9.148, 0.002234, 0.4255, 1.362, 0.1569, 0, 1.599, 1.446},
+        {QG_KERNEL_SKINNY32, 32, 4.727, 0.8457, 0, 0.7346, 12.84, 0.003592, 0.3285, 0.9272, 0.2843, 0.2869, 1.849, 1.544},
+        {QG_KERNEL_SKINNY64, 64, 5.981, 1.242, 0, 0.6692, 20.52, 0.004849, 0.2901, 1.317, 0.3073, 1.718, 1.807, 1.57},
+    },
+    3};
+
+struct call_form {
+  int a_align;    // 16: base and rows of A at multiples of 16 bytes, 4: of 4 bytes, 1: others
+  bool wide_out;  // 4-byte results
+  bool c_ragged;  // rows of u8 results off 16 bytes
+};
+
+double tile_price_us(const tile_price& c, int M, int N, int K, const call_form& f) {
+  const double kt = (double)ceil_div(K, 64), wgs = (double)ceil_div(M, c.bm) * (double)ceil_div(N, c.bn);
+  const bool byte = f.a_align == 1, rag = f.c_ragged && !f.wide_out;
+  const double fix = c.fix + (f.wide_out ? c.wide_fix : 0.0) + (rag ? c.rag_fix : 0.0);
+  const double step = c.lat * (byte ? c.byte_lat : 1.0) + c.crowd * fmin(wgs, 256.0) / 256.0;
+  const double alone = fmax(fix + kt * step, 2.5 + (double)M * (double)N * (f.wide_out ? 4.0 : 1.0) / (c.out * 1e6));
+  if (wgs <= 256.0) return alone * (1.0 + c.tall * (M >= N ? 1.0 : 4.0 * M >= 3.0 * N ? 0.5 : 0.0));
+  const double epi = c.epi + (f.wide_out ? c.wide_epi : 0.0) + (rag ? c.rag_epi : 0.0);
+  const double rounds = ceil(wgs / 256.0), steps = rounds + c.fill * (wgs / 256.0 - rounds);
+  return fmax(alone, 2.5 + rounds * epi + steps * kt * c.thr * (byte ? c.byte_thr : 1.0));
+}
+
+double stream_price_us(const stream_price& c, bool wide, int M, int N, int K, const call_form& f) {
+  const double blocks32 = (double)ceil_div(M, c.rows) * (double)ceil_div(N, 32), wgs = wide ? blocks32 : 2.0 * blocks32;
+  const bool byte = f.a_align == 1;
+  const double a_bytes = (double)M * (double)K;
+  double a_bound = 2.5 + a_bytes / (c.a_rate * 1e6);
+  if (a_bytes > k_stream_a_near) a_bound = fmax(a_bound, 2.5 + a_bytes * (double)ceil_div(N, 16) / (c.a_far * 1e7));
+  // waves of a workgroup and k blocks of a batch as in the launches
+  const int waves = !wide ? 16 : c.rows == 64 ? 8 : 4, per = !wide ? (c.rows == 64 ? 2 : 4) : c.rows == 64 ? 4 : 8;
+  const double n = (double)(ceil_div(ceil_div(ceil_div(K, 64), waves), per) - 1);
+  const double alone = fmax(c.fix + (f.wide_out ? c.wide_fix : 0.0) + (K * c.lat / 1024.0 + n * c.batch) * (byte ? c.byte_lat : 1.0), a_bound);
+  if (wgs <= 256.0) return alone;
+  const double each = c.wg + (f.wide_out ? c.wide_wg : 0.0) + K * c.wg_k * (byte ? c.byte_wg_k : 1.0);
+  return fmax(alone * (1.0 + c.second), 2.5 + wgs * each * 1e-3);
+}
+
+int price_select(int M, int N, int K, const call_form& f) {
+  const price_set& set = f.a_align == 16 ? k_price_16 : k_price_off;
+  int best = QG_KERNEL_TILE64;
+  double best_us = 1e300;
+  for (int i = 0; i < set.nstream; ++i) {
+    const stream_price& c = set.stream[i];
+    if (ceil_div(M, c.rows) > 65535) continue;
+    const bool wide = set.nstream == 6 && (i & 1);
+    if (set.nstream == 6) {
+      const bool is_wide = K % 2048 == 0 && (long long)ceil_div(M, c.rows) * ceil_div(N, 32) > 128;
+      if (wide != is_wide) continue;
+    }
+    const double us = stream_price_us(c, wide, M, N, K, f);
+    if (us < best_us) best_us = us, best = c.kernel;
+  }
+  const bool few = qg_tile128_few(M, N, K);
+  for (const tile_price& c : set.tile) {
+    if (c.kernel == QG_KERNEL_TILE128 && (c.bn == 64) != few) continue;
+    if (c.kernel == QG_KERNEL_TILE256 && K < 256) continue;  // 128 x 256 tiles there, without the loop priced here
+    const double us = tile_price_us(c, M, N, K, f);
     if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
@@ -216,12 +333,13 @@ int select_stream_kernel(int M, int N, int K) {
   return best;
 }
 
-int select_kernel(int M, int N, int K, bool few_ok = true) {
+// the caller's rule for the shape, or QG_KERNEL_AUTO
+int rule_kernel(int M, int N, int K) {
   for (int i = 0; i < g_nrules; ++i) {
     const qg_dispatch_rule& r = g_rules[i];
     if (M >= r.m_lo && M <= r.m_hi && N >= r.n_lo && N <= r.n_hi && K >= r.k_lo && K <= r.k_hi) return r.kernel;
   }
-  return builtin_select(M, N, K, few_ok);
+  return QG_KERNEL_AUTO;
 }
 
 hipError_t launch_rows(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
@@ -251,13 +369,6 @@ hipError_t launch_gemm(const qg_gemm_args& a, int mode, int kernel, hipStream_t 
   return hipSuccess;
 }
 
-// resolves QG_KERNEL_AUTO for a descriptor and checks an explicit choice against it: QG_OK, or
-// QG_EINVAL (unknown id / too many row blocks), QG_EUNSUPPORTED (tiled kernel on a split descriptor)
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool few_ok);
-
-// rows of A at multiples of 4 bytes (see builtin_select)
-bool word_rows(const uint8_t* A_dev, int lda) { return aligned(A_dev, 4) && lda % 4 == 0; }
-
 // kernel id valid for this M (the streaming kernels put row blocks on the 16-bit grid dimension)
 bool kernel_ok(int kernel, int M) {
   if (kernel < QG_KERNEL_AUTO || kernel > QG_KERNEL_LAST) return false;
@@ -266,17 +377,17 @@ bool kernel_ok(int kernel, int M) {
   return true;
 }
 
-int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel, bool few_ok) {
+// resolves QG_KERNEL_AUTO for a descriptor and checks an explicit choice against it: QG_OK, or
+// QG_EINVAL (unknown id / too many row blocks), QG_EUNSUPPORTED (tiled kernel on a split descriptor)
+int resolve_kernel(const qg_packed_b* Bp, int M, int* kernel) {
   if (!kernel_ok(*kernel, M)) return QG_EINVAL;
   if (Bp->split) {
     if (*kernel == QG_KERNEL_AUTO) *kernel = select_stream_kernel(M, Bp->N, Bp->K);
     if (*kernel > QG_KERNEL_SKINNY64) return QG_EUNSUPPORTED;
     return kernel_ok(*kernel, M) ? QG_OK : QG_EINVAL;
   }
-  if (*kernel == QG_KERNEL_AUTO) {
-    *kernel = select_kernel(M, Bp->N, Bp->K, few_ok);
-    if (!kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K, few_ok);
-  }
+  if (*kernel == QG_KERNEL_AUTO) *kernel = rule_kernel(M, Bp->N, Bp->K);
+  if (*kernel == QG_KERNEL_AUTO || !kernel_ok(*kernel, M)) *kernel = builtin_select(M, Bp->N, Bp->K);
   return QG_OK;
 }
 
@@ -333,6 +444,24 @@ int auto_ksplit(int kernel, int M, const qg_packed_b* Bp) {
   if (s > 16) s = 16;
   if (s < (rows == 64 ? 2 : 4)) return 1;
   return clamp_ksplit(Bp, s);
+}
+// QG_KERNEL_AUTO of one call.  A call that leaves kernel and split to the library and brings no workspace, or one that no
+// query asked for, gets the kernel of the closer prices, without a split (a split that the queries did not announce
+// must not be used: the caller's workspace may be anything).  All others get what the queries answer for.
+int resolve_call(const qg_packed_b* Bp, int M, int* kernel, int* ksplit, const call_form& f, const void* workspace_dev) {
+  if (*kernel != QG_KERNEL_AUTO || Bp->split || *ksplit < 0 || *ksplit > 1 || M <= 0) return resolve_kernel(Bp, M, kernel);
+  const int rule = rule_kernel(M, Bp->N, Bp->K);
+  if (rule != QG_KERNEL_AUTO && kernel_ok(rule, M)) return *kernel = rule, QG_OK;
+  if (*ksplit == 0 && workspace_dev != nullptr) {
+    const int k = builtin_select(M, Bp->N, Bp->K);
+    if (auto_ksplit(k, M, Bp) > 1) return *kernel = k, QG_OK;
+    *ksplit = 1;
+  }
+  *kernel = price_select(M, Bp->N, Bp->K, f);
+  return QG_OK;
+}
+int a_align(const uint8_t* A_dev, int lda) {
+  return aligned(A_dev, 16) && lda % 16 == 0 ? 16 : aligned(A_dev, 4) && lda % 4 == 0 ? 4 : 1;
 }
 // ksplit_req: 0 = built-in choice (1 without a workspace), otherwise the caller's.  Fills the workspace fields of `a`.
 int resolve_ksplit(const qg_packed_b* Bp, int M, int kernel, int ksplit_req, void* workspace_dev, size_t workspace_bytes,
@@ -422,9 +551,9 @@ const char* qg_kernel_name(int kernel) {
 
 int qg_kernel_select(int M, int N, int K) {
   if (M <= 0 || N <= 0 || K <= 0) return QG_EINVAL;
-  int k = select_kernel(M, N, K);
-  if (!kernel_ok(k, M)) k = builtin_select(M, N, K);
-  return k;
+  const int rule = rule_kernel(M, N, K);
+  if (rule != QG_KERNEL_AUTO && kernel_ok(rule, M)) return rule;
+  return price_select(M, N, K, {16, false, N % 16 != 0});
 }
 
 int qg_dispatch_set_rules(const qg_dispatch_rule* rules_host, int n) {
@@ -618,14 +747,14 @@ size_t qg_packed_b_nnz(const qg_packed_b* p) { return (p && p->split) ? (size_t)
 size_t qg_gemm_workspace_bytes(int M, const qg_packed_b* Bp) {
   if (!Bp || M <= 0 || Bp->kind != QG_KIND_GEMM) return 0;
   int kernel = QG_KERNEL_AUTO;
-  if (resolve_kernel(Bp, M, &kernel, false) != QG_OK) return 0;
+  if (resolve_kernel(Bp, M, &kernel) != QG_OK) return 0;
   const int s = auto_ksplit(kernel, M, Bp);
   return s > 1 ? splitk_ws(kernel, M, Bp->N, s).bytes() : 0;
 }
 
 size_t qg_gemm_splitk_workspace_bytes(int M, const qg_packed_b* Bp, int kernel, int ksplit) {
   if (!Bp || M <= 0 || Bp->kind != QG_KIND_GEMM || ksplit < 0 || ksplit > kMaxKsplit) return 0;
-  if (resolve_kernel(Bp, M, &kernel, false) != QG_OK) return 0;
+  if (resolve_kernel(Bp, M, &kernel) != QG_OK) return 0;
   if (kernel == QG_KERNEL_TILE128) {
     const int s = ksplit > 1 ? clamp_ksplit_tile128(Bp, ksplit) : 1;
     return s > 1 ? splitk_ws(kernel, M, Bp->N, s).bytes() : 0;
@@ -638,7 +767,7 @@ size_t qg_gemm_splitk_workspace_bytes(int M, const qg_packed_b* Bp, int kernel, 
 int qg_gemm_splitk_factor(int M, const qg_packed_b* Bp, int kernel, int ksplit) {
   if (!Bp || Bp->kind != QG_KIND_GEMM) return QG_ENULL;
   if (M <= 0 || ksplit < 0 || ksplit > kMaxKsplit) return QG_EINVAL;
-  const int rc = resolve_kernel(Bp, M, &kernel, false);
+  const int rc = resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   if (kernel == QG_KERNEL_TILE128) return ksplit > 1 ? clamp_ksplit_tile128(Bp, ksplit) : 1;
   if (kernel > QG_KERNEL_SKINNY64) return 1;
@@ -686,7 +815,7 @@ static int gemm_requant(const uint8_t* A_dev, int M, int lda, const qg_packed_b*
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, ksplit <= 1 && word_rows(A_dev, lda));
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), false, !aligned(C_dev, 16) || ldc % 16 != 0}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_requant(p, Bp->N);
@@ -751,7 +880,7 @@ static int gemm_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* B
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, ksplit <= 1 && word_rows(A_dev, lda));
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), true, false}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C32_dev && M != 0) return QG_ENULL;
   if (ldc < Bp->N) return QG_EINVAL;
@@ -797,14 +926,15 @@ int qg_gemm_u8s8_dequant_f32(const uint8_t* A_dev, int M, int lda, const qg_pack
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_kernel(Bp, M, &kernel, word_rows(A_dev, lda));
+  int ksplit = 0;
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), true, false}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_dequant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (ldc < Bp->N) return QG_EINVAL;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
-  rc = resolve_ksplit(Bp, M, kernel, 0, workspace_dev, 0, false, &a);
+  rc = resolve_ksplit(Bp, M, kernel, ksplit, workspace_dev, 0, false, &a);
   if (rc != QG_OK) return rc;
   a.bias = p->bias;
   a.scales = p->scales;
@@ -884,7 +1014,10 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   int rc = check_requant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel, workspace_dev != nullptr);
+  // (with a workspace the 8-bit call below runs on the quantized copy, whose rows are 16-byte aligned and which has no split)
+  int ksplit = 1;
+  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, false, !aligned(C_dev, 16) || ldc % 16 != 0}, nullptr)
+                     : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   {
     qg_gemm_args a = {};
@@ -923,7 +1056,8 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   int rc = check_dequant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  rc = resolve_kernel(Bp, M, &kernel, workspace_dev != nullptr);
+  int ksplit = 1;
+  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, true, false}, nullptr) : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {

@@ -1,0 +1,64 @@
+"""QG_KERNEL_AUTO by the closer prices: no call needs more than the queries announce, whatever the alignment of its operands,
+and the choice gives the bytes of a fixed kernel on the shapes where it turns from one kernel to another."""
+import ctypes
+
+import pytest
+
+from paper_2101_05615_amd import workloads as wl
+from test_automatic_choice import descriptor
+
+MS = [1, 2, 16, 17, 33, 48, 64, 65, 129, 300, 1000, 5748, 25284]
+NS = [16, 42, 64, 103, 256, 1024, 1531, 4096, 6304, 8192]
+KS = [17, 32, 128, 255, 256, 767, 768, 1216, 2048, 2816, 4096, 4097, 8192, 16384, 65536]
+
+
+def test_no_call_needs_more_than_was_announced():
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the calls that pass their checks would be launched")
+    from paper_2101_05615_amd import qgemm as q
+    split = 0
+    for M in MS:
+        for N in NS:
+            for K in KS:
+                h = ctypes.byref(descriptor(K, N))
+                p, dq = q.RequantParams(0, None, 4096, 1, 0, 0), q.DequantParams(0, None, 4096, 1, 0)
+                need = q.lib.qg_gemm_workspace_bytes(M, h)
+                split += need > 0
+                for a, lda, c, ldc in ((4096, K, 4096, N), (4096, K + (-K) % 16, 4096, N + (-N) % 16), (4100, K, 4097, N), (4097, K + 1, 4096, N)):
+                    # a workspace of no bytes: refused exactly where the query asks for some
+                    for rc in (q.lib.qg_gemm_u8s8_requant_splitk(a, M, lda, h, ctypes.byref(p), c, ldc, 4096, 0, None, 0, 0),
+                               q.lib.qg_gemm_u8s8_acc32_splitk(a, M, lda, h, 4096, ldc, None, 4096, 0, None, 0, 0)):
+                        assert rc == (q.EWORKSPACE if need else q.ELAUNCH), (M, N, K, a, lda, need, rc)
+                    # a workspace that cannot be used, where nothing uses one
+                    rc = q.lib.qg_gemm_u8s8_dequant_f32(a, M, lda, h, ctypes.byref(dq), 4096, ldc, 4097, None, 0)
+                    assert rc == (q.EALIGN if need else q.ELAUNCH), (M, N, K, a, lda, need, rc)
+    assert split > 50
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("a_off,lda_pad", [(0, 0), (4, 4), (1, 3)])
+@pytest.mark.parametrize("M,N,K", [(2, 6683, 2336), (6, 4996, 7488), (7, 6304, 2816), (49, 4938, 2048), (16, 42, 17), (63, 103, 255),
+                                   (300, 520, 256), (129, 1531, 767), (1000, 200, 768), (5748, 256, 316), (2600, 1100, 2064), (64, 256, 16384)])
+def test_choice_against_a_fixed_kernel(M, N, K, a_off, lda_pad):
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    case = wl.random_gemm(M + N + K, M, N, K)
+    lda = K + (-K) % 16 + lda_pad
+    store = torch.zeros(M * lda + 32, dtype=torch.uint8, device="cuda")
+    A = store[a_off:a_off + M * lda].view(M, lda)[:, :K]
+    A.copy_(torch.from_numpy(case.A))
+    Bp = q.pack_b(torch.from_numpy(case.B).cuda(), case.b_zp)
+    bias, scales = torch.from_numpy(case.bias).cuda(), torch.from_numpy(case.scales).cuda()
+    args = (A, case.a_zp, Bp, bias, scales)
+    want = q.gemm_u8s8_requant(*args, case.c_zp, case.relu, kernel="tile64")
+    ws = q.gemm_workspace(M, Bp)
+    for w in (None, ws, torch.zeros(1 << 10, dtype=torch.uint8, device="cuda") if ws is None else ws):
+        assert torch.equal(q.gemm_u8s8_requant(*args, case.c_zp, case.relu, workspace=w), want)
+    assert torch.equal(q.gemm_u8s8_acc32(A, Bp), q.gemm_u8s8_acc32(A, Bp, kernel="tile64"))
+    assert torch.equal(q.gemm_u8s8_dequant_f32(*args, case.relu), q.gemm_u8s8_dequant_f32(*args, case.relu, kernel="tile64"))
+    F = torch.randn((M, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
+    for fn, last in ((q.gemm_f32s8_requant, (case.c_zp, case.relu)), (q.gemm_f32s8_dequant_f32, (case.relu,))):
+        ref = fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, kernel="tile64")
+        assert torch.equal(fn(F, 0.02, case.a_zp, Bp, bias, scales, *last), ref)
+    torch.cuda.synchronize()
