@@ -1,0 +1,32 @@
+"""The group convolution with taps from memory (stride 2, or no padding) on one, two and four 32-channel blocks per workgroup: the
+edges of the rule, ragged pixel tiles, with and without a weight zero point, against the CPU oracle's direct convolution."""
+import pytest
+
+from paper_2101_05615_amd import workloads as wl
+from gpu_util import assert_same, say
+from test_gpu_conv_groups import env, run, want  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cfg", [
+    dict(Nb=1, H=7, W=9, C=128, G=32),                     # one block, 20 pixels
+    dict(Nb=2, H=129, W=63, C=64, G=64),                   # 4160 pixels, 33 tiles x 2 blocks: one
+    dict(Nb=1, H=255, W=255, C=64, G=8),                   # 16384 pixels, 128 tiles x 2 blocks: the last with one
+    dict(Nb=1, H=257, W=255, C=64, G=16),                  # 129 tiles x 2 blocks: the first with two
+    dict(Nb=1, H=255, W=257, C=96, G=24),                  # C off 64: one
+    dict(Nb=3, H=65, W=65, C=384, G=384),                  # 26 tiles x 12 blocks: two
+    dict(Nb=1, H=223, W=221, C=512, G=16),                 # 98 tiles x 16 blocks: four
+    dict(Nb=1, H=100, W=101, C=1024, G=256, R=1, S=1, pad=0),  # 1 x 1, 20 tiles x 32 blocks: two
+    dict(Nb=1, H=140, W=140, C=1024, G=1024, R=1, S=1, pad=0),  # 1 x 1, 39 tiles x 32 blocks, the last with two
+    dict(Nb=1, H=150, W=141, C=1024, G=32, R=1, S=1, pad=0),   # 1 x 1, 42 tiles x 32 blocks: four
+])
+@pytest.mark.parametrize("b_zp", [False, True])
+def test_blocks(env, cfg, b_zp):  # noqa: F811
+    q, torch, dev, oracle = env
+    cfg = dict(dict(stride=2), **cfg)
+    c = wl.random_conv(17, **cfg)
+    if not b_zp:
+        c.b_zp[:] = 0
+    say(f"{cfg} b_zp {b_zp}")
+    assert_same(run(c, q, torch, dev), want(c, oracle), str(cfg))
