@@ -797,11 +797,11 @@ struct same_plan {
   int ncb = 0, smem = 0;
   long long rounds = 1LL << 40;
 };
-same_plan plan_same(const qg_conv_args& a, int RS, int halo, bool raw) {
+same_plan plan_same(const qg_conv_args& a, int RS, int halo, bool raw, int max_ncb) {
   same_plan pl;
   const bool compact = !raw && compact_ok(a);
   const int npp = 128 + 2 * halo;
-  for (int ncb = 2; ncb >= 1 && pl.ncb == 0; --ncb) {
+  for (int ncb = max_ncb; ncb >= 1 && pl.ncb == 0; --ncb) {
     if (a.C % (ncb * 32) != 0) continue;
     const int smem = (compact ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 +
                      (raw ? (npp * ncb * 2 + 63) / 64 * 1024 + ncb * 32 : (npp + 1) * (ncb * 2 + 1) * 16);
@@ -821,11 +821,16 @@ hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
   // "same" convolution: whole input patch staged in LDS, if it fits
   const int R = RS == 9 ? 3 : 1;
   if (mfma_ok && a.stride == 1 && 2 * a.pad == R - 1 && a.Ho == a.H && a.Wo == a.W) {
-    // 64 channels per workgroup: about 39 KB of LDS at W = 56, so four workgroups share a CU and one's
-    // request burst overlaps the others' arithmetic (128 channels halve the weight traffic but leave two);
-    // 32 where C asks for it or the image is too wide for 64
+    // 64 channels per workgroup only with compact weights and a patch that leaves room for six workgroups on a CU (W up to about
+    // 80): there the weights and pixel positions of two blocks worked out once are worth 3 to 5 % (32 x 56 x 56 x 128 in groups of
+    // 4 11.9 us with 32 channels, 11.3 with 64).  Elsewhere 32: a workgroup waits for half the patch and its chain is half as long
+    // (7 x 7 x 128 4.0 -> 3.6, 2 x 112 x 112 x 256 in groups of 16 10.6 -> 8.5, 32 x 112 x 112 x 64 in groups of 32 29.2 -> 22.9).
+    // Over 294 layers, W 7 .. 112, within 0.1 % of the better one in the mean, 6 % at worst; 64 wherever C allows it was 10 % and
+    // 28 % off.  Wider images keep 64 channels where they fit.
     const int halo = a.pad * a.W + a.pad;
-    const same_plan own = plan_same(a, RS, halo, false), raw = plan_same(a, RS, halo, true);
+    same_plan own = plan_same(a, RS, halo, false, 2), raw = plan_same(a, RS, halo, true, 2);
+    if (a.W <= 112 && own.ncb == 2 && !(compact_ok(a) && 160 * 1024 / own.smem >= 6))
+      own = plan_same(a, RS, halo, false, 1), raw = plan_same(a, RS, halo, true, 1);
     // RAW (3 x 3): where it takes fewer rounds of the grid, the LDS of a wide patch being what bounds the workgroups a CU holds
     // -- measured over 308 layers, W 40 .. 1024: 32 x 83 x 83 x 64 in groups of 8 9.7 -> 8.1 us, 1 x 150 x 400 x 448 in groups of
     // 32 54 -> 35 --, and with more than one round from W = 256 on, where the register path waits for its loads four at a time

@@ -1,5 +1,6 @@
-"""The group convolution with taps from memory (stride 2, or no padding) on one, two and four 32-channel blocks per workgroup: the
-edges of the rule, ragged pixel tiles, with and without a weight zero point, against the CPU oracle's direct convolution."""
+"""32-channel blocks per workgroup of the group convolution: one, two and four with taps from memory (stride 2), one and two with the
+patch in LDS (stride 1).  The edges of the rules, ragged pixel tiles, with and without a weight zero point, against the CPU
+oracle's direct convolution."""
 import pytest
 
 from paper_2101_05615_amd import workloads as wl
@@ -20,6 +21,13 @@ pytestmark = pytest.mark.gpu
     dict(Nb=1, H=100, W=101, C=1024, G=256, R=1, S=1, pad=0),  # 1 x 1, 20 tiles x 32 blocks: two
     dict(Nb=1, H=140, W=140, C=1024, G=1024, R=1, S=1, pad=0),  # 1 x 1, 39 tiles x 32 blocks, the last with two
     dict(Nb=1, H=150, W=141, C=1024, G=32, R=1, S=1, pad=0),   # 1 x 1, 42 tiles x 32 blocks: four
+    # stride 1
+    dict(Nb=3, H=7, W=7, C=128, G=32, stride=1),           # one
+    dict(Nb=11, H=80, W=80, C=128, G=32, stride=1),        # compact weights, room for six on a CU: two
+    dict(Nb=6, H=112, W=112, C=128, G=64, stride=1),       # compact weights, room for five: one
+    dict(Nb=6, H=112, W=113, C=128, G=128, stride=1),      # wider: two
+    dict(Nb=5, H=56, W=56, C=192, G=6, stride=1),          # groups of 32: one
+    dict(Nb=9, H=83, W=83, C=128, G=8, stride=1),          # one, where the patch went straight to LDS with two
 ])
 @pytest.mark.parametrize("b_zp", [False, True])
 def test_blocks(env, cfg, b_zp):  # noqa: F811
