@@ -206,13 +206,15 @@ struct stream_price {
   double wide_fix, wide_wg, byte_lat, byte_wg_k;
 };
 struct price_set {
-  tile_price tile[8];      // the second of QG_KERNEL_TILE128 is the 128 x 64 form (rows at 16 bytes: 2 % below its fit, for near ties)
+  // the second of QG_KERNEL_TILE128 is the 128 x 64 form.  Rows at 16 bytes: it stands 2 % below its fit and the fix of
+  // QG_KERNEL_TILE64K1 0.1 us (64 x 64 x 128 3.2 us on it, 3.5 on the 16-row kernel): near ties, the mean is the same.
+  tile_price tile[8];
   stream_price stream[6];  // rows at 16 bytes: each kernel, and its wide form after it
   int nstream;
 };
 const price_set k_price_16 = {
     {
-        {QG_KERNEL_TILE64K1, 64, 64, 3.685, 0.1962, 0.07176, 0.1228, 0.1758, 0.3658, 2.121, 0.07015, 0.1381, 0.1352, 0.2825, 1, 1, 0},
+        {QG_KERNEL_TILE64K1, 64, 64, 3.585, 0.1962, 0.07176, 0.1228, 0.1758, 0.3658, 2.121, 0.07015, 0.1381, 0.1352, 0.2825, 1, 1, 0},
         {QG_KERNEL_TILE64, 64, 64, 3.951, 0.1109, 0.03765, 0.1061, 0.1983, 0.8019, 1.744, 0.1285, 0.1375, 0.1813, 0.3518, 1, 1, 0},
         {QG_KERNEL_TILE64K4, 64, 64, 4.44, 0.08052, 0.04065, 0.1095, 0.2493, 2.288, 5.487, 0.1631, 0.2359, 0.2057, 0.3153, 1, 1, 0},
         {QG_KERNEL_TILE64X32K8, 64, 32, 4.492, 0.0497, 0.02743, 0.06995, 0.2437, 2.313, 1.046, 0.276, 0.2533, 0.3191, 0.3403, 1, 1, 0},
