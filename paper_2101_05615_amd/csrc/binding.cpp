@@ -214,14 +214,13 @@ struct call_args {
   qg_requant_params p;
   int i[9];
 };
-struct call_object {
+struct call_object {  // base class of the prepared calls in qgemm.py, whose attributes keep alive what the addresses belong to
   PyObject_HEAD
   call_args c;
-  PyObject* keep;  // what the addresses belong to
 };
 
 PyObject* call_launch(PyObject* self, PyObject*) {
-  const call_args c = reinterpret_cast<call_object*>(self)->c;
+  const call_args c = reinterpret_cast<call_object*>(self)->c;  // (its own copy: another thread may change the stream)
   const uint8_t* const in = static_cast<const uint8_t*>(c.in);
   uint8_t* const out = static_cast<uint8_t*>(c.out);
   int rc;
@@ -244,37 +243,43 @@ PyObject* call_launch(PyObject* self, PyObject*) {
   return nullptr;
 }
 
-PyMethodDef call_methods[] = {{"launch", call_launch, METH_NOARGS, "Issues the call on its stream."}, {nullptr, nullptr, 0, nullptr}};
-PyTypeObject call_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
-
-// (kind, what to keep alive, input, weights, output, workspace, stream: addresses, a_zp, bias, scales: addresses, n_scales, c_zp, relu, the call's other ints ...)
-PyObject* prepare(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  if (n < 13) return PyErr_Format(PyExc_TypeError, "prepare: too few arguments");
+// (kind, input, weights, output, workspace: addresses, a_zp, bias, scales: addresses, n_scales, c_zp, relu, the call's other ints ...)
+PyObject* call_set(PyObject* self, PyObject* const* a, Py_ssize_t n) {
+  if (n < 11) return PyErr_Format(PyExc_TypeError, "_set: too few arguments");
   call_args c = {};
   c.kind = (int)PyLong_AsLong(a[0]);
   if (PyErr_Occurred()) return nullptr;
-  if (c.kind < 0 || c.kind >= CALL_KINDS || n != 13 + call_ints[c.kind]) return PyErr_Format(PyExc_TypeError, "prepare: wrong kind or number of arguments");
+  if (c.kind < 0 || c.kind >= CALL_KINDS || n != 11 + call_ints[c.kind]) return PyErr_Format(PyExc_TypeError, "_set: wrong kind or number of arguments");
   auto address = [](PyObject* o) { return o == Py_None ? nullptr : PyLong_AsVoidPtr(o); };
-  c.in = address(a[2]);
-  c.weights = static_cast<const qg_packed_b*>(address(a[3]));
-  c.out = address(a[4]);
-  c.workspace = address(a[5]);
-  c.stream = address(a[6]);
-  c.p.a_zp = (int)PyLong_AsLong(a[7]);
-  c.p.bias = static_cast<const int32_t*>(address(a[8]));
-  c.p.scales = static_cast<const float*>(address(a[9]));
-  c.p.n_scales = (int)PyLong_AsLong(a[10]);
-  c.p.c_zp = (int)PyLong_AsLong(a[11]);
-  c.p.relu = (int)PyLong_AsLong(a[12]);
-  for (int k = 0; k < call_ints[c.kind]; ++k) c.i[k] = (int)PyLong_AsLong(a[13 + k]);
+  c.in = address(a[1]);
+  c.weights = static_cast<const qg_packed_b*>(address(a[2]));
+  c.out = address(a[3]);
+  c.workspace = address(a[4]);
+  c.p.a_zp = (int)PyLong_AsLong(a[5]);
+  c.p.bias = static_cast<const int32_t*>(address(a[6]));
+  c.p.scales = static_cast<const float*>(address(a[7]));
+  c.p.n_scales = (int)PyLong_AsLong(a[8]);
+  c.p.c_zp = (int)PyLong_AsLong(a[9]);
+  c.p.relu = (int)PyLong_AsLong(a[10]);
+  for (int k = 0; k < call_ints[c.kind]; ++k) c.i[k] = (int)PyLong_AsLong(a[11 + k]);
   if (PyErr_Occurred()) return nullptr;
-  call_object* const o = PyObject_New(call_object, &call_type);
-  if (o) {
-    o->c = c;
-    o->keep = Py_NewRef(a[1]);
-  }
-  return reinterpret_cast<PyObject*>(o);
+  reinterpret_cast<call_object*>(self)->c = c;
+  Py_RETURN_NONE;
 }
+
+PyObject* call_set_stream(PyObject* self, PyObject* stream) {
+  void* const s = PyLong_AsVoidPtr(stream);
+  if (PyErr_Occurred()) return nullptr;
+  reinterpret_cast<call_object*>(self)->c.stream = s;
+  Py_RETURN_NONE;
+}
+
+#define QG_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f))
+PyMethodDef call_methods[] = {{"launch", call_launch, METH_NOARGS, "Issues the call on its stream."},
+                              {"_set", QG_FAST(call_set), METH_FASTCALL, nullptr},
+                              {"_set_stream", call_set_stream, METH_O, nullptr},
+                              {nullptr, nullptr, 0, nullptr}};
+PyTypeObject call_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
 // the functions and the exception that this module takes from Python
 PyObject* init(PyObject*, PyObject* args) {
@@ -286,11 +291,9 @@ PyObject* init(PyObject*, PyObject* args) {
   Py_RETURN_NONE;
 }
 
-#define QG_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f))
 PyMethodDef methods[] = {
     {"gemm_u8s8_requant", QG_FAST(gemm_u8s8_requant), METH_FASTCALL, nullptr},
     {"gemm_f32s8", QG_FAST(gemm_f32s8), METH_FASTCALL, nullptr},
-    {"prepare", QG_FAST(prepare), METH_FASTCALL, nullptr},
     {"init", init, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };
@@ -301,13 +304,15 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods};
 PyMODINIT_FUNC PyInit__binding() {
   call_type.tp_name = "_binding.Call";
   call_type.tp_basicsize = sizeof(call_object);
-  call_type.tp_flags = Py_TPFLAGS_DEFAULT;
+  call_type.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_BASETYPE;
   call_type.tp_methods = call_methods;
-  call_type.tp_dealloc = [](PyObject* o) {
-    Py_XDECREF(reinterpret_cast<call_object*>(o)->keep);
-    PyObject_Free(o);
-  };
+  call_type.tp_new = PyType_GenericNew;  // (zeroed: launch() of an object without arguments is refused by the call)
   if (PyType_Ready(&call_type) < 0) return nullptr;
   g_name_fast = PyUnicode_InternFromString("_fast");
-  return g_name_fast ? PyModule_Create(&module) : nullptr;
+  PyObject* const m = g_name_fast ? PyModule_Create(&module) : nullptr;
+  if (m && PyModule_AddObjectRef(m, "Call", reinterpret_cast<PyObject*>(&call_type)) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
 }

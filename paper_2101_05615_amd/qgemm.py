@@ -128,8 +128,7 @@ def _load_binding():
     spec = importlib.util.spec_from_file_location("_binding", path)
     m = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(m)
-    if hasattr(torch._C, "_cuda_getCurrentRawStream"):
-        m.init(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, QGemmError)
+    m.init(getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None), QGemmError)
     return m
 
 
@@ -364,24 +363,21 @@ def gemm_u8s8_requant(A, a_zp, Bp, bias, scales, c_zp, relu, out=None, workspace
     return out
 
 
-class _Prepared:
-    """A call whose arguments are marshalled once, for loops that repeat it; `launch()` issues it on the stream that was
-    current when the object was made (or last rebound)."""
+class _Prepared(_binding.Call):
+    """A call whose arguments are marshalled once, for loops that repeat it; `launch()`, a method of the extension module's
+    class, issues it on the stream that was current when the object was made (or last rebound)."""
 
     def _prepare(self, kind, keep, inp, weights, out, workspace, p, ints):
-        self._keep, self.out = keep, out
-        self._call_args = (kind, keep, inp.data_ptr(), weights.handle.value if weights.handle else None, out.data_ptr(),
-                           workspace.data_ptr() if workspace is not None else None)
-        self._call_rest = (p.a_zp, p.bias, p.scales, p.n_scales, p.c_zp, p.relu) + tuple(ints)
+        self._keep, self.out = keep, out   # (the base class holds addresses only)
+        self._set(kind, inp.data_ptr(), weights.handle.value if weights.handle else None, out.data_ptr(),
+                  workspace.data_ptr() if workspace is not None else None,
+                  p.a_zp, p.bias, p.scales, p.n_scales, p.c_zp, p.relu, *ints)
         self.rebind()
 
-    def launch(self):
-        self._call.launch()
-
     def rebind(self):
-        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph)."""
-        self._call = _binding.prepare(*self._call_args, _stream(), *self._call_rest)
-        self.launch = self._call.launch   # (straight into the module; it keeps the tensors alive by itself)
+        """Later launches go to the stream that is current now (e.g. the capturing stream of a graph), those through a
+        `launch` that was fetched before among them."""
+        self._set_stream(_stream())
         return self
 
 
