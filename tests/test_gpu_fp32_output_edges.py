@@ -1,5 +1,5 @@
 """fp32 output of the tiled kernels, whose MFMA operands change places for it: edges of tiles in both directions, unaligned output
-rows, and nothing written outside the rows.  Reference: the int32 product of the same kernel family through float64."""
+rows, and nothing written outside the rows.  Reference: the product in float64 on the CPU, exact for these operands."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +30,25 @@ def test_fp32_output_edges(kernel, K, M, N, pad):
         want[1:M + 1, :N] = (acc * scales.double()).float()
         torch.cuda.synchronize()
         assert torch.equal(store.cpu(), want), (kernel, M, N, K, pad, b_zp)
+
+
+@pytest.mark.parametrize("kernel", KERNELS)
+@pytest.mark.parametrize("ldc", [(1 << 20) - 1, 1 << 20])
+def test_rows_far_apart(kernel, ldc):
+    """Output rows 4 MiB apart: the widest that 32-bit offsets inside a tile reach, and the first that go by 64-bit addresses."""
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    M, N, K = 133, 70, 96
+    g = torch.Generator().manual_seed(ldc)
+    A = torch.randint(0, 256, (M, K), dtype=torch.uint8, generator=g)
+    B = torch.randint(-128, 128, (K, N), dtype=torch.int8, generator=g)
+    scales = torch.full((N,), 2.0 ** -10)
+    Bp = q.pack_b(B.cuda(), [3])
+    store = torch.full(((M + 1) * ldc,), -7.0, device="cuda")
+    out = store[:M * ldc].view(M, ldc)[:, :N]
+    q.gemm_u8s8_dequant_f32(A.cuda(), 100, Bp, None, scales.cuda(), False, out=out, kernel=kernel)
+    want = (((A.double() - 100) @ (B.double() - 3)) * 2.0 ** -10).float()   # exact, as above
+    torch.cuda.synchronize()
+    assert torch.equal(out.cpu(), want)
+    out.fill_(-7.0)
+    assert bool((store == -7.0).all())   # nothing else was written
