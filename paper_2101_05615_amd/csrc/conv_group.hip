@@ -724,14 +724,23 @@ hipError_t qg_launch_conv_dense_plain(const qg_conv_args& a, hipStream_t s) {
 
 // 32-channel blocks per workgroup of the kernel with taps from memory.  A wave's chain -- nine dependent rounds of loads and
 // NCB MFMAs each, NCB blocks of output pipeline -- grows with NCB, the input rows and pixel positions are worked out C / 32 / NCB
-// times.  At most one workgroup per CU with one block: the chain is all there is (7 x 7 x 128 of one image, stride 2, 4.1 us with
-// one block, 4.8 with two, 6.8 with four; 2592 pixels x 128 4.3, 5.6, 8.8).  Beyond, two while workgroups queue a few deep
-// (12544 pixels x 128 9.4, 7.9, 10.4; 3200 x 1024 15.8, 11.2, 11.8), then four (25088 x 256 24.5, 20.0, 16.3).  Over 294 layers
-// within 0.2 % of the best of the three in the mean, 15 % at worst; four wherever C allows it was 38 % off.
-int mfma_blocks(const qg_conv_args& a) {
+// times.  Workgroups go to the XCDs by their number, pixel tiles first: where the tiles are a multiple of eight, all channel slices
+// of a tile fall to one XCD and share its 128-byte lines (of four: to two).  Otherwise few channels per workgroup fetch a
+// line several times over.  us with one, two, four blocks, stride 2, 3 x 3:
+//   up to one workgroup per CU with one block the chain is all there is (1 x 7 x 7 x 128 4.1, 4.8, 6.8);
+//   up to three where the lines are shared (36750 pixels x 64, 288 tiles, 8.0, 9.6; 36963, 289 tiles, 9.7, 9.5);
+//   otherwise two blocks (12544 x 128 9.4, 7.9, 10.4) until workgroups queue six deep (1 x 1: five), except where four blocks give
+//   every CU one workgroup (3696 x 1024 17.8, 12.7, 11.6), and with shared lines always (18432 x 512 and more: four 1.0 .. 1.2 of two);
+//   then four (25088 x 256 24.5, 20.0, 16.3).
+// Over 3181 layers within 0.2 % of the best of the three in the mean, 19 % at worst; 3 of them more than 5 % behind four wherever C
+// allows it, which was 19 % off in the mean.
+int mfma_blocks(const qg_conv_args& a, int RS) {
   const long long tiles = std::min(((long long)a.Nb * a.Ho * a.Wo + 127) / 128, 2048LL), wgs = tiles * (a.C / 32);
-  if (wgs <= 256 || a.C % 64 != 0) return 1;
-  return wgs <= 5 * 256 || a.C % 128 != 0 ? 2 : 4;
+  if (wgs <= 256 || a.C % 64 != 0 || (tiles % 4 == 0 && wgs <= 3 * 256)) return 1;
+  if (a.C % 128 != 0) return 2;
+  if (tiles % 8 == 0) return 2;
+  if (wgs >= 832 && wgs <= 4 * 256) return 4;
+  return wgs <= (RS == 9 ? 6 : 5) * 256 ? 2 : 4;
 }
 template <int R, int S, int NCB>
 hipError_t launch_mfma(const qg_conv_args& a, hipStream_t s) {
@@ -846,7 +855,7 @@ hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
   // matrix-core kernel with taps fetched from global memory: needs whole 32-channel blocks and 16-byte aligned pixels
   if (mfma_ok && a.C % 32 == 0 && a.Cout == a.C &&
       reinterpret_cast<uintptr_t>(a.in) % 16 == 0 && reinterpret_cast<uintptr_t>(a.out) % 16 == 0) {
-    switch (mfma_blocks(a)) {
+    switch (mfma_blocks(a, RS)) {
       case 4: return RS == 9 ? launch_mfma<3, 3, 4>(a, s) : launch_mfma<1, 1, 4>(a, s);
       case 2: return RS == 9 ? launch_mfma<3, 3, 2>(a, s) : launch_mfma<1, 1, 2>(a, s);
       default: return RS == 9 ? launch_mfma<3, 3, 1>(a, s) : launch_mfma<1, 1, 1>(a, s);

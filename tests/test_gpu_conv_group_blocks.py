@@ -13,13 +13,20 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("cfg", [
     dict(Nb=1, H=7, W=9, C=128, G=32),                     # one block, 20 pixels
     dict(Nb=2, H=129, W=63, C=64, G=64),                   # 4160 pixels, 33 tiles x 2 blocks: one
-    dict(Nb=1, H=255, W=255, C=64, G=8),                   # 16384 pixels, 128 tiles x 2 blocks: the last with one
+    dict(Nb=1, H=255, W=255, C=64, G=8),                   # 16384 pixels, 128 tiles x 2 blocks: one
     dict(Nb=1, H=257, W=255, C=64, G=16),                  # 129 tiles x 2 blocks: the first with two
     dict(Nb=1, H=255, W=257, C=96, G=24),                  # C off 64: one
     dict(Nb=3, H=65, W=65, C=384, G=384),                  # 26 tiles x 12 blocks: two
     dict(Nb=1, H=223, W=221, C=512, G=16),                 # 98 tiles x 16 blocks: four
-    dict(Nb=1, H=100, W=101, C=1024, G=256, R=1, S=1, pad=0),  # 1 x 1, 20 tiles x 32 blocks: two
-    dict(Nb=1, H=140, W=140, C=1024, G=1024, R=1, S=1, pad=0),  # 1 x 1, 39 tiles x 32 blocks, the last with two
+    dict(Nb=1, H=219, W=219, C=512, G=128),                # 95 tiles x 16 blocks: two
+    dict(Nb=1, H=223, W=251, C=512, G=64),                 # 111 tiles x 16 blocks: four
+    dict(Nb=1, H=223, W=253, C=512, G=32),                 # 112 tiles, a multiple of eight: two
+    dict(Nb=1, H=119, W=121, C=896, G=28),                 # 29 tiles x 28 blocks: two
+    dict(Nb=1, H=121, W=121, C=896, G=224),                # 30 tiles x 28 blocks, at most one workgroup per CU with four: four
+    dict(Nb=1, H=191, W=253, C=192, G=48),                 # 96 tiles x 6 blocks, tiles a multiple of four: one
+    dict(Nb=1, H=191, W=257, C=192, G=48),                 # 97 tiles x 6 blocks: two
+    dict(Nb=1, H=100, W=101, C=1024, G=256, R=1, S=1, pad=0),  # 1 x 1, 20 tiles x 32 blocks: one
+    dict(Nb=1, H=140, W=140, C=1024, G=1024, R=1, S=1, pad=0),  # 1 x 1, 39 tiles x 32 blocks: two
     dict(Nb=1, H=150, W=141, C=1024, G=32, R=1, S=1, pad=0),   # 1 x 1, 42 tiles x 32 blocks: four
     # stride 1
     dict(Nb=3, H=7, W=7, C=128, G=32, stride=1),           # one
