@@ -802,24 +802,49 @@ hipError_t launch_same(const qg_conv_args& a, int smem, int halo, bool raw, hipS
 }
 
 // Channel slice (ncb blocks of 32), LDS and rounds of the grid of the stride-1 "same" kernel; ncb = 0: the patch does not fit.
+// A build of the "same" kernel for a layer: LDS bytes (0: it does not fit) and estimated microseconds.
 struct same_plan {
   int ncb = 0, smem = 0;
-  long long rounds = 1LL << 40;
+  bool raw = false;
+  double us = 1e300;
 };
-same_plan plan_same(const qg_conv_args& a, int RS, int halo, bool raw, int max_ncb) {
+// What a build takes with 32 or 64 channels per workgroup, patch through registers (whole fragments or compact weights) or
+// straight to LDS (RAW): pixels of a patch in units of 256, workgroups in units of one per CU.
+//   us = fix + pix * pixels + bzp + wgs * (wg + wg_pix * pixels + wg_bzp) + (rounds - 1) * round * pixels
+// bzp terms: with weight zero points, groups of 4 and more and groups of 1 and 2 (row offsets by more MFMAs); rounds: of as many
+// workgroups as run side by side, six with 32 channels, four with 64, two more with compact weights, and no more than the LDS holds.
+// 64 channels share pixel positions and weights, 32 wait for half the patch and hold twice as many workgroups; RAW waits less
+// where a wide patch is loaded four chunks at a time, and pays a pass over LDS.  Fitted to 3519 layers (5 .. 900 pixels
+// wide, 32 .. 1024 channels, 1 .. 32 images), 4 % off in the mean; the choice over 1173 others 1.002 of the best of the four (64
+// channels where they fit, RAW where it took fewer rounds: 1.06).  us with 32, 64 channels, RAW 32, 64: 8 x 54 x 155 x 64 in
+// groups of 2 6.8, 9.2, 7.3, 7.5; 18 x 20 x 486 x 64 in groups of 16 22.9, 29.0, 16.9, 27.6; 22 x 54 x 54 x 128 in groups of 4
+// 8.7, 7.9, 9.1, 8.6.
+struct same_price {
+  double fix, pix, wg, wg_pix, round, bzp, wg_bzp, bzp_narrow, wg_bzp_narrow;
+};
+const same_price k_same_price[2][3] = {
+    // whole fragments, compact weights, RAW
+    {{3.378, 0.0, 0.377, 0.194, 0.383, 0.194, 0.057, 0.263, 0.181},
+     {3.088, 0.258, 0.461, 0.146, 0.335, 0.289, 0.048, 0.082, 0.176},
+     {3.742, 0.015, 0.582, 0.092, 0.276, 0.188, 0.062, 0.238, 0.154}},
+    {{3.727, 0.29, 0.95, 0.007, 1.498, 0.313, 0.304, 0.527, 0.079},
+     {0.845, 3.285, 0.934, 0.135, 0.303, 1.138, 0.325, 0.466, 0.343},
+     {4.047, 0.161, 1.24, 0.0, 0.575, 0.538, 0.255, 0.466, 0.406}},
+};
+same_plan plan_same(const qg_conv_args& a, int RS, int halo, bool raw, int ncb) {
   same_plan pl;
   const bool compact = !raw && compact_ok(a);
   const int npp = 128 + 2 * halo;
-  for (int ncb = max_ncb; ncb >= 1 && pl.ncb == 0; --ncb) {
-    if (a.C % (ncb * 32) != 0) continue;
-    const int smem = (compact ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 +
-                     (raw ? (npp * ncb * 2 + 63) / 64 * 1024 + ncb * 32 : (npp + 1) * (ncb * 2 + 1) * 16);
-    if (smem > 160 * 1024) continue;
-    const long long wgs = (long long)((a.Nb * a.H * a.W + 127) / 128) * (a.C / (ncb * 32));
-    const int per_cu = std::min(160 * 1024 / smem, compact && !a.has_bzp ? 7 : 4);  // (more side by side changed nothing)
-    pl.ncb = ncb, pl.smem = smem;
-    pl.rounds = (wgs + 256LL * per_cu - 1) / (256LL * per_cu);
-  }
+  if (a.C % (ncb * 32) != 0) return pl;
+  const int smem = (compact ? ncb * 32 * RS * 4 : ncb * RS * QG_FRAG_BYTES) + ncb * 32 * 12 +
+                   (raw ? (npp * ncb * 2 + 63) / 64 * 1024 + ncb * 32 : (npp + 1) * (ncb * 2 + 1) * 16);
+  if (smem > 160 * 1024) return pl;
+  pl.ncb = ncb, pl.smem = smem, pl.raw = raw;
+  const same_price& p = k_same_price[ncb - 1][raw ? 2 : compact ? 1 : 0];
+  const double wgs = (double)((a.Nb * a.H * a.W + 127) / 128) * (a.C / (ncb * 32)) / 256.0, pixels = npp / 256.0;
+  const double side = std::min(160 * 1024 / smem, (ncb == 1 ? 6 : 4) + (compact ? 2 : 0));
+  pl.us = p.fix + p.pix * pixels + wgs * (p.wg + p.wg_pix * pixels) + (ceil(wgs / side) - 1.0) * p.round * pixels;
+  if (a.has_bzp) pl.us += a.lcg < 2 ? p.bzp_narrow + wgs * p.wg_bzp_narrow : p.bzp + wgs * p.wg_bzp;
   return pl;
 }
 
@@ -830,27 +855,17 @@ hipError_t qg_launch_conv_group(const qg_conv_args& a, int RS, hipStream_t s) {
   // "same" convolution: whole input patch staged in LDS, if it fits
   const int R = RS == 9 ? 3 : 1;
   if (mfma_ok && a.stride == 1 && 2 * a.pad == R - 1 && a.Ho == a.H && a.Wo == a.W) {
-    // 64 channels per workgroup only with compact weights and a patch that leaves room for six workgroups on a CU (W up to about
-    // 80): there the weights and pixel positions of two blocks worked out once are worth 3 to 5 % (32 x 56 x 56 x 128 in groups of
-    // 4 11.9 us with 32 channels, 11.3 with 64).  Elsewhere 32: a workgroup waits for half the patch and its chain is half as long
-    // (7 x 7 x 128 4.0 -> 3.6, 2 x 112 x 112 x 256 in groups of 16 10.6 -> 8.5, 32 x 112 x 112 x 64 in groups of 32 29.2 -> 22.9).
-    // Over 294 layers, W 7 .. 112, within 0.1 % of the better one in the mean, 6 % at worst; 64 wherever C allows it was 10 % and
-    // 28 % off.  Wider images keep 64 channels where they fit.
     const int halo = a.pad * a.W + a.pad;
-    same_plan own = plan_same(a, RS, halo, false, 2), raw = plan_same(a, RS, halo, true, 2);
-    if (a.W <= 112 && own.ncb == 2 && !(compact_ok(a) && 160 * 1024 / own.smem >= 6))
-      own = plan_same(a, RS, halo, false, 1), raw = plan_same(a, RS, halo, true, 1);
-    // RAW (3 x 3): where it takes fewer rounds of the grid, the LDS of a wide patch being what bounds the workgroups a CU holds
-    // -- measured over 308 layers, W 40 .. 1024: 32 x 83 x 83 x 64 in groups of 8 9.7 -> 8.1 us, 1 x 150 x 400 x 448 in groups of
-    // 32 54 -> 35 --, and with more than one round from W = 256 on, where the register path waits for its loads four at a time
-    // (117 x 512 x 448 53 -> 47).  Elsewhere the register path is ahead by 4 to 15 % (32 x 56 x 56 x 128 in groups of 4 10.9
-    // against 9.3).  Within 1 % of the better one in the mean, 6 % at worst.
-    if (RS == 9 && raw.ncb > 0 && (raw.rounds < own.rounds || (own.rounds > 1 && a.W >= 256)))
-      return raw.ncb == 2 ? launch_same<3, 3, 2>(a, raw.smem, halo, true, s) : launch_same<3, 3, 1>(a, raw.smem, halo, true, s);
-    if (own.ncb == 2)
-      return RS == 9 ? launch_same<3, 3, 2>(a, own.smem, halo, false, s) : launch_same<1, 1, 2>(a, own.smem, halo, false, s);
-    if (own.ncb == 1)
-      return RS == 9 ? launch_same<3, 3, 1>(a, own.smem, halo, false, s) : launch_same<1, 1, 1>(a, own.smem, halo, false, s);
+    same_plan best;
+    // 1 x 1: 32 channels (64 were 5 to 15 % slower over 1100 layers, but for a zero point and groups of 1 or 2 on more than five
+    // workgroups per CU, up to 5 % faster there), and no halo that RAW would help with
+    for (int form = 0; form < (RS == 9 ? 4 : 1); ++form) {
+      const same_plan pl = plan_same(a, RS, halo, form >= 2, 1 + (form & 1));
+      if (pl.us < best.us) best = pl;
+    }
+    if (best.ncb == 2) return launch_same<3, 3, 2>(a, best.smem, halo, best.raw, s);
+    if (best.ncb == 1)
+      return RS == 9 ? launch_same<3, 3, 1>(a, best.smem, halo, best.raw, s) : launch_same<1, 1, 1>(a, best.smem, halo, false, s);
   }
   // matrix-core kernel with taps fetched from global memory: needs whole 32-channel blocks and 16-byte aligned pixels
   if (mfma_ok && a.C % 32 == 0 && a.Cout == a.C &&

@@ -30,11 +30,15 @@ pytestmark = pytest.mark.gpu
     dict(Nb=1, H=150, W=141, C=1024, G=32, R=1, S=1, pad=0),   # 1 x 1, 42 tiles x 32 blocks: four
     # stride 1
     dict(Nb=3, H=7, W=7, C=128, G=32, stride=1),           # one
-    dict(Nb=11, H=80, W=80, C=128, G=32, stride=1),        # compact weights, room for six on a CU: two
-    dict(Nb=6, H=112, W=112, C=128, G=64, stride=1),       # compact weights, room for five: one
-    dict(Nb=6, H=112, W=113, C=128, G=128, stride=1),      # wider: two
+    dict(Nb=11, H=80, W=80, C=128, G=32, stride=1),        # compact weights: one (two next to it)
+    dict(Nb=6, H=112, W=112, C=128, G=64, stride=1),       # compact weights: one
+    dict(Nb=6, H=112, W=113, C=128, G=128, stride=1),      # the same
     dict(Nb=5, H=56, W=56, C=192, G=6, stride=1),          # groups of 32: one
-    dict(Nb=9, H=83, W=83, C=128, G=8, stride=1),          # one, where the patch went straight to LDS with two
+    dict(Nb=9, H=83, W=83, C=128, G=8, stride=1),          # one
+    dict(Nb=32, H=56, W=56, C=128, G=32, stride=1),        # compact weights, no zero point: two; with one: one
+    dict(Nb=22, H=54, W=54, C=128, G=32, stride=1),        # whole fragments, no zero point: two; with one: one
+    dict(Nb=2, H=9, W=746, C=64, G=32, stride=1),          # wide: one, where the patch of two fits as well
+    dict(Nb=1, H=40, W=400, C=192, G=24, stride=1),        # patch straight to LDS: two, with a zero point one
 ])
 @pytest.mark.parametrize("b_zp", [False, True])
 def test_blocks(env, cfg, b_zp):  # noqa: F811
