@@ -188,9 +188,9 @@ int qg_gemm_u8s8_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* 
  *                   workgroups per CU; many tiles and a short K)
  *   TILE64X32K8     64 x 32 with K split over eight sets of two waves (1024 threads;
  *                   at most one workgroup per CU and a long K: M up to 128 with N = K = 4096)
- * QG_KERNEL_AUTO picks by (M, N, K): first the rules installed with
- * qg_dispatch_set_rules (an offline autotune writes them), then a built-in
- * rule of thumb derived from the same measurements. */
+ * QG_KERNEL_AUTO picks by (M, N, K) from the rules installed with qg_dispatch_set_rules
+ * (an offline autotune writes them), then by built-in prices of the kernels for (M, N, K),
+ * the alignment of the rows of A and C and the kind of result. */
 #define QG_KERNEL_AUTO 0
 #define QG_KERNEL_SKINNY16 1
 #define QG_KERNEL_SKINNY32 2
@@ -205,7 +205,8 @@ int qg_gemm_u8s8_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* 
 #define QG_KERNEL_LAST 10
 /* Dense convolution only (qg_conv_dense_u8s8_requant): the kernels that keep the input patch of a pixel tile in LDS;
  * workgroup = 64 pixels x 128 channels, 128 x 64, 256 x 64 (eight waves), 256 x 128 (eight waves), 512 x 128 (eight
- * waves of 128 x 64: the form for many pixels and at least 96 output channels). */
+ * waves of 128 x 64: the form for many pixels and at least 96 output channels).  The first runs tiles of 64 x 64 or
+ * 64 x 128 with four or two wave sets that split K where there is at most one such tile per CU and K is long. */
 #define QG_KERNEL_PATCH64X128 11
 #define QG_KERNEL_PATCH128X64 12
 #define QG_KERNEL_PATCH256X64 13
@@ -216,10 +217,13 @@ int qg_gemm_u8s8_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* 
 /* Name of a kernel id ("skinny16", "tile128x256", "patch128x64", ...; "auto" for 0), NULL if invalid. */
 const char* qg_kernel_name(int kernel);
 
-/* The id QG_KERNEL_AUTO resolves to for this shape (never QG_KERNEL_AUTO) when the rows of A start at multiples
- * of 4 bytes and no K split is asked for; where that is the 128 x 64 form of QG_KERNEL_TILE128, other rows,
- * calls with ksplit > 1 and fp32 activations without a workspace run the best of the other kernels.
- * QG_EINVAL (negative) if a size is not positive. */
+/* The id (never QG_KERNEL_AUTO) that QG_KERNEL_AUTO resolves to for a dense product of this shape in the layout the
+ * kernels like best: N a multiple of 16 and K of 64 (others are answered as the next such N and K), every row of A
+ * and of C at a multiple of 16 bytes, uint8 results, no K split and no workspace for one.  The choice of a call also
+ * looks at what that leaves out, so another call may run another kernel: rows of A at multiples of 4 bytes or at any
+ * address, rows of C off 16 bytes, 4-byte results, K off 64 or 16, a workspace that qg_gemm_workspace_bytes asked for
+ * (the kernel that splits), ksplit > 1, outlier-split weights, fp32 activations without a workspace.
+ * A rule of the table below comes first.  QG_EINVAL (negative) if a size is not positive. */
 int qg_kernel_select(int M, int N, int K);
 
 /* One line of the dispatch table: shapes with m_lo <= M <= m_hi, n_lo <= N <= n_hi

@@ -214,13 +214,15 @@ def tune(q, torch, shapes, kernels=None, log=None, cold=False):
     kernels = kernels or [names[k] for k in range(1, q.KERNEL_LAST + 1)]
     rows = []
     for (M, N, K) in shapes:
-        t = time_cold_kernels(q, torch, M, N, K, kernels)[0] if cold else time_shape(q, torch, M, N, K, kernels)
+        # (the automatic choice is timed as a call of its own: which kernel it runs depends on the call's alignment too)
+        ask = list(kernels) + ["auto"]
+        t = time_cold_kernels(q, torch, M, N, K, ask)[0] if cold else time_shape(q, torch, M, N, K, ask)
+        auto = t.pop("auto")
         best = min(t, key=t.get)
-        auto = names[q.kernel_select(M, N, K)]
-        rows.append({"M": M, "N": N, "K": K, "best": best, "auto": auto, "us": t})
+        rows.append({"M": M, "N": N, "K": K, "best": best, "auto_us": auto, "us": t})
         if log:
             line = " ".join(f"{k}={v:9.1f}" for k, v in t.items())
-            log(f"{M:6d} {N:6d} {K:6d}  best {best:12s} auto {auto:12s} loss {t[auto] / t[best]:5.2f}x  {line}")
+            log(f"{M:6d} {N:6d} {K:6d}  best {best:12s} auto {auto:9.1f} loss {auto / t[best]:5.2f}x  {line}")
     return rows
 
 
@@ -230,14 +232,14 @@ def summary(rows):
     wins = {}
     for r in rows:
         wins[r["best"]] = wins.get(r["best"], 0) + 1
-    loss = [r["us"][r["auto"]] / r["us"][r["best"]] for r in rows]
+    loss = [r["auto_us"] / r["us"][r["best"]] for r in rows]
     worst = sorted(zip(loss, rows), key=lambda t: -t[0])[:5]
     out = [f"shapes: {len(rows)}",
            "fastest kernel, number of shapes: " + ", ".join(f"{k} {v}" for k, v in sorted(wins.items())),
            f"automatic choice vs measured best: geometric mean {math.exp(sum(map(math.log, loss)) / len(loss)):.4f}x, "
            f"within 5 % on {sum(l <= 1.05 for l in loss)} shapes, worst {max(loss):.2f}x"]
     for l, r in worst:
-        out.append(f"  worst: {r['M']}x{r['N']}x{r['K']} auto {r['auto']} {r['us'][r['auto']]:.1f} us, "
+        out.append(f"  worst: {r['M']}x{r['N']}x{r['K']} auto {r['auto_us']:.1f} us, "
                    f"best {r['best']} {r['us'][r['best']]:.1f} us ({l:.2f}x)")
     return "\n".join(out)
 

@@ -555,7 +555,7 @@ int qg_kernel_select(int M, int N, int K) {
   if (M <= 0 || N <= 0 || K <= 0) return QG_EINVAL;
   const int rule = rule_kernel(M, N, K);
   if (rule != QG_KERNEL_AUTO && kernel_ok(rule, M)) return rule;
-  return price_select(M, N, K, {16, false, N % 16 != 0});
+  return price_select(M, ceil_div(N, 16) * 16, ceil_div(K, 64) * 64, {16, false, false});
 }
 
 int qg_dispatch_set_rules(const qg_dispatch_rule* rules_host, int n) {

@@ -266,6 +266,7 @@ def kernel_id(kernel):
 
 
 def kernel_select(M, N, K):
+    """The kernel id of the automatic choice for the shape in the layout the kernels like best (qgemm.h: qg_kernel_select)."""
     k = lib.qg_kernel_select(M, N, K)
     if k < 0:
         raise QGemmError(k, "qg_kernel_select")

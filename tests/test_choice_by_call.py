@@ -36,6 +36,29 @@ def test_no_call_needs_more_than_was_announced():
     assert split > 50
 
 
+def test_kernel_select_answers_for_whole_steps():
+    from paper_2101_05615_amd import qgemm as q
+    for M in MS:
+        for N in NS:
+            for K in KS[:-1]:
+                assert q.kernel_select(M, N, K) == q.kernel_select(M, -(-N // 16) * 16, -(-K // 64) * 64), (M, N, K)
+
+
+def test_autotune_times_the_choice_of_the_call(monkeypatch):
+    """The reported loss is that of an "auto" call, not of the kernel that kernel_select names."""
+    from paper_2101_05615_amd import autotune, qgemm as q
+    asked = []
+
+    def timed(q_, torch_, M, N, K, kernels, *a):
+        asked.append(list(kernels))
+        return {k: 9.0 if k == "auto" else 10.0 + i if k != "tile64" else 6.0 for i, k in enumerate(kernels)}
+
+    monkeypatch.setattr(autotune, "time_shape", timed)
+    rows = autotune.tune(q, None, [(4, 16, 17)], log=lambda s: None)
+    assert "auto" in asked[0] and rows[0]["best"] == "tile64" and rows[0]["auto_us"] == 9.0 and "auto" not in rows[0]["us"]
+    assert "1.5000x" in autotune.summary(rows) and autotune.table_from_rows(rows) == [[4, 4, 16, 16, 17, 17, "tile64"]]
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("a_off,lda_pad", [(0, 0), (4, 4), (1, 3)])
 @pytest.mark.parametrize("M,N,K", [(2, 6683, 2336), (6, 4996, 7488), (7, 6304, 2816), (49, 4938, 2048), (16, 42, 17), (63, 103, 255),
