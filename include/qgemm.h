@@ -444,8 +444,8 @@ int qg_conv_groupwise_u8s8_requant(const uint8_t* in_nhwc, int Nb, int H, int W,
  *            LDS (1 x 1 filters, weights too large for the other, layers where it is
  *            estimated to be faster); any extents
  *   out_nhwc dev uint8 [Nb][Ho][Wo][Cout], Ho = (H + 2*pad - R)/stride + 1
- *   kernel   QG_KERNEL_AUTO (chosen from the extents by a cost model fitted to 3 x 3 and
- *            5 x 5 layers, the patch kernels below included), or QG_KERNEL_TILE64 / TILE64K4 / TILE64X32K8 / TILE64K1 /
+ *   kernel   QG_KERNEL_AUTO (chosen from the extents by prices fitted to layers of 1 x 1 to
+ *            7 x 7, the patch kernels below included), or QG_KERNEL_TILE64 / TILE64K4 / TILE64X32K8 / TILE64K1 /
  *            TILE128 / TILE128X256; every choice gives the same bytes.  The 128-row tiles run
  *            their hand-scheduled loop when Cin % 64 == 0, R*S <= 32 and K >= 256.  With
  *            Cin % 64 == 0 and R*S <= 32 the streaming kernels QG_KERNEL_SKINNY16 / 32 / 64

@@ -83,39 +83,6 @@ const tile_cost k_tile_cost[] = {
     {QG_KERNEL_TILE64K1, 64, 64, 2.714, 0.2482, 0.1361, 0.1909, 2.35e6},
     {QG_KERNEL_TILE64X32K8, 64, 32, 3.817, 0.05427, 0.0602, 2.585},
 };
-// The dense convolution runs the same tile loops with the im2col addressing folded into the requests; the same
-// formula, constants fitted to 272 layers (3 x 3 and 5 x 5, stride 1 and 2, 1 .. 32 images, 32 .. 512 channels; graph-replay
-// times), one set for whole 64-channel slices and one for the other channel counts, whose requests keep a tap per
-// lane.  Over 120 other layers the choice among all kernels is 1.009 of the measured best in the geometric mean, 6 by more
-// than 5 %, worst 1.18x; with the constants of before, fitted to older kernels, 1.094, 54 and 1.90x.
-const tile_cost k_conv_cost[] = {
-    {QG_KERNEL_TILE64K1, 64, 64, 3.33, 0.286, 0.11, 0.516},
-    {QG_KERNEL_TILE64, 64, 64, 4.07, 0.16, 0.115, 1.0},
-    {QG_KERNEL_TILE64K4, 64, 64, 5.14, 0.116, 0.115, 3.04},
-    {QG_KERNEL_TILE64X32K8, 64, 32, 5.57, 0.0815, 0.0794, 3.47},
-    {QG_KERNEL_TILE128, 128, 128, 5.33, 0.28, 0.239, 1.86},
-    {QG_KERNEL_TILE128X256, 128, 256, 9.17, 0.297, 0.371, 3.21},
-};
-const tile_cost k_conv_chunk_cost[] = {
-    {QG_KERNEL_TILE64K1, 64, 64, 3.68, 0.361, 0.114, 0.832},
-    {QG_KERNEL_TILE64, 64, 64, 4.33, 0.217, 0.145, 1.22},
-    {QG_KERNEL_TILE64K4, 64, 64, 5.28, 0.158, 0.168, 3.0},
-    {QG_KERNEL_TILE64X32K8, 64, 32, 6.15, 0.145, 0.0682, 4.42},
-    {QG_KERNEL_TILE128, 128, 128, 6.01, 0.546, 0.305, 2.86},
-    {QG_KERNEL_TILE128X256, 128, 256, 9.17, 0.88, 0.353, 4.01},
-};
-// "Same" convolutions (stride 1, output as large as the input) with Cin % 32 == 0 also have the kernels that keep the
-// input patch of a pixel tile in LDS; same formula, fitted to the layers of that kind among the 272.
-const tile_cost k_conv_patch_cost[] = {
-    {QG_KERNEL_PATCH64X128, 64, 128, 4.33, 0.147, 0.14, 0.86},
-    {QG_KERNEL_PATCH128X64, 128, 64, 4.51, 0.133, 0.114, 1.0},
-    {QG_KERNEL_PATCH256X64, 256, 64, 4.66, 0.174, 0.235, 1.15},
-    {QG_KERNEL_PATCH256, 256, 128, 5.24, 0.288, 0.395, 1.32},
-    {QG_KERNEL_PATCH512, 512, 128, 6.63, 0.581, 0.973, 3.72},
-};
-// ... and the builds of QG_KERNEL_PATCH64X128 for at most one tile per CU, with four and two wave sets
-const tile_cost k_conv_few4_cost = {QG_KERNEL_PATCH64X128, 64, 64, 5.45, 0.0453, 0.0, 0.0};
-const tile_cost k_conv_few2_cost = {QG_KERNEL_PATCH64X128, 64, 128, 5.7, 0.0924, 0.0, 0.0};
 const stream_cost k_stream_cost[] = {
     {QG_KERNEL_SKINNY16, 16, 3.826, 3.664e-06, 5.429, 0.002625},
     {QG_KERNEL_SKINNY32, 32, 3.918, 2.404e-05, 8.639, 0.0005841},
@@ -177,129 +144,143 @@ int builtin_select(int M, int N, int K) {
   return best;
 }
 
-// All other calls: the same idea with the terms that decide close races -- how full the chip is while at most one workgroup
-// runs on a CU, rows of A and C off 16 bytes, 4-byte outputs, the 128 x 64 form of the 128-row kernel, the streaming kernels'
-// wide form -- in two sets of prices, since rows of A that are not 16-byte aligned slow every kernel down,
-// but by very different factors (the streaming kernels by up to 1.8, 64 x 64 tiles by 1.1).
-//   tile, at most 256 workgroups   us = fix + kt * (lat + crowd * wgs / 256)             kt = ceil(K / 64)
+// All other calls: the same idea with the terms that decide close races, fitted anew.
+//   tile, at most 256 workgroups   us = fix + kt * (lat * (1 + tall * M / (M + N)) + crowd * wgs / 256)     kt = ceil(K / 64)
 //   beyond                         the larger of that and 2.5 + rounds * epi + kt * thr * (rounds - fill * (rounds - wgs / 256)),
 //                                  rounds = ceil(wgs / 256): a round that does not fill the chip runs faster
-//   streaming                      us = fix + K / 1024 * lat + n * batch; more than 256 workgroups: the larger of that times
-//                                  (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
-// Fitted to graph-replay times of all kernels on 7724 shapes (M 1 .. 65536, N 8 .. 8192, K 16 .. 8192, a quarter of them with
-// K a multiple of 2048).  Against the measured best kernel of other shapes the choice is 1.010 of it in the geometric mean
-// with rows at 16 bytes (1316 shapes, worst 1.52) and 1.006 with others (995, worst 1.24); the prices above, with one price of
-// the 128 x 64 form added, 1.032 (worst 2.18) and 1.049 (1.79).  Largest gains: long K over many columns
-// with few rows (9 x 7996 x 5824 16.4 -> 11.4 us) and tall shapes (20447 x 576 x 752 26.3 -> 21.5).
+//   streaming                      us = fix + K / 1024 * (lat + crowd * wgs / 256) + blocks * block + n * batch; more than 256
+//                                  workgroups: the larger of that times (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
+// and far more per megabyte of A beyond four, for both.  Fitted to graph-replay times of all kernels on 46417 shapes (M 1 .. 65536,
+// N 8 .. 8192, K 16 .. 16384, rows of A and C at all alignments, the three kinds of results, with and without zero points), three
+// sets of buffers in turn: first the times, then the loss of the choice.  Over 7600 other shapes the choice is 1.0035 of the best
+// kernel in the geometric mean, 1.32 at worst, 186 of them by more than 5 %.  The prices above: 1.050 and 2.8; a fit to the ordinary
+// shapes alone: 1.020 and 2.5 (tall shapes of few columns and a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
 struct tile_price {
   int kernel, bm, bn;
-  double fix, lat, crowd, thr, fill, epi, out;  // out: megabytes of output per microsecond
-  double rag_fix, rag_epi;                // u8 output, rows of C off 16 bytes
-  double wide_fix, wide_epi;              // 4-byte output
-  double byte_lat, byte_thr;              // rows of A off 4 bytes: factors on lat, on thr
-  double tall;                            // M >= N: so much more; half of it from M >= 3/4 N (fewer workgroups share a row of A)
+  double fix, lat, crowd, thr, fill, epi, out;         // out: megabytes of output per microsecond
+  double f32_fix, f32_epi, rag_fix, rag_epi;           // fp32 results; u8 results whose rows start off 16 bytes
+  double tail_fix, tail_epi;                           // K off 16: the bytes past it are masked one by one
+  double fix4, fix1, lat4, lat1, thr4, thr1;           // rows of A at multiples of 4 bytes, at any: additions and factors
+  double i32_fix, i32_epi, tall, far;                  // int32 results; fewer workgroups share a row of A; megabytes of A beyond 4
+  double left_fix, left_epi;                           // K off 64: the last tile is staged through registers
+  double bzp_fix, bzp_lat, bzp_thr;                    // weight zero points: the row sums; additions to lat and thr as factors
 };
 struct stream_price {
   int kernel, rows;
-  double fix, lat, batch, second, wg, wg_k;  // lat: per 1024 of K; batch: per batch of requests a wave makes after its first
-  double a_rate, a_far;                   // megabytes of A per us: one workgroup row's; all, in tens, once A is beyond the L2s
-  double wide_fix, wide_wg, byte_lat, byte_wg_k;
+  bool wide;                                           // the form of few fat waves (K a multiple of 2048, more than 128 super-blocks)
+  double fix, lat, batch, second, wg, wg_k;            // lat: per 1024 of K; batch: per batch of requests a wave makes after its first
+  double a_far;                                        // tens of megabytes of A per us, fetched once per column block from beyond the L2s
+  double f32_fix, f32_wg, tail_fix;
+  double fix4, fix1, lat4, lat1, wg_k4, wg_k1;
+  double straight;                                     // K whole batches of all waves: so much less
+  double i32_fix, i32_wg, far;
+  double bzp_fix, bzp_lat;
+  double crowd, block;                                 // per 1024 of K on a full chip; per k block of a wave
 };
-struct price_set {
-  // the second of QG_KERNEL_TILE128 is the 128 x 64 form.  Rows at 16 bytes: it stands 2 % below its fit and the fix of
-  // QG_KERNEL_TILE64K1 0.1 us (64 x 64 x 128 3.2 us on it, 3.5 on the 16-row kernel): near ties, the mean is the same.
-  tile_price tile[8];
-  stream_price stream[6];  // rows at 16 bytes: each kernel, and its wide form after it
-  int nstream;
+// The second of QG_KERNEL_TILE128 is the 128 x 64 form, which runs on at most one workgroup per CU (its terms beyond are zero), as the
+// wide forms only run on rows at 16 bytes.
+const tile_price k_tile_price[] = {
+    {QG_KERNEL_TILE64K1, 64, 64, 2.412, 0.2859, 0.02878, 0.1101, 0.3366, 0.2838, 5.877, 0.000065, 0.07622, 0.1249,
+     0.0928, 0.445, 0.006527, 0.1136, 0.2098, 0.9715, 0.8361, 1.142, 1.331, 1.51, 3.041, 0.0001168, 0.08669, 0.2804,
+     0.09552, 0.1591, 0.1329, 0.06869},
+    {QG_KERNEL_TILE64, 64, 64, 3.198, 0.116, 0.04054, 0.1004, 0.2102, 0.6698, 4.196, 0, 0.1119, 0.1202, 0.1159, 0.4147,
+     0.09634, 0.06138, 0.07334, 0.9586, 1.078, 1.09, 1.32, 1.56, 2.811, 0, 0.06911, 0.338, 0.1948, 0.1698, 0.08709,
+     0.06169},
+    {QG_KERNEL_TILE64K4, 64, 64, 3.974, 0.08286, 0.02518, 0.1063, 0.2371, 1.926, 3, 0.008089, 0.1839, 0.08701, 0.1884,
+     0.4139, 0.03725, 0.0009907, 0.1089, 1.05, 1.405, 1.064, 1.327, 1.52, 3.715, 0.03518, 0.07705, 0.342, 0.5083, 0.1992,
+     0.08803, 0.131},
+    {QG_KERNEL_TILE64X32K8, 64, 32, 3.918, 0.05038, 0.01538, 0.06413, 0.385, 2.255, 3, 0.1624, 0.08867, 0.07876, 0.3568,
+     0.4532, 0.2924, 0.05769, 0.2216, 1.019, 1.88, 1.334, 1.536, 1.14, 2.82, 0.007775, 0.07581, 0.5533, 0.3128, 0.2233,
+     0.07749, 0.1108},
+    {QG_KERNEL_TILE128, 128, 128, 4.674, 0.1251, 0.147, 0.284, 0.2988, 1.213, 4.878, 0.0001634, 0.5468, 0.3874, 0.3102,
+     0.2061, 0.05551, 0.007901, 0.0001859, 1.263, 1.46, 1.097, 1.256, 9.815, 11.79, 0.1426, 0.05725, 0.694, 0.327,
+     0.007568, 0.05964, 0.04459},
+    {QG_KERNEL_TILE128, 128, 64, 5.426, 0.0962, 0.03756, 0, 0, 0, 3, 0.4782, 0, 0.2711, 0, 0.467, 0, 0.2839, 1.366,
+     1.043, 1.36, 0, 0, 6.138, 0, 0.1545, 0.06416, 0.8221, 0, 0.01208, 0.05971, 0.01832},
+    {QG_KERNEL_TILE128X256, 128, 256, 7.296, 0.1909, 0.2372, 0.4356, 0.2471, 2.958, 4.972, 0.0002597, 0.2069, 0.4143,
+     0.5134, 0.7246, 0.1053, 0.3389, 0.3716, 1.145, 1.451, 1.076, 1.146, 21.77, 23.09, 0.001574, 0.05695, 0.2195, 0.488,
+     0.1331, 0.1019, 0.01175},
+    {QG_KERNEL_TILE256, 256, 256, 16.52, 0.2333, 0.5554, 0.7709, 0.4578, 12.36, 3.181, 0.0001982, 0.03314, 0.02852,
+     0.2106, 1.116, 0.8108, 0.3416, 0.0009741, 1.083, 2.04, 1.028, 1.267, 45.59, 52.39, 0.003552, 0.000098, 0.008314,
+     0.9841, 0.01655, 0.04981, 0.03198},
 };
-const price_set k_price_16 = {
-    {
-        {QG_KERNEL_TILE64K1, 64, 64, 3.585, 0.1962, 0.07176, 0.1228, 0.1758, 0.3658, 2.121, 0.07015, 0.1381, 0.1352, 0.2825, 1, 1, 0},
-        {QG_KERNEL_TILE64, 64, 64, 3.951, 0.1109, 0.03765, 0.1061, 0.1983, 0.8019, 1.744, 0.1285, 0.1375, 0.1813, 0.3518, 1, 1, 0},
-        {QG_KERNEL_TILE64K4, 64, 64, 4.44, 0.08052, 0.04065, 0.1095, 0.2493, 2.288, 5.487, 0.1631, 0.2359, 0.2057, 0.3153, 1, 1, 0},
-        {QG_KERNEL_TILE64X32K8, 64, 32, 4.492, 0.0497, 0.02743, 0.06995, 0.2437, 2.313, 1.046, 0.276, 0.2533, 0.3191, 0.3403, 1, 1, 0},
-        {QG_KERNEL_TILE128, 128, 128, 5.443, 0.1437, 0.147, 0.2762, 0.4156, 1.703, 10.51, 0, 0.4648, 1.467, 1.053, 1, 1, 0},
-        {QG_KERNEL_TILE128, 128, 64, 5.136, 0.09021, 0.06707, 0.1449, 0.2737, 0.007244, 0.9298, 0.4242, 0.1952, 0.4441, 0.04453, 1, 1, 0.17},
-        {QG_KERNEL_TILE128X256, 128, 256, 7.448, 0.2583, 0.2161, 0.4479, 0.4333, 3.381, 2.385, 0, 0.6444, 2.352, 0.7592, 1, 1, 0},
-        {QG_KERNEL_TILE256, 256, 256, 14.88, 0.3512, 0.4636, 0.8095, 0.4857, 10.36, 2.432, 0.6005, 1.198, 3.492, 0.4228, 1, 1, 0},
-    },
-    {
-        {QG_KERNEL_SKINNY16, 16, 3.998, 0.2013, 1.204, 0.5315, 6.898, 0.002001, 0.7701, 7.914, 0.1569, 0, 1, 1},
-        {QG_KERNEL_SKINNY16, 16, 3.09, 0.861, 0.2585, 0.3154, 0.7925, 0.003124, 0.3034, 1.351, 0, 0, 1, 1},
-        {QG_KERNEL_SKINNY32, 32, 4.373, 0.4228, 0.8754, 0.6385, 9.142, 0.002984, 0.5606, 4.705, 0.2843, 0.2869, 1, 1},
-        {QG_KERNEL_SKINNY32, 32, 3.453, 1.147, 0.09724, 0.4894, 4.349, 0.005273, 0.2899, 1.582, 0.1091, 0, 1, 1},
-        {QG_KERNEL_SKINNY64, 64, 4.742, 0.2631, 1.478, 0.7853, 10.34, 0.004393, 0.3371, 2.045, 0.3073, 1.718, 1, 1},
-        {QG_KERNEL_SKINNY64, 64, 4.392, 1.397, 0.02116, 0.7001, 10.07, 0.005733, 0.4112, 2.827, 0.1708, 0.5981, 1, 1},
-    },
-    6};
-const price_set k_price_off = {
-    {
-        {QG_KERNEL_TILE64K1, 64, 64, 3.997, 0.2076, 0.06951, 0.1385, 0.01215, 0.3748, 1.545, 0.05743, 0.191, 0.1352, 0.2825, 1.069, 1.09, 0},
-        {QG_KERNEL_TILE64, 64, 64, 4.407, 0.1238, 0.02299, 0.1155, 0, 0.831, 3.026, 0.09853, 0.1816, 0.1813, 0.3518, 1.173, 1.189, 0},
-        {QG_KERNEL_TILE64K4, 64, 64, 4.913, 0.09614, 0.02658, 0.1131, 0.1812, 2.709, 1.687, 0.1347, 0.1713, 0.2057, 0.3153, 1.345, 1.249, 0},
-        {QG_KERNEL_TILE64X32K8, 64, 32, 5.361, 0.05698, 0.03245, 0.08362, 0.1719, 2.893, 0.1426, 0.1281, 0.1673, 0.3191, 0.3403, 1.769, 1.451, 0},
-        {QG_KERNEL_TILE128, 128, 128, 5.638, 0.2323, 0.1034, 0.3049, 0.1808, 1.819, 17.04, 0.4865, 0.57, 1.467, 1.053, 1.167, 1.071, 0},
-        {QG_KERNEL_TILE128, 128, 64, 6.457, 0.1257, 0.05136, 0.002241, 0.2397, 0.4095, 1.567, 0.5513, 0.1302, 0.4441, 0.04453, 1.615, 0.5655, 0.03},
-        {QG_KERNEL_TILE128X256, 128, 256, 8.088, 0.3241, 0.17, 0.4741, 0.3709, 3.606, 9.42, 0.2809, 0.7998, 2.352, 0.7592, 1.183, 1.056, 0},
-        {QG_KERNEL_TILE256, 256, 256, 15.87, 0.4316, 0.37, 0.8081, 0.4086, 11.87, 1.916, 1.057, 0.6666, 3.492, 0.4228, 1.347, 1.202, 0},
-    },
-    {
-        {QG_KERNEL_SKINNY16, 16, 4.072, 0.4924, 0, 0.7103, 9.148, 0.002234, 0.4255, 1.362, 0.1569, 0, 1.599, 1.446},
-        {QG_KERNEL_SKINNY32, 32, 4.727, 0.8457, 0, 0.7346, 12.84, 0.003592, 0.3285, 0.9272, 0.2843, 0.2869, 1.849, 1.544},
-        {QG_KERNEL_SKINNY64, 64, 5.981, 1.242, 0, 0.6692, 20.52, 0.004849, 0.2901, 1.317, 0.3073, 1.718, 1.807, 1.57},
-    },
-    3};
+const stream_price k_stream_price[] = {
+    {QG_KERNEL_SKINNY16, 16, false, 3.248, 0.3011, 0.0103, 0.7545, 7.886, 0.002382, 1.5, 0.2053, 0.01181, 0.2656,
+     0.001259, 0.0007677, 1.014, 1.501, 1.362, 1.252, 0.9263, 0.005715, 0.007775, 0.1323, 0.00701, 0.01281, 0.2002,
+     0.01251},
+    {QG_KERNEL_SKINNY16, 16, true, 3.445, 0.3273, 0.4135, 0.6321, 2.408, 0.002726, 1.5, 0.000463, 0.5543, 0.3, 0, 0, 0,
+     0, 0, 0, 0, 2.667, 2.253, 0, 0.01066, 0.1154, 0.06927, 0.01455},
+    {QG_KERNEL_SKINNY32, 32, false, 3.794, 0.5317, 0.0001372, 0.6106, 8.619, 0.002875, 1.5, 0.1803, 0.01243, 1.051,
+     0.02942, 0.5228, 0.9083, 1.801, 1.195, 1.826, 1.573, 0, 0.008883, 0.1495, 0.005953, 0.0161, 0.2054, 0.003701},
+    {QG_KERNEL_SKINNY32, 32, true, 4.353, 0.5132, 0.5825, 0.6666, 3.653, 0.005709, 1.5, 0.001424, 3.269, 0.3, 0, 0, 0, 0,
+     0, 0, 0, 0.7229, 1.039, 0.02223, 0.337, 0.01741, 0.0857, 0.01577},
+    {QG_KERNEL_SKINNY64, 64, false, 4.311, 0.7306, 0.04666, 0.6025, 10.63, 0.004096, 0.3285, 0.3214, 0.4498, 1.922,
+     0.01813, 0.09132, 0.998, 2.093, 0.8926, 2.174, 1.303, 0.06318, 4.371, 0.1457, 0.004449, 0.004859, 0.2676, 0.004231},
+    {QG_KERNEL_SKINNY64, 64, true, 5.725, 0.6746, 0.7333, 0.6037, 10.68, 0.005933, 0.7131, 0.3424, 0.8863, 0.3, 0, 0, 0,
+     0, 0, 0, 0, 0.4748, 0.77, 0.07867, 0.01022, 0.007475, 0.2029, 0.01652},
+};
 
+enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
 struct call_form {
-  int a_align;    // 16: base and rows of A at multiples of 16 bytes, 4: of 4 bytes, 1: others
-  bool wide_out;  // 4-byte results
-  bool c_ragged;  // rows of u8 results off 16 bytes
+  int a_align;  // 16: base and rows of A at multiples of 16 bytes, 4: of 4 bytes, 1: others
+  out_kind out;
+  bool bzp;     // weight zero points
 };
+
+// (plain comparisons and integer rounds: the library functions are calls on the baseline target, and every call of the GEMM comes here)
+inline double larger(double a, double b) { return a > b ? a : b; }
+inline long long tiles_of(int M, int N, int bm, int bn) { return (long long)ceil_div(M, bm) * ceil_div(N, bn); }
+inline double rounds_of(long long wgs) { return (double)((wgs + 255) / 256); }
+inline double share_of_chip(long long wgs) { return wgs < 256 ? (double)wgs / 256.0 : 1.0; }
 
 double tile_price_us(const tile_price& c, int M, int N, int K, const call_form& f) {
-  const double kt = (double)ceil_div(K, 64), wgs = (double)ceil_div(M, c.bm) * (double)ceil_div(N, c.bn);
-  const bool byte = f.a_align == 1, rag = f.c_ragged && !f.wide_out;
-  const double fix = c.fix + (f.wide_out ? c.wide_fix : 0.0) + (rag ? c.rag_fix : 0.0);
-  const double step = c.lat * (byte ? c.byte_lat : 1.0) + c.crowd * fmin(wgs, 256.0) / 256.0;
-  const double alone = fmax(fix + kt * step, 2.5 + (double)M * (double)N * (f.wide_out ? 4.0 : 1.0) / (c.out * 1e6));
-  if (wgs <= 256.0) return alone * (1.0 + c.tall * (M >= N ? 1.0 : 4.0 * M >= 3.0 * N ? 0.5 : 0.0));
-  const double epi = c.epi + (f.wide_out ? c.wide_epi : 0.0) + (rag ? c.rag_epi : 0.0);
-  const double rounds = ceil(wgs / 256.0), steps = rounds + c.fill * (wgs / 256.0 - rounds);
-  return fmax(alone, 2.5 + rounds * epi + steps * kt * c.thr * (byte ? c.byte_thr : 1.0));
+  const double kt = (double)ceil_div(K, 64);
+  const long long wgs = tiles_of(M, N, c.bm, c.bn);
+  const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
+  const bool tail = K % 16 != 0, left = K % 64 != 0, wide = f.out >= OUT_F32;
+  const double out_fix[] = {0.0, c.rag_fix, c.f32_fix, c.i32_fix}, out_epi[] = {0.0, c.rag_epi, c.f32_epi, c.i32_epi};
+  const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_thr[] = {1.0, c.thr4, c.thr1};
+  const double fix = c.fix + out_fix[f.out] + a_fix[a] + (tail ? c.tail_fix : 0.0) + (left ? c.left_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0);
+  const double lat = c.lat * a_lat[a] * (f.bzp ? 1.0 + c.bzp_lat : 1.0) * (1.0 + c.tall * M / ((double)M + N));
+  double us = larger(fix + kt * (lat + c.crowd * share_of_chip(wgs)), 2.5 + (double)M * (double)N * (wide ? 4.0 : 1.0) / (c.out * 1e6));
+  if (wgs > 256) {
+    const double epi = c.epi + out_epi[f.out] + (tail ? c.tail_epi : 0.0) + (left ? c.left_epi : 0.0);
+    const double rounds = rounds_of(wgs), steps = rounds + c.fill * ((double)wgs / 256.0 - rounds);
+    us = larger(us, 2.5 + rounds * epi + steps * kt * c.thr * a_thr[a] * (f.bzp ? 1.0 + c.bzp_thr : 1.0));
+  }
+  return us + c.far * larger((double)M * (double)K * 1e-6 - 4.0, 0.0);
 }
 
-double stream_price_us(const stream_price& c, bool wide, int M, int N, int K, const call_form& f) {
-  const double blocks32 = (double)ceil_div(M, c.rows) * (double)ceil_div(N, 32), wgs = wide ? blocks32 : 2.0 * blocks32;
-  const bool byte = f.a_align == 1;
-  const double a_bytes = (double)M * (double)K;
-  double a_bound = 2.5 + a_bytes / (c.a_rate * 1e6);
-  if (a_bytes > k_stream_a_near) a_bound = fmax(a_bound, 2.5 + a_bytes * (double)ceil_div(N, 16) / (c.a_far * 1e7));
+double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
+  const long long blocks32 = tiles_of(M, N, c.rows, 32), wgs = c.wide ? blocks32 : 2 * blocks32;
+  const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
+  const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
+  const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_wg_k[] = {1.0, c.wg_k4, c.wg_k1};
   // waves of a workgroup and k blocks of a batch as in the launches
-  const int waves = !wide ? 16 : c.rows == 64 ? 8 : 4, per = !wide ? (c.rows == 64 ? 2 : 4) : c.rows == 64 ? 4 : 8;
-  const double n = (double)(ceil_div(ceil_div(ceil_div(K, 64), waves), per) - 1);
-  const double alone = fmax(c.fix + (f.wide_out ? c.wide_fix : 0.0) + (K * c.lat / 1024.0 + n * c.batch) * (byte ? c.byte_lat : 1.0), a_bound);
-  if (wgs <= 256.0) return alone;
-  const double each = c.wg + (f.wide_out ? c.wide_wg : 0.0) + K * c.wg_k * (byte ? c.byte_wg_k : 1.0);
-  return fmax(alone * (1.0 + c.second), 2.5 + wgs * each * 1e-3);
+  const int waves = !c.wide ? 16 : c.rows == 64 ? 8 : 4, per = !c.wide ? (c.rows == 64 ? 2 : 4) : c.rows == 64 ? 4 : 8;
+  const int blocks = ceil_div(ceil_div(K, 64), waves);  // of a wave
+  const double n = (double)(ceil_div(blocks, per) - 1), bzp = f.bzp ? 1.0 + c.bzp_lat : 1.0;
+  const double fix = c.fix + out_fix[f.out] + a_fix[a] + (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0) -
+                     (a == 0 && K % (64 * waves * per) == 0 ? c.straight : 0.0);
+  double us = fix + (K * (c.lat + c.crowd * share_of_chip(wgs)) / 1024.0 + blocks * c.block + n * c.batch) * bzp * a_lat[a];
+  if (wgs > 256) us = larger(us * (1.0 + c.second), 2.5 + (double)wgs * (c.wg + out_wg[f.out] + K * c.wg_k * bzp * a_wg_k[a]) * 1e-3);
+  const double a_bytes = (double)M * (double)K;
+  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, c.wide ? 32 : 16) / (c.a_far * 1e7));
+  return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0);
 }
 
 int price_select(int M, int N, int K, const call_form& f) {
-  const price_set& set = f.a_align == 16 ? k_price_16 : k_price_off;
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  for (int i = 0; i < set.nstream; ++i) {
-    const stream_price& c = set.stream[i];
+  for (const stream_price& c : k_stream_price) {
     if (ceil_div(M, c.rows) > 65535) continue;
-    const bool wide = set.nstream == 6 && (i & 1);
-    if (set.nstream == 6) {
-      const bool is_wide = K % 2048 == 0 && (long long)ceil_div(M, c.rows) * ceil_div(N, 32) > 128;
-      if (wide != is_wide) continue;
-    }
-    const double us = stream_price_us(c, wide, M, N, K, f);
+    const bool wide = f.a_align == 16 && K % 2048 == 0 && (long long)ceil_div(M, c.rows) * ceil_div(N, 32) > 128;
+    if (wide != c.wide) continue;
+    const double us = stream_price_us(c, M, N, K, f);
     if (us < best_us) best_us = us, best = c.kernel;
   }
   const bool few = qg_tile128_few(M, N, K);
-  for (const tile_price& c : set.tile) {
+  for (const tile_price& c : k_tile_price) {
     if (c.kernel == QG_KERNEL_TILE128 && (c.bn == 64) != few) continue;
     if (c.kernel == QG_KERNEL_TILE256 && K < 256) continue;  // 128 x 256 tiles there, without the loop priced here
     const double us = tile_price_us(c, M, N, K, f);
@@ -315,13 +296,104 @@ const stream_cost k_stream_cost_16wave[] = {
     {QG_KERNEL_SKINNY32, 32, 4.13, 1.99e-4, 10.33, 1.28e-3},
     {QG_KERNEL_SKINNY64, 64, 4.96, 3.88e-4, 14.26, 2.23e-3},
 };
-// The same kernels with the convolution's per-lane tap addressing in their requests: the streaming formula with
-// constants of their own (Cin % 64 == 0; the layers above).
-const stream_cost k_conv_stream_cost[] = {
-    {QG_KERNEL_SKINNY16, 16, 5.17, 4.81e-4, 11.1, 3.33e-3},
-    {QG_KERNEL_SKINNY32, 32, 5.8, 6.87e-4, 21.9, 2.38e-3},
-    {QG_KERNEL_SKINNY64, 64, 6.84, 1.32e-3, 24.4, 4.24e-3},
+// The dense convolution: the tile loops with the im2col addressing folded into the requests, the streaming kernels with
+// per-lane tap addressing (Cin % 64 == 0), and for "same" layers (stride 1, output as large as the input, Cin % 32 == 0) the kernels
+// that keep the input patch of a pixel tile in LDS.  Formulas as for the GEMM, with
+//   chunk       channel counts off 64, whose requests keep a tap per lane;  tap: 64 / Cin of the steps begin a new tap
+//   load        per KiB of patch;  half: channel counts off 64, whose last slab is half full
+//   pass        what does not run side by side, the LDS of a wide patch allowing few workgroups per CU, runs one after the
+//               other, each pass at so much of the pace of a workgroup alone
+// Fitted to 20690 layers (1 x 1 to 7 x 7, stride 1 and 2, 16 .. 512 channels in, 8 .. 512 out, 5 .. 200 pixels wide, 1 .. 32 images) as
+// the GEMM's.  Over 5172 others the choice is 1.0035 of the best kernel in the mean, 1.28 at worst, 124 by more than 5 % (constants
+// fitted to 272 ordinary layers: 1.017 and 2.6; to older kernels: 1.051).
+struct conv_tile_price {
+  int kernel, bm, bn;
+  double fix, lat, crowd, thr, fill, epi, out, rag_fix, rag_epi, chunk_fix, chunk_lat, chunk_thr, bzp_fix, tap_lat, tap_thr, tall, bzp_lat, bzp_thr;
 };
+struct conv_stream_price {
+  int kernel, rows;
+  double fix, lat, batch, second, wg, wg_k, a_far, rag_fix, bzp_fix, tap_lat, tap_wg_k, bzp_lat;
+};
+struct conv_patch_price {
+  int kernel, bm, bn;
+  double fix, lat, crowd, thr, fill, epi, rag_fix, rag_epi, load, load_thr, bzp_fix, bzp_load, half_lat, half_thr, pass;
+};
+const conv_tile_price k_conv_tile_price[] = {
+    {QG_KERNEL_TILE64K1, 64, 64, 2.621, 0.2996, 0.02843, 0.1181, 0, 0.3721, 1.687, 0.2414, 0.2388, 0.4666, 1.296, 1.17,
+     0.1126, 0.003831, 0, 0.1076, 0.09862, 0.1185},
+    {QG_KERNEL_TILE64, 64, 64, 3.379, 0.1517, 0.01472, 0.09318, 0.1842, 1.269, 3, 0.2444, 0.1268, 0.66, 1.219, 1.347,
+     0.01917, 0.09827, 0.1015, 0.1107, 0.05257, 0.09864},
+    {QG_KERNEL_TILE64K4, 64, 64, 4.535, 0.0883, 0.01584, 0.1078, 0.08981, 2.688, 3, 0.2518, 0.2099, 0.952, 1.272, 1.526,
+     0.08897, 0.7561, 0.5257, 0.1444, 0.05258, 0.0748},
+    {QG_KERNEL_TILE64X32K8, 64, 32, 5, 0.06172, 0.01282, 0.07016, 0.5492, 3.366, 3, 0.2932, 0.5349, 0.6883, 2.437, 2.334,
+     0.2064, 0.8822, 0.7738, 0.1045, 0.03078, 0.09294},
+    {QG_KERNEL_TILE128, 128, 128, 4.395, 0.1804, 0.05482, 0.2991, 0.6572, 1.667, 3, 0.4675, 1.152, 0.1934, 3.203, 1.21,
+     0.07541, 0.7189, 0.1407, 0.2448, 0.08744, 0.08856},
+    {QG_KERNEL_TILE128X256, 128, 256, 6.375, 0.1898, 0.1673, 0.4174, 0.5815, 3.169, 3, 1.243, 1.684, 0.1547, 3.392,
+     1.611, 0.02083, 1.924, 0.4226, 0.148, 0.05569, 0.0766},
+};
+const conv_stream_price k_conv_stream_price[] = {
+    {QG_KERNEL_SKINNY16, 16, 3.704, 0.1457, 0.03971, 0.6714, 6.865, 0.001644, 1, 0, 0, 15.68, 4.028, 0.004171},
+    {QG_KERNEL_SKINNY32, 32, 4.777, 0.3575, 0.1303, 0.7435, 8.375, 0.001792, 1, 0.01563, 0, 6.124, 7.619, 0.000097},
+    {QG_KERNEL_SKINNY64, 64, 4.424, 1.243, 0, 0.6602, 10.62, 0.002683, 1.057, 0.2616, 0.1031, 3.359, 8.129, 0.0002748},
+};
+const conv_patch_price k_conv_patch_price[] = {
+    {QG_KERNEL_PATCH64X128, 64, 128, 3.4, 0.0935, 0.03727, 0.1396, 0.8133, 1.005, 2.676, 3.501, 0.05252, 0.01825, 0.9731,
+     0.01964, 2.868, 0.8962, 0.9737},
+    {QG_KERNEL_PATCH128X64, 128, 64, 3.641, 0.1496, 0, 0.0842, 0.3523, 0.8482, 2.736, 2.735, 0.005236, 0.02926, 0.8379,
+     0.008291, 1.219, 1.102, 1.135},
+    {QG_KERNEL_PATCH256X64, 256, 64, 4.05, 0.1615, 0.001215, 0.1679, 0.2977, 1.637, 6.579, 5.846, 0.01247, 0.009308,
+     0.5507, 0.0143, 1.23, 1.17, 1.195},
+    {QG_KERNEL_PATCH256, 256, 128, 6.063, 0.2323, 0.0866, 0.2649, 0.2914, 3.118, 13.86, 13.33, 0.001793, 0, 1.036,
+     0.01437, 1.206, 1.216, 1.103},
+    {QG_KERNEL_PATCH512, 512, 128, 9.67, 0.3225, 0.2546, 0.5183, 0.2761, 7.22, 17.92, 33.57, 0.003051, 0.0001414, 1.853,
+     0.01148, 1.254, 0.574, 1.019},
+};
+// ... and the builds of QG_KERNEL_PATCH64X128 for at most one tile per CU, with four and two wave sets
+const conv_patch_price k_conv_few4_price =
+    {QG_KERNEL_PATCH64X128, 64, 64, 4.671, 0.05276, 0.01044, 0, 0, 0, 1.732, 0, 0.0001684, 0, 0.8553, 0.01451, 1.15, 0,
+     0};
+const conv_patch_price k_conv_few2_price =
+    {QG_KERNEL_PATCH64X128, 64, 128, 4.087, 0.08389, 0.01578, 0, 0, 0, 4.864, 0, 0.01644, 0, 0.9648, 0.009549, 1.266, 0,
+     0};
+
+double conv_tile_us(const conv_tile_price& c, const qg_gemm_args& a) {
+  const double kt = (double)ceil_div(a.K, 64), wgs = (double)ceil_div(a.M, c.bm) * (double)ceil_div(a.N, c.bn), M = a.M, N = a.N;
+  const bool chunk = a.cv_Cin % 64 != 0, rag = a.c_vec == 0;
+  const double tap = 64.0 / a.cv_Cin;
+  const double fix = c.fix + (rag ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) + (chunk ? c.chunk_fix : 0.0);
+  const double lat = c.lat * (chunk ? c.chunk_lat : 1.0 + c.tap_lat * tap) * (a.has_bzp ? 1.0 + c.bzp_lat : 1.0) * (1.0 + c.tall * M / (M + N));
+  const double alone = fmax(fix + kt * (lat + c.crowd * fmin(wgs, 256.0) / 256.0), 2.5 + M * N / (c.out * 1e6));
+  if (wgs <= 256.0) return alone;
+  const double rounds = ceil(wgs / 256.0), steps = rounds + c.fill * (wgs / 256.0 - rounds);
+  const double thr = c.thr * (chunk ? c.chunk_thr : 1.0 + c.tap_thr * tap) * (a.has_bzp ? 1.0 + c.bzp_thr : 1.0);
+  return fmax(alone, 2.5 + rounds * (c.epi + (rag ? c.rag_epi : 0.0)) + steps * kt * thr);
+}
+
+double conv_stream_us(const conv_stream_price& c, const qg_gemm_args& a) {
+  const double wgs = 2.0 * (double)ceil_div(a.M, c.rows) * (double)ceil_div(a.N, 32), tap = 64.0 / a.cv_Cin;
+  const double n = (double)(ceil_div(ceil_div(ceil_div(a.K, 64), 16), c.rows == 64 ? 2 : 4) - 1), bzp = a.has_bzp ? 1.0 + c.bzp_lat : 1.0;
+  double us = c.fix + (a.c_vec == 0 ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) +
+              (a.K * c.lat / 1024.0 + n * c.batch) * bzp * (1.0 + c.tap_lat * tap);
+  if (wgs > 256.0) us = fmax(us * (1.0 + c.second), 2.5 + wgs * (c.wg + a.K * c.wg_k * bzp * (1.0 + c.tap_wg_k * tap)) * 1e-3);
+  const double a_bytes = (double)a.M * (double)a.K;
+  if (a_bytes > k_stream_a_near) us = fmax(us, 2.5 + a_bytes * (double)ceil_div(a.N, 16) / (c.a_far * 1e7));
+  return us;
+}
+
+double conv_patch_us(const conv_patch_price& c, const qg_gemm_args& a, int per_cu) {
+  const double kt = (double)ceil_div(a.K, 64), wgs = (double)ceil_div(a.M, c.bm) * (double)ceil_div(a.N, c.bn);
+  const bool half = a.cv_Cin % 64 != 0;
+  const double kb = ((double)c.bm + (double)(a.cv_R - 1) * a.cv_W + a.cv_R - 1) * a.cv_Cin / 1024.0;
+  const double rag = a.c_vec ? 0.0 : fmin((double)a.N / c.bn, 1.0), bzp = a.has_bzp ? 1.0 : 0.0;
+  const double alone = c.fix + rag * c.rag_fix + bzp * (c.bzp_fix + kb * c.bzp_load) + kb * c.load +
+                       kt * (c.lat * (half ? c.half_lat : 1.0) + c.crowd * fmin(wgs, 256.0) / 256.0);
+  if (wgs <= 256.0) return alone;
+  const double rounds = ceil(wgs / 256.0), steps = rounds + c.fill * (wgs / 256.0 - rounds), passes = ceil(wgs / (256.0 * per_cu));
+  const double full = 2.5 + rounds * (c.epi + rag * c.rag_epi + kb * c.load_thr + bzp * kb * c.bzp_load) +
+                      steps * kt * c.thr * (half ? c.half_thr : 1.0);
+  return fmax(fmax(alone, full), passes > 1.0 ? 2.5 + passes * (alone - 2.5) * c.pass : 0.0);
+}
 
 int select_stream_kernel(int M, int N, int K) {
   int best = QG_KERNEL_SKINNY64;
@@ -465,6 +537,7 @@ int resolve_call(const qg_packed_b* Bp, int M, int* kernel, int* ksplit, const c
 int a_align(const uint8_t* A_dev, int lda) {
   return aligned(A_dev, 16) && lda % 16 == 0 ? 16 : aligned(A_dev, 4) && lda % 4 == 0 ? 4 : 1;
 }
+out_kind u8_kind(const uint8_t* C_dev, int ldc) { return aligned(C_dev, 16) && ldc % 16 == 0 ? OUT_U8 : OUT_U8_RAGGED; }
 // ksplit_req: 0 = built-in choice (1 without a workspace), otherwise the caller's.  Fills the workspace fields of `a`.
 int resolve_ksplit(const qg_packed_b* Bp, int M, int kernel, int ksplit_req, void* workspace_dev, size_t workspace_bytes,
                    bool bytes_known, qg_gemm_args* a) {
@@ -555,7 +628,7 @@ int qg_kernel_select(int M, int N, int K) {
   if (M <= 0 || N <= 0 || K <= 0) return QG_EINVAL;
   const int rule = rule_kernel(M, N, K);
   if (rule != QG_KERNEL_AUTO && kernel_ok(rule, M)) return rule;
-  return price_select(M, ceil_div(N, 16) * 16, ceil_div(K, 64) * 64, {16, false, false});
+  return price_select(M, ceil_div(N, 16) * 16, ceil_div(K, 64) * 64, {16, OUT_U8, false});
 }
 
 int qg_dispatch_set_rules(const qg_dispatch_rule* rules_host, int n) {
@@ -817,7 +890,7 @@ static int gemm_requant(const uint8_t* A_dev, int M, int lda, const qg_packed_b*
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), false, !aligned(C_dev, 16) || ldc % 16 != 0}, workspace_dev);
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), u8_kind(C_dev, ldc), Bp->has_bzp != 0}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_requant(p, Bp->N);
@@ -882,7 +955,7 @@ static int gemm_acc32(const uint8_t* A_dev, int M, int lda, const qg_packed_b* B
   qg_gemm_args a = {};
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
-  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), true, false}, workspace_dev);
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), OUT_I32, Bp->has_bzp != 0}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C32_dev && M != 0) return QG_ENULL;
   if (ldc < Bp->N) return QG_EINVAL;
@@ -929,7 +1002,7 @@ int qg_gemm_u8s8_dequant_f32(const uint8_t* A_dev, int M, int lda, const qg_pack
   int rc = gemm_common(A_dev, M, lda, Bp, &a);
   if (rc != QG_OK) return rc;
   int ksplit = 0;
-  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), true, false}, workspace_dev);
+  rc = resolve_call(Bp, M, &kernel, &ksplit, {a_align(A_dev, lda), OUT_F32, Bp->has_bzp != 0}, workspace_dev);
   if (rc != QG_OK) return rc;
   if (!C_dev && M != 0) return QG_ENULL;
   rc = check_dequant(p, Bp->N);
@@ -1018,7 +1091,7 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
   // (with a workspace the 8-bit call below runs on the quantized copy, whose rows are 16-byte aligned and which has no split)
   int ksplit = 1;
-  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, false, !aligned(C_dev, 16) || ldc % 16 != 0}, nullptr)
+  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0}, nullptr)
                      : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   {
@@ -1059,7 +1132,7 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
   int ksplit = 1;
-  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, true, false}, nullptr) : resolve_kernel(Bp, M, &kernel);
+  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, OUT_F32, Bp->has_bzp != 0}, nullptr) : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {
@@ -1136,27 +1209,20 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
   const bool stream_ok = Cin % QG_FRAG_K == 0 && R * S <= 32;
   if (kernel == QG_KERNEL_AUTO) {
     double best_us = 1e300;
-    for (const tile_cost& c : Cin % QG_FRAG_K == 0 ? k_conv_cost : k_conv_chunk_cost) {
-      const double us = tile_estimate(c, a.M, a.N, a.K);
+    for (const conv_tile_price& c : k_conv_tile_price) {
+      const double us = conv_tile_us(c, a);
       if (us < best_us) best_us = us, kernel = c.kernel;
     }
-    for (const tile_cost& c : k_conv_patch_cost) {
+    for (const conv_patch_price& c : k_conv_patch_price) {
       const int per_cu = qg_conv_patch_per_cu(a, c.kernel - QG_KERNEL_PATCH64X128);
       if (per_cu == 0) continue;
       const int sets = c.kernel == QG_KERNEL_PATCH64X128 ? qg_conv_patch_sets(a) : 0;
-      double us = tile_estimate(sets == 4 ? k_conv_few4_cost : sets == 2 ? k_conv_few2_cost : c, a.M, a.N, a.K);
-      if (sets == 0) {
-        // A wide patch leaves room for few workgroups per CU: what does not run side by side runs one after the
-        // other, each pass at the pace of a workgroup alone.
-        const double wgs = (double)ceil_div(a.M, c.bm) * (double)ceil_div(a.N, c.bn);
-        const double passes = ceil(wgs / (256.0 * per_cu));
-        us = fmax(us, 2.5 + passes * (c.fix + ceil_div(a.K, 64) * c.lat - 2.5));
-      }
+      const double us = conv_patch_us(sets == 4 ? k_conv_few4_price : sets == 2 ? k_conv_few2_price : c, a, per_cu);
       if (us < best_us) best_us = us, kernel = c.kernel;
     }
     if (stream_ok)
-      for (const stream_cost& c : k_conv_stream_cost) {
-        const double us = stream_estimate(c, a.M, a.N, a.K, false);
+      for (const conv_stream_price& c : k_conv_stream_price) {
+        const double us = conv_stream_us(c, a);
         if (ceil_div(a.M, c.rows) <= 65535 && us < best_us) best_us = us, kernel = c.kernel;
       }
   }

@@ -44,6 +44,23 @@ def test_kernel_select_answers_for_whole_steps():
                 assert q.kernel_select(M, N, K) == q.kernel_select(M, -(-N // 16) * 16, -(-K // 64) * 64), (M, N, K)
 
 
+@pytest.mark.parametrize("M,N,K,fast", [
+    # us with the kernel that an earlier fit chose, with the fastest
+    (7, 6304, 2816, ("tile64x32k8",)),                       # 7.8, 7.1
+    (69, 3616, 2048, ("tile64x32k8",)),                      # 9.6, 6.2
+    (827, 17, 15685, ("skinny16",)),                         # 25.1, 10.4: tall, few columns, long K
+    (1152, 32, 11840, ("skinny16",)),                        # 18.7, 8.7
+    (940, 64, 14177, ("skinny16",)),                         # 29.4, 16.1
+    (1340, 11, 3072, ("skinny16",)),                         # 7.5, 5.1
+    (64, 64, 128, ("tile64k1",)),                            # 3.5, 3.2
+    (9, 7996, 5824, ("tile64x32k8",)),                       # 15.1, 11.0
+    (39460, 865, 87, ("tile128",)),                          # 26.9, 22.3 (rows of A and C off 16 bytes; the choice is the same)
+])
+def test_shapes_that_were_slow(M, N, K, fast):
+    from paper_2101_05615_amd import qgemm as q
+    assert q.kernel_names()[q.kernel_select(M, N, K)] in fast
+
+
 def test_autotune_times_the_choice_of_the_call(monkeypatch):
     """The reported loss is that of an "auto" call, not of the kernel that kernel_select names."""
     from paper_2101_05615_amd import autotune, qgemm as q
