@@ -93,6 +93,19 @@ def test_fp32_activations(env):
         assert ("out" in kw) == (got is out)
     want8 = call(q, c, t, A=Aq)
     assert torch.equal(q.gemm_f32s8_requant(A, np.float32(20.0), c.a_zp, t["Bp"], t["bias"], t["scales"], c.c_zp, c.relu), want8)
+    # the module itself, not the path behind it: both outputs, own and given output and workspace
+    for c_zp, ref in ((None, want), (c.c_zp, want8)):
+        own = torch.zeros_like(ref)
+        for o, w in ((None, None), (None, ws), (own, None), (own, ws)):
+            relu = True if c_zp is None else c.relu
+            got = q._binding.gemm_f32s8(A, 20.0, c.a_zp, t["Bp"], t["bias"], t["scales"], c_zp, relu, o, w, 0)
+            assert got is not None and got.dtype == ref.dtype and torch.equal(got, ref), (c_zp, o is None, w is None)
+            assert o is None or got is own
+            own.zero_()
+        for k in ("tile64", "skinny32"):
+            got = q._binding.gemm_f32s8(A, 20.0, c.a_zp, t["Bp"], t["bias"], t["scales"], c_zp, relu, None, None, q.kernel_id(k))
+            assert got is not None and torch.equal(got, ref), k
+        assert q._binding.gemm_f32s8(A.double(), 20.0, c.a_zp, t["Bp"], t["bias"], t["scales"], c_zp, relu, None, None, 0) is None
     for bad in (0.0, float("nan")):
         with pytest.raises(q.QGemmError):
             q.gemm_f32s8_dequant_f32(A, bad, c.a_zp, t["Bp"], t["bias"], t["scales"], True)
@@ -117,3 +130,43 @@ def test_prepared_calls(env):
     with pytest.raises(q.QGemmError) as e:
         bad.launch()
     assert e.value.code == q.EINVAL and "qg_gemm_u8s8_requant" in str(e.value)
+
+
+def conv_operands(torch, c):
+    bias = None if c.bias is None else torch.from_numpy(c.bias).cuda()
+    return torch.from_numpy(c.inp).cuda(), bias, torch.from_numpy(c.scales).cuda()
+
+
+@pytest.mark.parametrize("cfg", [dict(Nb=2, H=9, W=14, C=64, G=16, pad=1, stride=2), dict(Nb=3, H=12, W=7, C=64, G=64, pad=1, stride=1),
+                                 dict(Nb=1, H=8, W=11, C=96, G=12, R=1, S=1, pad=0, stride=1)])
+def test_prepared_group_convolution(env, cfg):
+    q, torch, dev, *_ = env
+    c = wl.random_conv(23, **cfg)
+    x, bias, scales = conv_operands(torch, c)
+    Wp = q.pack_conv_w(torch.from_numpy(c.wgt).cuda(), c.b_zp)
+    want = q.conv_groupwise_u8s8_requant(x, Wp, c.a_zp, bias, scales, c.c_zp, c.relu, pad=c.pad, stride=c.stride)
+    out = torch.zeros_like(want)
+    q.PreparedConv(x, Wp, c.a_zp, bias, scales, c.c_zp, c.relu, c.pad, c.stride, out).launch()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("kernel", ["auto", "tile64", "patch128x64", "skinny16"])
+@pytest.mark.parametrize("cfg", [dict(Nb=2, H=9, W=14, C=64, Cout=72, pad=1, stride=1), dict(Nb=2, H=9, W=14, C=64, Cout=72, R=3, S=2, pad=0, stride=2),
+                                 dict(Nb=1, H=7, W=13, C=128, Cout=40, R=2, S=4, pad=1, stride=3)])
+def test_prepared_dense_convolution(env, cfg, kernel):
+    q, torch, dev, *_ = env
+    c = wl.random_conv(29, G=1, **cfg)
+    x, bias, scales = conv_operands(torch, c)
+    Wp = q.pack_conv_dense_w(torch.from_numpy(np.ascontiguousarray(c.wgt[0])).cuda(), c.b_zp)
+    want = q.conv_dense_u8s8_requant(x, Wp, c.a_zp, bias, scales, c.c_zp, c.relu, pad=c.pad, stride=c.stride, kernel="tile64k1")
+    out = torch.zeros_like(want)
+    call = q.PreparedConvDense(x, Wp, c.a_zp, bias, scales, c.c_zp, c.relu, c.pad, c.stride, out, kernel=kernel)
+    if kernel.startswith("patch") and c.stride != 1:
+        with pytest.raises(q.QGemmError) as e:   # (the kernel id arrived where it belongs)
+            call.launch()
+        assert e.value.code == q.EUNSUPPORTED and "qg_conv_dense_u8s8_requant" in str(e.value)
+        return
+    call.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
