@@ -6,7 +6,8 @@
 // from L2 again (R*S times the image through L2 -> LDS, one stage of latency per 64-deep step).  Here a workgroup
 // owns TP consecutive output pixels of the linear NHWC pixel sequence: the input pixel of tap (kh, kw) of output
 // pixel q is pixel q + (kh-pad)*W + (kw-pad) of the same sequence, so ONE contiguous run of TP + (R-1)*W + (S-1)
-// pixels holds every tap of the tile.  It is requested in one burst (one memory latency per workgroup); the A
+// pixels holds every tap of the tile.  It comes through registers, two or eight 16-byte chunks per thread in flight at a
+// time (ten rounds and more for a large patch), and is shifted to int8 on the way into LDS; the A
 // operand of an MFMA is then 16 consecutive channel bytes of a patch pixel, read from LDS at a per-lane address:
 // pixel base + tap offset (scalar) + channel offset.  Taps outside the image are redirected, by address, to a row
 // of theta_A bytes in LDS, so the consume path has no select.  Only the weights stream: 64-deep slabs of the packed
@@ -29,7 +30,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // in which it lets a CU hold one more workgroup and there are workgroups to fill the places: the other workgroups'
 // waves then cover the latency that the ring no longer does.
 constexpr int ring_slabs(int tn, bool deep, int ks = 1) {
-  return ks == 4 ? (tn <= 64 ? 6 : 4) : ks == 2 ? (tn <= 64 ? 6 : 5) : deep ? (tn <= 64 ? 8 : 6) : (tn <= 64 ? 4 : 3);
+  return ks == 4 ? 6 : ks == 2 ? 5 : deep ? (tn <= 64 ? 8 : 6) : (tn <= 64 ? 4 : 3);
 }
 
 // slab(0) && slab(1) && ... && slab(N-1): the ring, unrolled
@@ -87,10 +88,10 @@ template <int WM, int WN, int MB, int NBW, bool HAS_BZP, bool C64, bool DEEP, in
 __global__ __launch_bounds__(WM* WN * KS * 64) void qg_conv_patch_kernel(
     const uint8_t* const in, const int8_t* const Bp, const int npix, const int W, const int H, const int N, const int nb16,
     const int cpix, const int geom, const qg_gemm_args p) {
-  // The leading scalar arguments repeat what the request burst needs (cpix = Cin | bytes per image pixel << 16,
+  // The leading scalar arguments repeat what the patch's requests need (cpix = Cin | bytes per image pixel << 16,
   // geom = R | S << 8 | pad << 16 | theta_A << 24): the file is compiled with kernel-argument preloading, so they
   // arrive in scalar registers with the wave (the first 14 dwords do), and the cold trip to the argument buffer
-  // for the rest of p (first used after the burst) overlaps the patch's own.
+  // for the rest of p (first used after the first of them) overlaps the patch's own.
   constexpr int NW = WM * WN, NT = NW * KS * 64;  // NW: waves of one set; NT: threads of the workgroup
   static_assert(KS == 1 || (MB == 1 && NBW <= KS), "a block of the output has a wave set that finishes it");
   constexpr int TP = WM * MB * 32, TN = WN * NBW * 32;
