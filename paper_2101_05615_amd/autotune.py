@@ -214,12 +214,13 @@ def tune(q, torch, shapes, kernels=None, log=None, cold=False):
     kernels = kernels or [names[k] for k in range(1, q.KERNEL_LAST + 1)]
     rows = []
     for (M, N, K) in shapes:
-        # (the automatic choice is timed as a call of its own: which kernel it runs depends on the call's alignment too)
+        # (the automatic choice is timed as a call of its own, "auto_us": which kernel it runs depends on the call's alignment too;
+        # "auto" is the one that an aligned call runs)
         ask = list(kernels) + ["auto"]
         t = time_cold_kernels(q, torch, M, N, K, ask)[0] if cold else time_shape(q, torch, M, N, K, ask)
         auto = t.pop("auto")
         best = min(t, key=t.get)
-        rows.append({"M": M, "N": N, "K": K, "best": best, "auto_us": auto, "us": t})
+        rows.append({"M": M, "N": N, "K": K, "best": best, "auto": names[q.kernel_select(M, N, K)], "auto_us": auto, "us": t})
         if log:
             line = " ".join(f"{k}={v:9.1f}" for k, v in t.items())
             log(f"{M:6d} {N:6d} {K:6d}  best {best:12s} auto {auto:9.1f} loss {auto / t[best]:5.2f}x  {line}")

@@ -73,6 +73,7 @@ def test_autotune_times_the_choice_of_the_call(monkeypatch):
     monkeypatch.setattr(autotune, "time_shape", timed)
     rows = autotune.tune(q, None, [(4, 16, 17)], log=lambda s: None)
     assert "auto" in asked[0] and rows[0]["best"] == "tile64" and rows[0]["auto_us"] == 9.0 and "auto" not in rows[0]["us"]
+    assert rows[0]["auto"] == q.kernel_names()[q.kernel_select(4, 16, 17)]
     assert "1.5000x" in autotune.summary(rows) and autotune.table_from_rows(rows) == [[4, 4, 16, 16, 17, 17, "tile64"]]
 
 
