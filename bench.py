@@ -473,9 +473,9 @@ def main():
             r = autotune.tune(q, torch, [shape])[0]
             t = r["us"]
             nxt["kernel_family"].append({"M": shape[0], "N": shape[1], "K": shape[2], "auto": r["auto"],
-                                         "auto_us": round(t[r["auto"]], 2), "best": r["best"],
+                                         "auto_us": round(r["auto_us"], 2), "best": r["best"],
                                          "best_us": round(t[r["best"]], 2),
-                                         "TOPS": round(2.0 * shape[0] * shape[1] * shape[2] / t[r["auto"]] / 1e6, 1)})
+                                         "TOPS": round(2.0 * shape[0] * shape[1] * shape[2] / r["auto_us"] / 1e6, 1)})
         # fp32 ends: the quantization pass (5 bytes per element) and the fp32 output pipeline at the headline size
         Mq = Kq = 8192
         g = torch.Generator(device=dev)

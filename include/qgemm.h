@@ -219,10 +219,11 @@ const char* qg_kernel_name(int kernel);
 
 /* The id (never QG_KERNEL_AUTO) that QG_KERNEL_AUTO resolves to for a dense product of this shape in the layout the
  * kernels like best: N a multiple of 16 and K of 64 (others are answered as the next such N and K), every row of A
- * and of C at a multiple of 16 bytes, uint8 results, no K split and no workspace for one.  The choice of a call also
- * looks at what that leaves out, so another call may run another kernel: rows of A at multiples of 4 bytes or at any
- * address, rows of C off 16 bytes, 4-byte results, K off 64 or 16, a workspace that qg_gemm_workspace_bytes asked for
- * (the kernel that splits), ksplit > 1, outlier-split weights, fp32 activations without a workspace.
+ * and of C at a multiple of 16 bytes, uint8 results, weights without zero points, no K split and no workspace for one.
+ * The choice of a call also looks at what that leaves out, so another call may run another kernel: weight zero points,
+ * rows of A at multiples of 4 bytes or at any address, rows of C off 16 bytes, 4-byte results, K off 64 or 16, a
+ * workspace that qg_gemm_workspace_bytes asked for (the kernel that splits), ksplit > 1, outlier-split weights, fp32
+ * activations without a workspace.
  * A rule of the table below comes first.  QG_EINVAL (negative) if a size is not positive. */
 int qg_kernel_select(int M, int N, int K);
 

@@ -214,8 +214,8 @@ def tune(q, torch, shapes, kernels=None, log=None, cold=False):
     kernels = kernels or [names[k] for k in range(1, q.KERNEL_LAST + 1)]
     rows = []
     for (M, N, K) in shapes:
-        # (the automatic choice is timed as a call of its own, "auto_us": which kernel it runs depends on the call's alignment too;
-        # "auto" is the one that an aligned call runs)
+        # (the automatic choice is timed as a call of its own, "auto_us": which kernel it runs depends on the call's alignment and
+        # zero points too; "auto" is the one that kernel_select names)
         ask = list(kernels) + ["auto"]
         t = time_cold_kernels(q, torch, M, N, K, ask)[0] if cold else time_shape(q, torch, M, N, K, ask)
         auto = t.pop("auto")
