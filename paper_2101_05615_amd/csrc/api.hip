@@ -148,13 +148,16 @@ int builtin_select(int M, int N, int K) {
 //   tile, at most 256 workgroups   us = fix + kt * (lat * (1 + tall * M / (M + N)) + crowd * wgs / 256)     kt = ceil(K / 64)
 //   beyond                         the larger of that and 2.5 + rounds * epi + kt * thr * (rounds - fill * (rounds - wgs / 256)),
 //                                  rounds = ceil(wgs / 256): a round that does not fill the chip runs faster
-//   streaming                      us = fix + K / 1024 * (lat + crowd * wgs / 256) + blocks * block + n * batch; more than 256
-//                                  workgroups: the larger of that times (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
-// and far more per megabyte of A beyond four, for both.  Fitted to graph-replay times of all kernels on 46417 shapes (M 1 .. 65536,
-// N 8 .. 8192, K 16 .. 16384, rows of A and C at all alignments, the three kinds of results, with and without zero points), three
-// sets of buffers in turn: first the times, then the loss of the choice.  Over 7600 other shapes the choice is 1.0035 of the best
-// kernel in the geometric mean, 1.32 at worst, 186 of them by more than 5 %.  The prices above: 1.050 and 2.8; a fit to the ordinary
-// shapes alone: 1.020 and 2.5 (tall shapes of few columns and a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
+//   streaming                      us = fix + K / 1024 * (lat + crowd * wgs / 256) + blocks * block + n * batch + what is fetched; more
+//                                  than 256 workgroups: the larger of that times (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
+//   its form of few fat waves      (rows at 16 bytes, K a multiple of 2048, more than 128 super-blocks) in steps: a batch of requests
+//                                  per 2048 of K, rounds of 256 workgroups.  M 80, N 3072, K 2048: 480 workgroups 4.8 us, 576 7.3
+// and far more per megabyte of A beyond four.  Fitted to graph-replay times of all kernels on 46417 drawn shapes (M 1 .. 65536, N 8 ..
+// 8192, K 16 .. 16384, rows of A and C at all alignments, the three kinds of results, with and without zero points) and 5600 round
+// ones, three sets of buffers in turn: first the times, then the loss of the choice.  Over 7600 other drawn shapes the choice is 1.0034
+// of the best kernel in the geometric mean, 1.32 at worst, 178 of them by more than 5 %; over 1400 other round ones 1.0030, 1.20 and
+// 31.  The prices above: 1.050 and 1.026; a fit to ordinary shapes alone: 1.020 and 1.026, 2.5 at worst (tall shapes of few columns and
+// a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
 struct tile_price {
   int kernel, bm, bn;
   double fix, lat, crowd, thr, fill, epi, out;         // out: megabytes of output per microsecond
@@ -164,10 +167,10 @@ struct tile_price {
   double i32_fix, i32_epi, tall, far;                  // int32 results; fewer workgroups share a row of A; megabytes of A beyond 4
   double left_fix, left_epi;                           // K off 64: the last tile is staged through registers
   double bzp_fix, bzp_lat, bzp_thr;                    // weight zero points: the row sums; additions to lat and thr as factors
+  double b_far, b_near, half;                          // us per megabyte of B beyond b_near; last column of tiles at most half full: adds to lat
 };
 struct stream_price {
   int kernel, rows;
-  bool wide;                                           // the form of few fat waves (K a multiple of 2048, more than 128 super-blocks)
   double fix, lat, batch, second, wg, wg_k;            // lat: per 1024 of K; batch: per batch of requests a wave makes after its first
   double a_far;                                        // tens of megabytes of A per us, fetched once per column block from beyond the L2s
   double f32_fix, f32_wg, tail_fix;
@@ -176,48 +179,57 @@ struct stream_price {
   double i32_fix, i32_wg, far;
   double bzp_fix, bzp_lat;
   double crowd, block;                                 // per 1024 of K on a full chip; per k block of a wave
+  double fetch, near;                                  // us per megabyte that the XCDs fetch beyond so many
 };
-// The second of QG_KERNEL_TILE128 is the 128 x 64 form, which runs on at most one workgroup per CU (its terms beyond are zero), as the
-// wide forms only run on rows at 16 bytes.
+struct wide_price {
+  int kernel, rows;
+  double fix, lat, crowd, jump;                        // lat, crowd: per 2048 of K; jump: more than one batch
+  double round, round_lat, pair, pair_lat;             // for each round of 256 workgroups after the first, for each of 512
+  double fetch, near;
+  double f32_fix, i32_fix, bzp_fix, bzp_lat, far, wide_round;  // wide_round: 4-byte results, per round
+};
+// The second of QG_KERNEL_TILE128 is the 128 x 64 form, which runs on at most one workgroup per CU (its terms beyond are zero).
 const tile_price k_tile_price[] = {
-    {QG_KERNEL_TILE64K1, 64, 64, 2.412, 0.2859, 0.02878, 0.1101, 0.3366, 0.2838, 5.877, 0.000065, 0.07622, 0.1249,
-     0.0928, 0.445, 0.006527, 0.1136, 0.2098, 0.9715, 0.8361, 1.142, 1.331, 1.51, 3.041, 0.0001168, 0.08669, 0.2804,
-     0.09552, 0.1591, 0.1329, 0.06869},
-    {QG_KERNEL_TILE64, 64, 64, 3.198, 0.116, 0.04054, 0.1004, 0.2102, 0.6698, 4.196, 0, 0.1119, 0.1202, 0.1159, 0.4147,
-     0.09634, 0.06138, 0.07334, 0.9586, 1.078, 1.09, 1.32, 1.56, 2.811, 0, 0.06911, 0.338, 0.1948, 0.1698, 0.08709,
-     0.06169},
-    {QG_KERNEL_TILE64K4, 64, 64, 3.974, 0.08286, 0.02518, 0.1063, 0.2371, 1.926, 3, 0.008089, 0.1839, 0.08701, 0.1884,
-     0.4139, 0.03725, 0.0009907, 0.1089, 1.05, 1.405, 1.064, 1.327, 1.52, 3.715, 0.03518, 0.07705, 0.342, 0.5083, 0.1992,
-     0.08803, 0.131},
-    {QG_KERNEL_TILE64X32K8, 64, 32, 3.918, 0.05038, 0.01538, 0.06413, 0.385, 2.255, 3, 0.1624, 0.08867, 0.07876, 0.3568,
-     0.4532, 0.2924, 0.05769, 0.2216, 1.019, 1.88, 1.334, 1.536, 1.14, 2.82, 0.007775, 0.07581, 0.5533, 0.3128, 0.2233,
-     0.07749, 0.1108},
-    {QG_KERNEL_TILE128, 128, 128, 4.674, 0.1251, 0.147, 0.284, 0.2988, 1.213, 4.878, 0.0001634, 0.5468, 0.3874, 0.3102,
-     0.2061, 0.05551, 0.007901, 0.0001859, 1.263, 1.46, 1.097, 1.256, 9.815, 11.79, 0.1426, 0.05725, 0.694, 0.327,
-     0.007568, 0.05964, 0.04459},
-    {QG_KERNEL_TILE128, 128, 64, 5.426, 0.0962, 0.03756, 0, 0, 0, 3, 0.4782, 0, 0.2711, 0, 0.467, 0, 0.2839, 1.366,
-     1.043, 1.36, 0, 0, 6.138, 0, 0.1545, 0.06416, 0.8221, 0, 0.01208, 0.05971, 0.01832},
-    {QG_KERNEL_TILE128X256, 128, 256, 7.296, 0.1909, 0.2372, 0.4356, 0.2471, 2.958, 4.972, 0.0002597, 0.2069, 0.4143,
-     0.5134, 0.7246, 0.1053, 0.3389, 0.3716, 1.145, 1.451, 1.076, 1.146, 21.77, 23.09, 0.001574, 0.05695, 0.2195, 0.488,
-     0.1331, 0.1019, 0.01175},
-    {QG_KERNEL_TILE256, 256, 256, 16.52, 0.2333, 0.5554, 0.7709, 0.4578, 12.36, 3.181, 0.0001982, 0.03314, 0.02852,
-     0.2106, 1.116, 0.8108, 0.3416, 0.0009741, 1.083, 2.04, 1.028, 1.267, 45.59, 52.39, 0.003552, 0.000098, 0.008314,
-     0.9841, 0.01655, 0.04981, 0.03198},
+    {QG_KERNEL_TILE64K1, 64, 64, 2.379, 0.2932, 0.01648, 0.1083, 0.3038, 0.2923, 5.958, 0, 0.09458, 0.09551, 0.08843,
+     0.4098, 0.0001485, 0.1085, 0.2234, 0.9467, 0.7933, 1.137, 1.339, 1.536, 3.088, 0, 0.07322, 0.281, 0.05757, 0.1985,
+     0.1236, 0.1061, 0.09257, 2.034, 0.1429},
+    {QG_KERNEL_TILE64, 64, 64, 3.18, 0.1188, 0.0262, 0.1003, 0.2297, 0.6596, 4.039, 0, 0.1417, 0.1046, 0.1366, 0.3663,
+     0.09615, 0.09498, 0.0814, 0.908, 1.045, 1.087, 1.341, 1.607, 2.876, 0.03544, 0.05423, 0.3726, 0.1756, 0.1533,
+     0.1031, 0.1138, 0.03702, 5.898, 0.04424},
+    {QG_KERNEL_TILE64K4, 64, 64, 3.925, 0.08141, 0.01436, 0.1072, 0.3085, 1.888, 3, 0.1155, 0.2087, 0.1261, 0.1871,
+     0.395, 0.02942, 0.000062, 0.06287, 1.051, 1.419, 1.07, 1.339, 1.61, 3.744, 0.03794, 0.07046, 0.355, 0.515, 0.2,
+     0.1045, 0.1487, 0.01903, 0.005161, 0.03733},
+    {QG_KERNEL_TILE64X32K8, 64, 32, 3.889, 0.05234, 0.0141, 0.05647, 0.1724, 2.277, 3, 0.1677, 0.1599, 0.1178, 0.5721,
+     0.3305, 0.2734, 0.0001932, 0.1679, 1.085, 1.86, 1.402, 1.57, 1.172, 2.852, 0.008428, 0.06507, 0.6046, 0.3201,
+     0.2513, 0.06846, 0.2169, 0.358, 83.9, 0.01019},
+    {QG_KERNEL_TILE128, 128, 128, 4.588, 0.1417, 0.1085, 0.281, 0.4045, 1.211, 4.552, 0.06927, 0.6241, 0.4908, 0.3061,
+     0.1743, 0.01932, 0.1741, 0, 1.194, 1.42, 1.104, 1.299, 10.24, 11.93, 0.01551, 0.05237, 0.7058, 0.1994, 0.000086,
+     0.1634, 0.09938, 0.04505, 10.17, 0.1441},
+    {QG_KERNEL_TILE128, 128, 64, 5.169, 0.08882, 0.04409, 0, 0, 0, 3, 0.654, 0, 0.4652, 0, 0.5053, 0, 0.6046, 1.463,
+     1.016, 1.37, 0, 0, 6.708, 0, 0.08092, 0.05976, 0.9807, 0, 0.000098, 0.1067, 0.01832, 0.01736, 14.16, 0.04551},
+    {QG_KERNEL_TILE128X256, 128, 256, 6.811, 0.1843, 0.1932, 0.4171, 0.2032, 2.807, 5.18, 0.3315, 0.4456, 0.626, 0.5827,
+     0.4845, 0.03141, 0.6825, 0.8138, 1.077, 1.314, 1.101, 1.184, 22.27, 23.48, 0.0352, 0.06443, 0.2875, 0.3988, 0.1165,
+     0.201, 0.08051, 0.06708, 16.31, 0.3304},
+    {QG_KERNEL_TILE256, 256, 256, 15.64, 0.2597, 0.4748, 0.7312, 0.401, 10.36, 3.674, 0.00005, 0.0004028, 0.4451, 1.441,
+     1.151, 0.003431, 2.957, 0.0002237, 0.8557, 1.931, 1.107, 1.306, 46.77, 53.72, 0.000361, 0, 0.0003799, 2.048,
+     0.0006701, 0.1854, 0.1629, 0.0001407, 11.17, 0.1874},
 };
 const stream_price k_stream_price[] = {
-    {QG_KERNEL_SKINNY16, 16, false, 3.248, 0.3011, 0.0103, 0.7545, 7.886, 0.002382, 1.5, 0.2053, 0.01181, 0.2656,
-     0.001259, 0.0007677, 1.014, 1.501, 1.362, 1.252, 0.9263, 0.005715, 0.007775, 0.1323, 0.00701, 0.01281, 0.2002,
-     0.01251},
-    {QG_KERNEL_SKINNY16, 16, true, 3.445, 0.3273, 0.4135, 0.6321, 2.408, 0.002726, 1.5, 0.000463, 0.5543, 0.3, 0, 0, 0,
-     0, 0, 0, 0, 2.667, 2.253, 0, 0.01066, 0.1154, 0.06927, 0.01455},
-    {QG_KERNEL_SKINNY32, 32, false, 3.794, 0.5317, 0.0001372, 0.6106, 8.619, 0.002875, 1.5, 0.1803, 0.01243, 1.051,
-     0.02942, 0.5228, 0.9083, 1.801, 1.195, 1.826, 1.573, 0, 0.008883, 0.1495, 0.005953, 0.0161, 0.2054, 0.003701},
-    {QG_KERNEL_SKINNY32, 32, true, 4.353, 0.5132, 0.5825, 0.6666, 3.653, 0.005709, 1.5, 0.001424, 3.269, 0.3, 0, 0, 0, 0,
-     0, 0, 0, 0.7229, 1.039, 0.02223, 0.337, 0.01741, 0.0857, 0.01577},
-    {QG_KERNEL_SKINNY64, 64, false, 4.311, 0.7306, 0.04666, 0.6025, 10.63, 0.004096, 0.3285, 0.3214, 0.4498, 1.922,
-     0.01813, 0.09132, 0.998, 2.093, 0.8926, 2.174, 1.303, 0.06318, 4.371, 0.1457, 0.004449, 0.004859, 0.2676, 0.004231},
-    {QG_KERNEL_SKINNY64, 64, true, 5.725, 0.6746, 0.7333, 0.6037, 10.68, 0.005933, 0.7131, 0.3424, 0.8863, 0.3, 0, 0, 0,
-     0, 0, 0, 0, 0.4748, 0.77, 0.07867, 0.01022, 0.007475, 0.2029, 0.01652},
+    {QG_KERNEL_SKINNY16, 16, 3.259, 0.2898, 0.0621, 0.7321, 6.951, 0.002238, 1.5, 0.211, 0.0003486, 0.2618, 0.0004322,
+     0.000056, 0.9947, 1.503, 1.49, 1.373, 0.8615, 0.07123, 0.7987, 0.1232, 0.01934, 0.06101, 0.1997, 0.0005517, 0.01872,
+     27.09},
+    {QG_KERNEL_SKINNY32, 32, 3.797, 0.4371, 0, 0.5753, 8.16, 0.002703, 1.5, 0.1916, 0.3033, 1.095, 0.05719, 0.5562,
+     0.8669, 1.922, 1.176, 1.834, 1.263, 0, 0.45, 0.1253, 0, 0.1134, 0.01515, 0, 0.06855, 0.03129},
+    {QG_KERNEL_SKINNY64, 64, 4.482, 0.4499, 0.8834, 0.5566, 9.513, 0.003915, 0.3265, 0.3626, 1.032, 1.984, 0.03271,
+     0.1513, 1.088, 2.875, 0.9483, 2.296, 0.625, 0.0002661, 5.574, 0.2381, 0, 0, 0.1749, 0, 0, 28.37},
+};
+const wide_price k_wide_price[] = {
+    {QG_KERNEL_SKINNY16, 16, 3.018, 0.6309, 0.1771, 0.9375, 0.4238, 0.6907, 0.555, 0.02235, 0.06941, 12.78, 0.1961,
+     1.224, 0.1188, 0.04988, 0.04208, 0.04332},
+    {QG_KERNEL_SKINNY32, 32, 3.598, 0.3995, 0.3752, 0.8966, 1.602, 1.327, 0.00488, 0.002176, 0.0921, 5.651, 0.2962,
+     1.208, 0.1298, 0.00302, 0.03196, 0.03187},
+    {QG_KERNEL_SKINNY64, 64, 4.558, 0.5822, 0.5065, 1.33, 2.868, 1.367, 0.1138, 0.1226, 0.0964, 5.11, 0.3156, 1.342,
+     0.0004045, 0.0002729, 0.0002475, 0.3719},
 };
 
 enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
@@ -241,50 +253,65 @@ double tile_price_us(const tile_price& c, int M, int N, int K, const call_form& 
   const double out_fix[] = {0.0, c.rag_fix, c.f32_fix, c.i32_fix}, out_epi[] = {0.0, c.rag_epi, c.f32_epi, c.i32_epi};
   const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_thr[] = {1.0, c.thr4, c.thr1};
   const double fix = c.fix + out_fix[f.out] + a_fix[a] + (tail ? c.tail_fix : 0.0) + (left ? c.left_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0);
-  const double lat = c.lat * a_lat[a] * (f.bzp ? 1.0 + c.bzp_lat : 1.0) * (1.0 + c.tall * M / ((double)M + N));
+  const double lat = c.lat * a_lat[a] * (f.bzp ? 1.0 + c.bzp_lat : 1.0) * (1.0 + c.tall * M / ((double)M + N)) *
+                     (N % c.bn != 0 && N % c.bn <= c.bn / 2 ? 1.0 + c.half : 1.0);
   double us = larger(fix + kt * (lat + c.crowd * share_of_chip(wgs)), 2.5 + (double)M * (double)N * (wide ? 4.0 : 1.0) / (c.out * 1e6));
   if (wgs > 256) {
     const double epi = c.epi + out_epi[f.out] + (tail ? c.tail_epi : 0.0) + (left ? c.left_epi : 0.0);
     const double rounds = rounds_of(wgs), steps = rounds + c.fill * ((double)wgs / 256.0 - rounds);
     us = larger(us, 2.5 + rounds * epi + steps * kt * c.thr * a_thr[a] * (f.bzp ? 1.0 + c.bzp_thr : 1.0));
   }
-  return us + c.far * larger((double)M * (double)K * 1e-6 - 4.0, 0.0);
+  return us + c.far * larger((double)M * K * 1e-6 - 4.0, 0.0) + c.b_far * larger((double)K * N * 1e-6 - c.b_near, 0.0);
+}
+
+// megabytes that the XCDs fetch, an operand counted once for each: column block j of row block i runs on XCD (i * columns + j) % 8
+double fetched_mb(int M, int N, int K, int rows, int cols) {
+  const int columns = ceil_div(N, cols), row_blocks = ceil_div(M, rows), spread = columns % 8 ? 8 / (columns & -columns) : 1;
+  return ((double)(row_blocks < spread ? row_blocks : spread) * N + (double)(columns < 8 ? columns : 8) * M) * K * 1e-6;
 }
 
 double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
-  const long long blocks32 = tiles_of(M, N, c.rows, 32), wgs = c.wide ? blocks32 : 2 * blocks32;
+  const long long wgs = 2 * tiles_of(M, N, c.rows, 32);
   const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
   const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
   const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_wg_k[] = {1.0, c.wg_k4, c.wg_k1};
-  // waves of a workgroup and k blocks of a batch as in the launches
-  const int waves = !c.wide ? 16 : c.rows == 64 ? 8 : 4, per = !c.wide ? (c.rows == 64 ? 2 : 4) : c.rows == 64 ? 4 : 8;
-  const int blocks = ceil_div(ceil_div(K, 64), waves);  // of a wave
+  const int per = c.rows == 64 ? 2 : 4, blocks = ceil_div(ceil_div(K, 64), 16);  // of a batch, of a wave
   const double n = (double)(ceil_div(blocks, per) - 1), bzp = f.bzp ? 1.0 + c.bzp_lat : 1.0;
   const double fix = c.fix + out_fix[f.out] + a_fix[a] + (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0) -
-                     (a == 0 && K % (64 * waves * per) == 0 ? c.straight : 0.0);
-  double us = fix + (K * (c.lat + c.crowd * share_of_chip(wgs)) / 1024.0 + blocks * c.block + n * c.batch) * bzp * a_lat[a];
+                     (a == 0 && K % (1024 * per) == 0 ? c.straight : 0.0);
+  double us = fix + (K * (c.lat + c.crowd * share_of_chip(wgs)) / 1024.0 + blocks * c.block + n * c.batch) * bzp * a_lat[a] +
+              c.fetch * larger(fetched_mb(M, N, K, c.rows, 16) - c.near, 0.0);
   if (wgs > 256) us = larger(us * (1.0 + c.second), 2.5 + (double)wgs * (c.wg + out_wg[f.out] + K * c.wg_k * bzp * a_wg_k[a]) * 1e-3);
   const double a_bytes = (double)M * (double)K;
-  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, c.wide ? 32 : 16) / (c.a_far * 1e7));
+  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, 16) / (c.a_far * 1e7));
   return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0);
+}
+
+double wide_price_us(const wide_price& c, int M, int N, int K, const call_form& f) {
+  const long long wgs = tiles_of(M, N, c.rows, 32);
+  const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, rounds = rounds_of(wgs) - 1.0, pairs = (double)((wgs + 511) / 512) - 1.0;
+  const int n = K / 2048;
+  return c.fix + out_fix[f.out] + (f.bzp ? c.bzp_fix : 0.0) + n * (c.lat * (f.bzp ? 1.0 + c.bzp_lat : 1.0) + c.crowd * share_of_chip(wgs)) +
+         (n > 1 ? c.jump : 0.0) + rounds * (c.round + (f.out >= OUT_F32 ? c.wide_round : 0.0) + n * c.round_lat) + pairs * (c.pair + n * c.pair_lat) +
+         c.fetch * larger(fetched_mb(M, N, K, c.rows, 32) - c.near, 0.0) + c.far * larger((double)M * K * 1e-6 - 4.0, 0.0);
 }
 
 int price_select(int M, int N, int K, const call_form& f) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  for (const stream_price& c : k_stream_price) {
-    if (ceil_div(M, c.rows) > 65535) continue;
-    const bool wide = f.a_align == 16 && K % 2048 == 0 && (long long)ceil_div(M, c.rows) * ceil_div(N, 32) > 128;
-    if (wide != c.wide) continue;
-    const double us = stream_price_us(c, M, N, K, f);
-    if (us < best_us) best_us = us, best = c.kernel;
-  }
+  const auto wide = [&](int rows) { return f.a_align == 16 && K % 2048 == 0 && tiles_of(M, N, rows, 32) > 128; };
+  const auto take = [&](int kernel, double us) {
+    if (us < best_us) best_us = us, best = kernel;
+  };
+  for (const stream_price& c : k_stream_price)
+    if (ceil_div(M, c.rows) <= 65535 && !wide(c.rows)) take(c.kernel, stream_price_us(c, M, N, K, f));
+  for (const wide_price& c : k_wide_price)
+    if (ceil_div(M, c.rows) <= 65535 && wide(c.rows)) take(c.kernel, wide_price_us(c, M, N, K, f));
   const bool few = qg_tile128_few(M, N, K);
   for (const tile_price& c : k_tile_price) {
     if (c.kernel == QG_KERNEL_TILE128 && (c.bn == 64) != few) continue;
     if (c.kernel == QG_KERNEL_TILE256 && K < 256) continue;  // 128 x 256 tiles there, without the loop priced here
-    const double us = tile_price_us(c, M, N, K, f);
-    if (us < best_us) best_us = us, best = c.kernel;
+    take(c.kernel, tile_price_us(c, M, N, K, f));
   }
   return best;
 }

@@ -55,6 +55,13 @@ def test_kernel_select_answers_for_whole_steps():
     (64, 64, 128, ("tile64k1",)),                            # 3.5, 3.2
     (9, 7996, 5824, ("tile64x32k8",)),                       # 15.1, 11.0
     (39460, 865, 87, ("tile128",)),                          # 26.9, 22.3 (rows of A and C off 16 bytes; the choice is the same)
+    (80, 3072, 2048, ("skinny16",)),                         # 6.1, 4.8: rounds of the few-fat-waves form
+    (96, 2048, 2048, ("skinny32", "skinny16")),              # 5.3, 4.6
+    (640, 128, 8192, ("skinny16",)),                         # 9.7, 8.2
+    (320, 768, 8192, ("skinny32",)),                         # 12.7, 10.2
+    (2048, 128, 4096, ("tile64x32k8",)),                     # 9.8, 8.6
+    (12288, 384, 2048, ("tile128",)),                        # 21.3, 17.5: the last column of 256 half full
+    (32768, 4096, 256, ("tile128x256",)),                    # 82.8, 69.9
 ])
 def test_shapes_that_were_slow(M, N, K, fast):
     from paper_2101_05615_amd import qgemm as q
