@@ -905,7 +905,6 @@ static int gemm_common(const uint8_t* A_dev, int M, int lda, const qg_packed_b* 
   a->sp_entries = Bp->entries;
   a->sp_total = (int)Bp->nnz;
   a->lda = lda;
-  a->a_vec = aligned(A_dev, 16) && (lda % 16 == 0);
   a->ksplit = 1;
   a->ks_per = a->kb64;
   return QG_OK;
@@ -1098,10 +1097,7 @@ static int f32_fused_common(const float* A_dev, int M, int lda, float a_inv_scal
   if (!aligned(A_dev, 4)) return QG_EALIGN;
   int rc = gemm_common(reinterpret_cast<const uint8_t*>(A_dev), M, lda, Bp, a);
   if (rc != QG_OK) return rc;
-  a->a_vec = aligned(A_dev, 16) && (lda % 4 == 0);  // rows of floats that 16-byte loads may take
   a->q_inv = a_inv_scale;
-  a->q_lo = (float)(0 - a_zp);
-  a->q_hi = (float)(255 - a_zp);
   a->q_zp = (float)a_zp;
   *fused = true;
   return QG_OK;
@@ -1262,7 +1258,6 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
     if (!stream_ok) return QG_EUNSUPPORTED;
     a.ksplit = 1;
     a.ks_per = a.kb64;
-    a.a_vec = 1;
     a.c_vec = aligned(out, 4) && (ldc % 4 == 0);
     a.c_wt = (long long)a.M * N <= (1 << 18);
     const hipError_t e = qg_launch_conv_skinny(a, kernel, stream);

@@ -2,20 +2,20 @@
 // stresses ("M is sometimes very small", Appendix C; int32 accumulation for the
 // bandwidth-bound shapes, Sec. 4).  Every byte of B is used exactly once, so B
 // fragments go STRAIGHT from HBM into MFMA operand registers: the packed layout
-// makes each wave load one contiguous KiB (16 B per lane).  LDS is used only to
-// combine the partial sums of the 16 waves that split K.
+// makes each wave load one contiguous KiB (16 B per lane).
 //
-// One workgroup owns one 16-column fragment column of B over all of K; wave w
+// One workgroup owns one or two 16-column fragment columns of B over all of K; its 4 to 16 waves split K, and wave w
 // takes a contiguous range of 64-deep k blocks and issues a whole batch of loads
 // before the first MFMA so that the whole weight matrix is in flight at once; the next
-// batch's weights are requested before the wave waits for the current batch's activations.
+// batch is requested before the wave waits for the current one.
 // A (the row block, at most 64 rows) comes from L2, is row-summed on its raw bytes (v_sad_u8) and
 // shifted to int8 (xor 0x80) on the way, as in the large kernel.  Each wave stages its own K-slice of
 // the row block, batch by batch, through a private 4 or 8 KiB of LDS with global_load_lds: a request
 // reads whole 128- or 256-byte row segments (MFMA operand order would touch 16 rows x 64 B per load,
 // half-used lines, which cost more than the weight stream itself at 64 rows), and the fragments are then
-// fetched from LDS in operand order.  Unaligned A, ragged K and partial batches take the same route
-// with the lanes copying the bytes themselves.
+// fetched from LDS in operand order.  Rows at any address, any K and batches that K cuts take the same route (SRC_U8 below): copied
+// by the lanes, chunk by chunk and at the end of K byte by byte, such a batch held up its whole workgroup (1 x 4320 x 4122
+// 9.7 -> 5.8 us, 42 x 1408 x 5897 14.0 -> 7.4).
 //
 // Outlier-split weights (Sec. 2.2, B = B' + B_sparse): B' streams in at 4 bits per weight -- half the bytes
 // of the shape this kernel exists for -- and is widened to int8 operand dwords with two bit operations
@@ -26,7 +26,8 @@
 // (row, entry) pair and lane, added up in LDS, was what this took before: vector instructions, 16 rows of them per
 // entry, bound it (16 x 8192 x 8192, weights in the memory-side cache, with 0.7 % of outliers 17.5 -> 10.9 us; 0.1 % 10.8, 1 %
 // 11.2, 2 %, more than 64 entries in some batches, 13.2, and none at all, where batches skip this, 8.5; with 0.5 % 64 x 4096 x 4096
-// 13.4 -> 7.7, 64 x 8192 x 8192 44 -> 20).
+// 13.4 -> 7.7, 64 x 8192 x 8192 44 -> 20).  What is left is the chain request, widen, scatter, read of a batch; with the next batch's
+// requests in flight meanwhile and two columns per wave 16 x 8192 x 8192 with 0.5 % takes 10.3 us (13.3 before), 64 x 4864 x 6912 14.2 (17.6).
 //
 // M larger than the row block is covered by the second grid dimension: every row block streams
 // B again (from L2 / the memory-side cache when the blocks run close together), which beats the
@@ -60,9 +61,14 @@ __device__ __forceinline__ void request_a(const uint8_t* a_base, unsigned voff, 
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(a_base) : "memory");
 }
 
-// The same with a 64-bit per-lane address (the convolution's requests go to the image or to a table row).
+// The same with a 64-bit per-lane address (requests that may go to a table row).
 __device__ __forceinline__ void request_a64(const uint8_t* addr, unsigned lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(addr) : "memory");
+}
+
+// 4 bytes per lane, to lds + lane * 4
+__device__ __forceinline__ void request_dword(const void* addr, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(addr) : "memory");
 }
 
 // Explicit wait: at most LEFT vector-memory operations of this wave still in flight (they complete in order).
@@ -73,20 +79,14 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LEFT) : "memory");
 }
 
-// ANYALIGN: rows of A that are not 16-byte aligned.  The requests and vector loads take any address; the variant
-// exists so that the aligned one keeps its code (and its timing) to the instruction.
-// SIMPLE: the straight-line variant for the common case the host has checked -- 8-bit weights, 16-byte aligned
-// rows, K a whole number of 64-deep blocks and every wave of every slice a whole number of batches: no partial
-// batch, no lane-copied staging, every request issued by hand in a known order.
-// CPW (straight-line variant only): fragment columns per wave.  With two, a workgroup of four waves covers a whole
-// 32-column super-block: every activation fragment feeds two MFMAs, the workgroup stages half as many activation
-// bytes per weight byte, and few fat waves (16 weight loads in flight each) keep a large matrix streaming at the
-// rate of a plain read -- the shape for weights of tens of MiB, where the 16-wave form pays for its A traffic.
-// AF32: the activations are fp32 and are quantized to uint8 while they are staged (Appendix B: any packing routine for
-// A; Eq. (1) solved for the quantized value, the fixed sequence of the stand-alone quantization pass): the lanes load
-// 16 floats per 16-byte chunk of the staged block, convert and write the chunk to LDS, where row offsets and
-// fragments are taken from it as from any uint8 block.  A then points to floats and lda counts floats.
-// ACONV: the rows are the output pixels of a dense convolution and A is its NHWC image (the paper names convolution in
+// SRC: what a row of the staged block is.
+// SRC_U8: a row of A, from any address.  A batch that reaches past K requests the chunks behind it from a row of 0x80 bytes (the
+// int8 zero after the shift); the chunk that K cuts is loaded once, at the start, as the last 16 bytes of its row, and put in place
+// when its batch has arrived.
+// SRC_F32: fp32 activations, quantized to uint8 while they are staged (Appendix B: any packing routine for A; Eq. (1) solved for
+// the quantized value, the fixed sequence of the stand-alone quantization pass).  A then points to floats and lda counts
+// floats; a lane loads four consecutive floats, so that a load of the wave is 1 KiB of a row, and writes one dword of LDS.
+// SRC_CONV: the rows are the output pixels of a dense convolution and A is its NHWC image (the paper names convolution in
 // Sec. 1; im2col folded into the requests as in the tiled kernels): the K = R*S*Cin bytes of a row are R*S runs of
 // Cin channels (Cin a multiple of 64, so every 64-deep k block lies inside one filter tap), and the 16-byte chunk a
 // lane requests comes from its pixel at that tap, or from a constant row of theta_A bytes when the tap lies outside
@@ -94,34 +94,35 @@ __device__ __forceinline__ void wait_vm() {
 // row, 16-byte piece of the block), so the tap of a request is wave-uniform and lives on the scalar unit, moved on
 // block by block; a lane carries its pixel's byte offset and one validity bit per tap (R*S <= 32) per row block.
 // The staged batch is therefore laid out [k block][row block][16 rows][64 bytes] instead of whole row segments.
-template <int MODE, int MB, int NWAVES, int BATCH, bool B4, bool ANYALIGN, bool SIMPLE = false, int CPW = 1, bool AF32 = false,
-          bool ACONV = false>
-__global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8_t* A, const int8_t* Bp, const int M, const int N, const int K, const int kb64,
-                                                                   const int nb16_total, const int lda, const int ks_per, const int ksplit,
-                                                                   const qg_gemm_args p) {
+// CPW: fragment columns per wave.  With two, a workgroup covers a whole 32-column super-block: every activation fragment feeds
+// two MFMAs, the workgroup stages half as many activation bytes per weight byte, and few fat waves (16 weight loads in flight
+// each) keep a large matrix streaming at the rate of a plain read -- the shape for more workgroups than CUs.
+// DB: two staging regions per wave, so that a batch's activations are requested one batch ahead like its weights.
+// ONE: every wave of every slice has exactly one whole batch (checked by the host): straight code, nothing that K could cut
+// (16 x 4096 x 4096, 256 workgroups that start together: 4.60 us, 4.70 with the code for the other cases around it).
+constexpr int SRC_U8 = 0, SRC_F32 = 1, SRC_CONV = 2;
+template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool ONE = false>
+__global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAVES / 4) void qg_gemm_skinny_kernel(
+    const uint8_t* A, const int8_t* Bp, const int M, const int N, const int K, const int kb64, const int nb16_total, const int lda,
+    const int ks_per, const int ksplit, const qg_gemm_args p) {
   // The leading scalar arguments repeat what a wave needs before it can issue its first loads (the fields of the same
   // names in p): the file is compiled with kernel-argument preloading, so they arrive in scalar registers with the
   // wave instead of costing a cold trip to memory (measured: 0.4 us of a 5 us launch).
-  static_assert(!SIMPLE || (!B4 && !ANYALIGN), "the straight-line variant takes dense 8-bit weights and aligned rows");
-  static_assert(CPW == 1 || SIMPLE, "several fragment columns per wave: straight-line variant only");
-  static_assert(!AF32 || (!SIMPLE && !B4 && ANYALIGN), "fp32 activations: the lane-copied staging of the general variant");
-  static_assert(!ACONV || (!SIMPLE && !B4 && !ANYALIGN && !AF32), "convolution: the requested staging of the general variant");
-  static_assert(MB * CPW <= NWAVES && CPW <= BATCH, "one wave per (row block, fragment column) runs the output pipeline");
-  const bool a_vec = ANYALIGN || p.a_vec;  // whole 16-byte chunks may be moved as such
-  using chunk_t = typename std::conditional<ANYALIGN, qg_v4i_unaligned, v4i>::type;
+  static_assert(!B4 || (SRC == SRC_U8 && DB), "4-bit weights: rows of bytes, all requests of a batch one batch ahead");
+  static_assert(!ONE || (SRC == SRC_U8 && !B4 && !DB), "one whole batch of 8-bit weights and rows of bytes");
+  static_assert(SRC != SRC_F32 || !DB, "fp32 rows pass through registers, batch by batch");
+  static_assert(MB * CPW <= NWAVES, "one wave per (row block, fragment column) runs the output pipeline");
   // A through LDS (see the file header): per wave and batch, ROWS rows x ROWB bytes
   constexpr int ROWS = MB * 16, ROWB = BATCH * QG_FRAG_K, NCHUNK = ROWB / 16;
   constexpr int REGION = ROWS * ROWB, NREQ = REGION / 1024, RPR = 64 / NCHUNK;  // requests per batch, rows per request
   static_assert(NCHUNK == 8 || NCHUNK == 16 || NCHUNK == 32, "a request covers whole rows of 128, 256 or 512 bytes");
-  constexpr int PART_BYTES = NWAVES * MB * CPW * 64 * (int)sizeof(v4i);
-  constexpr int STAGE_BYTES = NWAVES * REGION;
-  // every wave leaves its K-split partial sums (MB * CPW KiB) at the start of its OWN staging region (MB * BATCH KiB) once
+  constexpr int WAVE_LDS = REGION * (DB ? 2 : 1);
+  // every wave leaves its K-split partial sums (MB * CPW KiB) at the start of its OWN staging region once
   // it is done with it: no wave waits for the others before it may write
-  static_assert(PART_BYTES <= STAGE_BYTES, "a wave's partial tile fits its staging region");
-  constexpr int UNION_BYTES = STAGE_BYTES;
+  static_assert(MB * CPW * 1024 <= WAVE_LDS, "a wave's partial tile fits its staging region");
+  static_assert(!B4 || REGION >= BATCH * QG_FRAG_BYTES, "the scattered fragments of a batch and column fit the wave's region");
   extern __shared__ __align__(16) unsigned char smem[];
-  int* rsp = reinterpret_cast<int*>(smem + UNION_BYTES);    // [mb][row][wave]
-  static_assert(!B4 || REGION >= BATCH * QG_FRAG_BYTES, "the scattered fragments of a batch fit the wave's region");
+  int* rsp = reinterpret_cast<int*>(smem + NWAVES * WAVE_LDS);    // [mb][row][wave]
 
   const int nb16 = blockIdx.x * CPW;  // first fragment column of this workgroup
   // columns held by fragment f: (f>>1)*32 + 16*(u&1) + 8*(f&1) + 4*(u>>1) + r, u<4, r<4
@@ -132,25 +133,23 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   const int ml = lane & 15, g = lane >> 4;
   const int m_base = blockIdx.y * (MB * 16);  // first row of this workgroup's row block
 
-  // The waves that run the output pipeline fetch its per-column constants early, not after the reduction -- but
-  // BEHIND the first batch's weight loads and activation requests (load_ep is called from the first batch): cold,
-  // they take a trip to HBM, and nothing on the request path may end up waiting for them (the compiler had paired
-  // a pending constant with an address computation and stalled the requests of exactly the wave the others wait for).
+  // The waves that run the output pipeline request its per-column constants early, not after the reduction -- but
+  // BEHIND the first batch's weight loads and activation requests: cold, they take a trip to HBM.  One request straight to LDS, 16
+  // columns of the four arrays, so that nothing waits for them and no registers are held (16 loads per lane before).
   // wave w < MB * CPW runs the output pipeline of row block w / CPW, fragment column nb16 + w % CPW
   const int red_mb = wave / CPW, red_c = wave % CPW;
   const int c0 = ((nb16 + red_c) >> 1) * 32 + 16 * (g & 1) + 8 * ((nb16 + red_c) & 1) + 4 * (g >> 1);  // this lane's 4 output columns
-  int ep_co[4] = {0, 0, 0, 0}, ep_bz[4] = {0, 0, 0, 0}, ep_bias[4] = {0, 0, 0, 0};
-  float ep_sc[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-  auto load_ep = [&]() {
+  int* const ep_s = rsp + NWAVES * ROWS + wave * 64;  // [column offset, theta_B, bias, scale][16 columns], waves w < MB * CPW
+  auto request_ep = [&]() {
     if (wave < MB * CPW) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int col = c0 + r;  // col_off / bzp are padded to N_pad, bias / scales are not
-        ep_co[r] = p.col_off[col];
-        ep_bz[r] = p.bzp[col];
-        ep_bias[r] = (MODE != QG_MODE_ACC32 && p.bias != nullptr && col < N) ? p.bias[col] : 0;
-        ep_sc[r] = (MODE != QG_MODE_ACC32 && col < N) ? p.scales[(size_t)col * p.scale_stride] : 1.0f;
+      const int u = (lane >> 2) & 3, col = ((nb16 + red_c) >> 1) * 32 + 16 * (u & 1) + 8 * ((nb16 + red_c) & 1) + 4 * (u >> 1) + (lane & 3);
+      // col_off / bzp are padded to N_pad, bias / scales are not
+      const void* src = (g == 0 ? p.col_off : p.bzp) + col;
+      if (MODE != QG_MODE_ACC32) {
+        if (g == 2) src = p.bias != nullptr && col < N ? static_cast<const void*>(p.bias + col) : qg_byte_rows.b[0];
+        if (g == 3) src = p.scales + (size_t)min(col, N - 1) * p.scale_stride;
       }
+      request_dword(src, (unsigned)(uintptr_t)((__attribute__((address_space(3))) int*)ep_s));
     }
   };
 
@@ -159,18 +158,20 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   // L2 channel at the same time)
   // (4-bit weights come in pairs of k blocks, so their slices hold an even number of blocks)
   // (ksplit > 1: this workgroup owns slice blockIdx.z of K, whole k blocks, an even number of them for 4-bit weights)
-  const int ks_begin = min(kb64, (int)blockIdx.z * ks_per), ks_end = min(kb64, ks_begin + ks_per);
+  // (plain shifts and additions up to the first loads: everything in front of them is latency)
+  const int blocks = B4 ? (int)((unsigned)(K + 2 * QG_FRAG_K - 1) / (2 * QG_FRAG_K) * 2) : (int)((unsigned)(K + QG_FRAG_K - 1) / QG_FRAG_K);  // that hold data
+  const int ks_begin = min(blocks, (int)blockIdx.z * ks_per), ks_end = min(blocks, ks_begin + ks_per);
   const int ks_len = ks_end - ks_begin;
-  const int per = B4 ? ((ks_len + 2 * NWAVES - 1) / (2 * NWAVES)) * 2 : (ks_len + NWAVES - 1) / NWAVES;
-  const int kb_begin = min(ks_end, ks_begin + ((wave + nb16) % NWAVES) * per);
+  const int per = B4 ? (int)((unsigned)(ks_len + 2 * NWAVES - 1) / (2 * NWAVES) * 2) : (int)((unsigned)(ks_len + NWAVES - 1) / NWAVES);
+  const int kb_begin = min(ks_end, ks_begin + (int)((wave + blockIdx.x) % NWAVES) * per);
   const int kb_end = min(ks_end, kb_begin + per);
 
   // outlier split: the entry offsets of all of this wave's batches, one per lane (batch b: lanes b and b+1), are
   // requested before anything else so that no batch waits for an offset before it can ask for its entries
-  int sp_offs = 0;
+  int sp_offs[CPW];
   if (B4 && kb_begin < kb_end) {
-    const int32_t* col = p.sp_ptr + (size_t)nb16 * kb64;
-    sp_offs = col[min(kb_begin + BATCH * lane, kb_end)];
+#pragma unroll
+    for (int c = 0; c < CPW; ++c) sp_offs[c] = p.sp_ptr[(size_t)(nb16 + c) * kb64 + min(kb_begin + BATCH * lane, kb_end)];
   }
 
   v4i acc[MB][CPW];
@@ -187,18 +188,23 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   const unsigned lane16 = lane * 16;
   const size_t b_step = (size_t)nb16_total * QG_FRAG_BYTES;  // one slab (8-bit: 64 deep, 4-bit: 128 deep) of the packed buffer
 
-  // per-lane byte offsets of the NREQ activation requests of a batch (a.a_vec: they fit 32 bits); with them the
+  // per-lane byte offsets of the NREQ activation requests of a batch; with them the
   // request address is a wave-uniform base plus a register that is never the target of a load, so issuing
   // the requests never has to wait for loads in flight
   unsigned a_off[NREQ];
-  // ACONV: of the piece a lane requests for row block mb: byte offset of its pixel at tap (0, 0), channel slice 0 (may
+  // at most a quarter of the block's rows exist: only they are requested (what LDS holds in place of the others reaches only
+  // accumulators that are never stored)
+  const bool few = SRC == SRC_U8 && NREQ % 4 == 0 && M - m_base <= ROWS / 4;
+  constexpr int FEW = NREQ / 4 > 0 ? NREQ / 4 : 1;
+  // SRC_CONV: of the piece a lane requests for row block mb: byte offset of its pixel at tap (0, 0), channel slice 0 (may
   // be negative) and the taps of that pixel that lie inside the image; wave-uniform: the tap of the next k block
   int cv_pix[MB];
   unsigned cv_mask[MB];
   int cv_cc = 0, cv_kw = 0, cv_kh = 0;
-  const int cv_nc = ACONV ? p.cv_Cin / QG_FRAG_K : 1;  // k blocks per tap
-  const uint8_t* const cv_azp_row = qg_byte_rows.b[ACONV ? p.cv_azp : 0];
-  if (ACONV) {
+  const int cv_nc = SRC == SRC_CONV ? p.cv_Cin / QG_FRAG_K : 1;  // k blocks per tap
+  const uint8_t* const cv_azp_row = qg_byte_rows.b[SRC == SRC_CONV ? p.cv_azp : 0];
+  const uint8_t* const pad_row = qg_byte_rows.b[128];
+  if (SRC == SRC_CONV) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int r = mb * 16 + (lane >> 2);
@@ -217,201 +223,272 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
     cv_cc = kb_begin - tap * cv_nc;
     cv_kh = tap / p.cv_S;
     cv_kw = tap - cv_kh * p.cv_S;
-  }
+  } else {
 #pragma unroll
-  for (int jj = 0; jj < NREQ; ++jj) {
-    const int r = jj * RPR + lane / NCHUNK;
-    a_off[jj] = (unsigned)min(m_base + r, M - 1) * (unsigned)lda + ((unsigned)((lane ^ r) & (NCHUNK - 1)) << 4);
+    for (int jj = 0; jj < NREQ; ++jj) {
+      const int r = jj * RPR + lane / NCHUNK;
+      a_off[jj] = (unsigned)min(m_base + r, M - 1) * (unsigned)lda + ((unsigned)((lane ^ r) & (NCHUNK - 1)) << 4);
+    }
   }
+  // SRC_U8: the last 16 bytes of row `lane` (K >= 16)
+  bool cut = false;  // (uniform) this wave has the chunk that K cuts
+  v4i row_end;
+  auto load_row_end = [&]() {
+    cut = SRC == SRC_U8 && (K & 15) != 0 && kb_end == blocks;
+    if (cut) {
+      const uint8_t* const row = A + (size_t)min(m_base + lane % ROWS, M - 1) * lda;
+      if (K >= 16)
+        row_end = *reinterpret_cast<const qg_v4i_unaligned*>(row + (K - 16));
+      else
+        row_end = qg_load_a_chunk(row, K, false);
+    }
+  };
 
-  // Weight requests of one batch: NLOAD loads of 16 bytes per lane, kept RAW (the 4-bit units are widened only
+  // Weight requests of one batch: 16 bytes per lane each, kept RAW (the 4-bit units are widened only
   // when they are consumed, so that nothing waits for them before the activations have been requested too).
-  constexpr int NLOAD = B4 ? BATCH / 2 : BATCH;
+  constexpr int NLOAD = (B4 ? BATCH / 2 : BATCH) * CPW;
   static_assert(!B4 || BATCH % 2 == 0, "4-bit weights are fetched in pairs of k blocks");
   // (every element is loaded unconditionally -- blocks past the end of the slice re-read its last block and are
   // never used -- so that the loaded registers are plain values and no copy has to wait for them)
-  auto load_b = [&](int kb0, v4i (&raw)[NLOAD]) {
+  const int8_t* wptr = bcol + (size_t)(B4 ? kb_begin >> 1 : kb_begin) * b_step;  // B4: kb_begin and kb_end are even
+  auto load_w = [&](int kb0, v4i (&raw)[NLOAD]) {  // batch by batch
+    constexpr int STEP = B4 ? 2 : 1;
 #pragma unroll
-    for (int i = 0; i < NLOAD; ++i) {
-      const int kbi = min(kb0 + (B4 ? 2 * i : i), kb_end - 1);  // B4: kb0 and kb_end are even
-      raw[i] = *reinterpret_cast<const v4i*>(bcol + (size_t)(B4 ? kbi >> 1 : kbi) * b_step + lane16);
+    for (int i = 0; i < NLOAD / CPW; ++i) {
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) raw[i * CPW + c] = *reinterpret_cast<const v4i*>(wptr + c * QG_FRAG_BYTES + lane16);  // (adjacent KiBs)
+      wptr += ONE || kb0 + (i + 1) * STEP < kb_end ? b_step : (size_t)0;
     }
   };
-  auto operand = [&](const v4i (&raw)[NLOAD], int j) -> v4i {
-    if (!B4) return raw[j];
-    const v4i w = raw[j >> 1];
+  auto operand = [&](const v4i (&raw)[NLOAD], int j, int c) -> v4i {
+    if (!B4) return raw[j * CPW + c];
+    const v4i w = raw[(j >> 1) * CPW + c];
     const unsigned lo = (unsigned)((j & 1) ? w.z : w.x), hi = (unsigned)((j & 1) ? w.w : w.y);
     return (v4i){(int)(lo & 0x0F0F0F0Fu), (int)((lo >> 4) & 0x0F0F0F0Fu), (int)(hi & 0x0F0F0F0Fu),
                  (int)((hi >> 4) & 0x0F0F0F0Fu)};
   };
 
-  // One batch: its weights were requested one batch earlier (into `cur`); request its activations and the NEXT
-  // batch's weights (into `nxt`), then wait for the activations only.  Requests complete in order, so
-  // "at most NLOAD outstanding" means that everything older than the next batch's weights has arrived.
-  auto batch = [&](int kb, const v4i (&cur)[NLOAD], v4i (&nxt)[NLOAD], const bool has_next, auto first_tag) {
-    constexpr bool FIRST = decltype(first_tag)::value;
-    // whole rows of BATCH k blocks are requested even when the slice ends earlier: the surplus lies inside the
-    // row (it is the next wave's slice) and is simply not consumed
-    const bool staged = ACONV || (!AF32 && a_vec && (kb + BATCH) * QG_FRAG_K <= K);
-    unsigned char* region = smem + wave * REGION;
-    // outlier split: this batch's entries are one run; the first 64 are requested one per lane right behind the
-    // activations (always exactly one request, clamped into the buffer, so that the wait below can count it)
-    int sp_e0 = 0, sp_ne = 0, sp_first = 0;
-    auto sparse_request = [&]() {
-      if (B4) {
-        const int b = (kb - kb_begin) / BATCH;  // at most 64 batches per wave: K <= 32768 gives 64 blocks to each of eight waves
-        sp_e0 = __shfl(sp_offs, b);
-        sp_ne = __shfl(sp_offs, b + 1) - sp_e0;
-        sp_first = p.sp_entries[min(sp_e0 + lane, max(p.sp_total, 1) - 1)];
-      }
-    };
-    v4i af[MB][BATCH];
-    if (staged) {
-      // ROWS rows x ROWB bytes of A: NREQ requests of RPR whole rows into this wave's LDS region, chunk c of
-      // row r stored at chunk c ^ r so that the operand-order reads below are bank-conflict free
-      const uint8_t* a_base = A + (size_t)kb * QG_FRAG_K;  // wave-uniform
-      const unsigned region_lds = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)region);
-      if (ACONV) {
-#pragma unroll
-        for (int j = 0; j < BATCH; ++j) {
-          // (wave-uniform) a k block past K -- the zero padding of the packed weights -- is staged as 0x80 bytes like
-          // all K padding, a tap outside the image as theta_A bytes
-          const bool in_k = cv_kh < p.cv_R;
-          const unsigned tapbit = in_k ? 1u << (cv_kh * p.cv_S + cv_kw) : 0u;
-          const int toff = (cv_kh * p.cv_W + cv_kw) * p.cv_pix + cv_cc * QG_FRAG_K;
-          const uint8_t* const other = in_k ? cv_azp_row : qg_byte_rows.b[128];
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb)
-            request_a64((cv_mask[mb] & tapbit) != 0 ? A + (cv_pix[mb] + toff) : other, region_lds + (j * MB + mb) * 1024);
-          if (++cv_cc == cv_nc) {
-            cv_cc = 0;
-            if (++cv_kw == p.cv_S) cv_kw = 0, ++cv_kh;
-          }
-        }
-      } else
-#pragma unroll
-      for (int jj = 0; jj < NREQ; ++jj) request_a(a_base, a_off[jj], region_lds + jj * 1024);
-      asm volatile("" ::: "memory");
-      if (FIRST) load_ep();
-      sparse_request();
-      asm volatile("" ::: "memory");
-      if (has_next) {
-        load_b(kb + BATCH, nxt);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLOAD) : "memory");
-      } else {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      }
-    } else {
-      // any pointer, lda and K, partial batches: the lanes copy the block into the region themselves, 16-byte
-      // chunk by chunk (bytes past K as 0x80, the int8 zero after the shift), in the same swizzled layout
-      const int nchunk = min(BATCH, kb_end - kb) * 4;  // 16-byte chunks per row that this batch will consume
-      if constexpr (AF32) {
-        const float* Af = reinterpret_cast<const float*>(A);
-        constexpr int CH = ROWS * NCHUNK / 64;  // chunks per lane of a full batch
-        if (p.a_vec && nchunk == NCHUNK && (kb + BATCH) * QG_FRAG_K <= K) {
-          // whole batch inside K, rows of floats 16-byte aligned: two chunks' loads at a time (8 x 16 bytes per lane in
-          // flight; more would not fit the 128 registers of a 16-wave workgroup), then convert
-          constexpr int GRP = (CH >= 2 && MB == 1) ? 2 : 1;
-#pragma unroll 1
-          for (int t0 = 0; t0 < CH; t0 += GRP) {
-            float4 v[GRP][4];
-#pragma unroll
-            for (int t = 0; t < GRP; ++t) {
-              const int i = lane + 64 * (t0 + t), r = i / NCHUNK, lc = i % NCHUNK;
-              const float4* src = reinterpret_cast<const float4*>(Af + (size_t)min(m_base + r, M - 1) * lda + kb * QG_FRAG_K + (lc << 4));
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[t][e] = src[e];
-            }
-#pragma unroll
-            for (int t = 0; t < GRP; ++t) {
-              const int i = lane + 64 * (t0 + t), r = i / NCHUNK, lc = i % NCHUNK;
-              v4i w;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                unsigned d = qg_quantize_pack(v[t][e].x, p.q_inv, p.q_lo, p.q_hi, p.q_zp, 0, 0);
-                d = qg_quantize_pack(v[t][e].y, p.q_inv, p.q_lo, p.q_hi, p.q_zp, 1, d);
-                d = qg_quantize_pack(v[t][e].z, p.q_inv, p.q_lo, p.q_hi, p.q_zp, 2, d);
-                w[e] = (int)qg_quantize_pack(v[t][e].w, p.q_inv, p.q_lo, p.q_hi, p.q_zp, 3, d);
-              }
-              *reinterpret_cast<v4i*>(region + (r * NCHUNK + ((lc ^ r) & (NCHUNK - 1))) * 16) = w;
-            }
-          }
-        } else {
-          // any pointer, lda and K, partial batches: element by element, positions past K as 0x80
-#pragma unroll 1
-          for (int i = lane; i < ROWS * nchunk; i += 64) {
-            const int r = i / nchunk, lc = i % nchunk;
-            const int k0 = kb * QG_FRAG_K + (lc << 4);
-            const float* src = Af + (size_t)min(m_base + r, M - 1) * lda + k0;
-            v4i w;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              unsigned d = 0x80808080u;
-#pragma unroll
-              for (int b = 0; b < 4; ++b)
-                if (k0 + 4 * e + b < K) d = qg_quantize_pack(src[4 * e + b], p.q_inv, p.q_lo, p.q_hi, p.q_zp, b, d);
-              w[e] = (int)d;
-            }
-            *reinterpret_cast<v4i*>(region + (r * NCHUNK + ((lc ^ r) & (NCHUNK - 1))) * 16) = w;
-          }
-        }
-      } else
-#pragma unroll 1
-      for (int i = lane; i < ROWS * nchunk; i += 64) {
-        const int r = i / nchunk, lc = i % nchunk;     // row, logical chunk
-        const int c = r * NCHUNK + ((lc ^ r) & (NCHUNK - 1));
-        const int k0 = kb * QG_FRAG_K + (lc << 4);
-        const uint8_t* src = A + (size_t)min(m_base + r, M - 1) * lda + k0;
-        v4i v;
-        if (a_vec && k0 + 16 <= K)
-          v = *reinterpret_cast<const chunk_t*>(src);
-        else
-          v = qg_load_a_chunk(src, K - k0, false);  // byte by byte, bytes past K as 0x80
-        *reinterpret_cast<v4i*>(region + c * 16) = v;
-      }
-      if (FIRST) load_ep();
-      sparse_request();
-      if (has_next) load_b(kb + BATCH, nxt);
-    }
-#pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+  unsigned char* const region0 = smem + wave * WAVE_LDS;
+  const unsigned region0_lds = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)region0);
+
+  // ROWS rows x ROWB bytes of A: NREQ requests of RPR whole rows into this wave's region `buf`, chunk c of
+  // row r stored at chunk c ^ r so that the operand-order reads below are bank-conflict free.  Whole rows of BATCH k blocks are
+  // requested even when the wave's part of K ends earlier: the surplus is not consumed.
+  auto request_rows = [&](int kb, int buf) {
+    const unsigned dst = region0_lds + buf * REGION;
+    if constexpr (SRC == SRC_CONV) {
 #pragma unroll
       for (int j = 0; j < BATCH; ++j) {
-        const int r = mb * 16 + ml;
-        if (ACONV)  // [k block][row block][row][piece ^ (row / 4 % 4)]
-          af[mb][j] = *reinterpret_cast<const v4i*>(region + (j * MB + mb) * 1024 + ml * QG_FRAG_K + (((g ^ (ml >> 2)) & 3) << 4));
-        else
-          af[mb][j] = *reinterpret_cast<const v4i*>(region + r * ROWB + ((((4 * j + g) ^ r) & (NCHUNK - 1)) << 4));
-      }
+        // (wave-uniform) a k block past K -- the zero padding of the packed weights -- is staged as 0x80 bytes like
+        // all K padding, a tap outside the image as theta_A bytes
+        const bool in_k = cv_kh < p.cv_R;
+        const unsigned tapbit = in_k ? 1u << (cv_kh * p.cv_S + cv_kw) : 0u;
+        const int toff = (cv_kh * p.cv_W + cv_kw) * p.cv_pix + cv_cc * QG_FRAG_K;
+        const uint8_t* const other = in_k ? cv_azp_row : pad_row;
 #pragma unroll
-    for (int j = 0; j < BATCH; ++j)
-      if (kb + j < kb_end) {
-        const v4i bfj = operand(cur, j);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].x, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].y, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].z, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].w, 0u, rs[mb]);
-          const v4i a = af[mb][j] ^ (int)0x80808080;
-          acc[mb][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bfj, a, acc[mb][0], 0, 0, 0);
+        for (int mb = 0; mb < MB; ++mb)
+          request_a64((cv_mask[mb] & tapbit) != 0 ? A + (cv_pix[mb] + toff) : other, dst + (j * MB + mb) * 1024);
+        if (++cv_cc == cv_nc) {
+          cv_cc = 0;
+          if (++cv_kw == p.cv_S) cv_kw = 0, ++cv_kh;
         }
       }
+    } else {
+      const uint8_t* const a_base = A + (size_t)kb * QG_FRAG_K;  // wave-uniform
+      if (ONE || (kb + BATCH) * QG_FRAG_K <= K) {
+        if (few) {
+#pragma unroll
+          for (int jj = 0; jj < FEW; ++jj) request_a(a_base, a_off[jj], dst + jj * 1024);
+        } else {
+#pragma unroll
+          for (int jj = 0; jj < NREQ; ++jj) request_a(a_base, a_off[jj], dst + jj * 1024);
+        }
+      } else {
+        int l = lane;
+        asm volatile("" : "+v"(l));  // (opaque: what the requests of this rare batch need is not kept in registers for it)
+#pragma unroll
+        for (int jj = 0; jj < NREQ; ++jj) {
+          if (few && jj >= FEW) break;
+          const int r = jj * RPR + l / NCHUNK, k0 = kb * QG_FRAG_K + (((l ^ r) & (NCHUNK - 1)) << 4);
+          request_a64(k0 + 16 <= K ? a_base + a_off[jj] : pad_row, dst + jj * 1024);
+        }
+      }
+    }
+  };
+  // the chunk that K cuts, over what its request left there
+  auto put_row_end = [&](int kb, int buf) {
+    const int c = (K >> 4) - kb * (QG_FRAG_K / 16);  // its place in the batch
+    if (cut && c < NCHUNK) {
+      const int nv = K & 15;
+      v4i v = row_end;
+      if (K >= 16) {
+        // the last nv bytes of the 16 to the front, 0x80 behind them
+        unsigned d[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i] = (unsigned)v[i], d[i + 4] = 0x80808080u;
+        const int drop = 16 - nv;
+        if (drop & 8) {
+#pragma unroll
+          for (int i = 0; i < 6; ++i) d[i] = d[i + 2];
+        }
+        if (drop & 4) {
+#pragma unroll
+          for (int i = 0; i < 5; ++i) d[i] = d[i + 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (int)__builtin_amdgcn_alignbyte(d[i + 1], d[i], drop & 3);
+      }
+      const int r = lane % ROWS;
+      if (lane < ROWS) *reinterpret_cast<v4i*>(region0 + buf * REGION + r * ROWB + (((c ^ r) & (NCHUNK - 1)) << 4)) = v;
+      asm volatile("" ::: "memory");  // (the operand reads below are of other lanes' chunks; LDS operations of a wave run in order)
+    }
+  };
+  // fp32 rows: four floats per lane, a load is 4 rows x 64 floats of one k block.  Only the blocks that the wave consumes and the
+  // rows that exist, GRP loads in flight.
+  auto convert_rows = [&](int kb) {
+    const float* const Af = reinterpret_cast<const float*>(A);
+    constexpr int GRP = 8;
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    typedef v4f v4f_any __attribute__((aligned(4)));
+    const int nblk = min(BATCH, kb_end - kb), groups = (min(ROWS, M - m_base) + 3) / 4;
+    const int sh = groups <= 1 ? 0 : 32 - __builtin_clz(groups - 1), total = nblk << sh;  // load i: block i >> sh, rows 4 (i mod 2^sh) ...
+    int l = lane;
+    asm volatile("" : "+v"(l));  // (opaque: nothing of this is kept in registers across the batches)
+    const int q = l & 15;        // this lane's dword of the block
+    auto convert = [&](auto whole_tag) {
+      constexpr bool WHOLE = decltype(whole_tag)::value;
+#pragma unroll 1
+      for (int t0 = 0; t0 < total; t0 += GRP) {
+        v4f v[GRP];
+#pragma unroll
+        for (int t = 0; t < GRP; ++t) {
+          const int i = min(t0 + t, total - 1), r = (i & ((1 << sh) - 1)) * 4 + (l >> 4), k = (kb + (i >> sh)) * QG_FRAG_K + q * 4;
+          const float* const row = Af + (size_t)min(m_base + r, M - 1) * lda;
+          if (WHOLE) {
+            v[t] = *reinterpret_cast<const v4f_any*>(row + k);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[t][e] = row[min(k + e, K - 1)];
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < GRP; ++t) {
+          const int i = min(t0 + t, total - 1), j = i >> sh, r = (i & ((1 << sh) - 1)) * 4 + (l >> 4);
+          unsigned d = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) d = qg_quantize_pack(v[t][e], p.q_inv, p.q_zp, e, d);
+          if (!WHOLE) {
+            const int nv = min(max(K - (kb + j) * QG_FRAG_K - q * 4, 0), 4);
+            const unsigned keep = nv == 4 ? 0xFFFFFFFFu : (1u << (8 * nv)) - 1u;
+            d = (d & keep) | (0x80808080u & ~keep);
+          }
+          *reinterpret_cast<unsigned*>(region0 + r * ROWB + (((4 * j + (q >> 2)) ^ r) & (NCHUNK - 1)) * 16 + (q & 3) * 4) = d;
+        }
+      }
+    };
+    if ((kb + nblk) * QG_FRAG_K <= K)
+      convert(std::true_type{});
+    else
+      convert(std::false_type{});
+    asm volatile("" ::: "memory");
+  };
+
+  // outlier split: a batch's entries are one run per fragment column; the first 64 are requested one per lane (always exactly one
+  // request, clamped into the buffer, so that the waits can count it)
+  struct entries {
+    int at[CPW], n[CPW], first[CPW];
+  };
+  auto request_entries = [&](int b, entries& e) {
+    if (B4) {
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) {  // at most 64 batches per wave: K <= 32768 gives 128 blocks to each of four waves
+        e.at[c] = __builtin_amdgcn_readlane(sp_offs[c], b);
+        e.n[c] = __builtin_amdgcn_readlane(sp_offs[c], b + 1) - e.at[c];
+        e.first[c] = p.sp_entries[min(e.at[c] + lane, max(p.sp_total, 1) - 1)];
+      }
+    }
+  };
+
+  auto consume = [&](int kb, int buf, const v4i (&cur)[NLOAD], const entries& ent) {
+    unsigned char* const region = region0 + buf * REGION;
+    // many outliers: the batch's entries beyond the first 64, four loads at a time, the first four in front of the dense products
+    // where registers allow it
+    constexpr bool EARLY = CPW == 1 || NWAVES < 16;
+    int more[CPW][4];
+    auto load_more = [&](int c, int i0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) more[c][u] = p.sp_entries[ent.at[c] + min(i0 + 64 * u + lane, ent.n[c] - 1)];
+    };
+    if (B4 && EARLY) {
+#pragma unroll
+      for (int c = 0; c < CPW; ++c)
+        if (ent.n[c] > 64) load_more(c, 64);
+    }
+    v4i af[MB][BATCH];
+    // (chunk 4 j + g of row r lies at (4 j + g) ^ r: the place of j = 0 with j turned into it.  Opaque, or the compiler keeps all
+    // the places in registers across the batches.)
+    int at = SRC == SRC_CONV ? ml * QG_FRAG_K + (((g ^ (ml >> 2)) & 3) << 4) : ml * ROWB + (((g ^ ml) & (NCHUNK - 1)) << 4);
+    asm volatile("" : "+v"(at));
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        if (SRC == SRC_CONV)  // [k block][row block][row][piece ^ (row / 4 % 4)]
+          af[mb][j] = *reinterpret_cast<const v4i*>(region + at + (j * MB + mb) * 1024);
+        else  // (rows 16 further: bit 4 of the row is turned into the chunk too)
+          af[mb][j] = *reinterpret_cast<const v4i*>(region + mb * (16 * ROWB) + (at ^ (((4 * j) ^ (mb * 16 & (NCHUNK - 1))) << 4)));
+      }
+    auto dense = [&](int j) {
+      v4i w[CPW];
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) w[c] = operand(cur, j, c);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].x, 0u, rs[mb]);
+        rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].y, 0u, rs[mb]);
+        rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].z, 0u, rs[mb]);
+        rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].w, 0u, rs[mb]);
+        af[mb][j] = af[mb][j] ^ (int)0x80808080;
+#pragma unroll
+        for (int c = 0; c < CPW; ++c) acc[mb][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[c], af[mb][j], acc[mb][c], 0, 0, 0);
+      }
+    };
+    if (ONE || kb + BATCH <= kb_end) {
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j) {
+        dense(j);
+        if (B4) __builtin_amdgcn_sched_barrier(0);  // (or all the widened weights of the batch are in registers at once)
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j)
+        if (kb + j < kb_end) dense(j);
+    }
     if (B4) {
       // sparse term of this batch.  The lanes hand each other bytes through the wave's region: its LDS operations run in order
       // -- the reads above, the zeros, the bytes, the reads --, and the empty statements keep the compiler, which looks at one
       // lane at a time, from reordering them or from taking a lane's own zeros for what it will read.
-      if (sp_ne > 0) {
+#pragma unroll
+      for (int c = 0; c < CPW; ++c) {
+        if (ent.n[c] <= 0) continue;
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int j = 0; j < BATCH; ++j) *reinterpret_cast<v4i*>(region + j * QG_FRAG_BYTES + lane * 16) = (v4i){0, 0, 0, 0};
         asm volatile("" ::: "memory");
-        for (int c0 = 0; c0 < sp_ne; c0 += 64) {
-          if (c0 + lane < sp_ne) {
-            const int ent = c0 == 0 ? sp_first : p.sp_entries[sp_e0 + c0 + lane];
-            const int kk = (ent & 0x7FFF) - kb * QG_FRAG_K, slot = (ent >> 16) & 15;
-            region[(kk >> 6) * QG_FRAG_BYTES + ((((kk >> 4) & 3) << 4) + slot) * 16 + (kk & 15)] = (unsigned char)(ent >> 24);
-          }
+        auto scatter = [&](int e) {
+          const int kk = (e & 0x7FFF) - kb * QG_FRAG_K, slot = (e >> 16) & 15;
+          region[(kk >> 6) * QG_FRAG_BYTES + ((((kk >> 4) & 3) << 4) + slot) * 16 + (kk & 15)] = (unsigned char)(e >> 24);
+        };
+        if (lane < ent.n[c]) scatter(ent.first[c]);
+        for (int i0 = 64; i0 < ent.n[c]; i0 += 4 * 64) {
+          int e[4];
+          if (!EARLY) load_more(c, i0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) e[u] = more[c][u];
+          if (EARLY && i0 + 4 * 64 < ent.n[c]) load_more(c, i0 + 4 * 64);
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (i0 + 64 * u + lane < ent.n[c]) scatter(e[u]);
         }
         asm volatile("" ::: "memory");
 #pragma unroll
@@ -419,92 +496,97 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
           if (kb + j < kb_end) {
             const v4i sf = *reinterpret_cast<const v4i*>(region + j * QG_FRAG_BYTES + lane * 16);
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-              acc[mb][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sf, af[mb][j] ^ (int)0x80808080, acc[mb][0], 0, 0, 0);
+            for (int mb = 0; mb < MB; ++mb) acc[mb][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(sf, af[mb][j], acc[mb][c], 0, 0, 0);
           }
-        asm volatile("" ::: "memory");  // these reads stay in front of the next batch's requests into the same region
+        asm volatile("" ::: "memory");  // these reads stay in front of the next requests into the same region
       }
     }
+    asm volatile("" ::: "memory");  // ... like the fragment reads
   };
 
-  if constexpr (SIMPLE) {
-    // per is a multiple of BATCH and at least BATCH (host-checked); everything below is wave-uniform control flow
-    const int nbatch = per / BATCH;
-    const int8_t* bptr = bcol + (size_t)kb_begin * b_step;
-    const uint8_t* aptr = A + (size_t)kb_begin * QG_FRAG_K;
-    unsigned char* region = smem + wave * REGION;
-    const unsigned region_lds = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char*)region);
-    auto issue_w = [&](int b, v4i (&raw)[BATCH * CPW]) {
-      const int8_t* bp = bptr + (size_t)b * BATCH * b_step;
-#pragma unroll
-      for (int i = 0; i < BATCH; ++i)
-#pragma unroll
-        for (int c = 0; c < CPW; ++c)  // the CPW fragments of one k block are adjacent KiBs
-          raw[i * CPW + c] = *reinterpret_cast<const v4i*>(bp + (size_t)i * b_step + c * QG_FRAG_BYTES + lane16);
-    };
-    // batch b: its weights were requested one batch earlier; request its activations, (first batch) the constants of
-    // the output pipeline, the next batch's weights; wait for everything older than those; consume
-    auto step = [&](int b, v4i (&cur)[BATCH * CPW], v4i (&nxt)[BATCH * CPW], auto first_tag) {
-      const uint8_t* ab = aptr + (size_t)b * (BATCH * QG_FRAG_K);
-#pragma unroll
-      for (int jj = 0; jj < NREQ; ++jj) request_a(ab, a_off[jj], region_lds + jj * 1024);
-      if (decltype(first_tag)::value) load_ep();
-      asm volatile("" ::: "memory");
-      if (b + 1 < nbatch) {
-        issue_w(b + 1, nxt);
-        wait_vm<BATCH * CPW>();
+  // Two register sets alternate.  A batch's weights are requested one batch ahead, its activations with them (DB) or at its
+  // start; requests complete in order, so "at most the next batch's outstanding" means that this one has arrived.
+  const int nbatch = kb_begin < kb_end ? (kb_end - kb_begin + BATCH - 1) / BATCH : 0;
+  auto step = [&](int b, int buf, v4i (&cur)[NLOAD], v4i (&nxt)[NLOAD], entries& ent, entries& ent_nxt) {
+    const int kb = kb_begin + b * BATCH;
+    const bool has_next = b + 1 < nbatch;
+    if constexpr (SRC == SRC_F32) {
+      convert_rows(kb);
+      if (b == 0) request_ep();
+      if (has_next) load_w(kb + BATCH, nxt);
+    } else if constexpr (DB) {
+      if (has_next) {
+        load_w(kb + BATCH, nxt);
+        request_rows(kb + BATCH, buf ^ 1);
+        request_entries(b + 1, ent_nxt);
+        asm volatile("" ::: "memory");
+        if (few)
+          wait_vm<NLOAD + FEW + (B4 ? CPW : 0)>();
+        else
+          wait_vm<NLOAD + NREQ + (B4 ? CPW : 0)>();
       } else {
         wait_vm<0>();
       }
-      v4i af[MB][BATCH];
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int j = 0; j < BATCH; ++j) {
-          const int r = mb * 16 + ml;
-          af[mb][j] = *reinterpret_cast<const v4i*>(region + r * ROWB + ((((4 * j + g) ^ r) & (NCHUNK - 1)) << 4));
-        }
-#pragma unroll
-      for (int j = 0; j < BATCH; ++j)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].x, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].y, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].z, 0u, rs[mb]);
-          rs[mb] = __builtin_amdgcn_sad_u8(af[mb][j].w, 0u, rs[mb]);
-          const v4i a = af[mb][j] ^ (int)0x80808080;
-#pragma unroll
-          for (int c = 0; c < CPW; ++c)
-            acc[mb][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(cur[j * CPW + c], a, acc[mb][c], 0, 0, 0);
-        }
-      asm volatile("" ::: "memory");  // the fragment reads stay in front of the next batch's requests into the same region
-    };
-    v4i w0[BATCH * CPW], w1[BATCH * CPW];
-    issue_w(0, w0);
-    step(0, w0, w1, std::true_type{});
-    for (int b = 1; b < nbatch; b += 2) {
-      step(b, w1, w0, std::false_type{});
-      if (b + 1 < nbatch) step(b + 1, w0, w1, std::false_type{});
+    } else {
+      if (b != 0) request_rows(kb, buf);
+      asm volatile("" ::: "memory");
+      if (has_next) {
+        load_w(kb + BATCH, nxt);
+        wait_vm<NLOAD>();
+      } else {
+        wait_vm<0>();
+      }
     }
-  } else
-  // two register sets alternate; the first batch is peeled (it also requests the output-pipeline constants)
-  if (kb_begin < kb_end) {
-    v4i braw0[NLOAD], braw1[NLOAD];
-    load_b(kb_begin, braw0);
-    batch(kb_begin, braw0, braw1, kb_begin + BATCH < kb_end, std::true_type{});
-    for (int kb = kb_begin + BATCH; kb < kb_end; kb += 2 * BATCH) {
-      batch(kb, braw1, braw0, kb + BATCH < kb_end, std::false_type{});
-      if (kb + BATCH < kb_end) batch(kb + BATCH, braw0, braw1, kb + 2 * BATCH < kb_end, std::false_type{});
+    put_row_end(kb, buf);
+    consume(kb, buf, cur, ent);
+  };
+  if constexpr (ONE) {
+    v4i w0[NLOAD];
+    load_w(kb_begin, w0);
+    request_rows(kb_begin, 0);
+    request_ep();
+    asm volatile("" ::: "memory");
+    wait_vm<0>();
+    consume(kb_begin, 0, w0, entries());
+  } else if (nbatch > 0) {
+    v4i w0[NLOAD], w1[NLOAD];
+    entries e0, e1;
+    if constexpr (B4) {  // (the offsets of the entries are waited for by the count of the loads behind them: no requests among those)
+      request_rows(kb_begin, 0);
+      load_row_end();
+      load_w(kb_begin, w0);
+      request_entries(0, e0);
+      request_ep();
+    } else {
+      load_w(kb_begin, w0);
+      if (SRC != SRC_F32) {
+        request_rows(kb_begin, 0);
+        load_row_end();
+        request_ep();
+      }
+    }
+    asm volatile("" ::: "memory");
+    step(0, 0, w0, w1, e0, e1);
+    for (int b = 1; b < nbatch; b += 2) {
+      step(b, DB ? 1 : 0, w1, w0, e1, e0);
+      if (b + 1 < nbatch) step(b + 1, 0, w0, w1, e0, e1);
     }
   } else {
-    load_ep();
+    request_ep();
   }
 
-  // ---- combine the 16 K-slices through LDS (a wave's fragment reads of its region are complete: the MFMAs consumed them)
+  wait_vm<0>();  // the output pipeline's constants (the waves without a part in it read what is there)
+  const int* const ep_r = wave < MB * CPW ? ep_s : rsp;
+  const v4i ep_co = *reinterpret_cast<const v4i*>(ep_r + 4 * g), ep_bz = *reinterpret_cast<const v4i*>(ep_r + 16 + 4 * g);
+  const v4i ep_bias = *reinterpret_cast<const v4i*>(ep_r + 32 + 4 * g);
+  const float4 ep_sc4 = *reinterpret_cast<const float4*>(ep_r + 48 + 4 * g);
+  const float ep_sc[4] = {ep_sc4.x, ep_sc4.y, ep_sc4.z, ep_sc4.w};
+
+  // ---- combine the waves' K-slices through LDS (a wave's fragment reads of its region are complete: the MFMAs consumed them)
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
 #pragma unroll
-    for (int c = 0; c < CPW; ++c) reinterpret_cast<v4i*>(smem + wave * REGION)[(mb * CPW + c) * 64 + lane] = acc[mb][c];
+    for (int c = 0; c < CPW; ++c) reinterpret_cast<v4i*>(region0)[(mb * CPW + c) * 64 + lane] = acc[mb][c];
     // the four lanes (ml, g = 0..3) of a row hold its byte sums over different k: add them with two lane swaps
     // (v_permlane32_swap / v_permlane16_swap; a shuffle through the LDS crossbar costs about 100 cycles each)
     const unsigned v = rs[mb];
@@ -523,7 +605,7 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
     static_assert(NWAVES % 4 == 0, "row sums are fetched four waves at a time");
     v4i t[NWAVES], tr[NWAVES / 4];
 #pragma unroll
-    for (int w = 0; w < NWAVES; ++w) t[w] = reinterpret_cast<const v4i*>(smem + w * REGION)[(mb * CPW + red_c) * 64 + lane];
+    for (int w = 0; w < NWAVES; ++w) t[w] = reinterpret_cast<const v4i*>(smem + w * WAVE_LDS)[(mb * CPW + red_c) * 64 + lane];
 #pragma unroll
     for (int w = 0; w < NWAVES / 4; ++w) tr[w] = reinterpret_cast<const v4i*>(rsp + (mb * 16 + ml) * NWAVES)[w];
 #pragma unroll
@@ -614,136 +696,68 @@ __global__ __launch_bounds__(NWAVES * 64) void qg_gemm_skinny_kernel(const uint8
   }
 }
 
-template <int MODE, int MB, int NWAVES, int BATCH, bool B4, bool ANYALIGN>
+template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool ONE = false>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
-  const int part = NWAVES * MB * 64 * (int)sizeof(v4i), stage = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K);
-  const int smem = (stage > part ? stage : part) + NWAVES * MB * 16 * (int)sizeof(int);
-  const int nfrag = ((a.N + 31) / 32) * 2;
+  constexpr int SMEM = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K) * (DB ? 2 : 1) + NWAVES * MB * 16 * (int)sizeof(int) + MB * CPW * 256;
+  static_assert(SMEM <= 160 * 1024, "LDS of a CU");
   const int mblocks = (a.M + MB * 16 - 1) / (MB * 16);
   if (mblocks > 65535 || a.ksplit < 1 || a.ksplit > 65535) return hipErrorInvalidValue;
   if (a.ksplit > 1 && (a.ws_cnt == nullptr || a.ws_slots == nullptr)) return hipErrorInvalidValue;
-  const dim3 grid(nfrag, mblocks, a.ksplit), block(NWAVES * 64);
-  if constexpr (!B4 && !ANYALIGN) {
-    // More 32-column super-blocks than half the CUs: few fat waves per workgroup, each streaming two fragment columns
-    // (four waves and batches of eight k blocks; eight waves and batches of four at 64 rows, whose staged batch is
-    // four times as large).  The 16-wave form would put two or more workgroups on a CU there, and a second
-    // one costs about as much as the first (80 x 1536 x 2048: 6.7 -> 3.4 us cold, 640 x 128 x 2048: 6.7 -> 3.7,
-    // 80 x 1024 x 4096: 6.9 -> 5.7).  Cold, 16 rows: 8192 x 4096 11.4 -> 9.4 us, 8192 x 8192 18.2 -> 15.0 (a plain
-    // read of the weights in the same launch shape: 14.4), 16384 x 16384 59.2 -> 48.7; 32 rows, 8192 x 8192:
-    // 21.0 -> 16.9; 64 rows: 8192 x 8192 26.3 -> 19.7, 2048 x 8192 10.8 -> 7.7, 128 x 8192 x 4096 27.7 -> 19.8 --
-    // every activation fragment feeds two MFMAs, so the workgroup stages half the activation bytes per weight byte,
-    // which at 64 rows is most of the traffic.  With 128 super-blocks or fewer half the CUs would idle and the
-    // 16-wave form stays ahead (16 x 4096 x 8192: 9.6 vs 10.9 us; 64 x 4096 x 4096: 8.1 vs 9.5).
-    constexpr int WN = MB == 4 ? 8 : 4, WB = MB == 4 ? 4 : 8, WC = 2;
-    if ((long long)((a.N + 31) / 32) * mblocks > 128 && a.K == a.kb64 * QG_FRAG_K && a.kb64 % a.ks_per == 0 &&
-        a.ks_per % (WN * WB) == 0) {
-      constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, WN, WB, false, false, true, WC>;
-      const int wpart = WN * MB * WC * 64 * (int)sizeof(v4i), wstage = WN * (MB * 16) * (WB * QG_FRAG_K);
-      const int wsmem = (wstage > wpart ? wstage : wpart) + WN * MB * 16 * (int)sizeof(int);
-      hipError_t e = qg_allow_smem<fn>(wsmem);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(fn, dim3((a.N + 31) / 32, mblocks, a.ksplit), dim3(WN * 64), wsmem, s, a.A, a.Bp, a.M, a.N, a.K, a.kb64,
-                         a.nb16, a.lda, a.ks_per, a.ksplit, a);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (!B4 && !ANYALIGN) {
-    // the straight-line variant: K is a whole number of blocks, all slices are equal and give every wave whole batches
-    if (a.K == a.kb64 * QG_FRAG_K && a.kb64 % a.ks_per == 0 && a.ks_per % (NWAVES * BATCH) == 0) {
-      constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, false, false, true>;
-      hipError_t e = qg_allow_smem<fn>(smem);
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(fn, grid, block, smem, s, a.A, a.Bp, a.M, a.N, a.K, a.kb64, a.nb16, a.lda, a.ks_per, a.ksplit, a);
-      return hipGetLastError();
-    }
-  }
-  hipError_t e = qg_allow_smem<qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, B4, ANYALIGN>>(smem);
+  constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, CPW, B4, SRC, DB, ONE>;
+  hipError_t e = qg_allow_smem<fn>(SMEM);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, B4, ANYALIGN>), grid, block, smem, s, a.A, a.Bp, a.M, a.N,
-                     a.K, a.kb64, a.nb16, a.lda, a.ks_per, a.ksplit, a);
+  hipLaunchKernelGGL(fn, dim3(((a.N + 31) / 32) * 2 / CPW, mblocks, a.ksplit), dim3(NWAVES * 64), SMEM, s, a.A, a.Bp, a.M, a.N, a.K,
+                     a.kb64, a.nb16, a.lda, a.ks_per, a.ksplit, a);
   return hipGetLastError();
 }
-
-// fp32 activations: the general variant with the converting staging (any alignment; a.a_vec says whether the rows of
-// floats are 16-byte aligned)
-template <int MODE, int MB, int NWAVES, int BATCH>
-hipError_t launch_af32(const qg_gemm_args& a, hipStream_t s) {
-  const int part = NWAVES * MB * 64 * (int)sizeof(v4i), stage = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K);
-  const int smem = (stage > part ? stage : part) + NWAVES * MB * 16 * (int)sizeof(int);
-  const int nfrag = ((a.N + 31) / 32) * 2;
-  const int mblocks = (a.M + MB * 16 - 1) / (MB * 16);
-  if (mblocks > 65535 || a.ksplit < 1 || a.ksplit > 65535) return hipErrorInvalidValue;
-  if (a.ksplit > 1 && (a.ws_cnt == nullptr || a.ws_slots == nullptr)) return hipErrorInvalidValue;
-  constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, false, true, false, 1, true>;
-  hipError_t e = qg_allow_smem<fn>(smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fn, dim3(nfrag, mblocks, a.ksplit), dim3(NWAVES * 64), smem, s, a.A, a.Bp, a.M, a.N, a.K, a.kb64, a.nb16,
-                     a.lda, a.ks_per, a.ksplit, a);
-  return hipGetLastError();
-}
-
-// dense convolution (a.cv_* describe it, a.A is the image): the general variant with the convolution's requests
-template <int MB, int NWAVES, int BATCH>
-hipError_t launch_conv(const qg_gemm_args& a, hipStream_t s) {
-  const int part = NWAVES * MB * 64 * (int)sizeof(v4i), stage = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K);
-  const int smem = (stage > part ? stage : part) + NWAVES * MB * 16 * (int)sizeof(int);
-  const int nfrag = ((a.N + 31) / 32) * 2;
-  const int mblocks = (a.M + MB * 16 - 1) / (MB * 16);
-  if (mblocks > 65535) return hipErrorInvalidValue;
-  constexpr auto fn = qg_gemm_skinny_kernel<QG_MODE_REQUANT, MB, NWAVES, BATCH, false, false, false, 1, false, true>;
-  hipError_t e = qg_allow_smem<fn>(smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(fn, dim3(nfrag, mblocks, 1), dim3(NWAVES * 64), smem, s, a.A, a.Bp, a.M, a.N, a.K, a.kb64, a.nb16, a.lda,
-                     a.kb64, 1, a);
-  return hipGetLastError();
-}
-
-// Outlier-split weights, eight or sixteen waves per workgroup: the chain of a workgroup's slowest wave, in halves of a batch of k
-// blocks.  Of the wave with the end of K, the blocks of a batch that reaches past it are copied lane by lane: a batch's time
-// each where single bytes are masked (K off the 16-byte grid), else half of that.  Every 64 outliers of a batch beyond the first
-// add another half (5 % of outliers: three).
-template <int BATCH>
-int split_chain(const qg_gemm_args& a, int waves) {
-  auto per_wave = [&](int blocks) { return (blocks + 2 * waves - 1) / (2 * waves) * 2; };  // (pairs of blocks, as in the kernel)
-  const int len = a.kb64 - (a.ksplit - 1) * a.ks_per, per = per_wave(len);  // the last slice of K
-  const int last = len - (len - 1) / per * per, full = (last - 1) / BATCH;  // blocks of the last wave, whole batches before its last one
-  const int copied = (a.kb64 - last + (full + 1) * BATCH) * QG_FRAG_K > a.K ? last - full * BATCH : 0;
-  const int batches = (per_wave(a.ks_per) + BATCH - 1) / BATCH, per_batch = 2 + (int)((long long)a.sp_total * BATCH * 16 / ((long long)a.kb64 * a.N * 64));
-  const int tail = per_batch * (full + 1) + copied * (a.K % 16 == 0 ? 1 : 2);
-  return tail > per_batch * batches ? tail : per_batch * batches;
-}
-// Eight where more than one workgroup falls to a CU (fewer waves, longer streams each: 16 x 8192 x 8192 15.5 -> 12.0 us) or
-// where their chain is no longer (64 x 512 x 5121 8.9 us against 12.0 with sixteen); sixteen where they shorten it (16 x 4096 x
-// 4096 4.3 against 4.5, 24 k blocks and a ragged end 4.6 against 5.3).  Over 1073 shapes of at most one workgroup per CU 0.5 %
-// behind the better one in the mean, 15 % at worst.
-template <int MB, int BATCH>
-bool split_few_waves(const qg_gemm_args& a) {
-  const long long wgs = (long long)(((a.N + 31) / 32) * 2) * ((a.M + MB * 16 - 1) / (MB * 16)) * a.ksplit;
-  return wgs > 256 || split_chain<BATCH>(a, 8) <= split_chain<BATCH>(a, 16);
-}
-// waves per workgroup and k blocks a wave requests at once, per row-block height
-template <int MODE, int MB, int BATCH, bool B4, bool ANYALIGN>
-hipError_t launch_waves(const qg_gemm_args& a, hipStream_t s) {
-  if constexpr (B4) {
-    if (split_few_waves<MB, BATCH>(a)) return launch<MODE, MB, 8, BATCH, B4, ANYALIGN>(a, s);
-  }
-  return launch<MODE, MB, 16, BATCH, B4, ANYALIGN>(a, s);
-}
-template <int MODE, bool B4, bool ANYALIGN>
-hipError_t launch_mb(const qg_gemm_args& a, int kernel, hipStream_t s) {
+// The build: waves, k blocks that a wave requests at once, fragment columns per wave.  Measured on some 150 shapes (M 1 .. 64, N
+// and K 512 .. 8192, graph replays, every build on each):
+//  - up to 16 k blocks four waves, up to 32 eight: one batch each, and the fewer waves there are to start and to add up the better
+//    (7 x 1408 x 891: sixteen waves 4.5 us, eight 3.65; 1 x 576 x 960 3.5 and, four, 3.0);
+//  - up to 64 sixteen waves (16 x 4096 x 4096: 5.2 against 6.2 with eight), beyond that eight again, whose batches follow each
+//    other without a gap (1 x 704 x 5888 4.0 against 4.5); with 4-bit weights, half the bytes per batch, sixteen throughout;
+//  - more workgroups of 16 columns than CUs: two fragment columns per wave (13 x 6400 x 3392 6.3 us; sixteen waves of one 8.2).
+//    With 4-bit weights and a long K sixteen waves do that too (16 x 8192 x 8192 with 0.5 % of outliers 10.2 against 12.2).  At most
+//    four rows and a long K, hardly any activations to share: four waves of one column again (3 x 4736 x 6848 8.4 us against 8.9, 2 x 7512 x 7936 11.1 against 12.3).
+template <int MODE, bool B4, int SRC>
+hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
+  constexpr bool DB = SRC != SRC_F32;
+  const int blocks = (a.K + QG_FRAG_K - 1) / QG_FRAG_K, kb = blocks < a.ks_per ? blocks : a.ks_per;
+  const int rows = 16 << (kernel - QG_KERNEL_SKINNY16);
+  const long long sb = (long long)((a.N + 31) / 32) * ((a.M + rows - 1) / rows) * a.ksplit;
+  const bool wide = sb > 128;
   switch (kernel) {
-    case QG_KERNEL_SKINNY16: return launch_waves<MODE, 1, 4, B4, ANYALIGN>(a, s);
-    case QG_KERNEL_SKINNY32: return launch_waves<MODE, 2, 4, B4, ANYALIGN>(a, s);
-    case QG_KERNEL_SKINNY64: return launch_waves<MODE, 4, 2, B4, ANYALIGN>(a, s);
+    case QG_KERNEL_SKINNY16:
+      if (kb <= 16 || (!B4 && wide && kb > 64 && a.M <= 4)) return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
+      if constexpr (B4) {
+        if (wide && sb <= 256 && kb > 36) return launch<MODE, 1, 16, 4, 2, B4, SRC, DB>(a, s);
+      }
+      if (wide) return launch<MODE, 1, 8, 4, 2, B4, SRC, DB>(a, s);
+      if constexpr (SRC == SRC_U8 && !B4) {
+        if (a.ks_per == 64 && a.K % (64 * QG_FRAG_K) == 0) return launch<MODE, 1, 16, 4, 1, B4, SRC, false, true>(a, s);
+      }
+      if (kb > 32 && (kb <= 64 || B4)) return launch<MODE, 1, 16, 4, 1, B4, SRC, B4>(a, s);  // (8-bit: one batch, nothing to request ahead)
+      return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);
+    case QG_KERNEL_SKINNY32:
+      if constexpr (!B4) {
+        if (wide && kb > 32) return launch<MODE, 2, 4, 4, 2, B4, SRC, DB>(a, s);
+        if (!wide && kb > 64) return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
+        if (!wide && kb > 32) return launch<MODE, 2, 16, 4, 1, B4, SRC, false>(a, s);  // (LDS for one batch per wave)
+      }
+      if constexpr (B4) {
+        if (!wide && kb > 32) return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
+      }
+      return wide ? launch<MODE, 2, 8, 4, 2, B4, SRC, DB>(a, s) : launch<MODE, 2, 8, 4, 1, B4, SRC, DB>(a, s);
+    case QG_KERNEL_SKINNY64:
+      return wide ? launch<MODE, 4, 8, 2, 2, B4, SRC, DB>(a, s) : launch<MODE, 4, 8, 2, 1, B4, SRC, DB>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
-
-template <bool B4, bool ANYALIGN>
+template <bool B4>
 hipError_t launch_mode(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
-  if (mode == QG_MODE_REQUANT) return launch_mb<QG_MODE_REQUANT, B4, ANYALIGN>(a, kernel, s);
-  if (mode == QG_MODE_DEQUANT) return launch_mb<QG_MODE_DEQUANT, B4, ANYALIGN>(a, kernel, s);
-  return launch_mb<QG_MODE_ACC32, B4, ANYALIGN>(a, kernel, s);
+  if (mode == QG_MODE_REQUANT) return launch_form<QG_MODE_REQUANT, B4, SRC_U8>(a, kernel, s);
+  if (mode == QG_MODE_DEQUANT) return launch_form<QG_MODE_DEQUANT, B4, SRC_U8>(a, kernel, s);
+  return launch_form<QG_MODE_ACC32, B4, SRC_U8>(a, kernel, s);
 }
 
 }  // namespace
@@ -751,35 +765,17 @@ hipError_t launch_mode(const qg_gemm_args& a, int mode, int kernel, hipStream_t 
 // Dense convolution on the streaming kernels: few output pixels and a long K.  Cin % 64 == 0, R*S <= 32.
 hipError_t qg_launch_conv_skinny(const qg_gemm_args& a, int kernel, hipStream_t s) {
   if (a.sp_ptr != nullptr || a.cv_Cin % QG_FRAG_K != 0 || a.cv_R * a.cv_S > 32 || a.ksplit != 1) return hipErrorInvalidValue;
-  switch (kernel) {
-    case QG_KERNEL_SKINNY16: return launch_conv<1, 16, 4>(a, s);
-    case QG_KERNEL_SKINNY32: return launch_conv<2, 16, 4>(a, s);
-    case QG_KERNEL_SKINNY64: return launch_conv<4, 16, 2>(a, s);
-    default: return hipErrorInvalidValue;
-  }
+  return launch_form<QG_MODE_REQUANT, false, SRC_CONV>(a, kernel, s);
 }
 
 // a.A points to fp32 activations (a.lda in floats, a.q_*: the quantization); mode: QG_MODE_REQUANT or QG_MODE_DEQUANT
 hipError_t qg_launch_gemm_skinny_f32(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
   if (a.sp_ptr != nullptr || mode == QG_MODE_ACC32) return hipErrorInvalidValue;
-  if (mode == QG_MODE_REQUANT) {
-    switch (kernel) {
-      case QG_KERNEL_SKINNY16: return launch_af32<QG_MODE_REQUANT, 1, 16, 4>(a, s);
-      case QG_KERNEL_SKINNY32: return launch_af32<QG_MODE_REQUANT, 2, 16, 4>(a, s);
-      case QG_KERNEL_SKINNY64: return launch_af32<QG_MODE_REQUANT, 4, 16, 2>(a, s);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (kernel) {
-    case QG_KERNEL_SKINNY16: return launch_af32<QG_MODE_DEQUANT, 1, 16, 4>(a, s);
-    case QG_KERNEL_SKINNY32: return launch_af32<QG_MODE_DEQUANT, 2, 16, 4>(a, s);
-    case QG_KERNEL_SKINNY64: return launch_af32<QG_MODE_DEQUANT, 4, 16, 2>(a, s);
-    default: return hipErrorInvalidValue;
-  }
+  return mode == QG_MODE_REQUANT ? launch_form<QG_MODE_REQUANT, false, SRC_F32>(a, kernel, s)
+                                 : launch_form<QG_MODE_DEQUANT, false, SRC_F32>(a, kernel, s);
 }
 
 hipError_t qg_launch_gemm_skinny(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
   // a.sp_ptr != null: Bp holds the 4-bit part of an outlier-split matrix
-  if (a.a_vec) return a.sp_ptr != nullptr ? launch_mode<true, false>(a, mode, kernel, s) : launch_mode<false, false>(a, mode, kernel, s);
-  return a.sp_ptr != nullptr ? launch_mode<true, true>(a, mode, kernel, s) : launch_mode<false, true>(a, mode, kernel, s);
+  return a.sp_ptr != nullptr ? launch_mode<true>(a, mode, kernel, s) : launch_mode<false>(a, mode, kernel, s);
 }

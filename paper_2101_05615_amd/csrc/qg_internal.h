@@ -103,7 +103,6 @@ struct qg_gemm_args {
   int lda, ldc;
   int ksplit;            // streaming kernels: slices of K that run as separate workgroups (>= 1)
   int ks_per;            // 64-deep blocks of K per slice (ceil; even for 4-bit weights)
-  int a_vec;             // A base and lda are multiples of 16 (the streaming kernels keep a variant for that case)
   int c_vec;             // output base and row pitch are multiples of 16 bytes (uint8 output of the streaming kernels: 4)
   int has_bzp;           // some theta_B != 0: the row-offset term of Eq. (2) is needed
   // ---- 64 bytes
@@ -124,7 +123,7 @@ struct qg_gemm_args {
   // K split across workgroups (streaming kernels): the caller's workspace (tickets, partial tiles)
   int32_t* ws_cnt;       // one ticket counter per (row block of 16, fragment column); zero between calls
   int32_t* ws_slots;     // ksplit slots of 272 int32 per counter
-  float q_inv, q_lo, q_hi, q_zp;  // fp32 activations quantized while staged: 1/alpha_A, -theta_A, 255 - theta_A, theta_A
+  float q_inv, q_zp;     // fp32 activations quantized while staged: 1/alpha_A, theta_A
   const int32_t* sp_ptr;      // outlier split: per-bucket offsets, or null for a dense 8-bit B
   const int32_t* sp_entries;  // outlier split: entries
   int sp_total;               // outlier split: number of entries (the buffer holds at least one)
@@ -248,14 +247,11 @@ __device__ __forceinline__ unsigned qg_requant_pack0(int x, float sc, unsigned p
   return __builtin_amdgcn_cvt_pk_u8_f32(p, pos, word);
 }
 // Quantization of one fp32 activation, Eq. (1) solved for the quantized value: ONE fp32 multiply, round to nearest
-// even, clamp in float to [-theta, 255 - theta], add theta; v_cvt_pk_u8_f32 converts the (exact, in-range) integer
-// and inserts it as byte `pos` of `word`.
-__device__ __forceinline__ unsigned qg_quantize_pack(float a, float inv, float lo, float hi, float zp_f, unsigned pos,
-                                                     unsigned word) {
+// even, clamp in float to [-theta, 255 - theta], add theta.  v_cvt_pk_u8_f32 converts with saturation, inserting byte `pos` of
+// `word`, so the clamp is the convert's: r + theta is exact while |r| < 2^24 and far outside [0, 255], on the same side, beyond.
+__device__ __forceinline__ unsigned qg_quantize_pack(float a, float inv, float zp_f, unsigned pos, unsigned word) {
   const float pr = a * inv;
-  const float r = __builtin_rintf(pr);
-  const float c = __builtin_amdgcn_fmed3f(r, lo, hi) + zp_f;
-  return __builtin_amdgcn_cvt_pk_u8_f32(c, pos, word);
+  return __builtin_amdgcn_cvt_pk_u8_f32(__builtin_rintf(pr) + zp_f, pos, word);
 }
 // fp32 output of one corrected accumulator: int32 -> fp32 (nearest even), ONE fp32 multiply, optional
 // max(., 0) (lo = 0 with ReLU, -inf without; a select, so no NaN-canonicalising extra instruction).

@@ -13,7 +13,7 @@ namespace {
 
 // One thread per 4 consecutive elements of a row (16 bytes in, 4 bytes out), grid-stride.
 __global__ __launch_bounds__(256) void qg_quantize_a_kernel(const float* __restrict__ A, int M, int K, int lda,
-                                                            float inv, float lo, float hi, float zp_f,
+                                                            float inv, float zp_f,
                                                             uint8_t* __restrict__ Aq, int ldq, int vec) {
   const int k4 = (K + 3) >> 2;
   const long long total = (long long)M * k4;
@@ -25,13 +25,13 @@ __global__ __launch_bounds__(256) void qg_quantize_a_kernel(const float* __restr
     uint8_t* dst = Aq + (size_t)row * ldq + k;
     if (vec && k + 4 <= K) {
       const float4 v = *reinterpret_cast<const float4*>(src);
-      unsigned w = qg_quantize_pack(v.x, inv, lo, hi, zp_f, 0, 0);
-      w = qg_quantize_pack(v.y, inv, lo, hi, zp_f, 1, w);
-      w = qg_quantize_pack(v.z, inv, lo, hi, zp_f, 2, w);
-      w = qg_quantize_pack(v.w, inv, lo, hi, zp_f, 3, w);
+      unsigned w = qg_quantize_pack(v.x, inv, zp_f, 0, 0);
+      w = qg_quantize_pack(v.y, inv, zp_f, 1, w);
+      w = qg_quantize_pack(v.z, inv, zp_f, 2, w);
+      w = qg_quantize_pack(v.w, inv, zp_f, 3, w);
       *reinterpret_cast<unsigned*>(dst) = w;
     } else {
-      for (int i = 0; i < 4 && k + i < K; ++i) dst[i] = (uint8_t)qg_quantize_pack(src[i], inv, lo, hi, zp_f, 0, 0);
+      for (int i = 0; i < 4 && k + i < K; ++i) dst[i] = (uint8_t)qg_quantize_pack(src[i], inv, zp_f, 0, 0);
     }
   }
 }
@@ -46,6 +46,6 @@ hipError_t qg_launch_quantize_a(const float* A, int M, int K, int lda, float inv
   long long blocks = (total + 255) / 256;
   if (blocks > 256 * 32) blocks = 256 * 32;  // a few thousand resident waves; the loop covers the rest
   hipLaunchKernelGGL(qg_quantize_a_kernel, dim3((unsigned)blocks), dim3(256), 0, s, A, M, K, lda, inv_scale,
-                     (float)(0 - a_zp), (float)(255 - a_zp), (float)a_zp, Aq, ldq, vec);
+                     (float)a_zp, Aq, ldq, vec);
   return hipGetLastError();
 }
