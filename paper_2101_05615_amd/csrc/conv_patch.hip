@@ -499,13 +499,10 @@ __global__ __launch_bounds__(WM* WN * KS * 64) void qg_conv_patch_kernel(
           }
         }
         uint8_t* dst = p.C + (size_t)row * p.ldc + col;
-        if (p.c_vec && col + 16 <= N) {
+        if (p.c_vec && col + 16 <= N)
           *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (col + i < N) dst[i] = (uint8_t)(out[i >> 2] >> (8 * (i & 3)));
-        }
+        else
+          qg_store_columns(dst, out, N - col);
       }
     }
   };

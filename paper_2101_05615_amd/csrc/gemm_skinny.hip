@@ -319,25 +319,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   auto put_row_end = [&](int kb, int buf) {
     const int c = (K >> 4) - kb * (QG_FRAG_K / 16);  // its place in the batch
     if (cut && c < NCHUNK) {
-      const int nv = K & 15;
-      v4i v = row_end;
-      if (K >= 16) {
-        // the last nv bytes of the 16 to the front, 0x80 behind them
-        unsigned d[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) d[i] = (unsigned)v[i], d[i + 4] = 0x80808080u;
-        const int drop = 16 - nv;
-        if (drop & 8) {
-#pragma unroll
-          for (int i = 0; i < 6; ++i) d[i] = d[i + 2];
-        }
-        if (drop & 4) {
-#pragma unroll
-          for (int i = 0; i < 5; ++i) d[i] = d[i + 1];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = (int)__builtin_amdgcn_alignbyte(d[i + 1], d[i], drop & 3);
-      }
+      const v4i v = K >= 16 ? qg_row_end_chunk(row_end, K & 15) : row_end;
       const int r = lane % ROWS;
       if (lane < ROWS) *reinterpret_cast<v4i*>(region0 + buf * REGION + r * ROWB + (((c ^ r) & (NCHUNK - 1)) << 4)) = v;
       asm volatile("" ::: "memory");  // (the operand reads below are of other lanes' chunks; LDS operations of a wave run in order)
@@ -667,9 +649,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
       else
         *reinterpret_cast<unsigned*>(dst) = out;
     } else {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (c0 + r < N) dst[r] = (uint8_t)(out >> (8 * r));
+      qg_store_columns(dst, {out, 0, 0, 0}, min(N - c0, 4));
     }
   } else if (MODE == QG_MODE_DEQUANT) {
     float out[4];

@@ -901,14 +901,8 @@ __global__ __launch_bounds__(NWM * NWN * KS * 64, PATH == PATH_ASM && KS > 1 ? 2
           uint8_t* dst = p.C + (size_t)row * p.ldc + col;
           if (full_cols) {
             *reinterpret_cast<uint4*>(dst) = make_uint4(out[0], out[1], out[2], out[3]);
-          } else if (col + 16 <= N) {
-            // any address: one 16-byte store all the same
-            *reinterpret_cast<qg_v4i_unaligned*>(dst) = (v4i){(int)out[0], (int)out[1], (int)out[2], (int)out[3]};
           } else {
-            // the lanes whose 16 columns N cuts
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-              if (col + i < N) dst[i] = (uint8_t)(out[i >> 2] >> ((i & 3) * 8));
+            qg_store_columns(dst, out, N - col);
           }
         }
       }
