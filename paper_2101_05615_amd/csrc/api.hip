@@ -270,6 +270,23 @@ double fetched_mb(int M, int N, int K, int rows, int cols) {
   return ((double)(row_blocks < spread ? row_blocks : spread) * N + (double)(columns < 8 ? columns : 8) * M) * K * 1e-6;
 }
 
+// what the builds of the streaming kernels share: extents of a launch
+struct stream_shape {
+  int kb, per, batches;  // k blocks, of a wave, batches after a wave's first
+  long long wgs;
+  qg_stream_build f;
+};
+stream_shape shape_of(int rows, int M, int N, int K, bool split) {
+  stream_shape s;
+  s.kb = ceil_div(K, 64);
+  const long long sb = tiles_of(M, N, rows, 32);
+  s.f = qg_stream_build_of(rows, s.kb, sb, M, split);
+  s.per = split ? 2 * ceil_div(s.kb, 2 * s.f.waves) : ceil_div(s.kb, s.f.waves);
+  s.batches = ceil_div(s.per, s.f.batch) - 1;
+  s.wgs = sb * 2 / s.f.columns;
+  return s;
+}
+
 double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
   const long long wgs = 2 * tiles_of(M, N, c.rows, 32);
   const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
@@ -324,22 +341,23 @@ const stream_cost k_stream_cost_16wave[] = {
     {QG_KERNEL_SKINNY64, 64, 4.96, 3.88e-4, 14.26, 2.23e-3},
 };
 // The dense convolution: the tile loops with the im2col addressing folded into the requests, the streaming kernels with
-// per-lane tap addressing (Cin % 64 == 0), and for "same" layers (stride 1, output as large as the input, Cin % 32 == 0) the kernels
+// per-lane tap addressing (Cin % 16 == 0), and for "same" layers (stride 1, output as large as the input, Cin % 32 == 0) the kernels
 // that keep the input patch of a pixel tile in LDS.  Formulas as for the GEMM, with
 //   chunk       channel counts off 64, whose requests keep a tap per lane;  tap: 64 / Cin of the steps begin a new tap
 //   load        per KiB of patch;  half: channel counts off 64, whose last slab is half full
 //   pass        what does not run side by side, the LDS of a wide patch allowing few workgroups per CU, runs one after the
 //               other, each pass at so much of the pace of a workgroup alone
 // Fitted to 20690 layers (1 x 1 to 7 x 7, stride 1 and 2, 16 .. 512 channels in, 8 .. 512 out, 5 .. 200 pixels wide, 1 .. 32 images) as
-// the GEMM's.  Over 5172 others the choice is 1.0035 of the best kernel in the mean, 1.28 at worst, 124 by more than 5 % (constants
-// fitted to 272 ordinary layers: 1.017 and 2.6; to older kernels: 1.051).
+// the GEMM's; the streaming kernels' terms again to 5000 layers when these kernels got faster and took channel counts off 64.  Over
+// 1500 others the choice is 1.005 of the best kernel in the mean, 1.37 at worst, 48 by more than 5 % (the former terms: 1.028).
 struct conv_tile_price {
   int kernel, bm, bn;
   double fix, lat, crowd, thr, fill, epi, out, rag_fix, rag_epi, chunk_fix, chunk_lat, chunk_thr, bzp_fix, tap_lat, tap_thr, tall, bzp_lat, bzp_thr;
 };
 struct conv_stream_price {
   int kernel, rows;
-  double fix, lat, batch, second, wg, wg_k, a_far, rag_fix, bzp_fix, tap_lat, tap_wg_k, bzp_lat;
+  double fix, fix8, fix16, lat, crowd, block, batch, second, wg, wg_k, bzp_fix, bzp_lat, rag_fix, rag_wg;
+  double chunk_fix, chunk_lat, chunk_wg_k, a_far, round, far, fetch, near;
 };
 struct conv_patch_price {
   int kernel, bm, bn;
@@ -359,10 +377,20 @@ const conv_tile_price k_conv_tile_price[] = {
     {QG_KERNEL_TILE128X256, 128, 256, 6.375, 0.1898, 0.1673, 0.4174, 0.5815, 3.169, 3, 1.243, 1.684, 0.1547, 3.392,
      1.611, 0.02083, 1.924, 0.4226, 0.148, 0.05569, 0.0766},
 };
+// (in pairs, as for the GEMM: up to 128 super-blocks, where the terms for more workgroups than CUs are left out, and more)
 const conv_stream_price k_conv_stream_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 3.704, 0.1457, 0.03971, 0.6714, 6.865, 0.001644, 1, 0, 0, 15.68, 4.028, 0.004171},
-    {QG_KERNEL_SKINNY32, 32, 4.777, 0.3575, 0.1303, 0.7435, 8.375, 0.001792, 1, 0.01563, 0, 6.124, 7.619, 0.000097},
-    {QG_KERNEL_SKINNY64, 64, 4.424, 1.243, 0, 0.6602, 10.62, 0.002683, 1.057, 0.2616, 0.1031, 3.359, 8.129, 0.0002748},
+    {QG_KERNEL_SKINNY16, 16, 3.179, 0.3758, 1.25, 0.0008043, 0.129, 0.193, 0.2321, 0, 0, 0, 0.0001065, 0, 0.004859, 0, 1.219,
+     0.002297, 0, 1, 0, 0.000076, 0.008103, 33.75},
+    {QG_KERNEL_SKINNY16, 16, 2.683, 1.776, 0.5, 0.0007659, 0.0003954, 0.001798, 0.7578, 0.186, 0.05215, 0.003142, 0.0004539,
+     0.0004355, 0.08225, 0.2894, 0.6832, 1.101, 0.9658, 1, 0.7804, 0.01493, 0.08158, 7.564},
+    {QG_KERNEL_SKINNY32, 32, 3.643, 0.1328, 1.176, 0.006866, 0.2389, 0.3819, 0.3824, 0, 0, 0, 0.01993, 0.000073, 0.08501, 0,
+     1.243, 0.4892, 0, 1, 0, 0.000071, 0.0008134, 86.16},
+    {QG_KERNEL_SKINNY32, 32, 4.389, 0.4313, 0.5, 0.009968, 0.02833, 0.1809, 0.3108, 0.0001235, 14.3, 0.00007, 0.0001865,
+     0.0001123, 0.2391, 0.1688, 0.6232, 1.411, 26.8, 0.8277, 2.836, 0.0106, 0.02866, 40.14},
+    {QG_KERNEL_SKINNY64, 64, 4.178, 0.1899, 0.5, 1.299, 0.4995, 0.01924, 0.00214, 0, 0, 0, 0.0149, 0.02231, 0.2289, 0, 0.5228,
+     1.317, 0, 1.009, 0, 0.000079, 0.01025, 0.01546},
+    {QG_KERNEL_SKINNY64, 64, 5.054, 0.2298, 0.5, 0.002852, 0.01836, 0.5464, 0.1645, 0.5519, 15.89, 0.006494, 0.02185, 0.00237,
+     0.1778, 0.003916, 0.09427, 1.519, 1.309, 0.6592, 0.2777, 0.007927, 0.03492, 0.2291},
 };
 const conv_patch_price k_conv_patch_price[] = {
     {QG_KERNEL_PATCH64X128, 64, 128, 3.4, 0.0935, 0.03727, 0.1396, 0.8133, 1.005, 2.676, 3.501, 0.05252, 0.01825, 0.9731,
@@ -398,14 +426,19 @@ double conv_tile_us(const conv_tile_price& c, const qg_gemm_args& a) {
 }
 
 double conv_stream_us(const conv_stream_price& c, const qg_gemm_args& a) {
-  const double wgs = 2.0 * (double)ceil_div(a.M, c.rows) * (double)ceil_div(a.N, 32), tap = 64.0 / a.cv_Cin;
-  const double n = (double)(ceil_div(ceil_div(ceil_div(a.K, 64), 16), c.rows == 64 ? 2 : 4) - 1), bzp = a.has_bzp ? 1.0 + c.bzp_lat : 1.0;
-  double us = c.fix + (a.c_vec == 0 ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) +
-              (a.K * c.lat / 1024.0 + n * c.batch) * bzp * (1.0 + c.tap_lat * tap);
-  if (wgs > 256.0) us = fmax(us * (1.0 + c.second), 2.5 + wgs * (c.wg + a.K * c.wg_k * bzp * (1.0 + c.tap_wg_k * tap)) * 1e-3);
+  const stream_shape s = shape_of(c.rows, a.M, a.N, a.K, false);
+  const bool chunk = a.cv_Cin % 64 != 0, rag = a.c_vec == 0;
+  const double bzp = a.has_bzp ? 1.0 + c.bzp_lat : 1.0;
+  double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (rag ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) +
+              (chunk ? c.chunk_fix : 0.0) +
+              (a.K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch) * bzp * (chunk ? c.chunk_lat : 1.0) +
+              c.fetch * fmax(fetched_mb(a.M, a.N, a.K, c.rows, 16 * s.f.columns) - c.near, 0.0);
+  if (s.wgs > 256)
+    us = fmax(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round,
+              2.5 + (double)s.wgs * (c.wg + (rag ? c.rag_wg : 0.0) + a.K * c.wg_k * bzp * (chunk ? c.chunk_wg_k : 1.0)) * 1e-3);
   const double a_bytes = (double)a.M * (double)a.K;
-  if (a_bytes > k_stream_a_near) us = fmax(us, 2.5 + a_bytes * (double)ceil_div(a.N, 16) / (c.a_far * 1e7));
-  return us;
+  if (a_bytes > k_stream_a_near) us = fmax(us, 2.5 + a_bytes * (double)ceil_div(a.N, 16 * s.f.columns) / (c.a_far * 1e7));
+  return us + c.far * fmax(a_bytes * 1e-6 - 4.0, 0.0);
 }
 
 double conv_patch_us(const conv_patch_price& c, const qg_gemm_args& a, int per_cu) {
@@ -1227,10 +1260,11 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
   a.cv_azp = p->a_zp;
   a.cv_in_bytes = in_bytes;
   // the tiled kernels, chosen by the same cost formula as a GEMM's; few pixels and a long K go to the 16-row streaming
-  // kernel where it applies (whole 64-channel slices, at most 32 taps), priced with the streaming formula and the
-  // constants measured for the convolution's requests
-  const bool stream_ok = Cin % QG_FRAG_K == 0 && R * S <= 32;
-  if (kernel == QG_KERNEL_AUTO) {
+  // kernel where it applies (at most 32 taps), priced with the streaming formula and the constants measured for the
+  // convolution's requests
+  const bool stream_ok = Cin % 16 == 0 && R * S <= 32;  // (asked for by id they take whole 64-channel slices only, as ever)
+  const bool explicit_kernel = kernel != QG_KERNEL_AUTO;
+  if (!explicit_kernel) {
     double best_us = 1e300;
     for (const conv_tile_price& c : k_conv_tile_price) {
       const double us = conv_tile_us(c, a);
@@ -1244,7 +1278,8 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
       if (us < best_us) best_us = us, kernel = c.kernel;
     }
     if (stream_ok)
-      for (const conv_stream_price& c : k_conv_stream_price) {
+      for (int i = 0; i < (Cin % QG_FRAG_K == 0 ? 3 : 2); ++i) {  // (64 rows take whole k blocks per tap)
+        const conv_stream_price& c = k_conv_stream_price[2 * i + (tiles_of(a.M, a.N, k_conv_stream_price[2 * i].rows, 32) > 128 ? 1 : 0)];
         const double us = conv_stream_us(c, a);
         if (ceil_div(a.M, c.rows) <= 65535 && us < best_us) best_us = us, kernel = c.kernel;
       }
@@ -1255,7 +1290,7 @@ int launch_conv_gemm(const uint8_t* in, int in_bytes, int Nb, int H, int W, int 
     return qg_launch_conv_patch(a, form, stream) == hipSuccess ? QG_OK : QG_ELAUNCH;
   }
   if (kernel <= QG_KERNEL_SKINNY64) {
-    if (!stream_ok) return QG_EUNSUPPORTED;
+    if (!stream_ok || (explicit_kernel && Cin % QG_FRAG_K != 0)) return QG_EUNSUPPORTED;
     a.ksplit = 1;
     a.ks_per = a.kb64;
     a.c_vec = aligned(out, 4) && (ldc % 4 == 0);

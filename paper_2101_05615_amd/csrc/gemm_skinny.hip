@@ -100,7 +100,9 @@ __device__ __forceinline__ void wait_vm() {
 // DB: two staging regions per wave, so that a batch's activations are requested one batch ahead like its weights.
 // ONE: every wave of every slice has exactly one whole batch (checked by the host): straight code, nothing that K could cut
 // (16 x 4096 x 4096, 256 workgroups that start together: 4.60 us, 4.70 with the code for the other cases around it).
-constexpr int SRC_U8 = 0, SRC_F32 = 1, SRC_CONV = 2;
+// SRC_CONV16: the same for any multiple of 16 channels.  A k block may then hold pieces of several taps, so the tap is per-lane
+// state, moved on by four 16-byte pieces per block (2 x 12 x 12 x 96 -> 128, 3 x 3, stride 2: 6.3 us on the tiles, 4.2 here).
+constexpr int SRC_U8 = 0, SRC_F32 = 1, SRC_CONV = 2, SRC_CONV16 = 3;
 template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool ONE = false>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAVES / 4) void qg_gemm_skinny_kernel(
     const uint8_t* A, const int8_t* Bp, const int M, const int N, const int K, const int kb64, const int nb16_total, const int lda,
@@ -112,6 +114,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   static_assert(!ONE || (SRC == SRC_U8 && !B4 && !DB), "one whole batch of 8-bit weights and rows of bytes");
   static_assert(SRC != SRC_F32 || !DB, "fp32 rows pass through registers, batch by batch");
   static_assert(MB * CPW <= NWAVES, "one wave per (row block, fragment column) runs the output pipeline");
+  constexpr bool CONV = SRC == SRC_CONV || SRC == SRC_CONV16;
   // A through LDS (see the file header): per wave and batch, ROWS rows x ROWB bytes
   constexpr int ROWS = MB * 16, ROWB = BATCH * QG_FRAG_K, NCHUNK = ROWB / 16;
   constexpr int REGION = ROWS * ROWB, NREQ = REGION / 1024, RPR = 64 / NCHUNK;  // requests per batch, rows per request
@@ -200,11 +203,12 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   // be negative) and the taps of that pixel that lie inside the image; wave-uniform: the tap of the next k block
   int cv_pix[MB];
   unsigned cv_mask[MB];
-  int cv_cc = 0, cv_kw = 0, cv_kh = 0;
-  const int cv_nc = SRC == SRC_CONV ? p.cv_Cin / QG_FRAG_K : 1;  // k blocks per tap
-  const uint8_t* const cv_azp_row = qg_byte_rows.b[SRC == SRC_CONV ? p.cv_azp : 0];
+  int cv_cc = 0, cv_kw = 0, cv_kh = 0;  // (SRC_CONV16: per lane, of the piece it requests; cv_cc in pieces)
+  const int cv_nc = CONV ? p.cv_Cin / (SRC == SRC_CONV16 ? 16 : QG_FRAG_K) : 1;  // k blocks (pieces) per tap
+  const int cv_wraps = SRC == SRC_CONV16 ? (4 + cv_nc - 1) / cv_nc : 0;  // taps that four pieces cross at most
+  const uint8_t* const cv_azp_row = qg_byte_rows.b[CONV ? p.cv_azp : 0];
   const uint8_t* const pad_row = qg_byte_rows.b[128];
-  if (SRC == SRC_CONV) {
+  if (CONV) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
       const int r = mb * 16 + (lane >> 2);
@@ -213,14 +217,18 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
       const int ho = t % p.cv_Ho, n = t / p.cv_Ho;
       const int h0 = ho * p.cv_stride - p.cv_pad, w0 = wo * p.cv_stride - p.cv_pad;
       // the lane's 16 bytes land at piece lane % 4 of its row's 64-byte block; that place holds logical piece (lane % 4) ^ (row / 4 % 4)
-      cv_pix[mb] = ((n * p.cv_H + h0) * p.cv_W + w0) * p.cv_pix + ((((lane & 3) ^ (lane >> 4)) & 3) << 4);
+      cv_pix[mb] = ((n * p.cv_H + h0) * p.cv_W + w0) * p.cv_pix + (SRC == SRC_CONV ? (((lane & 3) ^ (lane >> 4)) & 3) << 4 : 0);
+      // taps kw of [lo, hi) lie inside a row of the image: their bits once, shifted to each kh inside it (tap by tap, four compares
+      // each, the 25 taps of 15 x 14 x 17 x 64 -> 64 cost 1.8 us of 7.1, serial before the first request)
+      const int lo = w0 < 0 ? -w0 : 0, hi = p.cv_W - w0 < p.cv_S ? p.cv_W - w0 : p.cv_S;
+      const unsigned row = hi > lo ? (unsigned)((1ull << hi) - (1ull << lo)) : 0u;
       cv_mask[mb] = 0;
-      for (int kh = 0, tap = 0; kh < p.cv_R; ++kh)
-        for (int kw = 0; kw < p.cv_S; ++kw, ++tap)
-          if ((unsigned)(h0 + kh) < (unsigned)p.cv_H && (unsigned)(w0 + kw) < (unsigned)p.cv_W) cv_mask[mb] |= 1u << tap;
+      for (int kh = 0; kh < p.cv_R; ++kh)
+        if ((unsigned)(h0 + kh) < (unsigned)p.cv_H) cv_mask[mb] |= row << (kh * p.cv_S);
     }
-    const int tap = kb_begin / cv_nc;
-    cv_cc = kb_begin - tap * cv_nc;
+    const int at = SRC == SRC_CONV16 ? kb_begin * 4 + (((lane & 3) ^ (lane >> 4)) & 3) : kb_begin;
+    const int tap = at / cv_nc;
+    cv_cc = at - tap * cv_nc;
     cv_kh = tap / p.cv_S;
     cv_kw = tap - cv_kh * p.cv_S;
   } else {
@@ -276,7 +284,24 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   // requested even when the wave's part of K ends earlier: the surplus is not consumed.
   auto request_rows = [&](int kb, int buf) {
     const unsigned dst = region0_lds + buf * REGION;
-    if constexpr (SRC == SRC_CONV) {
+    if constexpr (SRC == SRC_CONV16) {
+#pragma unroll
+      for (int j = 0; j < BATCH; ++j) {
+        const bool in_k = cv_kh < p.cv_R;
+        const unsigned tapbit = in_k ? 1u << (cv_kh * p.cv_S + cv_kw) : 0u;
+        const int toff = (cv_kh * p.cv_W + cv_kw) * p.cv_pix + cv_cc * 16;
+        const uint8_t* const other = in_k ? cv_azp_row : pad_row;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          request_a64((cv_mask[mb] & tapbit) != 0 ? A + (cv_pix[mb] + toff) : other, dst + (j * MB + mb) * 1024);
+        cv_cc += 4;
+        for (int i = 0; i < cv_wraps; ++i)
+          if (cv_cc >= cv_nc) {
+            cv_cc -= cv_nc;
+            if (++cv_kw == p.cv_S) cv_kw = 0, ++cv_kh;
+          }
+      }
+    } else if constexpr (SRC == SRC_CONV) {
 #pragma unroll
       for (int j = 0; j < BATCH; ++j) {
         // (wave-uniform) a k block past K -- the zero padding of the packed weights -- is staged as 0x80 bytes like
@@ -409,13 +434,13 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     v4i af[MB][BATCH];
     // (chunk 4 j + g of row r lies at (4 j + g) ^ r: the place of j = 0 with j turned into it.  Opaque, or the compiler keeps all
     // the places in registers across the batches.)
-    int at = SRC == SRC_CONV ? ml * QG_FRAG_K + (((g ^ (ml >> 2)) & 3) << 4) : ml * ROWB + (((g ^ ml) & (NCHUNK - 1)) << 4);
+    int at = CONV ? ml * QG_FRAG_K + (((g ^ (ml >> 2)) & 3) << 4) : ml * ROWB + (((g ^ ml) & (NCHUNK - 1)) << 4);
     asm volatile("" : "+v"(at));
 #pragma unroll
     for (int j = 0; j < BATCH; ++j)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        if (SRC == SRC_CONV)  // [k block][row block][row][piece ^ (row / 4 % 4)]
+        if (CONV)  // [k block][row block][row][piece ^ (row / 4 % 4)]
           af[mb][j] = *reinterpret_cast<const v4i*>(region + at + (j * MB + mb) * 1024);
         else  // (rows 16 further: bit 4 of the row is turned into the chunk too)
           af[mb][j] = *reinterpret_cast<const v4i*>(region + mb * (16 * ROWB) + (at ^ (((4 * j) ^ (mb * 16 & (NCHUNK - 1))) << 4)));
@@ -690,48 +715,40 @@ hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
                      a.kb64, a.nb16, a.lda, a.ks_per, a.ksplit, a);
   return hipGetLastError();
 }
-// The build: waves, k blocks that a wave requests at once, fragment columns per wave.  Measured on some 150 shapes (M 1 .. 64, N
-// and K 512 .. 8192, graph replays, every build on each):
-//  - up to 16 k blocks four waves, up to 32 eight: one batch each, and the fewer waves there are to start and to add up the better
-//    (7 x 1408 x 891: sixteen waves 4.5 us, eight 3.65; 1 x 576 x 960 3.5 and, four, 3.0);
-//  - up to 64 sixteen waves (16 x 4096 x 4096: 5.2 against 6.2 with eight), beyond that eight again, whose batches follow each
-//    other without a gap (1 x 704 x 5888 4.0 against 4.5); with 4-bit weights, half the bytes per batch, sixteen throughout;
-//  - more workgroups of 16 columns than CUs: two fragment columns per wave (13 x 6400 x 3392 6.3 us; sixteen waves of one 8.2).
-//    With 4-bit weights and a long K sixteen waves do that too (16 x 8192 x 8192 with 0.5 % of outliers 10.2 against 12.2).  At most
-//    four rows and a long K, hardly any activations to share: four waves of one column again (3 x 4736 x 6848 8.4 us against 8.9, 2 x 7512 x 7936 11.1 against 12.3).
 template <int MODE, bool B4, int SRC>
 hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
   constexpr bool DB = SRC != SRC_F32;
+  if (kernel < QG_KERNEL_SKINNY16 || kernel > QG_KERNEL_SKINNY64) return hipErrorInvalidValue;
   const int blocks = (a.K + QG_FRAG_K - 1) / QG_FRAG_K, kb = blocks < a.ks_per ? blocks : a.ks_per;
   const int rows = 16 << (kernel - QG_KERNEL_SKINNY16);
   const long long sb = (long long)((a.N + 31) / 32) * ((a.M + rows - 1) / rows) * a.ksplit;
-  const bool wide = sb > 128;
-  switch (kernel) {
-    case QG_KERNEL_SKINNY16:
-      if (kb <= 16 || (!B4 && wide && kb > 64 && a.M <= 4)) return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
-      if constexpr (B4) {
-        if (wide && sb <= 256 && kb > 36) return launch<MODE, 1, 16, 4, 2, B4, SRC, DB>(a, s);
-      }
-      if (wide) return launch<MODE, 1, 8, 4, 2, B4, SRC, DB>(a, s);
+  const qg_stream_build f = qg_stream_build_of(rows, kb, sb, a.M, B4);
+  switch (rows * 10000 + f.waves * 100 + f.batch * 10 + f.columns) {
+    case 160441: return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
+    case 160841: return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);
+    case 160842: return launch<MODE, 1, 8, 4, 2, B4, SRC, DB>(a, s);
+    case 161641:
       if constexpr (SRC == SRC_U8 && !B4) {
         if (a.ks_per == 64 && a.K % (64 * QG_FRAG_K) == 0) return launch<MODE, 1, 16, 4, 1, B4, SRC, false, true>(a, s);
       }
-      if (kb > 32 && (kb <= 64 || B4)) return launch<MODE, 1, 16, 4, 1, B4, SRC, B4>(a, s);  // (8-bit: one batch, nothing to request ahead)
-      return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);
-    case QG_KERNEL_SKINNY32:
-      if constexpr (!B4) {
-        if (wide && kb > 32) return launch<MODE, 2, 4, 4, 2, B4, SRC, DB>(a, s);
-        if (!wide && kb > 64) return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
-        if (!wide && kb > 32) return launch<MODE, 2, 16, 4, 1, B4, SRC, false>(a, s);  // (LDS for one batch per wave)
-      }
-      if constexpr (B4) {
-        if (!wide && kb > 32) return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
-      }
-      return wide ? launch<MODE, 2, 8, 4, 2, B4, SRC, DB>(a, s) : launch<MODE, 2, 8, 4, 1, B4, SRC, DB>(a, s);
-    case QG_KERNEL_SKINNY64:
-      return wide ? launch<MODE, 4, 8, 2, 2, B4, SRC, DB>(a, s) : launch<MODE, 4, 8, 2, 1, B4, SRC, DB>(a, s);
-    default: return hipErrorInvalidValue;
+      return launch<MODE, 1, 16, 4, 1, B4, SRC, B4>(a, s);  // (8-bit: one batch, nothing to request ahead)
+    case 320841: return launch<MODE, 2, 8, 4, 1, B4, SRC, DB>(a, s);
+    case 320842: return launch<MODE, 2, 8, 4, 2, B4, SRC, DB>(a, s);
+    case 321621: return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
+    default: break;
   }
+  if constexpr (SRC != SRC_CONV16) {  // (64 rows: the choice for 1 of 1536 drawn layers, and 2 % slower there)
+    if (rows == 64)
+      return f.columns == 2 ? launch<MODE, 4, 8, 2, 2, B4, SRC, DB>(a, s) : launch<MODE, 4, 8, 2, 1, B4, SRC, DB>(a, s);
+  }
+  if (rows == 64) return hipErrorInvalidValue;
+  if constexpr (B4) {
+    if (f.waves == 16 && f.columns == 2) return launch<MODE, 1, 16, 4, 2, B4, SRC, DB>(a, s);
+  } else {
+    if (f.waves == 4) return launch<MODE, 2, 4, 4, 2, B4, SRC, DB>(a, s);
+    if (f.waves == 16) return launch<MODE, 2, 16, 4, 1, B4, SRC, false>(a, s);  // (LDS for one batch per wave)
+  }
+  return hipErrorInvalidValue;
 }
 template <bool B4>
 hipError_t launch_mode(const qg_gemm_args& a, int mode, int kernel, hipStream_t s) {
@@ -742,10 +759,11 @@ hipError_t launch_mode(const qg_gemm_args& a, int mode, int kernel, hipStream_t 
 
 }  // namespace
 
-// Dense convolution on the streaming kernels: few output pixels and a long K.  Cin % 64 == 0, R*S <= 32.
+// Dense convolution on the streaming kernels: few output pixels and a long K.  Cin % 16 == 0 (% 64 for the 64-row one), R*S <= 32.
 hipError_t qg_launch_conv_skinny(const qg_gemm_args& a, int kernel, hipStream_t s) {
-  if (a.sp_ptr != nullptr || a.cv_Cin % QG_FRAG_K != 0 || a.cv_R * a.cv_S > 32 || a.ksplit != 1) return hipErrorInvalidValue;
-  return launch_form<QG_MODE_REQUANT, false, SRC_CONV>(a, kernel, s);
+  if (a.sp_ptr != nullptr || a.cv_Cin % 16 != 0 || a.cv_R * a.cv_S > 32 || a.ksplit != 1) return hipErrorInvalidValue;
+  return a.cv_Cin % QG_FRAG_K == 0 ? launch_form<QG_MODE_REQUANT, false, SRC_CONV>(a, kernel, s)
+                                   : launch_form<QG_MODE_REQUANT, false, SRC_CONV16>(a, kernel, s);
 }
 
 // a.A points to fp32 activations (a.lda in floats, a.q_*: the quantization); mode: QG_MODE_REQUANT or QG_MODE_DEQUANT
