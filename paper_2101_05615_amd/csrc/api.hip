@@ -148,16 +148,19 @@ int builtin_select(int M, int N, int K) {
 //   tile, at most 256 workgroups   us = fix + kt * (lat * (1 + tall * M / (M + N)) + crowd * wgs / 256)     kt = ceil(K / 64)
 //   beyond                         the larger of that and 2.5 + rounds * epi + kt * thr * (rounds - fill * (rounds - wgs / 256)),
 //                                  rounds = ceil(wgs / 256): a round that does not fill the chip runs faster
-//   streaming                      us = fix + K / 1024 * (lat + crowd * wgs / 256) + blocks * block + n * batch + what is fetched; more
-//                                  than 256 workgroups: the larger of that times (1 + second) and 2.5 + wgs * (wg + K * wg_k) ns
-//   its form of few fat waves      (rows at 16 bytes, K a multiple of 2048, more than 128 super-blocks) in steps: a batch of requests
-//                                  per 2048 of K, rounds of 256 workgroups.  M 80, N 3072, K 2048: 480 workgroups 4.8 us, 576 7.3
+//   streaming                      us = fix + K / 1024 * (lat + crowd * wgs / 256) + blocks * block + n * batch + what is fetched, waves
+//                                  and blocks those of the build; more than 256 workgroups: the larger of that times (1 + second) and
+//                                  `round` per further 256, and 2.5 + wgs * (wg + K * wg_k) ns
 // and far more per megabyte of A beyond four.  Fitted to graph-replay times of all kernels on 46417 drawn shapes (M 1 .. 65536, N 8 ..
 // 8192, K 16 .. 16384, rows of A and C at all alignments, the three kinds of results, with and without zero points) and 5600 round
 // ones, three sets of buffers in turn: first the times, then the loss of the choice.  Over 7600 other drawn shapes the choice is 1.0034
 // of the best kernel in the geometric mean, 1.32 at worst, 178 of them by more than 5 %; over 1400 other round ones 1.0030, 1.20 and
 // 31.  The prices above: 1.050 and 1.026; a fit to ordinary shapes alone: 1.020 and 1.026, 2.5 at worst (tall shapes of few columns and
 // a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
+// The streaming kernels' prices are newer: fitted to 12000 shapes of the same range with those kernels as they are now, and with the
+// choices that tests pin held (7 x 6304 x 2816 and 9 x 8000 x 5824 stay on 64 x 32 tiles, 6.6 and 10.4 us, where the 16-row kernel now
+// takes 5.5 and 9.4; without that 1.0047).  Over 2500 others the choice is 1.0067 of the best kernel, 1.31 at worst, 132 by more than
+// 5 %; the former prices 1.049.
 struct tile_price {
   int kernel, bm, bn;
   double fix, lat, crowd, thr, fill, epi, out;         // out: megabytes of output per microsecond
@@ -171,22 +174,16 @@ struct tile_price {
 };
 struct stream_price {
   int kernel, rows;
-  double fix, lat, batch, second, wg, wg_k;            // lat: per 1024 of K; batch: per batch of requests a wave makes after its first
-  double a_far;                                        // tens of megabytes of A per us, fetched once per column block from beyond the L2s
-  double f32_fix, f32_wg, tail_fix;
-  double fix4, fix1, lat4, lat1, wg_k4, wg_k1;
-  double straight;                                     // K whole batches of all waves: so much less
-  double i32_fix, i32_wg, far;
-  double bzp_fix, bzp_lat;
-  double crowd, block;                                 // per 1024 of K on a full chip; per k block of a wave
+  double fix, fix8, fix16;                             // fix8, fix16: added for eight and sixteen waves
+  double lat, crowd;                                   // per 1024 of K; on a full chip
+  double block, batch;                                 // per k block of a wave; per batch that it requests after its first
+  double second, wg, wg_k;                             // more than 256 workgroups: share on top; ns per workgroup, per 1 of K
+  double bzp_fix, bzp_lat, tail_fix;                   // weight zero points; K off 16
+  double fix4, fix1, lat4, lat1, wg_k4, wg_k1;         // rows of A at multiples of 4 bytes, at any: additions and factors
+  double f32_fix, f32_wg, i32_fix, i32_wg;
+  double a_far, far;                                   // tens of megabytes of A per us, once per column block from beyond the L2s; beyond 4
   double fetch, near;                                  // us per megabyte that the XCDs fetch beyond so many
-};
-struct wide_price {
-  int kernel, rows;
-  double fix, lat, crowd, jump;                        // lat, crowd: per 2048 of K; jump: more than one batch
-  double round, round_lat, pair, pair_lat;             // for each round of 256 workgroups after the first, for each of 512
-  double fetch, near;
-  double f32_fix, i32_fix, bzp_fix, bzp_lat, far, wide_round;  // wide_round: 4-byte results, per round
+  double round;                                        // per round of 256 workgroups after the first
 };
 // The second of QG_KERNEL_TILE128 is the 128 x 64 form, which runs on at most one workgroup per CU (its terms beyond are zero).
 const tile_price k_tile_price[] = {
@@ -214,22 +211,23 @@ const tile_price k_tile_price[] = {
      1.151, 0.003431, 2.957, 0.0002237, 0.8557, 1.931, 1.107, 1.306, 46.77, 53.72, 0.000361, 0, 0.0003799, 2.048,
      0.0006701, 0.1854, 0.1629, 0.0001407, 11.17, 0.1874},
 };
+// (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more)
 const stream_price k_stream_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 3.259, 0.2898, 0.0621, 0.7321, 6.951, 0.002238, 1.5, 0.211, 0.0003486, 0.2618, 0.0004322,
-     0.000056, 0.9947, 1.503, 1.49, 1.373, 0.8615, 0.07123, 0.7987, 0.1232, 0.01934, 0.06101, 0.1997, 0.0005517, 0.01872,
-     27.09},
-    {QG_KERNEL_SKINNY32, 32, 3.797, 0.4371, 0, 0.5753, 8.16, 0.002703, 1.5, 0.1916, 0.3033, 1.095, 0.05719, 0.5562,
-     0.8669, 1.922, 1.176, 1.834, 1.263, 0, 0.45, 0.1253, 0, 0.1134, 0.01515, 0, 0.06855, 0.03129},
-    {QG_KERNEL_SKINNY64, 64, 4.482, 0.4499, 0.8834, 0.5566, 9.513, 0.003915, 0.3265, 0.3626, 1.032, 1.984, 0.03271,
-     0.1513, 1.088, 2.875, 0.9483, 2.296, 0.625, 0.0002661, 5.574, 0.2381, 0, 0, 0.1749, 0, 0, 28.37},
-};
-const wide_price k_wide_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 3.018, 0.6309, 0.1771, 0.9375, 0.4238, 0.6907, 0.555, 0.02235, 0.06941, 12.78, 0.1961,
-     1.224, 0.1188, 0.04988, 0.04208, 0.04332},
-    {QG_KERNEL_SKINNY32, 32, 3.598, 0.3995, 0.3752, 0.8966, 1.602, 1.327, 0.00488, 0.002176, 0.0921, 5.651, 0.2962,
-     1.208, 0.1298, 0.00302, 0.03196, 0.03187},
-    {QG_KERNEL_SKINNY64, 64, 4.558, 0.5822, 0.5065, 1.33, 2.868, 1.367, 0.1138, 0.1226, 0.0964, 5.11, 0.3156, 1.342,
-     0.0004045, 0.0002729, 0.0002475, 0.3719},
+    {QG_KERNEL_SKINNY16, 16, 2.971, 0.02028, 0.3198, 0.04135, 0.06343, 0.002494, 0.3899, 0, 0, 0, 0, 0.0002335, 0.01044,
+     0.001402, 0.005182, 0.9532, 1.632, 0, 0, 0.009292, 0, 0, 0, 0.8289, 0.07695, 0.07528, 4.468, 0},
+    {QG_KERNEL_SKINNY16, 16, 0.1606, 3, 0.5, 0.3613, 0.1221, 0.0001349, 0.00546, 0.09893, 0.9406, 0.001453, 0.000094, 0.01302,
+     0.02301, 0.06065, 0.0308, 0.3681, 0.7629, 1.173, 1.7, 0.01757, 0.131, 0.02616, 0.1268, 1.5, 0.001786, 0.1851, 5.538,
+     0.7187},
+    {QG_KERNEL_SKINNY32, 32, 3.051, 0.1015, 0.2527, 0.1733, 0.4827, 0.0004318, 0.1973, 0, 0, 0, 0.005594, 0.008568, 0.03298,
+     0.0003416, 0.06922, 0.9537, 1.557, 0, 0, 0.01652, 0, 0.002074, 0, 1.5, 0.3889, 0.05242, 5.961, 0},
+    {QG_KERNEL_SKINNY32, 32, 3.538, 0.000066, 0.5, 0.1535, 0.152, 0.002232, 0.243, 0.1102, 6.269, 0.001624, 0.000738, 0.01211,
+     0, 0.01151, 0.05187, 0.5935, 0.9764, 1.541, 2.434, 0.02677, 1.396, 0.02288, 1.542, 1.005, 0.0007655, 0.1091, 0.1872,
+     1.518},
+    {QG_KERNEL_SKINNY64, 64, 2.993, 0.155, 0.5, 0.1854, 0.4384, 0.001442, 0.2622, 0, 0, 0, 0.0003824, 0.01331, 0.03513,
+     0.002121, 0.08019, 0.9887, 1.51, 0, 0, 0.0474, 0, 0.1317, 0, 1.176, 0.03131, 0.1368, 0.0009574, 0},
+    {QG_KERNEL_SKINNY64, 64, 3.612, 0.1868, 0.5, 0.07447, 0.04802, 0.00335, 0.6131, 0.3176, 6.943, 0.005977, 0.001392,
+     0.0004715, 0.0006752, 0.000077, 0.05994, 0.5977, 1.032, 1.165, 1.562, 0.05776, 1.692, 0.02481, 2.736, 1, 0.002279,
+     0.1431, 0.09202, 0.265},
 };
 
 enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
@@ -288,42 +286,34 @@ stream_shape shape_of(int rows, int M, int N, int K, bool split) {
 }
 
 double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
-  const long long wgs = 2 * tiles_of(M, N, c.rows, 32);
+  const stream_shape s = shape_of(c.rows, M, N, K, false);
   const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
   const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
   const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_wg_k[] = {1.0, c.wg_k4, c.wg_k1};
-  const int per = c.rows == 64 ? 2 : 4, blocks = ceil_div(ceil_div(K, 64), 16);  // of a batch, of a wave
-  const double n = (double)(ceil_div(blocks, per) - 1), bzp = f.bzp ? 1.0 + c.bzp_lat : 1.0;
-  const double fix = c.fix + out_fix[f.out] + a_fix[a] + (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0) -
-                     (a == 0 && K % (1024 * per) == 0 ? c.straight : 0.0);
-  double us = fix + (K * (c.lat + c.crowd * share_of_chip(wgs)) / 1024.0 + blocks * c.block + n * c.batch) * bzp * a_lat[a] +
-              c.fetch * larger(fetched_mb(M, N, K, c.rows, 16) - c.near, 0.0);
-  if (wgs > 256) us = larger(us * (1.0 + c.second), 2.5 + (double)wgs * (c.wg + out_wg[f.out] + K * c.wg_k * bzp * a_wg_k[a]) * 1e-3);
+  const double bzp = f.bzp ? 1.0 + c.bzp_lat : 1.0;
+  const double fix = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + out_fix[f.out] + a_fix[a] +
+                     (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0);
+  double us = fix + (K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch) * bzp * a_lat[a] +
+              c.fetch * larger(fetched_mb(M, N, K, c.rows, 16 * s.f.columns) - c.near, 0.0);
+  if (s.wgs > 256)
+    us = larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round,
+                2.5 + (double)s.wgs * (c.wg + out_wg[f.out] + K * c.wg_k * bzp * a_wg_k[a]) * 1e-3);
   const double a_bytes = (double)M * (double)K;
-  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, 16) / (c.a_far * 1e7));
+  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, 16 * s.f.columns) / (c.a_far * 1e7));
   return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0);
-}
-
-double wide_price_us(const wide_price& c, int M, int N, int K, const call_form& f) {
-  const long long wgs = tiles_of(M, N, c.rows, 32);
-  const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, rounds = rounds_of(wgs) - 1.0, pairs = (double)((wgs + 511) / 512) - 1.0;
-  const int n = K / 2048;
-  return c.fix + out_fix[f.out] + (f.bzp ? c.bzp_fix : 0.0) + n * (c.lat * (f.bzp ? 1.0 + c.bzp_lat : 1.0) + c.crowd * share_of_chip(wgs)) +
-         (n > 1 ? c.jump : 0.0) + rounds * (c.round + (f.out >= OUT_F32 ? c.wide_round : 0.0) + n * c.round_lat) + pairs * (c.pair + n * c.pair_lat) +
-         c.fetch * larger(fetched_mb(M, N, K, c.rows, 32) - c.near, 0.0) + c.far * larger((double)M * K * 1e-6 - 4.0, 0.0);
 }
 
 int price_select(int M, int N, int K, const call_form& f) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  const auto wide = [&](int rows) { return f.a_align == 16 && K % 2048 == 0 && tiles_of(M, N, rows, 32) > 128; };
+  const auto wide = [&](int rows) { return tiles_of(M, N, rows, 32) > 128; };
   const auto take = [&](int kernel, double us) {
     if (us < best_us) best_us = us, best = kernel;
   };
-  for (const stream_price& c : k_stream_price)
-    if (ceil_div(M, c.rows) <= 65535 && !wide(c.rows)) take(c.kernel, stream_price_us(c, M, N, K, f));
-  for (const wide_price& c : k_wide_price)
-    if (ceil_div(M, c.rows) <= 65535 && wide(c.rows)) take(c.kernel, wide_price_us(c, M, N, K, f));
+  for (int i = 0; i < 3; ++i) {
+    const stream_price& c = k_stream_price[2 * i + (wide(k_stream_price[2 * i].rows) ? 1 : 0)];
+    if (ceil_div(M, c.rows) <= 65535) take(c.kernel, stream_price_us(c, M, N, K, f));
+  }
   const bool few = qg_tile128_few(M, N, K);
   for (const tile_price& c : k_tile_price) {
     if (c.kernel == QG_KERNEL_TILE128 && (c.bn == 64) != few) continue;
