@@ -303,7 +303,7 @@ double stream_price_us(const stream_price& c, int M, int N, int K, const call_fo
   return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0);
 }
 
-int price_select(int M, int N, int K, const call_form& f) {
+int price_select(int M, int N, int K, const call_form& f, double* price = nullptr) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
   const auto wide = [&](int rows) { return tiles_of(M, N, rows, 32) > 128; };
@@ -319,6 +319,59 @@ int price_select(int M, int N, int K, const call_form& f) {
     if (c.kernel == QG_KERNEL_TILE128 && (c.bn == 64) != few) continue;
     if (c.kernel == QG_KERNEL_TILE256 && K < 256) continue;  // 128 x 256 tiles there, without the loop priced here
     take(c.kernel, tile_price_us(c, M, N, K, f));
+  }
+  if (price != nullptr) *price = best_us;
+  return best;
+}
+
+// fp32 activations in one launch, the streaming kernels quantizing what they stage (every column block converts its rows of A again):
+//   conv, wg_c  per 16 rows: of a k block of a wave; of a workgroup, ns per 1 of K, where the chip is full
+// against the 8-bit call plus a pass over A.  Fitted to 8900 drawn calls with M up to 512; over 1488 others the choice is 1.004 of the
+// best form in the geometric mean and 0.890 of two launches, 15 of them slower by more than 4 %, 1.20 at worst.
+struct f32_price {
+  int kernel, rows;
+  double fix, fix8, fix16, lat, crowd, block, conv, batch, second, wg, wg_k, wg_c, bzp_fix, k_fix, u8_fix, round, fetch, near;
+};
+const f32_price k_f32_price[] = {
+    {QG_KERNEL_SKINNY16, 16, 3.154, 0.4998, 1.149, 0.207, 0.0006482, 0.0008539, 0.3092, 0.9886, 0, 0, 0, 0.0005, 0.009312,
+     0.06609, 0.1062, 0, 0.05619, 2.627},
+    {QG_KERNEL_SKINNY16, 16, 1.925, 1.706, 0.3, 0.3542, 0.1734, 0.0006506, 0.2207, 0.6133, 0.3216, 1.397, 0.002564, 0.002457,
+     0.03206, 0.09166, 0.07434, 0.7039, 0.1364, 4.446},
+    {QG_KERNEL_SKINNY32, 32, 3.367, 0.1267, 0.4395, 0.5418, 0.1668, 0.000826, 0.3319, 1.207, 0, 0, 0, 0.0005, 0.01582, 0.1281,
+     0.09172, 0, 0.08396, 3.195},
+    {QG_KERNEL_SKINNY32, 32, 3.137, 0.2841, 0.3, 0.9125, 0.1401, 0.009143, 0.2453, 0.004797, 0.02451, 5.927, 0.008223,
+     0.002056, 0.009162, 0.2016, 0.0179, 1.855, 0.1921, 5.14},
+    {QG_KERNEL_SKINNY64, 64, 3.075, 0.1398, 0.3, 1.151, 0.3381, 0.006236, 0.3566, 0.409, 0, 0, 0, 0.0005, 0.006206, 0.2464,
+     0.05655, 0, 0.06369, 0.02254},
+    {QG_KERNEL_SKINNY64, 64, 2.965, 0.1348, 0.3, 1.106, 0.1626, 0.4953, 0.3453, 0.01991, 0.1733, 12.34, 0.008612, 0.002153,
+     0.0005398, 0.2798, 0, 0.3165, 0.07423, 2.414},
+};
+const double k_quantize_fix = 1.872, k_quantize_mb = 1.263, k_quantize_most = 1.381;  // us; per million entries of A; up to so many
+
+double f32_price_us(const f32_price& c, int M, int N, int K, out_kind out, bool bzp) {
+  const stream_shape s = shape_of(c.rows, M, N, K, false);
+  const double g = ceil_div(M < c.rows ? M : c.rows, 4) / 4.0;
+  const int cols = 16 * s.f.columns, columns = ceil_div(N, cols), near = columns < 8 ? columns : 8;
+  double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (bzp ? c.bzp_fix : 0.0) + (K % 64 != 0 ? c.k_fix : 0.0) +
+              (out < OUT_F32 ? c.u8_fix : 0.0) + K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * (c.block + c.conv * g) +
+              s.batches * c.batch + c.fetch * larger(fetched_mb(M, N, K, c.rows, cols) + 3e-6 * near * M * K - c.near, 0.0);
+  if (s.wgs > 256)
+    us = larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round, 2.5 + (double)s.wgs * (c.wg + K * (c.wg_k + c.wg_c * g)) * 1e-3);
+  return us;
+}
+
+// the kernel for one launch, or QG_KERNEL_AUTO where two launches are estimated to be faster
+int f32_select(int M, int N, int K, const call_form& f) {
+  if (M > 512) return QG_KERNEL_AUTO;  // 64 rows at a time, A would be converted by every column block for each of many row blocks
+  double best_us;
+  price_select(M, N, K, f, &best_us);
+  const double entries = (double)M * (double)K * 1e-6;
+  best_us += k_quantize_fix + k_quantize_mb * (entries < k_quantize_most ? entries : k_quantize_most);
+  int best = QG_KERNEL_AUTO;
+  for (int i = 0; i < 3; ++i) {
+    const f32_price& c = k_f32_price[2 * i + (tiles_of(M, N, k_f32_price[2 * i].rows, 32) > 128 ? 1 : 0)];
+    const double us = f32_price_us(c, M, N, K, f.out, f.bzp);
+    if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
 }
@@ -1093,6 +1146,20 @@ size_t qg_gemm_f32_workspace_bytes(int M, const qg_packed_b* Bp) {
   return (size_t)M * (size_t)f32_ldq(Bp);  // what a tiled kernel needs; a streaming kernel needs none
 }
 
+// With a workspace: the kernel of an automatic call, and whether it quantizes A itself.
+static int f32_resolve(const qg_packed_b* Bp, int M, int* kernel, bool* one_launch, const call_form& f) {
+  if (*kernel == QG_KERNEL_AUTO && !Bp->split && M > 0 && rule_kernel(M, Bp->N, Bp->K) == QG_KERNEL_AUTO) {
+    const int k = f32_select(M, Bp->N, Bp->K, f);
+    if (k != QG_KERNEL_AUTO) {
+      *kernel = k;
+      *one_launch = true;
+      return QG_OK;
+    }
+  }
+  int ksplit = 1;
+  return resolve_call(Bp, M, kernel, &ksplit, f, nullptr);
+}
+
 static int quantize_into_workspace(const float* A_dev, int M, int lda, float a_inv_scale, const qg_packed_b* Bp,
                                    int a_zp, void* workspace_dev, void* stream) {
   if (!Bp || (!A_dev && M != 0)) return QG_ENULL;
@@ -1105,23 +1172,25 @@ static int quantize_into_workspace(const float* A_dev, int M, int lda, float a_i
                            f32_ldq(Bp), stream);
 }
 
-// fp32 activations on a streaming kernel for a caller without a workspace: ONE launch -- the kernel quantizes the block it stages
-// (Appendix B: any packing routine for A; row offsets come from the staged block in the same pass).  Fills the
-// common fields of `a`; returns QG_OK with *fused = false when the kernel in use is a tiled one.
+// fp32 activations on a streaming kernel: ONE launch -- the kernel quantizes the block it stages (Appendix B: any packing routine
+// for A; row offsets come from the staged block in the same pass) and, where there is a workspace, leaves the quantized rows there
+// as the separate pass does.  For a caller without a workspace whatever streaming kernel is in use; with one where QG_KERNEL_AUTO
+// finds it faster (`one_launch`: 64 x 1024 x 1024 6.2 -> 4.8 us, 16 x 4096 x 4096 6.5 -> 6.2; 512 x 4096 x 4096 stays in two).  Fills the common
+// fields of `a`; returns QG_OK with *fused = false for two launches.
 static int f32_fused_common(const float* A_dev, int M, int lda, float a_inv_scale, int a_zp, const qg_packed_b* Bp,
-                            int kernel, const void* workspace_dev, qg_gemm_args* a, bool* fused) {
+                            int kernel, bool one_launch, void* workspace_dev, qg_gemm_args* a, bool* fused) {
   *fused = false;
-  // With a workspace at hand the separate quantization pass is the faster form even here (every 16-column
-  // workgroup of a streaming kernel would convert all of A again: 16 x 4096 x 4096 7.8 us fused, 5.8 us in two
-  // launches), so the one-launch form serves the caller that has none.
-  if (kernel > QG_KERNEL_SKINNY64 || Bp->split || workspace_dev != nullptr) return QG_OK;
+  if (kernel > QG_KERNEL_SKINNY64 || Bp->split || (workspace_dev != nullptr && !one_launch)) return QG_OK;
   if (!A_dev && M != 0) return QG_ENULL;
+  if (workspace_dev != nullptr && !aligned(workspace_dev, 16)) return QG_EALIGN;
   if (lda < Bp->K || a_zp < 0 || a_zp > 255 || !(a_inv_scale > 0.0f) || !isfinite(a_inv_scale)) return QG_EINVAL;
   if (!aligned(A_dev, 4)) return QG_EALIGN;
   int rc = gemm_common(reinterpret_cast<const uint8_t*>(A_dev), M, lda, Bp, a);
   if (rc != QG_OK) return rc;
   a->q_inv = a_inv_scale;
   a->q_zp = (float)a_zp;
+  a->q_copy = static_cast<uint8_t*>(workspace_dev);
+  a->q_ldq = f32_ldq(Bp);
   *fused = true;
   return QG_OK;
 }
@@ -1136,14 +1205,14 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
   // (with a workspace the 8-bit call below runs on the quantized copy, whose rows are 16-byte aligned and which has no split)
-  int ksplit = 1;
-  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0}, nullptr)
+  bool one_launch = false;
+  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0})
                      : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   {
     qg_gemm_args a = {};
     bool fused = false;
-    rc = f32_fused_common(A_dev, M, lda, a_inv_scale, p->a_zp, Bp, kernel, workspace_dev, &a, &fused);
+    rc = f32_fused_common(A_dev, M, lda, a_inv_scale, p->a_zp, Bp, kernel, one_launch, workspace_dev, &a, &fused);
     if (rc != QG_OK) return rc;
     if (fused) {
       a.bias = p->bias;
@@ -1177,14 +1246,14 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   int rc = check_dequant(p, Bp->N);
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
-  int ksplit = 1;
-  rc = workspace_dev ? resolve_call(Bp, M, &kernel, &ksplit, {16, OUT_F32, Bp->has_bzp != 0}, nullptr) : resolve_kernel(Bp, M, &kernel);
+  bool one_launch = false;
+  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, OUT_F32, Bp->has_bzp != 0}) : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {
     qg_gemm_args a = {};
     bool fused = false;
-    rc = f32_fused_common(A_dev, M, lda, a_inv_scale, p->a_zp, Bp, kernel, workspace_dev, &a, &fused);
+    rc = f32_fused_common(A_dev, M, lda, a_inv_scale, p->a_zp, Bp, kernel, one_launch, workspace_dev, &a, &fused);
     if (rc != QG_OK) return rc;
     if (fused) {
       a.bias = p->bias;

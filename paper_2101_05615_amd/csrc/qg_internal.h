@@ -124,6 +124,8 @@ struct qg_gemm_args {
   int32_t* ws_cnt;       // one ticket counter per (row block of 16, fragment column); zero between calls
   int32_t* ws_slots;     // ksplit slots of 272 int32 per counter
   float q_inv, q_zp;     // fp32 activations quantized while staged: 1/alpha_A, theta_A
+  uint8_t* q_copy;         // ... and where the quantized rows are kept as well (null: nowhere), rows of q_ldq bytes, a multiple of 16
+  int q_ldq;
   const int32_t* sp_ptr;      // outlier split: per-bucket offsets, or null for a dense 8-bit B
   const int32_t* sp_entries;  // outlier split: entries
   int sp_total;               // outlier split: number of entries (the buffer holds at least one)
