@@ -159,7 +159,7 @@ int builtin_select(int M, int N, int K) {
 // a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
 // The streaming kernels' prices are newer: fitted to 12000 shapes of the same range with those kernels as they are now, and with the
 // choices that tests pin held (7 x 6304 x 2816 and 9 x 8000 x 5824 stay on 64 x 32 tiles, 6.6 and 10.4 us, where the 16-row kernel now
-// takes 5.5 and 9.4; without that 1.0047).  Over 2500 others the choice is 1.0067 of the best kernel, 1.31 at worst, 132 by more than
+// takes 5.5 and 9.4; without that 1.0047).  Over 2500 others the choice is 1.0064 of the best kernel, 1.31 at worst, 127 by more than
 // 5 %; the former prices 1.049.
 struct tile_price {
   int kernel, bm, bn;
@@ -211,23 +211,27 @@ const tile_price k_tile_price[] = {
      1.151, 0.003431, 2.957, 0.0002237, 0.8557, 1.931, 1.107, 1.306, 46.77, 53.72, 0.000361, 0, 0.0003799, 2.048,
      0.0006701, 0.1854, 0.1629, 0.0001407, 11.17, 0.1874},
 };
-// (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more)
+// (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more; last the
+// four waves of one column that up to four rows and a long K get there)
 const stream_price k_stream_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 2.971, 0.02028, 0.3198, 0.04135, 0.06343, 0.002494, 0.3899, 0, 0, 0, 0, 0.0002335, 0.01044,
-     0.001402, 0.005182, 0.9532, 1.632, 0, 0, 0.009292, 0, 0, 0, 0.8289, 0.07695, 0.07528, 4.468, 0},
-    {QG_KERNEL_SKINNY16, 16, 0.1606, 3, 0.5, 0.3613, 0.1221, 0.0001349, 0.00546, 0.09893, 0.9406, 0.001453, 0.000094, 0.01302,
-     0.02301, 0.06065, 0.0308, 0.3681, 0.7629, 1.173, 1.7, 0.01757, 0.131, 0.02616, 0.1268, 1.5, 0.001786, 0.1851, 5.538,
-     0.7187},
-    {QG_KERNEL_SKINNY32, 32, 3.051, 0.1015, 0.2527, 0.1733, 0.4827, 0.0004318, 0.1973, 0, 0, 0, 0.005594, 0.008568, 0.03298,
-     0.0003416, 0.06922, 0.9537, 1.557, 0, 0, 0.01652, 0, 0.002074, 0, 1.5, 0.3889, 0.05242, 5.961, 0},
-    {QG_KERNEL_SKINNY32, 32, 3.538, 0.000066, 0.5, 0.1535, 0.152, 0.002232, 0.243, 0.1102, 6.269, 0.001624, 0.000738, 0.01211,
-     0, 0.01151, 0.05187, 0.5935, 0.9764, 1.541, 2.434, 0.02677, 1.396, 0.02288, 1.542, 1.005, 0.0007655, 0.1091, 0.1872,
-     1.518},
-    {QG_KERNEL_SKINNY64, 64, 2.993, 0.155, 0.5, 0.1854, 0.4384, 0.001442, 0.2622, 0, 0, 0, 0.0003824, 0.01331, 0.03513,
-     0.002121, 0.08019, 0.9887, 1.51, 0, 0, 0.0474, 0, 0.1317, 0, 1.176, 0.03131, 0.1368, 0.0009574, 0},
-    {QG_KERNEL_SKINNY64, 64, 3.612, 0.1868, 0.5, 0.07447, 0.04802, 0.00335, 0.6131, 0.3176, 6.943, 0.005977, 0.001392,
-     0.0004715, 0.0006752, 0.000077, 0.05994, 0.5977, 1.032, 1.165, 1.562, 0.05776, 1.692, 0.02481, 2.736, 1, 0.002279,
-     0.1431, 0.09202, 0.265},
+    {QG_KERNEL_SKINNY16, 16, 2.972, 0.02374, 0.3301, 0.03331, 0.05872, 0.002065, 0.409, 0, 0, 0, 0, 0.000305, 0.01195,
+     0.001714, 0.00669, 0.9591, 1.659, 0, 0, 0.01122, 0, 0, 0, 0.9798, 0.05142, 0.0831, 4.52, 0},
+    {QG_KERNEL_SKINNY16, 16, 0.1589, 2.896, 0.5, 0.3652, 0.1226, 0.0001379, 0.006053, 0.09703, 0.9483, 0.001508, 0.0001353,
+     0.0163, 0.04268, 0.1732, 0.1048, 0.3852, 0.852, 1.087, 1.679, 0.02464, 0.1646, 0.04969, 0.1119, 1.5, 0.0008501, 0.1957,
+     5.648, 0.7205},
+    {QG_KERNEL_SKINNY32, 32, 2.975, 0.172, 0.294, 0.1452, 0.5058, 0.0004213, 0.2335, 0, 0, 0, 0.008251, 0.02309, 0.03354,
+     0.001015, 0.05344, 0.9836, 1.621, 0, 0, 0.02527, 0, 0.007942, 0, 1.5, 0.4275, 0.04901, 1.965, 0},
+    {QG_KERNEL_SKINNY32, 32, 3.606, 0.000087, 0.5, 0.1488, 0.1486, 0.002211, 0.2263, 0.09813, 6.074, 0.001309, 0.0009126,
+     0.01467, 0, 0.02021, 0.0858, 0.667, 1.07, 1.94, 3.134, 0.03379, 1.615, 0.0288, 1.857, 1.008, 0.001006, 0.1074, 0.1865,
+     1.756},
+    {QG_KERNEL_SKINNY64, 64, 2.999, 0.1551, 0.5, 0.142, 0.6079, 0.001093, 0.2672, 0, 0, 0, 0.0001118, 0.0105, 0.03573,
+     0.001851, 0.07367, 1.005, 1.543, 0, 0, 0.06086, 0, 0.1452, 0, 1.138, 0.01149, 0.1435, 0.0009459, 0},
+    {QG_KERNEL_SKINNY64, 64, 3.498, 0.1809, 0.5, 0.07875, 0.05079, 0.003475, 0.6565, 0.3479, 6.234, 0.006161, 0.001999,
+     0.0005912, 0.0009273, 0.0001087, 0.09943, 0.6244, 1.131, 1.149, 1.505, 0.1037, 1.991, 0.03532, 3.226, 1.383, 0.002418,
+     0.1425, 0.09456, 0.5264},
+    {QG_KERNEL_SKINNY16, 16, 0.3606, 2.606, 0.5, 0.223, 0.08238, 0.000091, 0.003036, 0.1129, 2.203, 0.0019, 0.0006388,
+     0.02709, 0.102, 0.2903, 0.1066, 0.9289, 1.025, 1.044, 0.924, 0.1885, 0.3277, 0.3048, 0.06851, 1.5, 0.007077, 0.07079,
+     3.001, 2.78},
 };
 
 enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
@@ -311,7 +315,8 @@ int price_select(int M, int N, int K, const call_form& f, double* price = nullpt
     if (us < best_us) best_us = us, best = kernel;
   };
   for (int i = 0; i < 3; ++i) {
-    const stream_price& c = k_stream_price[2 * i + (wide(k_stream_price[2 * i].rows) ? 1 : 0)];
+    const int at = !wide(k_stream_price[2 * i].rows) ? 2 * i : i == 0 && M <= 4 && K > 64 * 64 ? 6 : 2 * i + 1;
+    const stream_price& c = k_stream_price[at];
     if (ceil_div(M, c.rows) <= 65535) take(c.kernel, stream_price_us(c, M, N, K, f));
   }
   const bool few = qg_tile128_few(M, N, K);
