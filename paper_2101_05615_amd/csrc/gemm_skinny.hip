@@ -156,9 +156,8 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     }
   };
 
-  // K slices are dealt to the waves rotated by the workgroup index, so that at any instant the workgroups
-  // of an XCD read DIFFERENT lines of A (all of them read all of A; unrotated they would all hit the same
-  // L2 channel at the same time)
+  // K slices are dealt to the waves rotated from workgroup to workgroup (qg_stream_slice): unrotated the workgroups of an XCD
+  // would all hit the same L2 channel at the same time
   // (4-bit weights come in pairs of k blocks, so their slices hold an even number of blocks)
   // (ksplit > 1: this workgroup owns slice blockIdx.z of K, whole k blocks, an even number of them for 4-bit weights)
   // (plain shifts and additions up to the first loads: everything in front of them is latency)
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   const int ks_begin = min(blocks, (int)blockIdx.z * ks_per), ks_end = min(blocks, ks_begin + ks_per);
   const int ks_len = ks_end - ks_begin;
   const int per = B4 ? (int)((unsigned)(ks_len + 2 * NWAVES - 1) / (2 * NWAVES) * 2) : (int)((unsigned)(ks_len + NWAVES - 1) / NWAVES);
-  const int kb_begin = min(ks_end, ks_begin + (int)((wave + blockIdx.x) % NWAVES) * per);
+  const int kb_begin = min(ks_end, ks_begin + qg_stream_slice(wave, blockIdx.x, NWAVES) * per);
   const int kb_end = min(ks_end, kb_begin + per);
 
   // outlier split: the entry offsets of all of this wave's batches, one per lane (batch b: lanes b and b+1), are

@@ -6,6 +6,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "qg_stream.h"
 #include "qgemm.h"
 
 // ---------------------------------------------------------------------------
@@ -339,35 +340,6 @@ inline hipError_t qg_allow_smem(int bytes) {
   return e;
 }
 #endif
-
-// The build of a streaming kernel: waves of a workgroup, k blocks that a wave requests at once, fragment columns per wave.  kb: k blocks
-// of a slice; sb: super-blocks of `rows` rows x 32 columns, slices counted; split: 4-bit weights.  Measured on some 150 shapes
-// (M 1 .. 64, N and K 512 .. 8192, graph replays, every build on each):
-//  - up to 16 k blocks four waves, up to 32 eight: one batch each, and the fewer waves there are to start and to add up the better
-//    (7 x 1408 x 891: sixteen waves 4.5 us, eight 3.65; 1 x 576 x 960 3.5 and, four, 3.0);
-//  - up to 64 sixteen waves (16 x 4096 x 4096: 5.2 against 6.2 with eight), beyond that eight again, whose batches follow each
-//    other without a gap (1 x 704 x 5888 4.0 against 4.5); with 4-bit weights, half the bytes per batch, sixteen throughout;
-//  - more workgroups of 16 columns than CUs: two fragment columns per wave (13 x 6400 x 3392 6.3 us; sixteen waves of one 8.2).
-//    With 4-bit weights and a long K sixteen waves do that too (16 x 8192 x 8192 with 0.5 % of outliers 10.2 against 12.2).  At most
-//    four rows and a long K, hardly any activations to share: four waves of one column again (3 x 4736 x 6848 8.4 us against 8.9,
-//    2 x 7512 x 7936 11.1 against 12.3).
-struct qg_stream_build {
-  int waves, batch, columns;
-};
-static inline qg_stream_build qg_stream_build_of(int rows, int kb, long long sb, int M, bool split) {
-  const bool wide = sb > 128;
-  if (rows == 16) {
-    if (kb <= 16 || (!split && wide && kb > 64 && M <= 4)) return {4, 4, 1};
-    if (wide) return split && sb <= 256 && kb > 36 ? qg_stream_build{16, 4, 2} : qg_stream_build{8, 4, 2};
-    return kb > 32 && (kb <= 64 || split) ? qg_stream_build{16, 4, 1} : qg_stream_build{8, 4, 1};
-  }
-  if (rows == 32) {
-    if (wide) return split || kb <= 32 ? qg_stream_build{8, 4, 2} : qg_stream_build{4, 4, 2};
-    if (kb <= 32) return {8, 4, 1};
-    return split || kb > 64 ? qg_stream_build{16, 2, 1} : qg_stream_build{16, 4, 1};
-  }
-  return {8, 2, wide ? 2 : 1};
-}
 
 // launchers (each returns a hipError_t from hipGetLastError after the launch)
 hipError_t qg_launch_pack_b(const int8_t* B, int K, int N, int ldb, int transposed, int K_pad, int N_pad,
