@@ -341,7 +341,8 @@ int qg_quantize_a_f32(const float* A_dev, int M, int K, int lda, float inv_scale
  *    quantized copy, two launches on `stream`.  QG_KERNEL_AUTO with up to 512 rows
  *    takes ONE launch of a streaming kernel (below) where that is estimated to be
  *    faster, which also stores the quantized rows.  The quantized copy stays in
- *    the workspace either way.
+ *    the workspace either way.  C may lie over A here (two launches then); the
+ *    workspace may overlap neither.
  *  - workspace_dev == NULL and a streaming kernel (kernel, or what QG_KERNEL_AUTO
  *    resolves to, is QG_KERNEL_SKINNY*; dense descriptor): ONE launch, nothing
  *    written but C.  The kernel quantizes the block of A it stages, with the

@@ -1151,9 +1151,17 @@ size_t qg_gemm_f32_workspace_bytes(int M, const qg_packed_b* Bp) {
   return (size_t)M * (size_t)f32_ldq(Bp);  // what a tiled kernel needs; a streaming kernel needs none
 }
 
-// With a workspace: the kernel of an automatic call, and whether it quantizes A itself.
-static int f32_resolve(const qg_packed_b* Bp, int M, int* kernel, bool* one_launch, const call_form& f) {
-  if (*kernel == QG_KERNEL_AUTO && !Bp->split && M > 0 && rule_kernel(M, Bp->N, Bp->K) == QG_KERNEL_AUTO) {
+// whether rows of the fp32 A share memory with rows of C
+static bool f32_in_place(const float* A_dev, int M, int lda, int K, const void* C_dev, int ldc, int N, size_t c_size) {
+  if (M <= 0) return false;
+  const uintptr_t a = reinterpret_cast<uintptr_t>(A_dev), c = reinterpret_cast<uintptr_t>(C_dev);
+  return a < c + ((size_t)(M - 1) * ldc + N) * c_size && c < a + ((size_t)(M - 1) * lda + K) * sizeof(float);
+}
+
+// With a workspace: the kernel of an automatic call, and whether it quantizes A itself.  Not where C lies over A: the two launches
+// have read all of A before they write C, in one launch every column block reads A while others already write.
+static int f32_resolve(const qg_packed_b* Bp, int M, int* kernel, bool* one_launch, const call_form& f, bool in_place) {
+  if (*kernel == QG_KERNEL_AUTO && !in_place && !Bp->split && M > 0 && rule_kernel(M, Bp->N, Bp->K) == QG_KERNEL_AUTO) {
     const int k = f32_select(M, Bp->N, Bp->K, f);
     if (k != QG_KERNEL_AUTO) {
       *kernel = k;
@@ -1211,7 +1219,8 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
   // (with a workspace the 8-bit call below runs on the quantized copy, whose rows are 16-byte aligned and which has no split)
   bool one_launch = false;
-  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0})
+  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0},
+                                 f32_in_place(A_dev, M, lda, Bp->K, C_dev, ldc, Bp->N, 1))
                      : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   {
@@ -1252,7 +1261,9 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   if (rc != QG_OK) return rc;
   if (M < 0 || ldc < Bp->N) return QG_EINVAL;
   bool one_launch = false;
-  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, OUT_F32, Bp->has_bzp != 0}) : resolve_kernel(Bp, M, &kernel);
+  rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, OUT_F32, Bp->has_bzp != 0},
+                                   f32_in_place(A_dev, M, lda, Bp->K, C_dev, ldc, Bp->N, sizeof(float)))
+                     : resolve_kernel(Bp, M, &kernel);
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {

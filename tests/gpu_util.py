@@ -47,3 +47,36 @@ def oracle_gemm(case, oracle, rows=None):
     A = case.A if rows is None else np.ascontiguousarray(case.A[rows])
     return oracle.gemm_u8s8_requant(A, case.a_zp, case.B, case.b_zp, case.bias, case.scales, case.c_zp,
                                     case.relu)
+
+
+def kernels_of(call):
+    """The (mangled) names of the kernels that `call` launches, in order: it is recorded into a graph, whose nodes are read.  Says
+    which kernel a call that leaves the choice to the library really runs."""
+    import ctypes
+    import torch
+    hip = ctypes.CDLL("libamdhip64.so", mode=ctypes.RTLD_GLOBAL)   # (the one that torch has loaded)
+    vp, u = ctypes.c_void_p, ctypes.c_uint
+
+    class KernelNodeParams(ctypes.Structure):
+        _fields_ = [("block", u * 3), ("extra", vp), ("func", vp), ("grid", u * 3), ("params", vp), ("lds", u)]
+
+    def ok(rc):
+        assert rc == 0, f"HIP error {rc}"
+
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    graph, n = vp(g.raw_cuda_graph()), ctypes.c_size_t()
+    ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(n)))
+    nodes = (vp * n.value)()
+    ok(hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)))
+    hip.hipKernelNameRefByPtr.argtypes, hip.hipKernelNameRefByPtr.restype = [vp, vp], ctypes.c_char_p
+    names = []
+    for node in nodes:
+        kind, p = ctypes.c_int(-1), KernelNodeParams()
+        ok(hip.hipGraphNodeGetType(vp(node), ctypes.byref(kind)))
+        assert kind.value == 0, f"a graph node of type {kind.value}"
+        ok(hip.hipGraphKernelNodeGetParams(vp(node), ctypes.byref(p)))
+        names.append(hip.hipKernelNameRefByPtr(p.func, None).decode())
+    return names
