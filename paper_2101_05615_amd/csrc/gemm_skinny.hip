@@ -98,12 +98,12 @@ __device__ __forceinline__ void wait_vm() {
 // two MFMAs, the workgroup stages half as many activation bytes per weight byte, and few fat waves (16 weight loads in flight
 // each) keep a large matrix streaming at the rate of a plain read -- the shape for more workgroups than CUs.
 // DB: two staging regions per wave, so that a batch's activations are requested one batch ahead like its weights.
-// ONE: every wave of every slice has exactly one whole batch (checked by the host): straight code, nothing that K could cut
-// (16 x 4096 x 4096, 256 workgroups that start together: 4.60 us, 4.70 with the code for the other cases around it).
+// WHOLE: every wave of every slice has whole batches and nothing that K could cut (checked by the host): one batch without DB, straight
+// code then, any number with it.
 // SRC_CONV16: the same for any multiple of 16 channels.  A k block may then hold pieces of several taps, so the tap is per-lane
 // state, moved on by four 16-byte pieces per block (2 x 12 x 12 x 96 -> 128, 3 x 3, stride 2: 6.3 us on the tiles, 4.2 here).
 constexpr int SRC_U8 = 0, SRC_F32 = 1, SRC_CONV = 2, SRC_CONV16 = 3;
-template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool ONE = false>
+template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool WHOLE = false>
 __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAVES / 4) void qg_gemm_skinny_kernel(
     const uint8_t* A, const int8_t* Bp, const int M, const int N, const int K, const int kb64, const int nb16_total, const int lda,
     const int ks_per, const int ksplit, const qg_gemm_args p) {
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   // names in p): the file is compiled with kernel-argument preloading, so they arrive in scalar registers with the
   // wave instead of costing a cold trip to memory (measured: 0.4 us of a 5 us launch).
   static_assert(!B4 || (SRC == SRC_U8 && DB), "4-bit weights: rows of bytes, all requests of a batch one batch ahead");
-  static_assert(!ONE || (SRC == SRC_U8 && !B4 && !DB), "one whole batch of 8-bit weights and rows of bytes");
+  static_assert(!WHOLE || (SRC == SRC_U8 && !B4), "whole batches of 8-bit weights and rows of bytes");
   static_assert(SRC != SRC_F32 || !DB, "fp32 rows pass through registers, batch by batch");
   static_assert(MB * CPW <= NWAVES, "one wave per (row block, fragment column) runs the output pipeline");
   constexpr bool CONV = SRC == SRC_CONV || SRC == SRC_CONV16;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   bool cut = false;  // (uniform) this wave has the chunk that K cuts
   v4i row_end;
   auto load_row_end = [&]() {
-    cut = SRC == SRC_U8 && (K & 15) != 0 && kb_end == blocks;
+    cut = SRC == SRC_U8 && !WHOLE && (K & 15) != 0 && kb_end == blocks;
     if (cut) {
       const uint8_t* const row = A + (size_t)min(m_base + lane % ROWS, M - 1) * lda;
       if (K >= 16)
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     for (int i = 0; i < NLOAD / CPW; ++i) {
 #pragma unroll
       for (int c = 0; c < CPW; ++c) raw[i * CPW + c] = *reinterpret_cast<const v4i*>(wptr + c * QG_FRAG_BYTES + lane16);  // (adjacent KiBs)
-      wptr += ONE || kb0 + (i + 1) * STEP < kb_end ? b_step : (size_t)0;
+      wptr += WHOLE || kb0 + (i + 1) * STEP < kb_end ? b_step : (size_t)0;
     }
   };
   auto operand = [&](const v4i (&raw)[NLOAD], int j, int c) -> v4i {
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
       }
     } else {
       const uint8_t* const a_base = A + (size_t)kb * QG_FRAG_K;  // wave-uniform
-      if (ONE || (kb + BATCH) * QG_FRAG_K <= K) {
+      if (WHOLE || (kb + BATCH) * QG_FRAG_K <= K) {
         if (few) {
 #pragma unroll
           for (int jj = 0; jj < FEW; ++jj) request_a(a_base, a_off[jj], dst + jj * 1024);
@@ -341,6 +341,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   };
   // the chunk that K cuts, over what its request left there
   auto put_row_end = [&](int kb, int buf) {
+    if (WHOLE) return;
     const int c = (K >> 4) - kb * (QG_FRAG_K / 16);  // its place in the batch
     if (cut && c < NCHUNK) {
       const v4i v = K >= 16 ? qg_row_end_chunk(row_end, K & 15) : row_end;
@@ -364,7 +365,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     // 0: a batch inside K; 1: K ends in it (the last four floats of the row for whatever begins past them, the bytes shifted into
     // place: 0.95 of the time with four loads per lane, K off 64); 2: K < 4, float by float
     auto convert = [&](auto form) {
-      constexpr bool WHOLE = decltype(form)::value == 0;
+      constexpr bool INSIDE = decltype(form)::value == 0;
 #pragma unroll 1
       for (int t0 = 0; t0 < total; t0 += GRP) {
         v4f v[GRP];
@@ -372,9 +373,9 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
         for (int t = 0; t < GRP; ++t) {
           const int i = min(t0 + t, total - 1), r = (i & ((1 << sh) - 1)) * 4 + (l >> 4), k = (kb + (i >> sh)) * QG_FRAG_K + q * 4;
           const float* const row = Af + (size_t)min(m_base + r, M - 1) * lda;
-          if (WHOLE) {
+          if (INSIDE) {
             v[t] = *reinterpret_cast<const v4f_any*>(row + k);
-          } else if (decltype(form)::value == 1) { 
+          } else if (decltype(form)::value == 1) {
             const int at = min(k, K - 4);
             v[t] = *reinterpret_cast<const v4f_any*>(row + at);
           } else {
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
           unsigned d = 0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) d = qg_quantize_pack(v[t][e], p.q_inv, p.q_zp, e, d);
-          if (!WHOLE) {
+          if (!INSIDE) {
             if (decltype(form)::value == 1) d >>= 8 * min(max((kb + j) * QG_FRAG_K + q * 4 - (K - 4), 0), 3);
             const int nv = min(max(K - (kb + j) * QG_FRAG_K - q * 4, 0), 4);
             const unsigned keep = nv == 4 ? 0xFFFFFFFFu : (1u << (8 * nv)) - 1u;
@@ -467,7 +468,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
         for (int c = 0; c < CPW; ++c) acc[mb][c] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[c], af[mb][j], acc[mb][c], 0, 0, 0);
       }
     };
-    if (ONE || kb + BATCH <= kb_end) {
+    if (WHOLE || kb + BATCH <= kb_end) {
 #pragma unroll
       for (int j = 0; j < BATCH; ++j) {
         dense(j);
@@ -579,7 +580,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     consume(kb, buf, cur, ent);
     if (has_next) copy_rows(kb);
   };
-  if constexpr (ONE) {
+  if constexpr (WHOLE && !DB) {
     v4i w0[NLOAD];
     load_w(kb_begin, w0);
     request_rows(kb_begin, 0);
@@ -734,14 +735,14 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   }
 }
 
-template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool ONE = false>
+template <int MODE, int MB, int NWAVES, int BATCH, int CPW, bool B4, int SRC, bool DB, bool WHOLE = false>
 hipError_t launch(const qg_gemm_args& a, hipStream_t s) {
   constexpr int SMEM = NWAVES * (MB * 16) * (BATCH * QG_FRAG_K) * (DB ? 2 : 1) + NWAVES * MB * 16 * (int)sizeof(int) + MB * CPW * 256;
   static_assert(SMEM <= 160 * 1024, "LDS of a CU");
   const int mblocks = (a.M + MB * 16 - 1) / (MB * 16);
   if (mblocks > 65535 || a.ksplit < 1 || a.ksplit > 65535) return hipErrorInvalidValue;
   if (a.ksplit > 1 && (a.ws_cnt == nullptr || a.ws_slots == nullptr)) return hipErrorInvalidValue;
-  constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, CPW, B4, SRC, DB, ONE>;
+  constexpr auto fn = qg_gemm_skinny_kernel<MODE, MB, NWAVES, BATCH, CPW, B4, SRC, DB, WHOLE>;
   hipError_t e = qg_allow_smem<fn>(SMEM);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fn, dim3(((a.N + 31) / 32) * 2 / CPW, mblocks, a.ksplit), dim3(NWAVES * 64), SMEM, s, a.A, a.Bp, a.M, a.N, a.K,
@@ -756,15 +757,23 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
   const int rows = 16 << (kernel - QG_KERNEL_SKINNY16);
   const long long sb = (long long)((a.N + 31) / 32) * ((a.M + rows - 1) / rows) * a.ksplit;
   const qg_stream_build f = qg_stream_build_of(rows, kb, sb, a.M, B4);
+  if constexpr (SRC == SRC_U8 && !B4) {
+    // Whole batches in every wave of every slice.  One batch: 13 x 3328 x 1024 2.67 us on the build for any K, 2.46 so (four waves), 16 x 640
+    // x 2048 2.82 and 2.61 (eight); several ahead of each other: 8 x 4832 x 4096 5.61 and 5.47, 16 x 14048 x 4096 10.50 and 10.42.
+    // Four waves with several batches are not faster so (M up to 4 and a long K: 1.00 to 1.04).
+    if (rows == 16 && a.K % QG_FRAG_K == 0 && kb * a.ksplit == blocks && kb % (f.waves * f.batch) == 0) {
+      const bool one = kb == f.waves * f.batch;
+      if (one && f.waves == 4 && f.columns == 1) return launch<MODE, 1, 4, 4, 1, B4, SRC, false, true>(a, s);
+      if (one && f.waves == 8 && f.columns == 1) return launch<MODE, 1, 8, 4, 1, B4, SRC, false, true>(a, s);
+      if (one && f.waves == 16) return launch<MODE, 1, 16, 4, 1, B4, SRC, false, true>(a, s);
+      if (f.waves == 8 && f.columns == 2) return launch<MODE, 1, 8, 4, 2, B4, SRC, true, true>(a, s);
+    }
+  }
   switch (rows * 10000 + f.waves * 100 + f.batch * 10 + f.columns) {
     case 160441: return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
     case 160841: return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);
     case 160842: return launch<MODE, 1, 8, 4, 2, B4, SRC, DB>(a, s);
-    case 161641:
-      if constexpr (SRC == SRC_U8 && !B4) {
-        if (a.ks_per == 64 && a.K % (64 * QG_FRAG_K) == 0) return launch<MODE, 1, 16, 4, 1, B4, SRC, false, true>(a, s);
-      }
-      return launch<MODE, 1, 16, 4, 1, B4, SRC, B4>(a, s);  // (8-bit: one batch, nothing to request ahead)
+    case 161641: return launch<MODE, 1, 16, 4, 1, B4, SRC, B4>(a, s);  // (8-bit: one batch, nothing to request ahead)
     case 320841: return launch<MODE, 2, 8, 4, 1, B4, SRC, DB>(a, s);
     case 320842: return launch<MODE, 2, 8, 4, 2, B4, SRC, DB>(a, s);
     case 321621: return launch<MODE, 2, 16, 2, 1, B4, SRC, DB>(a, s);
