@@ -416,7 +416,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   auto request_entries = [&](int b, entries& e) {
     if (B4) {
 #pragma unroll
-      for (int c = 0; c < CPW; ++c) {  // at most 64 batches per wave: K <= 32768 gives 128 blocks to each of four waves
+      for (int c = 0; c < CPW; ++c) {  // at most 32 batches per wave: K <= 32768 gives 128 blocks to each of four waves, four a batch
         e.at[c] = __builtin_amdgcn_readlane(sp_offs[c], b);
         e.n[c] = __builtin_amdgcn_readlane(sp_offs[c], b + 1) - e.at[c];
         e.first[c] = p.sp_entries[min(e.at[c] + lane, max(p.sp_total, 1) - 1)];
@@ -785,6 +785,7 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
   }
   if (rows == 64) return hipErrorInvalidValue;
   if constexpr (B4) {
+    if (rows == 32) return f.batch == 2 && f.waves == 8 ? launch<MODE, 2, 8, 2, 1, B4, SRC, DB>(a, s) : hipErrorInvalidValue;
     if (f.waves == 16 && f.columns == 2) return launch<MODE, 1, 16, 4, 2, B4, SRC, DB>(a, s);
   } else {
     if (f.waves == 4) return launch<MODE, 2, 4, 4, 2, B4, SRC, DB>(a, s);

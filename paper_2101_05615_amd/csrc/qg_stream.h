@@ -18,7 +18,10 @@
 //  - more workgroups of 16 columns than CUs: two fragment columns per wave (13 x 6400 x 3392 6.3 us; sixteen waves of one 8.2).
 //    With 4-bit weights and a long K sixteen waves do that too (16 x 8192 x 8192 with 0.5 % of outliers 10.2 against 12.2).  At most
 //    four rows and a long K, hardly any activations to share: four waves of one column again (3 x 4736 x 6848 8.4 us against 8.9,
-//    2 x 7512 x 7936 11.1 against 12.3).
+//    2 x 7512 x 7936 11.1 against 12.3);
+//  - 4-bit weights on more than 256 super-blocks: a wave's scatter of two columns in turn is what the workgroups of a CU wait for, so one
+//    column again, four waves or batches of two.  140 shapes of M 1 .. 128: 16 rows 0.64 to 0.96 of the time of two columns (7 x 8352 x 2240
+//    with 0.5 %: 6.7 us, 4.8 so), 32 rows 0.73 to 1.08 in the mean 0.86 (58 x 4608 x 5440 with 2 %: 19.0, 15.4 so); up to 256 they lose.
 struct qg_stream_build {
   int waves, batch, columns;
 };
@@ -26,10 +29,12 @@ static inline qg_stream_build qg_stream_build_of(int rows, int kb, long long sb,
   const bool wide = sb > 128;
   if (rows == 16) {
     if (kb <= 16 || (!split && wide && kb > 64 && M <= 4)) return {4, 4, 1};
-    if (wide) return split && sb <= 256 && kb > 36 ? qg_stream_build{16, 4, 2} : qg_stream_build{8, 4, 2};
+    if (split && sb > 256) return {4, 4, 1};
+    if (wide) return split && kb > 36 ? qg_stream_build{16, 4, 2} : qg_stream_build{8, 4, 2};
     return kb > 32 && (kb <= 64 || split) ? qg_stream_build{16, 4, 1} : qg_stream_build{8, 4, 1};
   }
   if (rows == 32) {
+    if (split && sb > 256) return {8, 2, 1};
     if (wide) return split || kb <= 32 ? qg_stream_build{8, 4, 2} : qg_stream_build{4, 4, 2};
     if (kb <= 32) return {8, 4, 1};
     return split || kb > 64 ? qg_stream_build{16, 2, 1} : qg_stream_build{16, 4, 1};
