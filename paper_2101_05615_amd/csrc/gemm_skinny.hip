@@ -769,6 +769,12 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
       if (f.waves == 8 && f.columns == 2) return launch<MODE, 1, 8, 4, 2, B4, SRC, true, true>(a, s);
     }
   }
+  if constexpr (B4) {
+    if (f.waves == 4 && f.batch == 2) {
+      if (rows == 16) return launch<MODE, 1, 4, 2, 1, B4, SRC, DB>(a, s);
+      return rows == 32 ? launch<MODE, 2, 4, 2, 1, B4, SRC, DB>(a, s) : launch<MODE, 4, 4, 2, 1, B4, SRC, DB>(a, s);
+    }
+  }
   switch (rows * 10000 + f.waves * 100 + f.batch * 10 + f.columns) {
     case 160441: return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
     case 160841: return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);
@@ -785,7 +791,6 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
   }
   if (rows == 64) return hipErrorInvalidValue;
   if constexpr (B4) {
-    if (rows == 32) return f.batch == 2 && f.waves == 8 ? launch<MODE, 2, 8, 2, 1, B4, SRC, DB>(a, s) : hipErrorInvalidValue;
     if (f.waves == 16 && f.columns == 2) return launch<MODE, 1, 16, 4, 2, B4, SRC, DB>(a, s);
   } else {
     if (f.waves == 4) return launch<MODE, 2, 4, 4, 2, B4, SRC, DB>(a, s);

@@ -20,25 +20,31 @@
 //    four rows and a long K, hardly any activations to share: four waves of one column again (3 x 4736 x 6848 8.4 us against 8.9,
 //    2 x 7512 x 7936 11.1 against 12.3);
 //  - 4-bit weights on more than 256 super-blocks: a wave's scatter of two columns in turn is what the workgroups of a CU wait for, so one
-//    column again, four waves or batches of two.  140 shapes of M 1 .. 128: 16 rows 0.64 to 0.96 of the time of two columns (7 x 8352 x 2240
-//    with 0.5 %: 6.7 us, 4.8 so), 32 rows 0.73 to 1.08 in the mean 0.86 (58 x 4608 x 5440 with 2 %: 19.0, 15.4 so); up to 256 they lose.
+//    column again, and four waves, whose regions leave room for more workgroups per CU, most of all with batches of two.  460 shapes of M
+//    1 .. 512: 16 rows 0.64 to 0.96 of the time of two columns with batches of four (7 x 8352 x 2240 with 0.5 %: 6.7 us, 4.8 so), from 513
+//    on 0.74 to 0.98 of that with batches of two; 32 rows 0.71 to 0.96 of eight waves, which had taken 0.73 to 1.08 of two columns; 64 rows
+//    only up to 8 k blocks (0.79 to 0.98; from 9 to 16 0.93 to 1.16).  Up to 256 super-blocks all of these lose.  (The offsets of a wave's batches lie one per lane,
+//    the last one's end included: at most 63 batches, so batches of two end at 256 k blocks, 32 of them per wave.)
+//    65 to 96 k blocks on 128 super-blocks and less: the second batch of sixteen waves would be half empty, eight take three (0.94 to
+//    0.96, with more than 1 % of outliers 1.03 to 1.05; 9 x 1600 x 6144 4.7 us, 4.1).
 struct qg_stream_build {
   int waves, batch, columns;
 };
 static inline qg_stream_build qg_stream_build_of(int rows, int kb, long long sb, int M, bool split) {
   const bool wide = sb > 128;
   if (rows == 16) {
-    if (kb <= 16 || (!split && wide && kb > 64 && M <= 4)) return {4, 4, 1};
-    if (split && sb > 256) return {4, 4, 1};
+    if ((kb <= 16 && !(split && sb > 512)) || (!split && wide && kb > 64 && M <= 4)) return {4, 4, 1};
+    if (split && sb > 256) return sb > 512 && kb <= 256 ? qg_stream_build{4, 2, 1} : qg_stream_build{4, 4, 1};
     if (wide) return split && kb > 36 ? qg_stream_build{16, 4, 2} : qg_stream_build{8, 4, 2};
-    return kb > 32 && (kb <= 64 || split) ? qg_stream_build{16, 4, 1} : qg_stream_build{8, 4, 1};
+    return kb > 32 && (kb <= 64 || (split && kb > 96)) ? qg_stream_build{16, 4, 1} : qg_stream_build{8, 4, 1};
   }
   if (rows == 32) {
-    if (split && sb > 256) return {8, 2, 1};
+    if (split && sb > 256 && kb <= 256) return {4, 2, 1};
     if (wide) return split || kb <= 32 ? qg_stream_build{8, 4, 2} : qg_stream_build{4, 4, 2};
     if (kb <= 32) return {8, 4, 1};
     return split || kb > 64 ? qg_stream_build{16, 2, 1} : qg_stream_build{16, 4, 1};
   }
+  if (split && sb > 256 && kb <= 8) return {4, 2, 1};
   return {8, 2, wide ? 2 : 1};
 }
 

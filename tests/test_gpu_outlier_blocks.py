@@ -12,9 +12,15 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("frac", [0.0, 0.01, 0.1, 1.0])
 @pytest.mark.parametrize("kernel,build,M,N,K,a_off", [
     ("skinny16", (1, 4, 4, 1), 7, 8230, 1100, 0), ("skinny16", (1, 4, 4, 1), 40, 2900, 4163, 3), ("skinny16", (1, 4, 4, 1), 33, 2752, 2176, 5),
+    ("skinny16", (1, 4, 2, 1), 50, 4300, 1100, 0), ("skinny16", (1, 4, 2, 1), 130, 1900, 4163, 3), ("skinny16", (1, 4, 2, 1), 97, 2350, 300, 5),
     ("skinny16", (1, 16, 4, 2), 32, 4096, 2560, 0), ("skinny16", (1, 8, 4, 2), 32, 4070, 2300, 0),   # 256: not yet
-    ("skinny32", (2, 8, 2, 1), 65, 2900, 1030, 0), ("skinny32", (2, 8, 2, 1), 8, 8240, 130, 1), ("skinny32", (2, 8, 2, 1), 97, 2080, 4163, 2),
+    ("skinny16", (1, 8, 4, 1), 9, 200, 6144, 0), ("skinny16", (1, 8, 4, 1), 20, 70, 4163, 1), ("skinny16", (1, 16, 4, 1), 9, 200, 6200, 0),
+    ("skinny32", (2, 4, 2, 1), 65, 2900, 1030, 0), ("skinny32", (2, 4, 2, 1), 8, 8240, 130, 1), ("skinny32", (2, 4, 2, 1), 97, 2080, 4163, 2),
     ("skinny32", (2, 8, 4, 2), 64, 4096, 1100, 0),
+    ("skinny64", (4, 4, 2, 1), 65, 4300, 500, 0), ("skinny64", (4, 4, 2, 1), 130, 2750, 130, 3), ("skinny64", (4, 8, 2, 2), 65, 4300, 530, 0),
+    # batches of two end where a wave would have more offsets than lanes
+    ("skinny16", (1, 4, 2, 1), 300, 864, 16384, 0), ("skinny16", (1, 4, 4, 1), 300, 864, 16400, 0),
+    ("skinny32", (2, 4, 2, 1), 300, 830, 16384, 0), ("skinny32", (2, 8, 4, 2), 300, 830, 16400, 0),
 ])
 def test_many_blocks(frac, kernel, build, M, N, K, a_off):
     import torch
