@@ -157,10 +157,11 @@ int builtin_select(int M, int N, int K) {
 // of the best kernel in the geometric mean, 1.32 at worst, 178 of them by more than 5 %; over 1400 other round ones 1.0030, 1.20 and
 // 31.  The prices above: 1.050 and 1.026; a fit to ordinary shapes alone: 1.020 and 1.026, 2.5 at worst (tall shapes of few columns and
 // a long K: 827 x 17 x 15685 25.1 us, 10.4 on the 16-row kernel).
-// The streaming kernels' prices are newer: fitted to 12000 shapes of the same range with those kernels as they are now, and with the
-// choices that tests pin held (7 x 6304 x 2816 and 9 x 8000 x 5824 stay on 64 x 32 tiles, 6.6 and 10.4 us, where the 16-row kernel now
-// takes 5.5 and 9.4; without that 1.0047).  Over 2500 others the choice is 1.0064 of the best kernel, 1.31 at worst, 127 by more than
-// 5 %; the former prices 1.049.
+// The streaming kernels' prices are newer: fitted to 39000 shapes, columns up to 32768 and K of whole 256, 1024 and 2048 among them, with
+// those kernels as they are now (times scaled to the price of the best tiled kernel on each, then the loss of the choice; no choice is
+// held).  Over 3000 others the choice is 1.0048 of the best kernel, 104 by more than 5 %; the former prices, which had two choices held,
+// 1.0151 and 306, and on up to 24 rows with 2048 columns and more 1.033, now 1.0062 (9 x 6208 x 6752 10.9 us, 8.9 now; 14 x 5632 x 3648
+// 7.1, 5.8).  On 1200 large products 1.0094, by the prices of the tiled kernels.
 struct tile_price {
   int kernel, bm, bn;
   double fix, lat, crowd, thr, fill, epi, out;         // out: megabytes of output per microsecond
@@ -184,6 +185,9 @@ struct stream_price {
   double a_far, far;                                   // tens of megabytes of A per us, once per column block from beyond the L2s; beyond 4
   double fetch, near;                                  // us per megabyte that the XCDs fetch beyond so many
   double round;                                        // per round of 256 workgroups after the first
+  double b_far, b_near;                                // us per megabyte of B beyond b_near
+  double whole;                                        // so much less where the batches of all waves are whole
+  double more_second, more_wg_k;                       // more than one row block, which share the weights: second; factor of wg_k
 };
 // The second of QG_KERNEL_TILE128 is the 128 x 64 form, which runs on at most one workgroup per CU (its terms beyond are zero).
 const tile_price k_tile_price[] = {
@@ -211,27 +215,40 @@ const tile_price k_tile_price[] = {
      1.151, 0.003431, 2.957, 0.0002237, 0.8557, 1.931, 1.107, 1.306, 46.77, 53.72, 0.000361, 0, 0.0003799, 2.048,
      0.0006701, 0.1854, 0.1629, 0.0001407, 11.17, 0.1874},
 };
-// (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more; last the
-// four waves of one column that up to four rows and a long K get there)
+// (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more; then the
+// other builds and depths beyond 128: 16 rows, four waves of one column, for up to four rows and a long K and for up to 16 k blocks; 32
+// rows, up to 32 k blocks; 16 rows, up to 32)
 const stream_price k_stream_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 2.972, 0.02374, 0.3301, 0.03331, 0.05872, 0.002065, 0.409, 0, 0, 0, 0, 0.000305, 0.01195,
-     0.001714, 0.00669, 0.9591, 1.659, 0, 0, 0.01122, 0, 0, 0, 0.9798, 0.05142, 0.0831, 4.52, 0},
-    {QG_KERNEL_SKINNY16, 16, 0.1589, 2.896, 0.5, 0.3652, 0.1226, 0.0001379, 0.006053, 0.09703, 0.9483, 0.001508, 0.0001353,
-     0.0163, 0.04268, 0.1732, 0.1048, 0.3852, 0.852, 1.087, 1.679, 0.02464, 0.1646, 0.04969, 0.1119, 1.5, 0.0008501, 0.1957,
-     5.648, 0.7205},
-    {QG_KERNEL_SKINNY32, 32, 2.975, 0.172, 0.294, 0.1452, 0.5058, 0.0004213, 0.2335, 0, 0, 0, 0.008251, 0.02309, 0.03354,
-     0.001015, 0.05344, 0.9836, 1.621, 0, 0, 0.02527, 0, 0.007942, 0, 1.5, 0.4275, 0.04901, 1.965, 0},
-    {QG_KERNEL_SKINNY32, 32, 3.606, 0.000087, 0.5, 0.1488, 0.1486, 0.002211, 0.2263, 0.09813, 6.074, 0.001309, 0.0009126,
-     0.01467, 0, 0.02021, 0.0858, 0.667, 1.07, 1.94, 3.134, 0.03379, 1.615, 0.0288, 1.857, 1.008, 0.001006, 0.1074, 0.1865,
-     1.756},
-    {QG_KERNEL_SKINNY64, 64, 2.999, 0.1551, 0.5, 0.142, 0.6079, 0.001093, 0.2672, 0, 0, 0, 0.0001118, 0.0105, 0.03573,
-     0.001851, 0.07367, 1.005, 1.543, 0, 0, 0.06086, 0, 0.1452, 0, 1.138, 0.01149, 0.1435, 0.0009459, 0},
-    {QG_KERNEL_SKINNY64, 64, 3.498, 0.1809, 0.5, 0.07875, 0.05079, 0.003475, 0.6565, 0.3479, 6.234, 0.006161, 0.001999,
-     0.0005912, 0.0009273, 0.0001087, 0.09943, 0.6244, 1.131, 1.149, 1.505, 0.1037, 1.991, 0.03532, 3.226, 1.383, 0.002418,
-     0.1425, 0.09456, 0.5264},
-    {QG_KERNEL_SKINNY16, 16, 0.3606, 2.606, 0.5, 0.223, 0.08238, 0.000091, 0.003036, 0.1129, 2.203, 0.0019, 0.0006388,
-     0.02709, 0.102, 0.2903, 0.1066, 0.9289, 1.025, 1.044, 0.924, 0.1885, 0.3277, 0.3048, 0.06851, 1.5, 0.007077, 0.07079,
-     3.001, 2.78},
+    {QG_KERNEL_SKINNY16, 16, 2.983, 0.02822, 0.4741, 0.05277, 0.09842, 5.28e-05, 0.4466, 0, 0, 0, 3.543e-05, 0.0001109,
+     2.635e-05, 0.04294, 0.09123, 1.033, 1.5, 0, 0, 0, 0, 0, 0, 0.9646, 0.1252, 0.04834, 3.62, 0, 0.0002, 70, 0.3493,
+     0, 0},
+    {QG_KERNEL_SKINNY16, 16, 0.1835, 3.345, 0.5, 0.01965, 0.001042, 0.0001344, 0.5185, 0.007127, 0.1403, 0.002334,
+     0.009597, 0.06298, 6.566e-05, 0.126, 0.02872, 0.9085, 1.581, 0.9083, 1.414, 0.0007144, 0.5192, 0.03076, 1.939,
+     1.5, 0.01412, 0.0865, 4.574, 1.375, 0.07699, 54.84, 0.1727, 0.1886, 1.417},
+    {QG_KERNEL_SKINNY32, 32, 3.253, 0.1344, 0.6943, 0.05584, 0.01053, 4.352e-05, 0.513, 0, 0, 0, 0.00434, 0.03572,
+     0.07619, 0.05571, 0.4104, 1.079, 1.805, 0, 0, 0.0007931, 0, 2.402e-05, 0, 0.8106, 0.1573, 0.06216, 0.004036, 0,
+     0.0002, 70, 0, 0, 0},
+    {QG_KERNEL_SKINNY32, 32, 3.322, 0.0002, 0.5, 0.02931, 0.1067, 0.0002637, 0.2814, 0.2265, 0.02392, 0.0009932,
+     0.001088, 0.108, 0.01154, 0.01654, 0.1137, 1.037, 1.971, 1.695, 3.052, 0.1929, 0.05645, 0.03491, 0.0003043,
+     0.9501, 0.001606, 0.07357, 0.1386, 1.427, 0.03674, 2.958, 0, 0.362, 1.985},
+    {QG_KERNEL_SKINNY64, 64, 3.235, 0.1673, 0.5, 0.1411, 0.1045, 0.0001145, 0.3719, 0, 0, 0, 0.005093, 0.05883, 0.1144,
+     0.1041, 0.2901, 1.201, 2.144, 0, 0, 0.163, 0, 0.4691, 0, 2.087, 0.2004, 0.06998, 0.0004859, 0, 0.0002, 70, 0, 0,
+     0},
+    {QG_KERNEL_SKINNY64, 64, 3.521, 0.1821, 0.5, 0.1256, 0.005196, 7.668e-05, 0.4534, 0.5234, 6.514, 0.003999, 0.1165,
+     0.1458, 0.2133, 0.06736, 0.4308, 1.16, 1.977, 1.394, 1.881, 0.122, 0.1533, 0.0002338, 0.2097, 1.912, 0.000961,
+     0.1102, 0.06496, 2.123, 0.0002, 140.4, 0, 0.2827, 1.416},
+    {QG_KERNEL_SKINNY16, 16, 1.903, 2.606, 0.5, 0.1963, 0.07251, 0.0001901, 0.1182, 0.07707, 0.4461, 0.001301, 0.0198,
+     0.1311, 0.01446, 0.003134, 0.1067, 1.052, 1.128, 0.9856, 0.9931, 0.005627, 0.03856, 0.04532, 0.005549, 1.5,
+     0.007077, 0.06172, 1.077, 1.26, 0.08207, 73.4, 0.01, 0.09177, 1},
+    {QG_KERNEL_SKINNY16, 16, 1.344, 2.896, 0.5, 5.368e-05, 2.095e-05, 0, 0.006053, 0.04129, 1.606, 6.097e-05, 0.09463,
+     0.003243, 0.04371, 0.0541, 0.4061, 0.02498, 0.02293, 6.854, 11.76, 0.0007712, 0.1865, 0, 0, 1.5, 0.3297, 0.09574,
+     0.1461, 0.6666, 0.0002, 70, 0.6227, 0.2078, 0.2314},
+    {QG_KERNEL_SKINNY32, 32, 3.676, 0.0002025, 0.5, 0.003235, 0.003171, 3.276e-05, 0.2263, 0.1643, 6.496, 0.006098,
+     0.008458, 0.03281, 0.1052, 0.09962, 0.243, 0.00297, 38.2, 1.109, 1.27, 0.04818, 0.05044, 0.1093, 3.298, 1.008,
+     0.02535, 0.07889, 0.06179, 2.329, 0.0002, 70, 0, 0.1023, 0.08342},
+    {QG_KERNEL_SKINNY16, 16, 0.1639, 2.988, 0.5, 0.1175, 0.06546, 0.0001377, 0.3826, 0.0003874, 1.832, 0.001001,
+     0.0195, 0.07932, 0.08213, 0.009258, 0.1466, 1.15, 1.628, 0.9652, 1.059, 0.005616, 0.6934, 0.009526, 0.0002023,
+     1.5, 0, 0.1091, 6.622, 1.005, 0.03082, 68.34, 0.007549, 0.08187, 0.5645},
 };
 
 enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
@@ -259,7 +276,8 @@ double tile_price_us(const tile_price& c, int M, int N, int K, const call_form& 
                      (N % c.bn != 0 && N % c.bn <= c.bn / 2 ? 1.0 + c.half : 1.0);
   double us = larger(fix + kt * (lat + c.crowd * share_of_chip(wgs)), 2.5 + (double)M * (double)N * (wide ? 4.0 : 1.0) / (c.out * 1e6));
   if (wgs > 256) {
-    const double epi = c.epi + out_epi[f.out] + (tail ? c.tail_epi : 0.0) + (left ? c.left_epi : 0.0);
+    // (what 4-byte results cost goes by the columns there are: 53310 x 12 x 256 to int32 10.8 us on the 64-row kernel, 6.9 on 64 x 64 tiles)
+    const double epi = c.epi + out_epi[f.out] * (c.bn <= 64 && N < c.bn ? (double)N / c.bn : 1.0) + (tail ? c.tail_epi : 0.0) + (left ? c.left_epi : 0.0);
     const double rounds = rounds_of(wgs), steps = rounds + c.fill * ((double)wgs / 256.0 - rounds);
     us = larger(us, 2.5 + rounds * epi + steps * kt * c.thr * a_thr[a] * (f.bzp ? 1.0 + c.bzp_thr : 1.0));
   }
@@ -278,7 +296,7 @@ struct stream_shape {
   long long wgs;
   qg_stream_build f;
 };
-stream_shape shape_of(int rows, int M, int N, int K, bool split) {
+stream_shape shape_of(int rows, int M, int N, int K, bool split = false) {
   stream_shape s;
   s.kb = ceil_div(K, 64);
   const long long sb = tiles_of(M, N, rows, 32);
@@ -290,33 +308,42 @@ stream_shape shape_of(int rows, int M, int N, int K, bool split) {
 }
 
 double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
-  const stream_shape s = shape_of(c.rows, M, N, K, false);
-  const int a = f.a_align == 16 ? 0 : f.a_align == 4 ? 1 : 2;
+  const stream_shape s = shape_of(c.rows, M, N, K);
+  // (with a quarter of the rows or less a quarter of them is requested, and their alignment hardly counts)
+  const int a = f.a_align == 16 || 4 * M <= c.rows ? 0 : f.a_align == 4 ? 1 : 2;
   const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
   const double a_fix[] = {0.0, c.fix4, c.fix1}, a_lat[] = {1.0, c.lat4, c.lat1}, a_wg_k[] = {1.0, c.wg_k4, c.wg_k1};
   const double bzp = f.bzp ? 1.0 + c.bzp_lat : 1.0;
   const double fix = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + out_fix[f.out] + a_fix[a] +
-                     (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0);
+                     (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0) - (c.rows == 16 && qg_stream_whole(s.f, s.kb, K) ? c.whole : 0.0);
   double us = fix + (K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch) * bzp * a_lat[a] +
               c.fetch * larger(fetched_mb(M, N, K, c.rows, 16 * s.f.columns) - c.near, 0.0);
   if (s.wgs > 256)
-    us = larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round,
-                2.5 + (double)s.wgs * (c.wg + out_wg[f.out] + K * c.wg_k * bzp * a_wg_k[a]) * 1e-3);
+    us = larger(us * (1.0 + (M > c.rows ? c.more_second : c.second)) + (rounds_of(s.wgs) - 1.0) * c.round,
+                2.5 + (double)s.wgs * (c.wg + out_wg[f.out] + K * c.wg_k * (M > c.rows ? c.more_wg_k : 1.0) * bzp * a_wg_k[a]) * 1e-3);
   const double a_bytes = (double)M * (double)K;
   if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, 16 * s.f.columns) / (c.a_far * 1e7));
-  return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0);
+  return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0) + c.b_far * larger((double)K * N * 1e-6 - c.b_near, 0.0);
+}
+
+// the row of k_stream_price for the kernel of 16 << i rows
+const stream_price& stream_row(int i, int M, int N, int K) {
+  if (tiles_of(M, N, 16 << i, 32) <= 128) return k_stream_price[2 * i];
+  if (i == 0 && K <= 16 * 64) return k_stream_price[7];
+  if (i == 0 && M <= 4 && K > 64 * 64) return k_stream_price[6];
+  if (i == 0 && K <= 32 * 64) return k_stream_price[9];
+  if (i == 1 && K <= 32 * 64) return k_stream_price[8];
+  return k_stream_price[2 * i + 1];
 }
 
 int price_select(int M, int N, int K, const call_form& f, double* price = nullptr) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
-  const auto wide = [&](int rows) { return tiles_of(M, N, rows, 32) > 128; };
   const auto take = [&](int kernel, double us) {
     if (us < best_us) best_us = us, best = kernel;
   };
   for (int i = 0; i < 3; ++i) {
-    const int at = !wide(k_stream_price[2 * i].rows) ? 2 * i : i == 0 && M <= 4 && K > 64 * 64 ? 6 : 2 * i + 1;
-    const stream_price& c = k_stream_price[at];
+    const stream_price& c = stream_row(i, M, N, K);
     if (ceil_div(M, c.rows) <= 65535) take(c.kernel, stream_price_us(c, M, N, K, f));
   }
   const bool few = qg_tile128_few(M, N, K);
@@ -331,30 +358,35 @@ int price_select(int M, int N, int K, const call_form& f, double* price = nullpt
 
 // fp32 activations in one launch, the streaming kernels quantizing what they stage (every column block converts its rows of A again):
 //   conv, wg_c  per 16 rows: of a k block of a wave; of a workgroup, ns per 1 of K, where the chip is full
-// against the 8-bit call plus a pass over A.  Fitted to 8900 drawn calls with M up to 512; over 1488 others the choice is 1.004 of the
-// best form in the geometric mean and 0.890 of two launches, 15 of them slower by more than 4 %, 1.20 at worst.
+// against the 8-bit call plus a pass over A.  Fitted to 5000 drawn calls with M up to 512 and every form on each, the two launches as
+// priced above; over 1200 others the choice is 1.0045 of the best form in the geometric mean, 41 of them slower by more than 5 %, 1.22 at
+// worst.  Rows as of k_stream_price: in pairs, then 16 rows and up to 16 k blocks, 32 rows and up to 32.
 struct f32_price {
   int kernel, rows;
   double fix, fix8, fix16, lat, crowd, block, conv, batch, second, wg, wg_k, wg_c, bzp_fix, k_fix, u8_fix, round, fetch, near;
 };
 const f32_price k_f32_price[] = {
-    {QG_KERNEL_SKINNY16, 16, 3.154, 0.4998, 1.149, 0.207, 0.0006482, 0.0008539, 0.3092, 0.9886, 0, 0, 0, 0.0005, 0.009312,
-     0.06609, 0.1062, 0, 0.05619, 2.627},
-    {QG_KERNEL_SKINNY16, 16, 1.925, 1.706, 0.3, 0.3542, 0.1734, 0.0006506, 0.2207, 0.6133, 0.3216, 1.397, 0.002564, 0.002457,
-     0.03206, 0.09166, 0.07434, 0.7039, 0.1364, 4.446},
-    {QG_KERNEL_SKINNY32, 32, 3.367, 0.1267, 0.4395, 0.5418, 0.1668, 0.000826, 0.3319, 1.207, 0, 0, 0, 0.0005, 0.01582, 0.1281,
-     0.09172, 0, 0.08396, 3.195},
-    {QG_KERNEL_SKINNY32, 32, 3.137, 0.2841, 0.3, 0.9125, 0.1401, 0.009143, 0.2453, 0.004797, 0.02451, 5.927, 0.008223,
-     0.002056, 0.009162, 0.2016, 0.0179, 1.855, 0.1921, 5.14},
-    {QG_KERNEL_SKINNY64, 64, 3.075, 0.1398, 0.3, 1.151, 0.3381, 0.006236, 0.3566, 0.409, 0, 0, 0, 0.0005, 0.006206, 0.2464,
-     0.05655, 0, 0.06369, 0.02254},
-    {QG_KERNEL_SKINNY64, 64, 2.965, 0.1348, 0.3, 1.106, 0.1626, 0.4953, 0.3453, 0.01991, 0.1733, 12.34, 0.008612, 0.002153,
-     0.0005398, 0.2798, 0, 0.3165, 0.07423, 2.414},
+    {QG_KERNEL_SKINNY16, 16, 3.073, 0.7941, 1.994, 0.0215, 0, 0.001986, 0.3066, 1.283, 0, 0, 0, 0, 0.001766, 0.05171,
+     0.149, 0, 0.08193, 8.374},
+    {QG_KERNEL_SKINNY16, 16, 0.1651, 3.949, 0.3, 0.000151, 3.551e-05, 0, 0.1556, 1.262, 0.002061, 2.118, 0.002785,
+     0.004633, 0.07578, 0.117, 0.001036, 2.871, 0.1647, 7.094},
+    {QG_KERNEL_SKINNY32, 32, 3.292, 0.1257, 0.2957, 0.7867, 6.27e-05, 0.0001959, 0.2005, 0.6206, 0, 0, 0, 0, 0.000607,
+     0.1884, 0.07534, 0, 0.08566, 1.905},
+    {QG_KERNEL_SKINNY32, 32, 4.393, 0.2841, 0.3, 0.1312, 0.4362, 0.002248, 0.2928, 0.5154, 0.02406, 5.859, 0.006754,
+     0.001693, 0.02888, 0.04974, 0.1788, 0.003774, 0.04396, 3.747},
+    {QG_KERNEL_SKINNY64, 64, 3.411, 0.1551, 0.3, 0.599, 0.00013, 6.944e-05, 0.2565, 0.8151, 0, 0, 0, 0, 4.335e-05,
+     0.1963, 0.0003498, 0, 0.113, 0.7546},
+    {QG_KERNEL_SKINNY64, 64, 3.138, 0.1427, 0.3, 0.483, 0.01722, 0.4916, 0.3054, 0.009889, 0.05034, 8.62, 0.008627,
+     0.002157, 0.08039, 0.03217, 0, 2.353, 0.05803, 3.17},
+    {QG_KERNEL_SKINNY16, 16, 1.438, 1.706, 0.3, 0.5419, 0.2651, 0, 0.1907, 0.6133, 0.1328, 1.962, 0, 0.006917,
+     0.004586, 0.0676, 0.04746, 0.07502, 0.2399, 5.655},
+    {QG_KERNEL_SKINNY32, 32, 2.977, 0.2696, 0.3, 0.02247, 0.06102, 0.3001, 0.2331, 0.004797, 0.07649, 6.056, 0.007601,
+     0.001901, 0.01136, 0.1155, 0, 1.42, 0.141, 4.751},
 };
-const double k_quantize_fix = 1.872, k_quantize_mb = 1.263, k_quantize_most = 1.381;  // us; per million entries of A; up to so many
+const double k_quantize_fix = 1.666, k_quantize_mb = 1.165, k_quantize_most = 0.27;  // us; per million entries of A; up to so many
 
 double f32_price_us(const f32_price& c, int M, int N, int K, out_kind out, bool bzp) {
-  const stream_shape s = shape_of(c.rows, M, N, K, false);
+  const stream_shape s = shape_of(c.rows, M, N, K);
   const double g = ceil_div(M < c.rows ? M : c.rows, 4) / 4.0;
   const int cols = 16 * s.f.columns, columns = ceil_div(N, cols), near = columns < 8 ? columns : 8;
   double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (bzp ? c.bzp_fix : 0.0) + (K % 64 != 0 ? c.k_fix : 0.0) +
@@ -363,6 +395,12 @@ double f32_price_us(const f32_price& c, int M, int N, int K, out_kind out, bool 
   if (s.wgs > 256)
     us = larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round, 2.5 + (double)s.wgs * (c.wg + K * (c.wg_k + c.wg_c * g)) * 1e-3);
   return us;
+}
+
+// the row of k_f32_price for the kernel of 16 << i rows
+const f32_price& f32_row(int i, int M, int N, int K) {
+  if (tiles_of(M, N, 16 << i, 32) <= 128) return k_f32_price[2 * i];
+  return k_f32_price[i == 0 && K <= 16 * 64 ? 6 : i == 1 && K <= 32 * 64 ? 7 : 2 * i + 1];
 }
 
 // the kernel for one launch, or QG_KERNEL_AUTO where two launches are estimated to be faster
@@ -374,7 +412,7 @@ int f32_select(int M, int N, int K, const call_form& f) {
   best_us += k_quantize_fix + k_quantize_mb * (entries < k_quantize_most ? entries : k_quantize_most);
   int best = QG_KERNEL_AUTO;
   for (int i = 0; i < 3; ++i) {
-    const f32_price& c = k_f32_price[2 * i + (tiles_of(M, N, k_f32_price[2 * i].rows, 32) > 128 ? 1 : 0)];
+    const f32_price& c = f32_row(i, M, N, K);
     const double us = f32_price_us(c, M, N, K, f.out, f.bzp);
     if (us < best_us) best_us = us, best = c.kernel;
   }
@@ -474,7 +512,7 @@ double conv_tile_us(const conv_tile_price& c, const qg_gemm_args& a) {
 }
 
 double conv_stream_us(const conv_stream_price& c, const qg_gemm_args& a) {
-  const stream_shape s = shape_of(c.rows, a.M, a.N, a.K, false);
+  const stream_shape s = shape_of(c.rows, a.M, a.N, a.K);
   const bool chunk = a.cv_Cin % 64 != 0, rag = a.c_vec == 0;
   const double bzp = a.has_bzp ? 1.0 + c.bzp_lat : 1.0;
   double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (rag ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) +

@@ -46,22 +46,35 @@ def test_kernel_select_answers_for_whole_steps():
 
 @pytest.mark.parametrize("M,N,K,fast", [
     # us with the kernel that an earlier fit chose, with the fastest
-    (7, 6304, 2816, ("tile64x32k8",)),                       # 7.8, 7.1
+    (7, 6304, 2816, ("skinny16",)),                          # 6.4 on the 64 x 32 tile, 5.3
     (69, 3616, 2048, ("tile64x32k8",)),                      # 9.6, 6.2
     (827, 17, 15685, ("skinny16",)),                         # 25.1, 10.4: tall, few columns, long K
     (1152, 32, 11840, ("skinny16",)),                        # 18.7, 8.7
     (940, 64, 14177, ("skinny16",)),                         # 29.4, 16.1
     (1340, 11, 3072, ("skinny16",)),                         # 7.5, 5.1
     (64, 64, 128, ("tile64k1",)),                            # 3.5, 3.2
-    (9, 7996, 5824, ("tile64x32k8",)),                       # 15.1, 11.0
+    (9, 7996, 5824, ("skinny16",)),                          # 10.1 on the 64 x 32 tile, 9.2
     (39460, 865, 87, ("tile128",)),                          # 26.9, 22.3 (rows of A and C off 16 bytes; the choice is the same)
     (80, 3072, 2048, ("skinny16",)),                         # 6.1, 4.8: rounds of the few-fat-waves form
     (96, 2048, 2048, ("skinny32", "skinny16")),              # 5.3, 4.6
     (640, 128, 8192, ("skinny16",)),                         # 9.7, 8.2
     (320, 768, 8192, ("skinny32",)),                         # 12.7, 10.2
-    (2048, 128, 4096, ("tile64x32k8",)),                     # 9.8, 8.6
+    (2048, 128, 4096, ("tile64x32k8", "skinny32")),          # 9.8, 8.0 on both
     (12288, 384, 2048, ("tile128",)),                        # 21.3, 17.5: the last column of 256 half full
     (32768, 4096, 256, ("tile128x256",)),                    # 82.8, 69.9
+    # 5 to 16 rows and more than 4096 columns: tiles had been chosen there
+    (9, 6208, 6752, ("skinny16",)),                          # 10.9, 8.9
+    (14, 5632, 3648, ("skinny16",)),                         # 7.1, 5.8
+    (5, 7680, 3536, ("skinny16",)),                          # 8.2, 6.6
+    (5, 6016, 4096, ("skinny16",)),                          # 7.5, 6.1
+    (15, 4800, 4096, ("skinny16",)),                         # 6.5, 5.5
+    (5, 6208, 6752, ("skinny16",)),
+    (8, 16384, 2048, ("skinny16",)),                         # 7.8, 7.1
+    (16, 14336, 4096, ("skinny16",)),                        # 11.2, 10.6
+    (4, 14336, 4096, ("skinny16",)),                         # 11.0, 10.1
+    (16, 11008, 4096, ("skinny16", "tile64k4")),             # 9.4 and 9.5
+    (16, 28672, 4096, ("tile64", "tile128")),                # 20.2 and 20.5, 24.4 on the 16-row kernel
+    (16, 8192, 8192, ("skinny16",)),                         # 12.9, 12.6
 ])
 def test_shapes_that_were_slow(M, N, K, fast):
     from paper_2101_05615_amd import qgemm as q
