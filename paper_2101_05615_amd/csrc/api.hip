@@ -419,8 +419,66 @@ int f32_select(int M, int N, int K, const call_form& f) {
   return best;
 }
 
-// cheapest streaming kernel (outlier-split descriptors run on these only; the constants were fitted when they always ran on
-// sixteen waves and added their sparse term lane by lane: the times are lower now, most of all with 64 rows)
+// Outlier-split weights in a call without a workspace: terms as of k_stream_price, and
+//   sp, more            per batch and column of a wave: any outliers; for every 64 of them beyond the first
+//   wg_sp, wg_more      the same where the chip is full, ns per workgroup and 1 of K; wg_more per 1 % of outliers
+// Per kernel a row for up to 128 super-blocks of rows x 32 columns, up to 256 and more.  Fitted to 5000 drawn calls (M 1 .. 512, N and K
+// 64 .. 12288, up to 10 % of outliers); over 1200 others the choice is 1.002 of the best kernel in the geometric mean, 22 by more than
+// 5 %, 1.18 at worst.  The former constants, below, 1.015, 592 of 6200 and 1.73: they are of kernels with another sparse term.
+struct split_price {
+  int kernel, rows;
+  double fix, fix8, fix16, lat, crowd, block, batch, sp, more, second, wg, wg_k, wg_sp, wg_more, round;
+  double bzp_fix, fix4, fix1, f32_fix, f32_wg, i32_fix, i32_wg;
+};
+const split_price k_split_price[] = {
+    {QG_KERNEL_SKINNY16, 16, 2.485, 0.007827, 0.4168, 0.2054, 0.1653, 0.003457, 0.2409, 0.2594, 0.09838, 0, 0, 0, 0, 0,
+     0, 0.002537, 0.0109, 0.1063, 0.04752, 0, 2.446e-05, 0},
+    {QG_KERNEL_SKINNY16, 16, 1.752, 0.6388, 0.9435, 0.166, 0.4928, 0.003034, 0.369, 0.393, 0.1301, 0.06173, 0.907,
+     0.0002001, 0.0004947, 9.921e-05, 0.2166, 3.449e-05, 7.298e-05, 0.02186, 0.005837, 0.1272, 2.765e-05, 0.0676},
+    {QG_KERNEL_SKINNY16, 16, 1.89, 0.1, 0.3, 0.3568, 0.2379, 0.0008896, 0.6251, 0.1649, 0.08464, 0.2748, 0.6685,
+     0.001008, 0.0002278, 0.0001061, 0.2239, 0.06024, 0.1226, 0.1455, 0.001569, 0.01837, 0, 0.0001049},
+    {QG_KERNEL_SKINNY32, 32, 2.77, 0.08423, 0.2733, 0.3434, 0.169, 0.006214, 0.1397, 0.2137, 0.1076, 0, 0, 0, 0, 0, 0,
+     0.07214, 0.05136, 0.3462, 0.01976, 0, 5.08e-05, 0},
+    {QG_KERNEL_SKINNY32, 32, 3.142, 0.09819, 0.3, 0.1572, 0.67, 0.001538, 0.5676, 0.2399, 0.1337, 0.3, 4, 0.002,
+     0.0005, 0.0002, 0.5, 0.0005637, 0, 0.01894, 0.005244, 0.001, 6.265e-05, 0.001},
+    {QG_KERNEL_SKINNY32, 32, 1.214, 0.1, 0.3, 0.6091, 0.4061, 0.0187, 0.3597, 0.1358, 0.1242, 0.1712, 0.4243, 0.002043,
+     0.000657, 0.0001401, 0.6441, 2.85e-05, 2.289e-05, 0.4325, 0.06362, 0.01155, 0.03444, 0.2135},
+    {QG_KERNEL_SKINNY64, 64, 2.868, 0.07966, 0.3, 0.256, 0.5971, 0.01902, 0.3058, 0.2105, 0.2004, 0, 0, 0, 0, 0, 0,
+     0.0005317, 0.1179, 0.1774, 0.07447, 0, 0.1116, 0},
+    {QG_KERNEL_SKINNY64, 64, 3.211, 0.08918, 0.3, 0.8051, 0.2196, 0.01089, 0.09034, 0.2015, 0.1958, 0.3, 4, 0.002,
+     0.0005, 0.0002, 0.5, 0, 0.02823, 0.1422, 0.2584, 0.001, 1.034, 0.001},
+    {QG_KERNEL_SKINNY64, 64, 2.806, 0.8921, 0.3, 0.2751, 0.1834, 0.06699, 0.6894, 0.2093, 0.6949, 0.4064, 8.089,
+     0.00487, 0.001473, 0.0004593, 0.2568, 0.7752, 0.000188, 1.409, 1.694, 3.591, 0.0001071, 1.391},
+};
+
+// outliers: their share of the weights
+double split_price_us(const split_price& c, int M, int N, int K, double outliers, const call_form& f) {
+  const stream_shape s = shape_of(c.rows, M, N, K, true);
+  const double any = outliers > 0.0 ? 1.0 : 0.0;
+  const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
+  const double fix = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + out_fix[f.out] + (f.bzp ? c.bzp_fix : 0.0) +
+                     (f.a_align == 16 ? 0.0 : f.a_align == 4 ? c.fix4 : c.fix1);
+  const double us = fix + K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch +
+                    (s.batches + 1) * s.f.columns * (any * c.sp + larger(outliers * 1024.0 * s.f.batch - 64.0, 0.0) / 64.0 * c.more);
+  if (s.wgs <= 256) return us;
+  return larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round,
+                2.5 + (double)s.wgs * (c.wg + out_wg[f.out] + K * (c.wg_k + any * c.wg_sp + outliers * 100.0 * c.wg_more)) * 1e-3);
+}
+
+int split_select(int M, int N, int K, double outliers, const call_form& f) {
+  int best = QG_KERNEL_SKINNY64;
+  double best_us = 1e300;
+  for (int i = 0; i < 3; ++i) {
+    const long long sb = tiles_of(M, N, 16 << i, 32);
+    const split_price& c = k_split_price[3 * i + (sb > 256 ? 2 : sb > 128 ? 1 : 0)];
+    const double us = split_price_us(c, M, N, K, outliers, f);
+    if (ceil_div(M, c.rows) <= 65535 && us < best_us) best_us = us, best = c.kernel;
+  }
+  return best;
+}
+
+// What the queries about K splits and workspaces of outlier-split weights go by, and calls that ask for a split or bring a workspace for one
+// (one answer for a shape; the constants are of the time when these weights always ran on sixteen waves)
 const stream_cost k_stream_cost_16wave[] = {
     {QG_KERNEL_SKINNY16, 16, 3.58, 7.3e-5, 7.55, 0.74e-3},
     {QG_KERNEL_SKINNY32, 32, 4.13, 1.99e-4, 10.33, 1.28e-3},
@@ -659,7 +717,7 @@ int auto_ksplit(int kernel, int M, const qg_packed_b* Bp) {
   const int rows = 16 << (kernel - QG_KERNEL_SKINNY16);
   const long long wgs = (long long)ceil_div(M, rows) * (2 * ceil_div(Bp->N, 32));
   if (wgs * 2 > 256) return 1;
-  int s = Bp->K_pad / QG_FRAG_K / (16 * 4);  // 16 waves x 4 blocks (outlier-split slices on eight waves: twice as many each)
+  int s = Bp->K_pad / QG_FRAG_K / (16 * 4);  // 16 waves x 4 blocks (slices on fewer waves have as many more each)
   if (s > 256 / wgs) s = (int)(256 / wgs);
   if (s > 16) s = 16;
   if (s < (rows == 64 ? 2 : 4)) return 1;
@@ -669,7 +727,17 @@ int auto_ksplit(int kernel, int M, const qg_packed_b* Bp) {
 // query asked for, gets the kernel of the closer prices, without a split (a split that the queries did not announce
 // must not be used: the caller's workspace may be anything).  All others get what the queries answer for.
 int resolve_call(const qg_packed_b* Bp, int M, int* kernel, int* ksplit, const call_form& f, const void* workspace_dev) {
-  if (*kernel != QG_KERNEL_AUTO || Bp->split || *ksplit < 0 || *ksplit > 1 || M <= 0) return resolve_kernel(Bp, M, kernel);
+  if (*kernel != QG_KERNEL_AUTO || *ksplit < 0 || *ksplit > 1 || M <= 0) return resolve_kernel(Bp, M, kernel);
+  if (Bp->split) {
+    if (*ksplit == 0 && workspace_dev != nullptr) {
+      const int k = select_stream_kernel(M, Bp->N, Bp->K);
+      if (auto_ksplit(k, M, Bp) > 1) return resolve_kernel(Bp, M, kernel);
+      *ksplit = 1;
+    }
+    const int k = split_select(M, Bp->N, Bp->K, (double)Bp->nnz / ((double)Bp->N * Bp->K), f);
+    if (!kernel_ok(k, M)) return resolve_kernel(Bp, M, kernel);  // (too many row blocks for any)
+    return *kernel = k, QG_OK;
+  }
   const int rule = rule_kernel(M, Bp->N, Bp->K);
   if (rule != QG_KERNEL_AUTO && kernel_ok(rule, M)) return *kernel = rule, QG_OK;
   if (*ksplit == 0 && workspace_dev != nullptr) {
