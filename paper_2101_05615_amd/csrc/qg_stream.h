@@ -55,14 +55,15 @@ static inline bool qg_stream_whole(const qg_stream_build& f, int kb, int K) {
   return K % 64 == 0 && (kb == round || (f.waves == 8 && f.columns == 2 && kb % round == 0));
 }
 
-// The K slice that wave `wave` of workgroup `block` takes.  Workgroups go round-robin over the 8 XCDs: block / 8 turns the slices from one
-// workgroup of an XCD to the next, so that those, which all read all of A, request different lines of it at any instant, and `block`
-// does so between the XCDs.  Turned by `block` alone the workgroups of an XCD had one order for eight waves, two for sixteen: 7 x 4544 x
-// 6144 7.5 us, 6.9 so, 16 x 8192 x 8192 12.5 and 12.1, 175 shapes with more than 4096 columns and K from 4096 on 0.98.  Four waves by
-// `block` alone: short K, where a k block's wave is best the same in the workgroups of a CU (K up to 64 1.01 to 1.09 the other way, fp32
-// rows up to 1.27: 123 x 640 x 16 3.3 us, 3.8), and up to four rows, whose A is small (no difference).
+// The K slice that wave `wave` of workgroup `block` takes.  Workgroups go round-robin over the 8 XCDs; all workgroups of an XCD read all of
+// A, and those that start on different slices request different lines of it.  Turned by `block` alone eight waves start on one slice in all
+// workgroups of an XCD (block / 8 adds the turn there: 7 x 4544 x 6144 7.5 us, 6.9 so, 16 x 8192 x 8192 12.5 and 12.1, 175 shapes with more
+// than 4096 columns and K from 4096 on 0.98), sixteen on two.  Those and four stay with `block` alone: sixteen make one batch each, K
+// up to 4096, and every step before the first request counts (1.008 with the other, 16 x 4096 x 4096 4.55 and 4.68); four serve short K,
+// where a k block's wave is best the same in the workgroups of a CU (K up to 64 1.01 to 1.09, fp32 rows up to 1.27: 123 x 640 x 16 3.3 us
+// and 3.8).
 QG_STREAM_FN int qg_stream_slice(int wave, unsigned block, int waves) {
-  return (int)((wave + block + (waves == 4 ? 0u : block >> 3)) % waves);
+  return (int)((wave + block + (waves == 8 ? block >> 3 : 0u)) % waves);
 }
 
 #endif
