@@ -284,31 +284,35 @@ double tile_price_us(const tile_price& c, int M, int N, int K, const call_form& 
   return us + c.far * larger((double)M * K * 1e-6 - 4.0, 0.0) + c.b_far * larger((double)K * N * 1e-6 - c.b_near, 0.0);
 }
 
-// megabytes that the XCDs fetch, an operand counted once for each: column block j of row block i runs on XCD (i * columns + j) % 8
-double fetched_mb(int M, int N, int K, int rows, int cols) {
-  const int columns = ceil_div(N, cols), row_blocks = ceil_div(M, rows), spread = columns % 8 ? 8 / (columns & -columns) : 1;
-  return ((double)(row_blocks < spread ? row_blocks : spread) * N + (double)(columns < 8 ? columns : 8) * M) * K * 1e-6;
-}
-
-// what the builds of the streaming kernels share: extents of a launch
+// what the builds of the streaming kernels share: extents of a launch (powers of two throughout: shifts, no divisions)
 struct stream_shape {
   int kb, per, batches;  // k blocks, of a wave, batches after a wave's first
-  long long wgs;
+  int row_blocks, columns;
+  long long sb, wgs;     // super-blocks of rows x 32 columns, workgroups
   qg_stream_build f;
 };
+inline int ceil_shift(int a, int s) { return ((a - 1) >> s) + 1; }  // a >= 1
 stream_shape shape_of(int rows, int M, int N, int K, bool split = false) {
   stream_shape s;
-  s.kb = ceil_div(K, 64);
-  const long long sb = tiles_of(M, N, rows, 32);
-  s.f = qg_stream_build_of(rows, s.kb, sb, M, split);
-  s.per = split ? 2 * ceil_div(s.kb, 2 * s.f.waves) : ceil_div(s.kb, s.f.waves);
-  s.batches = ceil_div(s.per, s.f.batch) - 1;
-  s.wgs = sb * 2 / s.f.columns;
+  s.kb = ceil_shift(K, 6);
+  s.row_blocks = ceil_shift(M, __builtin_ctz(rows));
+  s.sb = (long long)s.row_blocks * ceil_shift(N, 5);
+  s.f = qg_stream_build_of(rows, s.kb, s.sb, M, split);
+  const int w = __builtin_ctz(s.f.waves);
+  s.per = split ? 2 * ceil_shift(s.kb, w + 1) : ceil_shift(s.kb, w);
+  s.batches = ceil_shift(s.per, __builtin_ctz(s.f.batch)) - 1;
+  s.columns = ceil_shift(N, s.f.columns == 2 ? 5 : 4);
+  s.wgs = s.f.columns == 2 ? s.sb : 2 * s.sb;
   return s;
 }
 
-double stream_price_us(const stream_price& c, int M, int N, int K, const call_form& f) {
-  const stream_shape s = shape_of(c.rows, M, N, K);
+// megabytes that the XCDs fetch, an operand counted once for each: column block j of row block i runs on XCD (i * columns + j) % 8
+double fetched_mb(const stream_shape& s, int M, int N, int K) {
+  const int spread = s.columns % 8 ? 8 >> __builtin_ctz(s.columns) : 1;
+  return ((double)(s.row_blocks < spread ? s.row_blocks : spread) * N + (double)(s.columns < 8 ? s.columns : 8) * M) * K * 1e-6;
+}
+
+double stream_price_us(const stream_price& c, const stream_shape& s, int M, int N, int K, const call_form& f) {
   // (with a quarter of the rows or less a quarter of them is requested, and their alignment hardly counts)
   const int a = f.a_align == 16 || 4 * M <= c.rows ? 0 : f.a_align == 4 ? 1 : 2;
   const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
@@ -317,18 +321,18 @@ double stream_price_us(const stream_price& c, int M, int N, int K, const call_fo
   const double fix = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + out_fix[f.out] + a_fix[a] +
                      (K % 16 != 0 ? c.tail_fix : 0.0) + (f.bzp ? c.bzp_fix : 0.0) - (c.rows == 16 && qg_stream_whole(s.f, s.kb, K) ? c.whole : 0.0);
   double us = fix + (K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch) * bzp * a_lat[a] +
-              c.fetch * larger(fetched_mb(M, N, K, c.rows, 16 * s.f.columns) - c.near, 0.0);
+              c.fetch * larger(fetched_mb(s, M, N, K) - c.near, 0.0);
   if (s.wgs > 256)
     us = larger(us * (1.0 + (M > c.rows ? c.more_second : c.second)) + (rounds_of(s.wgs) - 1.0) * c.round,
                 2.5 + (double)s.wgs * (c.wg + out_wg[f.out] + K * c.wg_k * (M > c.rows ? c.more_wg_k : 1.0) * bzp * a_wg_k[a]) * 1e-3);
   const double a_bytes = (double)M * (double)K;
-  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)ceil_div(N, 16 * s.f.columns) / (c.a_far * 1e7));
+  if (a_bytes > k_stream_a_near) us = larger(us, 2.5 + a_bytes * (double)s.columns / (c.a_far * 1e7));
   return us + c.far * larger(a_bytes * 1e-6 - 4.0, 0.0) + c.b_far * larger((double)K * N * 1e-6 - c.b_near, 0.0);
 }
 
 // the row of k_stream_price for the kernel of 16 << i rows
-const stream_price& stream_row(int i, int M, int N, int K) {
-  if (tiles_of(M, N, 16 << i, 32) <= 128) return k_stream_price[2 * i];
+const stream_price& stream_row(int i, const stream_shape& s, int M, int K) {
+  if (s.sb <= 128) return k_stream_price[2 * i];
   if (i == 0 && K <= 16 * 64) return k_stream_price[7];
   if (i == 0 && M <= 4 && K > 64 * 64) return k_stream_price[6];
   if (i == 0 && K <= 32 * 64) return k_stream_price[9];
@@ -343,8 +347,9 @@ int price_select(int M, int N, int K, const call_form& f, double* price = nullpt
     if (us < best_us) best_us = us, best = kernel;
   };
   for (int i = 0; i < 3; ++i) {
-    const stream_price& c = stream_row(i, M, N, K);
-    if (ceil_div(M, c.rows) <= 65535) take(c.kernel, stream_price_us(c, M, N, K, f));
+    const stream_shape s = shape_of(16 << i, M, N, K);
+    const stream_price& c = stream_row(i, s, M, K);
+    if (s.row_blocks <= 65535) take(c.kernel, stream_price_us(c, s, M, N, K, f));
   }
   const bool few = qg_tile128_few(M, N, K);
   for (const tile_price& c : k_tile_price) {
@@ -385,21 +390,20 @@ const f32_price k_f32_price[] = {
 };
 const double k_quantize_fix = 1.666, k_quantize_mb = 1.165, k_quantize_most = 0.27;  // us; per million entries of A; up to so many
 
-double f32_price_us(const f32_price& c, int M, int N, int K, out_kind out, bool bzp) {
-  const stream_shape s = shape_of(c.rows, M, N, K);
+double f32_price_us(const f32_price& c, const stream_shape& s, int M, int N, int K, out_kind out, bool bzp) {
   const double g = ceil_div(M < c.rows ? M : c.rows, 4) / 4.0;
-  const int cols = 16 * s.f.columns, columns = ceil_div(N, cols), near = columns < 8 ? columns : 8;
+  const int near = s.columns < 8 ? s.columns : 8;
   double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (bzp ? c.bzp_fix : 0.0) + (K % 64 != 0 ? c.k_fix : 0.0) +
               (out < OUT_F32 ? c.u8_fix : 0.0) + K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * (c.block + c.conv * g) +
-              s.batches * c.batch + c.fetch * larger(fetched_mb(M, N, K, c.rows, cols) + 3e-6 * near * M * K - c.near, 0.0);
+              s.batches * c.batch + c.fetch * larger(fetched_mb(s, M, N, K) + 3e-6 * near * M * K - c.near, 0.0);
   if (s.wgs > 256)
     us = larger(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round, 2.5 + (double)s.wgs * (c.wg + K * (c.wg_k + c.wg_c * g)) * 1e-3);
   return us;
 }
 
 // the row of k_f32_price for the kernel of 16 << i rows
-const f32_price& f32_row(int i, int M, int N, int K) {
-  if (tiles_of(M, N, 16 << i, 32) <= 128) return k_f32_price[2 * i];
+const f32_price& f32_row(int i, const stream_shape& s, int K) {
+  if (s.sb <= 128) return k_f32_price[2 * i];
   return k_f32_price[i == 0 && K <= 16 * 64 ? 6 : i == 1 && K <= 32 * 64 ? 7 : 2 * i + 1];
 }
 
@@ -412,8 +416,9 @@ int f32_select(int M, int N, int K, const call_form& f) {
   best_us += k_quantize_fix + k_quantize_mb * (entries < k_quantize_most ? entries : k_quantize_most);
   int best = QG_KERNEL_AUTO;
   for (int i = 0; i < 3; ++i) {
-    const f32_price& c = f32_row(i, M, N, K);
-    const double us = f32_price_us(c, M, N, K, f.out, f.bzp);
+    const stream_shape s = shape_of(16 << i, M, N, K);
+    const f32_price& c = f32_row(i, s, K);
+    const double us = f32_price_us(c, s, M, N, K, f.out, f.bzp);
     if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
@@ -452,8 +457,7 @@ const split_price k_split_price[] = {
 };
 
 // outliers: their share of the weights
-double split_price_us(const split_price& c, int M, int N, int K, double outliers, const call_form& f) {
-  const stream_shape s = shape_of(c.rows, M, N, K, true);
+double split_price_us(const split_price& c, const stream_shape& s, int K, double outliers, const call_form& f) {
   const double any = outliers > 0.0 ? 1.0 : 0.0;
   const double out_fix[] = {0.0, 0.0, c.f32_fix, c.i32_fix}, out_wg[] = {0.0, 0.0, c.f32_wg, c.i32_wg};
   const double fix = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + out_fix[f.out] + (f.bzp ? c.bzp_fix : 0.0) +
@@ -469,10 +473,10 @@ int split_select(int M, int N, int K, double outliers, const call_form& f) {
   int best = QG_KERNEL_SKINNY64;
   double best_us = 1e300;
   for (int i = 0; i < 3; ++i) {
-    const long long sb = tiles_of(M, N, 16 << i, 32);
-    const split_price& c = k_split_price[3 * i + (sb > 256 ? 2 : sb > 128 ? 1 : 0)];
-    const double us = split_price_us(c, M, N, K, outliers, f);
-    if (ceil_div(M, c.rows) <= 65535 && us < best_us) best_us = us, best = c.kernel;
+    const stream_shape s = shape_of(16 << i, M, N, K, true);
+    const split_price& c = k_split_price[3 * i + (s.sb > 256 ? 2 : s.sb > 128 ? 1 : 0)];
+    const double us = split_price_us(c, s, K, outliers, f);
+    if (s.row_blocks <= 65535 && us < best_us) best_us = us, best = c.kernel;
   }
   return best;
 }
@@ -576,12 +580,12 @@ double conv_stream_us(const conv_stream_price& c, const qg_gemm_args& a) {
   double us = c.fix + (s.f.waves == 8 ? c.fix8 : s.f.waves == 16 ? c.fix16 : 0.0) + (rag ? c.rag_fix : 0.0) + (a.has_bzp ? c.bzp_fix : 0.0) +
               (chunk ? c.chunk_fix : 0.0) +
               (a.K / 1024.0 * (c.lat + c.crowd * share_of_chip(s.wgs)) + s.per * c.block + s.batches * c.batch) * bzp * (chunk ? c.chunk_lat : 1.0) +
-              c.fetch * fmax(fetched_mb(a.M, a.N, a.K, c.rows, 16 * s.f.columns) - c.near, 0.0);
+              c.fetch * fmax(fetched_mb(s, a.M, a.N, a.K) - c.near, 0.0);
   if (s.wgs > 256)
     us = fmax(us * (1.0 + c.second) + (rounds_of(s.wgs) - 1.0) * c.round,
               2.5 + (double)s.wgs * (c.wg + (rag ? c.rag_wg : 0.0) + a.K * c.wg_k * bzp * (chunk ? c.chunk_wg_k : 1.0)) * 1e-3);
   const double a_bytes = (double)a.M * (double)a.K;
-  if (a_bytes > k_stream_a_near) us = fmax(us, 2.5 + a_bytes * (double)ceil_div(a.N, 16 * s.f.columns) / (c.a_far * 1e7));
+  if (a_bytes > k_stream_a_near) us = fmax(us, 2.5 + a_bytes * (double)s.columns / (c.a_far * 1e7));
   return us + c.far * fmax(a_bytes * 1e-6 - 4.0, 0.0);
 }
 

@@ -51,8 +51,8 @@ static inline qg_stream_build qg_stream_build_of(int rows, int kb, long long sb,
 // Whether a 16-row kernel on 8-bit weights (and bytes of A) takes the build without the code for a K that cuts a batch: kb k blocks of a
 // slice, K a whole number of them, every wave with whole batches.
 static inline bool qg_stream_whole(const qg_stream_build& f, int kb, int K) {
-  const int round = f.waves * f.batch;
-  return K % 64 == 0 && (kb == round || (f.waves == 8 && f.columns == 2 && kb % round == 0));
+  const int round = f.waves * f.batch;  // (a power of two)
+  return K % 64 == 0 && (kb == round || (f.waves == 8 && f.columns == 2 && (kb & (round - 1)) == 0));
 }
 
 // The K slice that wave `wave` of workgroup `block` takes.  Workgroups go round-robin over the 8 XCDs; all workgroups of an XCD read all of
