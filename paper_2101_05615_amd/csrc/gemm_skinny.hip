@@ -759,9 +759,11 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
   const qg_stream_build f = qg_stream_build_of(rows, kb, sb, a.M, B4);
   if constexpr (SRC == SRC_U8 && !B4) {
     // Whole batches in every wave of every slice.  One batch: 13 x 3328 x 1024 2.67 us on the build for any K, 2.46 so (four waves), 16 x 640
-    // x 2048 2.82 and 2.61 (eight); several ahead of each other: 8 x 4832 x 4096 5.61 and 5.47, 16 x 14048 x 4096 10.50 and 10.42.
+    // x 2048 2.82 and 2.61 (eight), 80 x 1536 x 2048 3.52 and 3.43 (two columns; 12 shapes 0.96 to 1.01 of the loop over batches, which
+    // holds two regions); several ahead of each other: 8 x 4832 x 4096 5.61 and 5.47, 16 x 14048 x 4096 10.50 and 10.42.
     // Four waves with several batches are not faster so (M up to 4 and a long K: 1.00 to 1.04).
     if (rows == 16 && kb * a.ksplit == blocks && qg_stream_whole(f, kb, a.K)) {
+      if (f.columns == 2 && kb == f.waves * f.batch) return launch<MODE, 1, 8, 4, 2, B4, SRC, false, true>(a, s);
       if (f.columns == 2) return launch<MODE, 1, 8, 4, 2, B4, SRC, true, true>(a, s);
       if (f.waves == 4) return launch<MODE, 1, 4, 4, 1, B4, SRC, false, true>(a, s);
       if (f.waves == 8) return launch<MODE, 1, 8, 4, 1, B4, SRC, false, true>(a, s);

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K,ksplit,waves,columns,whole", [
     (1, 40, 1024, 1, 4, 1, True), (16, 4128, 1024, 1, 4, 1, True), (13, 70, 1024, 1, 4, 1, True),
-    (5, 300, 2048, 1, 8, 1, True), (16, 64, 4096, 1, 16, 1, True), (3, 4128, 2048, 1, 8, 2, True),
+    (5, 300, 2048, 1, 8, 1, True), (16, 64, 4096, 1, 16, 1, True), (3, 4128, 2048, 1, 8, 2, True), (80, 1520, 2048, 1, 8, 2, True),
     (16, 4100, 4096, 1, 8, 2, True), (17, 2080, 6144, 1, 8, 2, True),
     (16, 48, 4096, 2, 8, 1, True), (7, 48, 4096, 4, 4, 1, True), (16, 48, 8192, 2, 16, 1, True),   # slices
     (5, 300, 1023, 1, 4, 1, False), (5, 300, 1025, 1, 8, 1, False), (5, 300, 960, 1, 4, 1, False), (5, 300, 1088, 1, 8, 1, False),
@@ -38,8 +38,9 @@ def test_whole_batches(M, N, K, ksplit, waves, columns, whole):
             q.gemm_u8s8_requant_splitk(A, c.a_zp, Bp, bias, scales, c.c_zp, c.relu, ws, out=C, kernel="skinny16", ksplit=ksplit)
     (name,) = kernels_of(call)
     # <mode, row blocks, waves, batch, columns, 4-bit, source, ahead, whole>
-    m = re.search(r"qg_gemm_skinny_kernelILi0ELi1ELi(\d+)ELi4ELi(\d+)ELb0ELi0ELb[01]ELb([01])EE", name)
-    assert m and (int(m.group(1)), int(m.group(2)), m.group(3) == "1") == (waves, columns, whole), name
+    m = re.search(r"qg_gemm_skinny_kernelILi0ELi1ELi(\d+)ELi4ELi(\d+)ELb0ELi0ELb([01])ELb([01])EE", name)
+    assert m and (int(m.group(1)), int(m.group(2)), m.group(4) == "1") == (waves, columns, whole), name
+    assert not whole or (m.group(3) == "1") == (K // ksplit > 64 * 4 * waves), name   # one batch: none requested ahead
     for _ in range(2):
         C.fill_(0xEE)
         call()
