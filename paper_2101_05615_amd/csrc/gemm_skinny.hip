@@ -776,6 +776,14 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
       return rows == 32 ? launch<MODE, 2, 4, 2, 1, B4, SRC, DB>(a, s) : launch<MODE, 4, 4, 2, 1, B4, SRC, DB>(a, s);
     }
   }
+  if constexpr (SRC == SRC_F32) {
+    // fp32 rows: the conversion is what a wave spends its time on, nothing is requested ahead, so a long K takes all the waves there are.
+    // 64 rows: 42 x 3714 x 3840 21.8 us with eight, 18.7 so; 68 shapes of up to 128 super-blocks 0.82 to 0.96, K of 2560 1.02 to 1.05; up to
+    // 16 k blocks a wave has one batch either way.  16 rows: 117 x 64 x 7680 13.3 us and 11.1, 46 shapes 0.80 to 1.00; from 65 to 95 k blocks
+    // 0.93 to 1.08, the second batch of sixteen waves half empty.
+    if (rows == 64 && f.columns == 1 && kb > 16) return launch<MODE, 4, 16, 2, 1, B4, SRC, DB>(a, s);
+    if (rows == 16 && f.columns == 1 && f.waves == 8 && kb >= 96) return launch<MODE, 1, 16, 4, 1, B4, SRC, DB>(a, s);
+  }
   switch (rows * 10000 + f.waves * 100 + f.batch * 10 + f.columns) {
     case 160441: return launch<MODE, 1, 4, 4, 1, B4, SRC, DB>(a, s);
     case 160841: return launch<MODE, 1, 8, 4, 1, B4, SRC, DB>(a, s);

@@ -48,3 +48,27 @@ def test_copy_of_every_build(build, batches, M, N, K):
             results.append(fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, workspace=ws, kernel=kernel))
             assert torch.equal(ws[:M * ldq].view(M, ldq), Aq) and bool((ws[M * ldq:] == 0xEE).all()), kernel
         assert torch.equal(*results)
+
+
+# without a workspace, by id: 64 rows from 17 k blocks on and 16 rows from 96 on run on sixteen waves
+@pytest.mark.parametrize("build,M,N,K", [
+    ((4, 8, 2, 1), 42, 300, 1024), ((4, 16, 2, 1), 42, 300, 1025), ((4, 16, 2, 1), 64, 70, 2048), ((4, 16, 2, 1), 61, 49, 2111),
+    ((4, 16, 2, 1), 130, 500, 4099), ((4, 16, 2, 1), 33, 13, 7168), ((4, 8, 2, 2), 64, 4128, 1088),
+    ((1, 8, 4, 1), 16, 48, 6080), ((1, 16, 4, 1), 16, 48, 6081), ((1, 16, 4, 1), 10, 43, 8192), ((1, 16, 4, 1), 117, 64, 7683),
+    ((1, 8, 4, 2), 16, 4128, 6144), ((1, 4, 4, 1), 3, 4128, 6144),
+], ids=str)
+def test_sixteen_waves(build, M, N, K):
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    say(f"fp32 by id {build} {M} {N} {K}")
+    case = wl.random_gemm(M + N + K, M, N, K)
+    F = (torch.randn(M * (K + 1) + 8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(K)) * 3)[3:3 + M * (K + 1)].view(M, K + 1)[:, :K]
+    Bp = q.pack_b(torch.from_numpy(case.B).cuda(), case.b_zp)
+    bias, scales = torch.from_numpy(case.bias).cuda(), torch.from_numpy(case.scales).cuda()
+    kernel = f"skinny{16 * build[0]}"
+    for fn, last in ((q.gemm_f32s8_requant, (case.c_zp, case.relu)), (q.gemm_f32s8_dequant_f32, (case.relu,))):
+        (name,) = kernels_of(lambda: fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, workspace=q.NO_WORKSPACE, kernel=kernel))
+        m = re.search(r"qg_gemm_skinny_kernelILi\dELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb0ELi1E", name)
+        assert m and tuple(int(v) for v in m.groups()) == build, name
+        got = fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, workspace=q.NO_WORKSPACE, kernel=kernel)
+        assert torch.equal(got, fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, kernel="tile64"))
