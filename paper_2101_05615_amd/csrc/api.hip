@@ -407,13 +407,10 @@ const f32_price& f32_row(int i, const stream_shape& s, int K) {
   return k_f32_price[i == 0 && K <= 16 * 64 ? 6 : i == 1 && K <= 32 * 64 ? 7 : 2 * i + 1];
 }
 
-// the kernel for one launch, or QG_KERNEL_AUTO where two launches are estimated to be faster
-int f32_select(int M, int N, int K, const call_form& f) {
-  if (M > 512) return QG_KERNEL_AUTO;  // 64 rows at a time, A would be converted by every column block for each of many row blocks
-  double best_us;
-  price_select(M, N, K, f, &best_us);
-  const double entries = (double)M * (double)K * 1e-6;
-  best_us += k_quantize_fix + k_quantize_mb * (entries < k_quantize_most ? entries : k_quantize_most);
+const int k_f32_most_rows = 512;  // 64 rows at a time, A would be converted by every column block for each of many row blocks
+
+// the best kernel for one launch; best_us: what it has to beat, or QG_KERNEL_AUTO is the answer
+int f32_one_launch(int M, int N, int K, const call_form& f, double best_us) {
   int best = QG_KERNEL_AUTO;
   for (int i = 0; i < 3; ++i) {
     const stream_shape s = shape_of(16 << i, M, N, K);
@@ -422,6 +419,15 @@ int f32_select(int M, int N, int K, const call_form& f) {
     if (us < best_us) best_us = us, best = c.kernel;
   }
   return best;
+}
+
+// the kernel for one launch, or QG_KERNEL_AUTO where two launches are estimated to be faster
+int f32_select(int M, int N, int K, const call_form& f) {
+  if (M > k_f32_most_rows) return QG_KERNEL_AUTO;
+  double best_us;
+  price_select(M, N, K, f, &best_us);
+  const double entries = (double)M * (double)K * 1e-6;
+  return f32_one_launch(M, N, K, f, best_us + k_quantize_fix + k_quantize_mb * (entries < k_quantize_most ? entries : k_quantize_most));
 }
 
 // Outlier-split weights in a call without a workspace: terms as of k_stream_price, and
@@ -1283,6 +1289,15 @@ static int f32_resolve(const qg_packed_b* Bp, int M, int* kernel, bool* one_laun
   return resolve_call(Bp, M, kernel, &ksplit, f, nullptr);
 }
 
+// Without a workspace: whether one launch serves the call is builtin_select's answer, whatever the call's form (tiled kernels need the
+// workspace), and where it does, the streaming kernel goes by the prices above.
+static int f32_resolve_alone(const qg_packed_b* Bp, int M, int* kernel, const call_form& f) {
+  const bool choose = *kernel == QG_KERNEL_AUTO && !Bp->split && M > 0 && M <= k_f32_most_rows && rule_kernel(M, Bp->N, Bp->K) == QG_KERNEL_AUTO;
+  const int rc = resolve_kernel(Bp, M, kernel);
+  if (rc == QG_OK && choose && *kernel <= QG_KERNEL_SKINNY64) *kernel = f32_one_launch(M, Bp->N, Bp->K, f, 1e300);
+  return rc;
+}
+
 static int quantize_into_workspace(const float* A_dev, int M, int lda, float a_inv_scale, const qg_packed_b* Bp,
                                    int a_zp, void* workspace_dev, void* stream) {
   if (!Bp || (!A_dev && M != 0)) return QG_ENULL;
@@ -1331,7 +1346,7 @@ int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale,
   bool one_launch = false;
   rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0},
                                  f32_in_place(A_dev, M, lda, Bp->K, C_dev, ldc, Bp->N, 1))
-                     : resolve_kernel(Bp, M, &kernel);
+                     : f32_resolve_alone(Bp, M, &kernel, {16, u8_kind(C_dev, ldc), Bp->has_bzp != 0});
   if (rc != QG_OK) return rc;
   {
     qg_gemm_args a = {};
@@ -1373,7 +1388,7 @@ int qg_gemm_f32s8_dequant_f32(const float* A_dev, int M, int lda, float a_inv_sc
   bool one_launch = false;
   rc = workspace_dev ? f32_resolve(Bp, M, &kernel, &one_launch, {16, OUT_F32, Bp->has_bzp != 0},
                                    f32_in_place(A_dev, M, lda, Bp->K, C_dev, ldc, Bp->N, sizeof(float)))
-                     : resolve_kernel(Bp, M, &kernel);
+                     : f32_resolve_alone(Bp, M, &kernel, {16, OUT_F32, Bp->has_bzp != 0});
   if (rc != QG_OK) return rc;
   if (!aligned(C_dev, 4)) return QG_EALIGN;
   {

@@ -72,3 +72,23 @@ def test_sixteen_waves(build, M, N, K):
         assert m and tuple(int(v) for v in m.groups()) == build, name
         got = fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, workspace=q.NO_WORKSPACE, kernel=kernel)
         assert torch.equal(got, fn(F, 0.02, case.a_zp, Bp, bias, scales, *last, kernel="tile64"))
+
+
+# without a workspace, the choice left to the library: us on the kernel of the queries, on this one
+@pytest.mark.parametrize("M,N,K,rows", [(39, 2393, 1792, 16),    # 11.3, 6.4
+                                        (78, 1603, 3264, 16),    # 18.7, 10.1
+                                        (68, 1967, 1054, 32),    # 9.6, 6.1
+                                        (16, 4096, 4096, 16)])
+def test_choice_without_a_workspace(M, N, K, rows):
+    import torch
+    from paper_2101_05615_amd import qgemm as q
+    say(f"fp32 without a workspace {M} {N} {K}")
+    case = wl.random_gemm(M + N + K, M, N, K)
+    F = torch.randn((M, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(K)) * 3
+    Bp = q.pack_b(torch.from_numpy(case.B).cuda(), case.b_zp)
+    scales = torch.from_numpy(case.scales).cuda()
+    for fn, last in ((q.gemm_f32s8_requant, (case.c_zp, case.relu)), (q.gemm_f32s8_dequant_f32, (case.relu,))):
+        (name,) = kernels_of(lambda: fn(F, 0.02, case.a_zp, Bp, None, scales, *last, workspace=q.NO_WORKSPACE))
+        m = re.search(r"qg_gemm_skinny_kernelILi\dELi(\d+)E", name)
+        assert m and 16 * int(m.group(1)) == rows, name
+        assert torch.equal(fn(F, 0.02, case.a_zp, Bp, None, scales, *last, workspace=q.NO_WORKSPACE), fn(F, 0.02, case.a_zp, Bp, None, scales, *last, kernel="tile64"))
