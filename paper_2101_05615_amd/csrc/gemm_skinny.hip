@@ -98,8 +98,8 @@ __device__ __forceinline__ void wait_vm() {
 // two MFMAs, the workgroup stages half as many activation bytes per weight byte, and few fat waves (16 weight loads in flight
 // each) keep a large matrix streaming at the rate of a plain read -- the shape for more workgroups than CUs.
 // DB: two staging regions per wave, so that a batch's activations are requested one batch ahead like its weights.
-// WHOLE: every wave of every slice has whole batches and nothing that K could cut (checked by the host): one batch without DB, straight
-// code then, any number with it.
+// WHOLE: every wave of every slice has whole batches and nothing that K could cut (checked by the host): any number with DB or with
+// batches of eight, otherwise one, straight code then.
 // SRC_CONV16: the same for any multiple of 16 channels.  A k block may then hold pieces of several taps, so the tap is per-lane
 // state, moved on by four 16-byte pieces per block (2 x 12 x 12 x 96 -> 128, 3 x 3, stride 2: 6.3 us on the tiles, 4.2 here).
 constexpr int SRC_U8 = 0, SRC_F32 = 1, SRC_CONV = 2, SRC_CONV16 = 3;
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
   static_assert(!WHOLE || (SRC == SRC_U8 && !B4), "whole batches of 8-bit weights and rows of bytes");
   static_assert(SRC != SRC_F32 || !DB, "fp32 rows pass through registers, batch by batch");
   static_assert(MB * CPW <= NWAVES, "one wave per (row block, fragment column) runs the output pipeline");
-  constexpr bool CONV = SRC == SRC_CONV || SRC == SRC_CONV16;
+  constexpr bool CONV = SRC == SRC_CONV || SRC == SRC_CONV16, ONE = WHOLE && !DB && BATCH < 8;
   // A through LDS (see the file header): per wave and batch, ROWS rows x ROWB bytes
   constexpr int ROWS = MB * 16, ROWB = BATCH * QG_FRAG_K, NCHUNK = ROWB / 16;
   constexpr int REGION = ROWS * ROWB, NREQ = REGION / 1024, RPR = 64 / NCHUNK;  // requests per batch, rows per request
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(NWAVES * 64, NWAVES == 4 ? (MB == 1 ? 2 : 1) : NWAV
     consume(kb, buf, cur, ent);
     if (has_next) copy_rows(kb);
   };
-  if constexpr (WHOLE && !DB) {
+  if constexpr (ONE) {
     v4i w0[NLOAD];
     load_w(kb_begin, w0);
     request_rows(kb_begin, 0);
@@ -763,6 +763,7 @@ hipError_t launch_form(const qg_gemm_args& a, int kernel, hipStream_t s) {
     // holds two regions); several ahead of each other: 8 x 4832 x 4096 5.61 and 5.47, 16 x 14048 x 4096 10.50 and 10.42.
     // Four waves with several batches are not faster so (M up to 4 and a long K: 1.00 to 1.04).
     if (rows == 16 && kb * a.ksplit == blocks && qg_stream_whole(f, kb, a.K)) {
+      if (qg_stream_far(f, kb, sb)) return launch<MODE, 1, 4, 8, 2, B4, SRC, false, true>(a, s);
       if (f.columns == 2 && kb == f.waves * f.batch) return launch<MODE, 1, 8, 4, 2, B4, SRC, false, true>(a, s);
       if (f.columns == 2) return launch<MODE, 1, 8, 4, 2, B4, SRC, true, true>(a, s);
       if (f.waves == 4) return launch<MODE, 1, 4, 4, 1, B4, SRC, false, true>(a, s);

@@ -55,6 +55,12 @@ static inline bool qg_stream_whole(const qg_stream_build& f, int kb, int K) {
   return K % 64 == 0 && (kb == round || (f.waves == 8 && f.columns == 2 && (kb & (round - 1)) == 0));
 }
 
+// Of those, two columns per wave with 8192 or more of K and 64 M weights (rows counted, 16 at a time) or more take four waves, batches of
+// eight k blocks and activations requested at the start of a batch: what is streamed comes from HBM, and it does so faster to fewer waves
+// with longer requests (16 x 8192 x 16384 28.4 us with eight, 25.2 so; 40 x 4096 x 16384 28.2 and 24.1; 16 x 8192 x 8192, weights from HBM,
+// 16.0 and 15.0).  Below either bound eight are the faster: 12 x 5120 x 10240 10.4 and 11.4 us, 33 x 8192 x 4096 11.7 and 11.9.
+static inline bool qg_stream_far(const qg_stream_build& f, int kb, long long sb) { return f.columns == 2 && kb >= 128 && kb * sb >= 32768; }
+
 // The K slice that wave `wave` of workgroup `block` takes.  Workgroups go round-robin over the 8 XCDs; all workgroups of an XCD read all of
 // A, and those that start on different slices request different lines of it.  Turned by `block` alone eight waves start on one slice in all
 // workgroups of an XCD (block / 8 adds the turn there: 7 x 4544 x 6144 7.5 us, 6.9 so, 16 x 8192 x 8192 12.5 and 12.1, 175 shapes with more

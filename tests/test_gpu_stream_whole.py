@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     (5, 300, 2048, 1, 8, 1, True), (16, 64, 4096, 1, 16, 1, True), (3, 4128, 2048, 1, 8, 2, True), (80, 1520, 2048, 1, 8, 2, True),
     (16, 4100, 4096, 1, 8, 2, True), (17, 2080, 6144, 1, 8, 2, True),
     (16, 48, 4096, 2, 8, 1, True), (7, 48, 4096, 4, 4, 1, True), (16, 48, 8192, 2, 16, 1, True),   # slices
+    # four waves, batches of eight: K from 8192 on and 64 M weights and more, rows counted 16 at a time
+    (5, 8192, 8192, 1, 4, 2, True), (16, 6580, 10240, 1, 4, 2, True), (130, 890, 16384, 1, 4, 2, True), (16, 4096, 16384, 2, 4, 2, True),
+    (16, 8160, 8192, 1, 8, 2, True), (16, 8200, 8128, 1, 8, 2, False), (3, 8192, 8192, 1, 4, 1, False),
     (5, 300, 1023, 1, 4, 1, False), (5, 300, 1025, 1, 8, 1, False), (5, 300, 960, 1, 4, 1, False), (5, 300, 1088, 1, 8, 1, False),
     (16, 64, 8192, 1, 8, 1, False), (16, 4100, 4032, 1, 8, 2, False), (16, 48, 4032, 2, 8, 1, False), (7, 48, 4096, 3, 8, 1, False),
 ])
@@ -38,9 +41,10 @@ def test_whole_batches(M, N, K, ksplit, waves, columns, whole):
             q.gemm_u8s8_requant_splitk(A, c.a_zp, Bp, bias, scales, c.c_zp, c.relu, ws, out=C, kernel="skinny16", ksplit=ksplit)
     (name,) = kernels_of(call)
     # <mode, row blocks, waves, batch, columns, 4-bit, source, ahead, whole>
-    m = re.search(r"qg_gemm_skinny_kernelILi0ELi1ELi(\d+)ELi4ELi(\d+)ELb0ELi0ELb([01])ELb([01])EE", name)
-    assert m and (int(m.group(1)), int(m.group(2)), m.group(4) == "1") == (waves, columns, whole), name
-    assert not whole or (m.group(3) == "1") == (K // ksplit > 64 * 4 * waves), name   # one batch: none requested ahead
+    m = re.search(r"qg_gemm_skinny_kernelILi0ELi1ELi(\d+)ELi([48])ELi(\d+)ELb0ELi0ELb([01])ELb([01])EE", name)
+    assert m and (int(m.group(1)), int(m.group(3)), m.group(5) == "1") == (waves, columns, whole), name
+    assert int(m.group(2)) == (8 if whole and (waves, columns) == (4, 2) else 4), name
+    assert not whole or (m.group(4) == "1") == (waves == 8 and K // ksplit > 64 * 4 * waves), name   # one batch: none requested ahead
     for _ in range(2):
         C.fill_(0xEE)
         call()
