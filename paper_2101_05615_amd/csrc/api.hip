@@ -217,7 +217,8 @@ const tile_price k_tile_price[] = {
 };
 // (in pairs: up to 128 super-blocks of rows x 32 columns, where the terms for more workgroups than CUs are left out, and more; then the
 // other builds and depths beyond 128: 16 rows, four waves of one column, for up to four rows and a long K and for up to 16 k blocks; 32
-// rows, up to 32 k blocks; 16 rows, up to 32)
+// rows, up to 32 k blocks; 16 rows, up to 32; 16 rows, four waves with batches of eight.  That one is fitted to 230 drawn
+// shapes of its range, up to 400 M weights: 1.028 of the best kernel, 1.033 by the second row)
 const stream_price k_stream_price[] = {
     {QG_KERNEL_SKINNY16, 16, 2.983, 0.02822, 0.4741, 0.05277, 0.09842, 5.28e-05, 0.4466, 0, 0, 0, 3.543e-05, 0.0001109,
      2.635e-05, 0.04294, 0.09123, 1.033, 1.5, 0, 0, 0, 0, 0, 0, 0.9646, 0.1252, 0.04834, 3.62, 0, 0.0002, 70, 0.3493,
@@ -249,6 +250,9 @@ const stream_price k_stream_price[] = {
     {QG_KERNEL_SKINNY16, 16, 0.1639, 2.988, 0.5, 0.1175, 0.06546, 0.0001377, 0.3826, 0.0003874, 1.832, 0.001001,
      0.0195, 0.07932, 0.08213, 0.009258, 0.1466, 1.15, 1.628, 0.9652, 1.059, 0.005616, 0.6934, 0.009526, 0.0002023,
      1.5, 0, 0.1091, 6.622, 1.005, 0.03082, 68.34, 0.007549, 0.08187, 0.5645},
+    {QG_KERNEL_SKINNY16, 16, 0.1835, 2.442, 0.5, 0.01965, 0.001042, 0.02858, 0.3986, 0.2733, 2.584, 0.002622, 0.009597,
+     0.4563, 6.566e-05, 0.126, 0.02872, 0.8811, 0.0008504, 0.7344, 1.249, 0.0007144, 0.5192, 0.03076, 1.939, 1.5,
+     0.0008048, 0.08125, 18.52, 2.52, 0.04573, 10.04, 0.1727, 0.423, 1.235},
 };
 
 enum out_kind { OUT_U8, OUT_U8_RAGGED, OUT_F32, OUT_I32 };  // RAGGED: rows of C off 16 bytes
@@ -290,6 +294,7 @@ struct stream_shape {
   int row_blocks, columns;
   long long sb, wgs;     // super-blocks of rows x 32 columns, workgroups
   qg_stream_build f;
+  bool far;              // four waves, batches of eight (8-bit weights and rows of bytes)
 };
 inline int ceil_shift(int a, int s) { return ((a - 1) >> s) + 1; }  // a >= 1
 stream_shape shape_of(int rows, int M, int N, int K, bool split = false) {
@@ -298,6 +303,7 @@ stream_shape shape_of(int rows, int M, int N, int K, bool split = false) {
   s.row_blocks = ceil_shift(M, __builtin_ctz(rows));
   s.sb = (long long)s.row_blocks * ceil_shift(N, 5);
   s.f = qg_stream_build_of(rows, s.kb, s.sb, M, split);
+  s.far = rows == 16 && !split && qg_stream_whole(s.f, s.kb, K) && qg_stream_far(s.f, s.kb, s.sb);
   const int w = __builtin_ctz(s.f.waves);
   s.per = split ? 2 * ceil_shift(s.kb, w + 1) : ceil_shift(s.kb, w);
   s.batches = ceil_shift(s.per, __builtin_ctz(s.f.batch)) - 1;
@@ -333,6 +339,7 @@ double stream_price_us(const stream_price& c, const stream_shape& s, int M, int 
 // the row of k_stream_price for the kernel of 16 << i rows
 const stream_price& stream_row(int i, const stream_shape& s, int M, int K) {
   if (s.sb <= 128) return k_stream_price[2 * i];
+  if (s.far) return k_stream_price[10];
   if (i == 0 && K <= 16 * 64) return k_stream_price[7];
   if (i == 0 && M <= 4 && K > 64 * 64) return k_stream_price[6];
   if (i == 0 && K <= 32 * 64) return k_stream_price[9];

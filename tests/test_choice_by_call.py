@@ -75,6 +75,11 @@ def test_kernel_select_answers_for_whole_steps():
     (16, 11008, 4096, ("skinny16", "tile64k4")),             # 9.4 and 9.5
     (16, 28672, 4096, ("tile64", "tile128")),                # 20.2 and 20.5, 24.4 on the 16-row kernel
     (16, 8192, 8192, ("skinny16",)),                         # 12.9, 12.6
+    # a long K and weights beyond the caches
+    (16, 8192, 16384, ("skinny16",)),                        # 26.6 on the 64 x 64 tile with four sets, 25.2
+    (8, 7168, 18432, ("skinny16",)),                         # 25.7, 24.8
+    (16, 6144, 24576, ("skinny16",)),                        # 33.9, 30.6
+    (16, 8192, 10240, ("skinny16",)),                        # 19.0, 17.5
 ])
 def test_shapes_that_were_slow(M, N, K, fast):
     from paper_2101_05615_amd import qgemm as q
