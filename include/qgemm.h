@@ -329,8 +329,8 @@ int qg_gemm_u8s8_dequant_f32(const uint8_t* A_dev, int M, int lda, const qg_pack
  * "packing" pass of the pipeline, one launch.
  *   A_dev   dev, float, row-major M x K, lda >= K (elements)
  *   Aq_dev  dev, uint8, row-major M x K, ldq >= K; must not alias A
- * No alignment required; 16-byte aligned A_dev with lda % 4 == 0 and 4-byte
- * aligned Aq_dev with ldq % 4 == 0 take the vector path. */
+ * A_dev 4-byte aligned, as floats are; 4-byte aligned Aq_dev with ldq % 4 == 0
+ * takes the vector path, 16-byte loads from any row of A. */
 int qg_quantize_a_f32(const float* A_dev, int M, int K, int lda, float inv_scale, int a_zp,
                       uint8_t* Aq_dev, int ldq, void* stream);
 
@@ -348,8 +348,10 @@ int qg_quantize_a_f32(const float* A_dev, int M, int K, int lda, float inv_scale
  *    written but C.  The kernel quantizes the block of A it stages, with the
  *    sequence of qg_quantize_a_f32, and takes row offsets from the staged block
  *    in the same pass (Appendix B: row offsets computed while packing A).
- *    A_dev 4-byte aligned; 16-byte aligned rows (A_dev % 16 == 0, lda % 4 == 0)
- *    take the vector loads.
+ *    A_dev 4-byte aligned; rows at any multiple of 4 bytes take 16-byte loads.
+ *    Whether a call with QG_KERNEL_AUTO is served is the same for every call of
+ *    a shape; up to 512 rows the streaming kernel then is the one that is
+ *    estimated to be the fastest for these activations.
  *    workspace_dev == NULL with a tiled kernel is QG_EWORKSPACE. */
 size_t qg_gemm_f32_workspace_bytes(int M, const qg_packed_b* Bp);
 int qg_gemm_f32s8_requant(const float* A_dev, int M, int lda, float a_inv_scale, const qg_packed_b* Bp,

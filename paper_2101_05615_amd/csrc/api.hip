@@ -83,13 +83,14 @@ const tile_cost k_tile_cost[] = {
     {QG_KERNEL_TILE64K1, 64, 64, 2.714, 0.2482, 0.1361, 0.1909, 2.35e6},
     {QG_KERNEL_TILE64X32K8, 64, 32, 3.817, 0.05427, 0.0602, 2.585},
 };
+// (Of the streaming kernels' former builds, sixteen waves throughout: what was announced by them stays announced.)
 const stream_cost k_stream_cost[] = {
     {QG_KERNEL_SKINNY16, 16, 3.826, 3.664e-06, 5.429, 0.002625},
     {QG_KERNEL_SKINNY32, 32, 3.918, 2.404e-05, 8.639, 0.0005841},
     {QG_KERNEL_SKINNY64, 64, 3.821, 0.0004905, 9.136, 0.002971},
 };
-// The 16-row kernel's four-wave form (more than 128 super-blocks of 16 rows x 32 columns, K a multiple of 2048,
-// dense weights): the same formula per super-block.
+// The 16-row kernel on more than 128 super-blocks of 16 rows x 32 columns with K a multiple of 2048 and dense weights, which all ran in
+// a form of four waves then (that form serves large ones only now): the same formula per super-block.
 const stream_cost k_stream_wide_cost = {QG_KERNEL_SKINNY16, 16, 3.191, 0.0002712, 4.302e-05, 0.001958};
 // A streaming workgroup re-reads its rows of A for every 16 columns; with few columns to share them that
 // traffic comes from far memory, row piece by row piece, at about this many bytes per microsecond.
@@ -126,8 +127,8 @@ double tile_estimate(const tile_cost& c, int M, int N, int K) {
   return us;
 }
 
-// What the queries about K splits and workspaces, calls that ask for a split, calls that bring a workspace for one and fp32
-// activations without a workspace go by: one answer for a shape, whatever the alignment of the operands.
+// What the queries about K splits and workspaces, calls that ask for a split and calls that bring a workspace for one go by, and whether
+// fp32 activations without a workspace are served: one answer for a shape, whatever the alignment of the operands.
 int builtin_select(int M, int N, int K) {
   int best = QG_KERNEL_TILE64;
   double best_us = 1e300;
@@ -1320,8 +1321,8 @@ static int quantize_into_workspace(const float* A_dev, int M, int lda, float a_i
 // fp32 activations on a streaming kernel: ONE launch -- the kernel quantizes the block it stages (Appendix B: any packing routine
 // for A; row offsets come from the staged block in the same pass) and, where there is a workspace, leaves the quantized rows there
 // as the separate pass does.  For a caller without a workspace whatever streaming kernel is in use; with one where QG_KERNEL_AUTO
-// finds it faster (`one_launch`: 64 x 1024 x 1024 6.2 -> 4.8 us, 16 x 4096 x 4096 6.5 -> 6.2; 512 x 4096 x 4096 stays in two).  Fills the common
-// fields of `a`; returns QG_OK with *fused = false for two launches.
+// finds it faster (`one_launch`: 16 x 512 x 512 4.6 us in two launches, 3.8 so; 16 x 4096 x 4096, 5.6 in two and 6.7 so, stays in two, and so does
+// 512 x 4096 x 4096).  Fills the common fields of `a`; returns QG_OK with *fused = false for two launches.
 static int f32_fused_common(const float* A_dev, int M, int lda, float a_inv_scale, int a_zp, const qg_packed_b* Bp,
                             int kernel, bool one_launch, void* workspace_dev, qg_gemm_args* a, bool* fused) {
   *fused = false;

@@ -234,8 +234,8 @@ __device__ __forceinline__ qg_v4i qg_load_a_chunk(const uint8_t* p, int kvalid, 
 }
 
 // The first n of 16 output columns to dst (n <= 0: none), any address: one 16-byte store, or the powers of two that n is made of.
-// Single bytes, up to 15 stores per row, held up the workgroups of the last columns: 999 x 1531 x 2048 10.5 us on the 128 x 64
-// tiles, 9.1 with 1536 columns.
+// Single bytes, up to 15 stores per row, held up the workgroups of the last columns: 999 x 1531 x 2048 on the 128 x 64 tiles 10.4 us,
+// 10.0 so (rows of C 1536 bytes apart 9.7 and 9.1; 1536 columns 9.3 either way).
 __device__ __forceinline__ void qg_store_columns(uint8_t* dst, const unsigned (&w)[4], int n) {
   typedef unsigned u32_any __attribute__((aligned(1)));
   typedef unsigned short u16_any __attribute__((aligned(1)));
